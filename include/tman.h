@@ -19,7 +19,7 @@
  * Accuracy.  The fp16 paths (tman_mpgemv, tman_mpgemv_x, tman_mpgemm) reproduce the exact product
  * y = x * dequant(W)^T to within 2e-3 of max(|y[n][m]|, rms_m y[n][:]) per token.  That figure is a
  * statistical statement, about five standard deviations of the rounding noise the method itself fixes
- * (16-bit table entries or fp16 weights, Sec. 4.1 / 4.3: rms 2-3e-4 of rms(y); the fp16 result: up to
+ * (16-bit table entries or fp16 weights, Sec. 4.1 / 4.3: rms 2-3e-4 of rms(y), one token less; the fp16 result: up to
  * 4.9e-4), not a hard bound: among 1500 random shapes one output in 52,000 of one case reached 2.07e-3,
  * and a token whose one or two outputs cancel to nearly zero can exceed it.  In tman_mpgemm a dequantized
  * weight may differ from fp16((code - zero) * scale) by one fp16 step (about 5 % do: the constant
@@ -120,6 +120,8 @@ int tman_build_lut_batch(int32_t count, const void *const *x, int32_t N, const i
  *   y[n][m] = sum_G scale[m][G] * ( sum_i 2^i sum_{j in G} T[n][j][idx_i[m][j]] - zero[m][G] * S[n][G] )
  * where idx_i[m][j] is the 4-bit pattern of bit-plane i over weights 4j..4j+3 (sign form:
  * scale * (2 * sum_j T - S)).  fp16 table entries, fp32 accumulation, fp16 result.
+ * For N = 1 the kernel is that of tman_mpgemv_x below: it takes the activations out of the tables (T[j][1 << t] is
+ * x[4j + t]) and sums integer products, which rounds less than adding fp16 table entries does.
  *   packed    : from tman_pack_weights for the same shape
  *   lut       : from tman_build_lut(x, N, shape->K, shape->group)
  *   y         : fp16 [N][M]
@@ -146,7 +148,8 @@ int tman_mpgemv(const tman_shape_t *shape, const void *packed, const void *lut, 
  * and reused for every decode step.
  * tman_mpgemv_batch_run launches the batch described by `desc`; `count`, `shapes` and `N` must be the
  * ones given to prepare.  Results are identical to `count` separate tman_mpgemv calls up to the
- * order of the fp32 additions across K, and deterministic for a given batch.
+ * order of the fp32 additions across K, and deterministic for a given batch.  One-token batches are numbered for
+ * balance like those of tman_mpgemv_x.
  */
 #define TMAN_MAX_BATCH 256
 size_t tman_mpgemv_batch_desc_bytes(int32_t count);
@@ -170,7 +173,8 @@ int tman_mpgemv_batch_run(int32_t count, const tman_shape_t *shapes, int32_t N, 
  *   tman_build_lut_i16 : x fp16 [N][K], 1 <= N <= 8 -> lut (tman_lut_i16_bytes(N, K, group) bytes, 16-byte
  *                        aligned): int16 entries laid out as the fp16 tables, int32 block sums, int32 e[n].
  *                        The _batch form follows tman_build_lut_batch.
- *   tman_mpgemv_i16    : arguments, workspace rules and determinism of tman_mpgemv, `lut` from tman_build_lut_i16.
+ *   tman_mpgemv_i16    : arguments, workspace rules and determinism of tman_mpgemv, `lut` from tman_build_lut_i16
+ *                        (N = 1 goes to the kernel of tman_mpgemv_x, which takes xq out of the tables: same integers).
  *   tman_mpgemv_i16_batch_run : launches a batch whose descriptor table tman_mpgemv_batch_prepare wrote with
  *                        integer table buffers in `lut` (the two table buffers have the same geometry).
  */
@@ -183,13 +187,16 @@ int tman_mpgemv_i16(const tman_shape_t *shape, const void *packed, const void *l
 int tman_mpgemv_i16_batch_run(int32_t count, const tman_shape_t *shapes, int32_t N, const void *desc, void *stream);
 
 /*
- * Decoding mpGEMV of ONE token with the table precompute inside the lookup kernel (Sec. 2.2, Sec. 4.3 for
- * the lookups; Sec. 5 moves the precompute into a kernel of its own because it is costly on the paper's
- * hardware, whereas here a kernel boundary costs more than the precompute).  Every workgroup builds the
- * tables of its own K segment (at most 4096 columns: 1024 tables, 32 KB) in LDS from the activations,
- * exactly as tman_build_lut computes them (fp32 sums in ascending order, one rounding to fp16; the same
- * group sums), and then performs the same lookups as tman_mpgemv.  The result is what
- * tman_build_lut + tman_mpgemv give for N = 1, up to the order of the fp32 additions across K.
+ * Decoding mpGEMV of ONE token from the activations themselves, in one launch (Sec. 2.2; the lookups of Sec. 4.3 cost
+ * more vector instructions on this hardware than the sums they replace, and Sec. 5's separate precompute costs a
+ * kernel boundary).  Every workgroup turns the activations of its own K segment (at most 4096 columns) into fixed-point
+ * numbers: every quantization block gets the smallest power-of-two step 2^e with max |x| / 2^e < 2^14, and
+ * X = round_to_nearest_even(x / 2^e) is written with four signed 4-bit digits, whose products with the codes the dot
+ * product unit sums exactly:
+ *   y[m] = sum_G 2^e[G] * scale[m][G] * ( sum_{k in G} q[m][k] X[k] - zero[m][G] * sum_{k in G} X[k] )
+ * (sign form: 2^e * scale * (2 sum q X - sum X)), scales applied in fp32, fp16 result.  Activations within a factor 16
+ * of their block's largest enter unrounded.  Infinities and NaN are kept out of the integers and added as
+ * (q - zero) * scale * x.
  *   x         : fp16 [K], device, 16-byte aligned
  *   y         : fp16 [M]
  *   workspace : tman_mpgemv_workspace_bytes(shape, 1) bytes, under the rules of tman_mpgemv (the size for
@@ -206,7 +213,7 @@ int tman_mpgemv_x_batch_prepare(int32_t count, const tman_shape_t *shapes, const
 int tman_mpgemv_x_batch_run(int32_t count, const tman_shape_t *shapes, const void *desc, void *stream);
 /*
  * Balance.  A batch of up to 8 GEMVs whose workgroups (one per 64-row block and K segment) are all resident at
- * once -- at most 8 per compute unit, fewer when the tables of the longest segment take more LDS -- is launched
+ * once -- at most 8 per compute unit, 5 of the longest segments -- is launched
  * as a one-dimensional grid whose workgroup ids the library assigns: on this chip a launch that fits is dealt out
  * by position, workgroup i to compute unit i mod (number of units), so the numbering decides which workgroups
  * share a unit, and it is chosen so that every unit gets the same number of tile blocks (tiling.decode_balance;
@@ -333,12 +340,12 @@ int tman_mpgemv_noalloc(const tman_shape_t *shape, const void *packed, const voi
  * on-chip-memory constraints, the prefill and the decoding loop nest covering the same M and K extents of the one
  * weight copy).  The shared tile block is fixed by the packed layout (64 rows x 128 columns, which is Eq. 2 and
  * Eq. 3 by construction); free is how many tile blocks one workgroup takes:
- *   decode_seg_tiles / _many   K tiles per workgroup of tman_mpgemv for 1-2 / 4-8 tokens
- *   decode_x_seg_tiles         tman_mpgemv_x: a K of at most this many tiles, and at most decode_x_whole_bytes of
- *                              packed weights per row block, is ONE segment; it is at most 32 (Eq. 1: the tables
- *                              of a segment, 1 KB per tile, live in the workgroup's 32 KB of LDS)
+ *   decode_seg_tiles / _many   K tiles per workgroup of tman_mpgemv for 2 / 3-8 tokens
+ *   decode_x_seg_tiles         one token: a K of at most this many tiles, and at most decode_x_whole_bytes of
+ *                              packed weights per row block, is ONE segment; it is at most 32 (Eq. 1: what a
+ *                              workgroup keeps of its activations lives in LDS; 32 tiles are two passes of its lanes)
  *   decode_x_long_seg_tiles    ... a longer K is cut into equal segments of at most this many tiles
- *   decode_balance             1: batches of tman_mpgemv_x and of the small-batch tman_mpgemm number their
+ *   decode_balance             1: one-token batches and batches of the small-batch tman_mpgemm number their
  *                              workgroups for equal work per compute unit (see tman_mpgemv_x_batch_order),
  *                              0: plain grids
  *   small_seg_tiles            K tiles per workgroup of tman_mpgemm for N <= 32

@@ -156,115 +156,6 @@ __device__ __forceinline__ void issue_weights(Stage<B, NP, GemvCfg<B, NP, GQ, HZ
 }
 
 
-__device__ __forceinline__ uint32_t index_into(uint32_t idx_word, uint32_t base, uint32_t selector) {
-    uint32_t r;
-    asm("v_perm_b32 %0, %1, %2, %3" : "=v"(r) : "v"(idx_word), "v"(base), "s"(selector));
-    return r;
-}
-
-// Sum over blocks of W consecutive lanes (W = 8, 16 or 32), every lane of a block receiving the block's sum.
-// A butterfly: at each step a lane adds the sum of the neighbouring sub-block, which all lanes of that
-// sub-block hold, so the mirror permutations of DPP serve as well as an exchange with lane ^ d.
-template <int CTRL>
-__device__ __forceinline__ float add_dpp(float v) {
-    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-template <int W>
-__device__ __forceinline__ float sum_over_lanes(float v) {
-    v = add_dpp<0xB1>(v);   // quad_perm [1,0,3,2]: lane ^ 1
-    v = add_dpp<0x4E>(v);   // quad_perm [2,3,0,1]: lane ^ 2
-    v = add_dpp<0x141>(v);  // row_half_mirror: the other quad of 8 lanes
-    if constexpr (W >= 16) v = add_dpp<0x140>(v);  // row_mirror: the other half of 16 lanes
-    if constexpr (W >= 32)  // lane ^ 16 (crosses DPP rows)
-        v += __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F));
-    return v;
-}
-
-// One table of the one-token kernels: `xw` holds the table's four fp16 activations; the 16 entries (entry p = sum
-// of the activations whose bit of p is set, added in ascending order, rounded to fp16 once) go to LDS at
-// lt + j * 32, and the sum of every quantization group (TPG consecutive tables, held by TPG consecutive lanes)
-// to ls + (j / TPG) * 4.  All lanes take part in the lane sum; `live` false stores nothing.
-template <int TPG>
-__device__ __forceinline__ void store_table(const u32x2& xw, int j, bool live, uint32_t lt, uint32_t ls) {
-    // (copy the elements out first: a bit cast applied directly to a vector element reads element 0)
-    const uint32_t w01 = xw.x, w23 = xw.y;
-    const half2_t x01 = __builtin_bit_cast(half2_t, w01), x23 = __builtin_bit_cast(half2_t, w23);
-    const float v[4] = {(float)x01[0], (float)x01[1], (float)x23[0], (float)x23[1]};
-    float e[16];
-    e[0] = 0.f;
-    e[1] = v[0];
-    e[2] = v[1];
-    e[3] = v[0] + v[1];
-#pragma unroll
-    for (int p = 4; p < 8; ++p) e[p] = p == 4 ? v[2] : e[p - 4] + v[2];
-#pragma unroll
-    for (int p = 8; p < 16; ++p) e[p] = p == 8 ? v[3] : e[p - 8] + v[3];
-    half8_t lo, hi;
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-        lo[p] = (_Float16)e[p];
-        hi[p] = (_Float16)e[p + 8];
-    }
-    const float gs = sum_over_lanes<TPG>((v[0] + v[1]) + (v[2] + v[3]));
-    if (live) {
-        store_lds<u32x4>(lt + j * 32, __builtin_bit_cast(u32x4, lo));
-        store_lds<u32x4>(lt + j * 32 + 16, __builtin_bit_cast(u32x4, hi));
-        if (j % TPG == 0) store_lds<float>(ls + (j / TPG) * 4, gs);
-    }
-}
-
-// Lookups of one tile block; `tbase` is the LDS address of the tile's 32 tables, `sbase` of its group sums.
-template <int B, int GQ, bool HZ>
-__device__ __forceinline__ void consume_weights(const Stage<B, 1, GemvCfg<B, 1, GQ, HZ>::MPL>& s, uint32_t tbase,
-                                                uint32_t sbase, const uint32_t (&sel)[4], const float (&pw)[B],
-                                                float& y) {
-    using Cfg = GemvCfg<B, 1, GQ, HZ>;
-    constexpr uint32_t NIB = 0x1E1E1E1Eu;  // index * 2 bytes, one per byte
-    constexpr int TSTRIDE = 32;
-    constexpr int W = 4 * B;
-    constexpr int WPG = (GQ / 32) * B;
-    auto fetch = [&](int wi, _Float16 (&e)[8]) {
-        const int kb32 = wi / B, i = wi % B;
-        const int v = (kb32 * 32) / Cfg::CH;
-        const int ksub = ((kb32 * 32) % Cfg::CH) / 32;
-        const int tb = (kb32 * 8) * TSTRIDE;
-        const uint32_t w = word_of(s.c[v], ksub * B + i);
-        const uint32_t xe = (w << 1) & NIB;
-        const uint32_t xo = (w >> 3) & NIB;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            e[2 * k] = load_lds<_Float16>(index_into(xe, tbase, sel[k]) + (tb + (2 * k) * TSTRIDE));
-            e[2 * k + 1] = load_lds<_Float16>(index_into(xo, tbase, sel[k]) + (tb + (2 * k + 1) * TSTRIDE));
-        }
-    };
-    _Float16 e[2][8];
-    float a = 0.f;
-    fetch(0, e[0]);
-#pragma unroll
-    for (int wi = 0; wi < W; ++wi) {
-        if (wi + 1 < W) fetch(wi + 1, e[(wi + 1) & 1]);
-        if (wi % WPG == 0) a = 0.f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) a = fmaf(pw[wi % B], (float)e[wi & 1][u], a);
-        if (wi % WPG == WPG - 1) {
-            const int gi = wi / WPG;
-            const int mo = gi * Cfg::MSZ;
-            const uint32_t mw = s.meta[mo / 4];
-            const float sc = half_bits_to_float((mo % 4) ? (mw >> 16) : (mw & 0xffffu));
-            const float gs = load_lds<float>(sbase + gi * 4);
-            if constexpr (HZ) {
-                const float z = half_bits_to_float(mw >> 16);
-                y = fmaf(sc, fmaf(-z, gs, a), y);
-            } else {
-                y = fmaf(sc, fmaf(2.f, a, -gs), y);
-            }
-        }
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-
 // kernel arguments: the descriptor itself for a single GEMV, the device table for a batch
 template <bool SINGLE>
 struct KernelArgs;
@@ -293,11 +184,17 @@ template <bool SINGLE>
 __device__ __forceinline__ const GemvDesc& desc_of(const OrderedArgs& a, int g) {
     return a.descs[g];
 }
+// wave-uniform loads from constant memory (scalar loads)
+template <typename T>
+using const_ptr = const T __attribute__((address_space(4)))*;
+
 // (GEMV, workgroup of the GEMV) of this workgroup: from the numbering, or from the 2-D grid
 template <bool SINGLE, typename Args>
 __device__ __forceinline__ void workgroup_of(const Args& a, int& g, int& wg_local) {
     if constexpr (__is_same(Args, OrderedArgs)) {
-        const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.order[blockIdx.x]);
+        // entries in pairs, one scalar load (the numbering has room for an even number)
+        const uint32_t pair = reinterpret_cast<const_ptr<uint32_t>>(reinterpret_cast<uintptr_t>(a.order))[blockIdx.x >> 1];
+        const uint32_t e = (blockIdx.x & 1) ? pair >> 16 : pair & 0xffffu;
         g = (int)(e >> 13);
         wg_local = (int)(e & 0x1fffu);
     } else {
@@ -312,6 +209,28 @@ __device__ __forceinline__ const GemvDesc& desc_of(const KernelArgs<SINGLE>& a, 
         return a.single;
     } else {
         return a.descs[g];
+    }
+}
+
+// The descriptor as a value, fetched whole by scalar loads: one memory round trip instead of one per group of fields.
+template <bool SINGLE, typename Args>
+__device__ __forceinline__ GemvDesc desc_value(const Args& a, int g) {
+    if constexpr (__is_same(Args, KernelArgs<true>)) {
+        return a.single;
+    } else {
+        typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+        struct alignas(8) Words {
+            uint32_t w[20];
+        } raw;
+        static_assert(sizeof(GemvDesc) == sizeof(Words), "descriptor size");
+        const uintptr_t p = reinterpret_cast<uintptr_t>(a.descs + g);
+        const u32x16 lo = *reinterpret_cast<const_ptr<u32x16>>(p);
+        const u32x4 hi = *reinterpret_cast<const_ptr<u32x4>>(p + 64);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) raw.w[i] = lo[i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) raw.w[16 + i] = hi[i];
+        return __builtin_bit_cast(GemvDesc, raw);
     }
 }
 

@@ -83,19 +83,19 @@ __device__ __forceinline__ void report_header_mismatch(int* status) {
 // The tile counts below are the library's tiling (Sec. 4.1 "Unified tiling strategy"): defaults found by the
 // measured search in paper_2511_11248_amd/tune.py, replaceable at run time with tman_set_tiling (which checks the
 // constraints that play the part of Eq. 1-4 on this machine).
-constexpr int kGemvXSegmentTiles = 32;  // tables one workgroup of the one-token kernel can hold (32 KB of LDS)
+constexpr int kGemvXSegmentTiles = 32;  // K tiles one workgroup of the one-token kernel can take
 tman_tiling_t current_tiling();
 
 // One GEMV of a decode launch, as the kernel sees it.
 struct GemvDesc {
     const uint8_t* tiles;  // first tile block (past the header)
-    const uint8_t* lut_t;  // fp16 tables; for the kernel that builds its own tables: the activations, fp16 [K]
-    const uint8_t* lut_s;  // fp32 group sums (unused by that kernel)
+    const uint8_t* lut_t;  // tables (fp16 or int16); for tman_mpgemv_x and tman_mpgemm: the activations, fp16
+    const uint8_t* lut_s;  // group sums behind the tables
     void* y;               // fp16 [N][M]
     int32_t* tickets;      // [n_row_blocks], zero between launches
     float* partial;        // [n_row_blocks][n_seg][NP][64]
     int M, N, n_row_blocks, n_ktiles;
-    int wg_begin;          // index of this GEMV's first workgroup in the launch
+    uint32_t seg_recip;    // floor((2^32 - 1) / n_seg)
     int n_seg;             // K segments per row block
     int seg_tiles;         // tiles per segment (the last may be shorter)
     int K;                 // columns of W
@@ -109,13 +109,11 @@ struct GemvPlan {
 };
 GemvPlan plan_gemv(const Layout& L, int N);
 GemvPlan plan_segments(const Layout& L, int np, int max_seg);
-// Plan of the one-token kernel that builds its tables itself: at most 32 tiles per segment (32 KB of tables
-// in LDS), 24 when K has to be cut anyway.
+// Plan of the one-token kernel: at most 32 tiles per segment.
 GemvPlan plan_gemv_x(const Layout& L);
 void fill_desc_plan(GemvDesc& d, const Layout& L, const GemvPlan& p, const void* packed, const void* lut, int N, void* y,
-                    void* workspace, int wg_begin);
-void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace,
-               int wg_begin);
+                    void* workspace);
+void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace);
 
 // launchers (each returns a tman_status)
 int launch_pack(const Layout& L, const uint8_t* codes, const void* scales, const void* zeros, void* packed,
@@ -133,11 +131,12 @@ int launch_mpgemv(const Layout& L, const void* packed, const void* lut, int N, v
                   hipStream_t st);
 int launch_mpgemv_batch(int bits, int group, int has_zero, int N, const GemvDesc* descs_dev, int n_gemv,
                         int max_workgroups, hipStream_t st);
-// one token, tables built inside the lookup kernel from the activations x (fp16 [K])
+// one token; the activations come as such (fp16 [K]) or in tables made by tman_build_lut / tman_build_lut_i16
+enum class TokenSource { kActivations, kTables, kTablesI16 };
 void fill_desc_x(GemvDesc& d, const Layout& L, const void* packed, const void* x, void* y, void* workspace);
-int launch_mpgemv_x(const Layout& L, const void* packed, const void* x, void* y, void* workspace, hipStream_t st);
-int launch_mpgemv_x_batch(int bits, int group, int has_zero, const GemvDesc* descs_dev, int n_gemv, int max_workgroups,
-                          int max_seg_tiles, hipStream_t st);
+int launch_mpgemv_x(TokenSource source, const Layout& L, const void* packed, const void* x, void* y, void* workspace,
+                    hipStream_t st);
+int launch_mpgemv_x_batch(TokenSource source, int bits, int group, int has_zero, const GemvDesc* descs_dev, int n_gemv, int max_workgroups, int max_seg_tiles, hipStream_t st);
 constexpr int kOrderedMaxWorkgroups = 4096;  // room in a descriptor table for a numbering of the workgroups
 // workgroups of a numbered launch (0: plain grid) and the numbering, for the plans of any of the decode kernels
 int ordered_workgroups_of(int count, const Layout* L, const GemvPlan* plans, int n_units, int per_unit);
@@ -151,7 +150,7 @@ int ordered_workgroups_small(int count, const Layout* L, int n_units);
 bool order_workgroups_small(int count, const Layout* L, int n_units, std::vector<uint16_t>* order);
 int launch_mpgemm_small_ordered(int bits, int group, int has_zero, const GemvDesc* descs_dev, int n_gemv,
                                 const uint16_t* order_dev, int n_wg, hipStream_t st);
-int launch_mpgemv_x_ordered(int bits, int group, int has_zero, const GemvDesc* descs_dev, int n_gemv,
+int launch_mpgemv_x_ordered(TokenSource source, int bits, int group, int has_zero, const GemvDesc* descs_dev, int n_gemv,
                             const uint16_t* order_dev, int n_wg, int max_seg_tiles, hipStream_t st);
 // a handful of tokens on the matrix cores, scheduled like the decoding kernels (tman_mpgemm with N <= 32, and its batch form)
 GemvPlan plan_small(const Layout& L);

@@ -44,7 +44,7 @@ GemvPlan plan_small(const Layout& L) {
 }
 
 void fill_desc_small(GemvDesc& d, const Layout& L, const void* packed, const void* x, int N, void* y, void* workspace) {
-    fill_desc_plan(d, L, plan_small(L), packed, x, N, y, workspace, 0);
+    fill_desc_plan(d, L, plan_small(L), packed, x, N, y, workspace);
     d.lut_s = nullptr;
 }
 

@@ -25,9 +25,8 @@
 // All GEMVs of a decode step can share one launch (descriptor table), so the machine is filled even
 // though one layer alone is too small.
 //
-// mpgemv_kernel serves 1 to 8 tokens and reads the tables tman_build_lut made (Sec. 5: the precompute as a
-// kernel of its own, shared by the layers fed from one activation).  The one-token kernel that builds its
-// tables itself is in tman_mpgemv_x.hip.
+// mpgemv_kernel serves 2 to 8 tokens and reads the tables tman_build_lut made (Sec. 5: the precompute as a
+// kernel of its own, shared by the layers fed from one activation).  One token goes to tman_mpgemv_x.hip.
 #include <algorithm>
 #include <vector>
 
@@ -58,7 +57,7 @@ GemvPlan plan_gemv(const Layout& L, int N) {
 }
 
 void fill_desc_plan(GemvDesc& d, const Layout& L, const GemvPlan& p, const void* packed, const void* lut, int N,
-                           void* y, void* workspace, int wg_begin) {
+                           void* y, void* workspace) {
     d.tiles = static_cast<const uint8_t*>(packed) + kHeaderBytes;
     d.lut_t = static_cast<const uint8_t*>(lut);
     d.lut_s = d.lut_t + (size_t)L.n_ktiles * kTableBytesPerKTile * p.np;
@@ -69,15 +68,14 @@ void fill_desc_plan(GemvDesc& d, const Layout& L, const GemvPlan& p, const void*
     d.N = N;
     d.n_row_blocks = L.n_row_blocks;
     d.n_ktiles = L.n_ktiles;
-    d.wg_begin = wg_begin;
+    d.seg_recip = 0xFFFFFFFFu / (uint32_t)p.n_seg;
     d.n_seg = p.n_seg;
     d.seg_tiles = p.seg_tiles;
     d.K = L.K;
 }
 
-void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace,
-               int wg_begin) {
-    fill_desc_plan(d, L, plan_gemv(L, N), packed, lut, N, y, workspace, wg_begin);
+void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace) {
+    fill_desc_plan(d, L, N == 1 ? plan_gemv_x(L) : plan_gemv(L, N), packed, lut, N, y, workspace);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -85,8 +83,9 @@ void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut
 
 int launch_mpgemv(const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace,
                   hipStream_t st) {
+    if (N == 1) return launch_mpgemv_x(TokenSource::kTables, L, packed, lut, y, workspace, st);
     KernelArgs<true> a;
-    fill_desc(a.single, L, packed, lut, N, y, workspace, 0);
+    fill_desc(a.single, L, packed, lut, N, y, workspace);
     a.n_gemv = 1;
     a.status = device_status_word();
     if (!a.status) return TMAN_ERR_LAUNCH;

@@ -26,11 +26,9 @@ __device__ __forceinline__ void issue_tile(Stage<B, NP, GemvCfg<B, NP, GQ, HZ>::
 // A table entry as it comes out of LDS: NP 16-bit values (the NP tokens of one pattern), fp16 numbers or, with
 // integer tables, int16 numbers.
 template <int NP, bool INT> struct EntryT;
-template <> struct EntryT<1, false> { typedef _Float16 type; };
 template <> struct EntryT<2, false> { typedef half2_t type; };
 template <> struct EntryT<4, false> { typedef half4_t type; };
 template <> struct EntryT<8, false> { typedef half8_t type; };
-template <> struct EntryT<1, true> { typedef int16_t type; };   // (a sign-extending LDS read)
 template <> struct EntryT<2, true> { typedef uint32_t type; };
 template <> struct EntryT<4, true> { typedef u32x2 type; };
 template <> struct EntryT<8, true> { typedef u32x4 type; };
@@ -39,7 +37,7 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 
 // Plane weights 2^i ("shift and accumulate") in the two forms the accumulation uses.
 //
-// One or two tokens: a uniform float, the entry is added with a mixed-precision FMA.
+// Two tokens: a uniform float, the entry is added with a mixed-precision FMA.
 // Four or eight tokens: a lookup returns the entries of 4 (8) tokens for the lane's row, and adding them with
 // one FMA per token makes the kernel bound by vector instruction issue.  The matrix pipe does the same
 // additions in one 4x4x4 MFMA per four tokens: with the 64 lanes as 16 blocks of 4, lane (b, j) supplies as
@@ -82,9 +80,7 @@ struct Accum<NP, false> {
     }
     template <int B>
     __device__ __forceinline__ void add(const typename EntryT<NP, false>::type& e, const PlaneWeights<B, NP>& w, int plane) {
-        if constexpr (NP == 1) {
-            a[0] = fmaf(w.pw[plane], (float)e, a[0]);
-        } else if constexpr (NP == 2) {
+        if constexpr (NP == 2) {
 #pragma unroll
             for (int n = 0; n < NP; ++n) a[n] = fmaf(w.pw[plane], (float)e[n], a[n]);
         } else if constexpr (NP == 4) {
@@ -116,9 +112,7 @@ struct Accum<NP, true> {
     static __device__ __forceinline__ int high_half(uint32_t w) { return (int)w >> 16; }
     template <int B>
     __device__ __forceinline__ void add(const typename EntryT<NP, true>::type& e, const PlaneWeights<B, NP>&, int plane) {
-        if constexpr (NP == 1) {
-            a[0] += (int)e << plane;
-        } else if constexpr (NP == 2) {
+        if constexpr (NP == 2) {
             a[0] += low_half(e) << plane;
             a[1] += high_half(e) << plane;
         } else {
@@ -339,7 +333,6 @@ static int launch_group(int group, const KernelArgs<SINGLE>& a, int n_wg, hipStr
 template <int B, bool HZ, bool SINGLE, bool INT>
 static int launch_tokens(int np, int group, const KernelArgs<SINGLE>& a, int n_wg, hipStream_t st) {
     switch (np) {
-        case 1: return launch_group<B, 1, HZ, SINGLE, INT>(group, a, n_wg, st);
         case 2: return launch_group<B, 2, HZ, SINGLE, INT>(group, a, n_wg, st);
         case 4: return launch_group<B, 4, HZ, SINGLE, INT>(group, a, n_wg, st);
         default: return launch_group<B, 8, HZ, SINGLE, INT>(group, a, n_wg, st);

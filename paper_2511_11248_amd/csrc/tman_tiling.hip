@@ -8,9 +8,8 @@
 // Eq. 3 by construction (a prefill workgroup covers 1..4 tile blocks in M and walks K in four 32-column stages
 // per tile block; a decoding wave covers one tile block in M and the 32 tables of its 128 columns).  What
 // remains free, and what tman_set_tiling can change, is how many tile blocks one workgroup takes:
-//   decode_*            K tiles per decoding workgroup (its K segment); the one-token kernel keeps the tables of
-//                       its whole segment in LDS, so there the segment is bounded like K_lut in Eq. 1:
-//                       seg_tiles x 1 KB of tables <= the 32 KB a workgroup requests;
+//   decode_*            K tiles per decoding workgroup (its K segment); the one-token kernel keeps the activations of
+//                       its whole segment in LDS, so there the segment is bounded like K_lut in Eq. 1: 32 tiles;
 //   decode_balance    whether the workgroups of a one-token batch are numbered for equal work per compute unit
 //                       (not a tile size, but it decides which segment length is best);
 //   prefill_row_blocks  tile blocks in M per prefill workgroup; Eq. 4 reads ring (4) x stage bytes <= 160 KB of
@@ -25,7 +24,7 @@
 
 namespace tman {
 
-static constexpr tman_tiling_t kDefaultTiling = {32, 24, 32, 17, 81920, 43, 0, 1, 0, 0};
+static constexpr tman_tiling_t kDefaultTiling = {32, 24, 32, 17, 163840, 43, 0, 1, 0, 0};
 static std::mutex tiling_mutex;
 static tman_tiling_t tiling_now = kDefaultTiling;
 
@@ -39,9 +38,8 @@ static int check_tiling(const tman_tiling_t& t) {
     constexpr int kLdsBytes = 160 * 1024, kRing = 4;
     if (t.decode_seg_tiles < 1 || t.decode_seg_tiles_many < 1 || t.small_seg_tiles < 1) return TMAN_ERR_SHAPE;
     if (t.decode_seg_tiles > 4096 || t.decode_seg_tiles_many > 4096 || t.small_seg_tiles > 4096) return TMAN_ERR_SHAPE;
-    // Eq. 1: the tables of a one-token segment (1 KB per tile) must fit the workgroup's 32 KB
-    if (t.decode_x_seg_tiles < 1 || t.decode_x_seg_tiles * kTableBytesPerKTile > kGemvXSegmentTiles * kTableBytesPerKTile)
-        return TMAN_ERR_SHAPE;
+    // Eq. 1: a one-token segment is what the lanes of a workgroup turn into digits in two passes
+    if (t.decode_x_seg_tiles < 1 || t.decode_x_seg_tiles > kGemvXSegmentTiles) return TMAN_ERR_SHAPE;
     if (t.decode_x_long_seg_tiles < 1 || t.decode_x_long_seg_tiles > t.decode_x_seg_tiles) return TMAN_ERR_SHAPE;
     if (t.decode_x_whole_bytes < 1024) return TMAN_ERR_SHAPE;
     if (t.decode_balance != 0 && t.decode_balance != 1) return TMAN_ERR_SHAPE;

@@ -352,11 +352,11 @@ int tman_mpgemv_noalloc(const tman_shape_t *shape, const void *packed, const voi
  *   prefill_row_blocks         tile blocks in M per workgroup of the tiled prefill kernel, 1..4 (Eq. 4: four
  *                              stage buffers of rows x 80 + 256 x 64 bytes within 160 KB of LDS), 0 = chosen per
  *                              call from the grid it gives
- *   prefill_k_split            tman_mpgemm for N > 32: a grid that leaves compute units idle even with one tile block per
- *                              workgroup goes to a kernel whose four waves split K (each dequantizes its own stages in
- *                              registers; the partial sums meet in LDS in a fixed order): 0 = there, when K >= 2048,
- *                              with the tile chosen per call; 1 = never; 2 / 3 = every call, with the 64 rows x 256
- *                              tokens / 128 rows x 128 tokens tile
+ *   prefill_k_split            tman_mpgemm for N > 32: short prompts and grids that leave compute units idle go to a kernel
+ *                              whose waves split K (each dequantizes its own stages in registers; the partial sums
+ *                              meet in LDS in a fixed order), with tiles of 64 x 64, 64 x 128 or 128 x 128 rows x
+ *                              tokens: 0 = where a model of the grids' times says so, 1 = never, 2 / 3 = every call,
+ *                              with the 64 rows x 256 tokens / 128 rows x 128 tokens tile
  *   i8_token_blocks            tman_mpgemm_i8: 1 = the kernel with 128 x 128 tiles (weights and activations through
  *                              LDS), 3 / 4 / 7 = the kernel whose waves dequantize their own 64 rows in registers and
  *                              share 96 / 128 / 224 tokens of activations through LDS, 9 = the kernel whose four waves

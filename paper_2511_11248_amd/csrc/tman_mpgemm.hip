@@ -62,8 +62,17 @@ struct GemmArgs {
     _Float16* y;
     int M, N, K, n_row_blocks, n_ktiles;
     int m_tiles, n_tiles;
+    int per_xcd;  // workgroups dealt to each XCD
     int* status;  // the library's status word
 };
+
+// Tile of this workgroup, token tiles fastest.  Consecutive workgroup ids go to consecutive XCDs; every XCD gets an
+// equal run of consecutive tiles, so the token tiles that share the weights of one row tile sit on one XCD and its L2,
+// and no XCD has a workgroup more than another (dealing out whole row tiles left 3 x 12 workgroups for the 32 units
+// of one XCD at 17 row tiles x 12 token tiles: 70 instead of 38 us).  May lie past the last tile.
+__device__ __forceinline__ int tile_of_workgroup(const GemmArgs& a) {
+    return (int)(blockIdx.x % kXcds) * a.per_xcd + (int)(blockIdx.x / kXcds);
+}
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 // raw buffer resource: loads at or beyond `bytes` return zero
@@ -124,10 +133,7 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
-    // Tile of this workgroup.  Consecutive workgroup ids go to consecutive XCDs; the n_tiles workgroups
-    // that share the weights of one row tile get ids that are 8 apart, i.e. the same XCD and L2.
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    const int mt = (slot / a.n_tiles) * kXcds + xcd, nt = slot % a.n_tiles;
+    const int tile = tile_of_workgroup(a), mt = tile / a.n_tiles, nt = tile % a.n_tiles;
     // A blob packed for another shape or layout: say so and leave y alone.  (The check is folded into the one
     // exit below: a second exit after this load makes the compiler keep the dequantization state in scratch
     // memory.)
@@ -437,38 +443,41 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// One row block per workgroup (grids that would otherwise leave compute units idle): 64 rows x 256 tokens, the
-// four waves split K.  Wave w takes the 32-column stages w, w + 4, ... whole: it dequantizes the stage's weights in
-// registers (lane = row; v_permlane32_swap makes the MFMA operands, as in the small-batch kernel), brings the
-// stage's activations into its own LDS buffers and multiplies them with all 256 tokens.  So every weight is still
-// dequantized once per 256 tokens, no weight goes through LDS, a wave reads 0.5 KB of LDS per MFMA instead of
-// 1.5 KB, and the waves never wait for one another until the end, where their four partial tiles meet in LDS
-// (added in wave order: results do not depend on timing).
-// Two shapes of the tile: 64 rows x 256 tokens, or 128 rows x 128 tokens (every wave then dequantizes two row
-// blocks per stage and needs half the activation bytes per MFMA; its activation buffers are half as large, so
-// four instead of two of them fit and the requests run three own stages ahead instead of one).
+// Grids that would otherwise leave compute units idle: the W waves of a workgroup split K.  Wave w takes the 32-column
+// stages w, w + W, ... whole: it dequantizes the stage's weights in registers (lane = row; v_permlane32_swap makes the
+// MFMA operands, as in the small-batch kernel), brings the stage's activations into its own LDS buffers and multiplies
+// them with all tokens of the tile.  So a weight is dequantized once per tile, no weight goes through LDS, a wave reads
+// 0.5 KB of LDS per MFMA instead of 1.5 KB, and the waves never wait for one another until the end, where their
+// partial tiles meet in LDS (added in wave order: results do not depend on timing).
+// Shapes of the tile (RBW row blocks x 32 TT tokens): 64 rows x 64 tokens with four waves (two workgroups share a
+// compute unit) or eight, 64 x 128, 128 x 128 (every wave dequantizes two row blocks per stage and needs half the
+// activation bytes per MFMA), and 64 x 256 where the tiling asks for it.  What bounds a wave is the sum of its
+// dequantization (about 90 vector instructions per 32 columns and row block, which hide only in part behind its own
+// MFMAs) and its MFMAs (128 cycles per 32 columns and 32 tokens): a narrow tile costs more dequantization per token
+// but spreads the work over more units and multiplies less padding.
 constexpr int kKsSets = 4;  // register sets of packed weights = own stages in flight per wave
-template <int RBW, int TT>
+template <int RBW, int TT, int W>
 struct KsTile {
     static constexpr int TN = 32 * TT, TM = 64 * RBW;
     static constexpr int XBytes = TN * kStageK * 2;           // activations of a stage
-    static constexpr int NBuf = 128 * 1024 / (4 * XBytes);   // activation buffers per wave
+    static constexpr int NBuf = 128 * 1024 / (W * XBytes) < 4 ? 128 * 1024 / (W * XBytes) : 4;  // activation buffers per wave
     static constexpr int XLoads = TN / 16;                    // requests per stage (16 token rows each)
     static constexpr int PartRow = TM * 4 + 16;               // bytes per token of a wave's partial tile in LDS
     static constexpr int PartBytes = (TN / 2) * PartRow;      // ... of half of its tokens
-    static constexpr int LdsBytes = 4 * NBuf * XBytes > 4 * PartBytes ? 4 * NBuf * XBytes : 4 * PartBytes;
-    static_assert(RBW * TT == 8 && NBuf >= 2 && LdsBytes <= 160 * 1024, "tile of the K-split kernel");
+    static constexpr int LdsBytes = W * NBuf * XBytes > W * PartBytes ? W * NBuf * XBytes : W * PartBytes;
+    static_assert(TT % 2 == 0 && RBW * TT <= 8 && NBuf >= 2 && LdsBytes <= 160 * 1024, "tile of the K-split kernel");
+    static_assert((NBuf & (NBuf - 1)) == 0, "buffers are numbered modulo a power of two");
 };
 
-template <int B, int GQ, bool HZ, int RBW, int TT>
-__global__ void __launch_bounds__(256, 1) mpgemm_ksplit_kernel(GemmArgs a) {
-    using T = KsTile<RBW, TT>;
+template <int B, int GQ, bool HZ, int RBW, int TT, int W>
+__global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
+    using T = KsTile<RBW, TT, W>;
+    constexpr int kMfmas = 2 * RBW * TT;  // of a 16-column step
     constexpr int MSZ = HZ ? 4 : 2;
     constexpr int TB = B * 1024 + 64 * (kKTile / GQ) * MSZ;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    const int mt = (slot / a.n_tiles) * kXcds + xcd, nt = slot % a.n_tiles;
+    const int tile = tile_of_workgroup(a), mt = tile / a.n_tiles, nt = tile % a.n_tiles;
     const bool header_ok = header_matches(a.tiles, a.M, a.K, B, GQ, HZ ? 1 : 0);
     if (!header_ok && blockIdx.x == 0 && threadIdx.x == 0) report_header_mismatch(a.status);
     if (mt >= (header_ok ? a.m_tiles : 0)) return;
@@ -477,9 +486,9 @@ __global__ void __launch_bounds__(256, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n0 = nt * T::TN;
     const int k_stages = a.K / kStageK;
-    // own stages of this wave: wave, wave + 4, ...; the loop runs whole rounds of kKsSets own stages (a stage past
+    // own stages of this wave: wave, wave + W, ...; the loop runs whole rounds of kKsSets own stages (a stage past
     // K has empty sources: zero weights, zero activations)
-    const int n_own = (k_stages + 3) / 4, n_own_pad = (n_own + kKsSets - 1) & ~(kKsSets - 1);
+    const int n_own = (k_stages + W - 1) / W, n_own_pad = (n_own + kKsSets - 1) & ~(kKsSets - 1);
     const int r = lane & 31, h = lane >> 5;
 
     float16_t acc[RBW][2][TT];
@@ -493,8 +502,8 @@ __global__ void __launch_bounds__(256, 1) mpgemm_ksplit_kernel(GemmArgs a) {
                 for (int v = 0; v < 16; ++v) acc[b][hb][nb][v] = 0.f;
 
     WRegs<B> wr[kKsSets][RBW];
-    auto load_wregs = [&](int set, int i) {  // own stage i = stage 4 i + wave, every row block of the tile
-        const int t = 4 * i + wave;
+    auto load_wregs = [&](int set, int i) {  // own stage i = stage W i + wave, every row block of the tile
+        const int t = W * i + wave;
 #pragma unroll
         for (int b = 0; b < RBW; ++b) {
             const int rb = mt * RBW + b;
@@ -511,7 +520,7 @@ __global__ void __launch_bounds__(256, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     const uint32_t x16rows = 16u * (uint32_t)a.K * 2u;
     uint8_t* const xbuf = smem + wave * T::NBuf * T::XBytes;
     auto load_x = [&](int i) {
-        const int t = 4 * i + wave;
+        const int t = W * i + wave;
         const rsrc_t rx = make_rsrc(xsrc, t < k_stages ? xbytes : 0u);
         uint8_t* dst = xbuf + (i & (T::NBuf - 1)) * T::XBytes;
 #pragma unroll
@@ -597,9 +606,9 @@ __global__ void __launch_bounds__(256, 1) mpgemm_ksplit_kernel(GemmArgs a) {
             dequant_part(0, (u + 1) % kKsSets, (u + 1) & 1);
             mfmas(u & 1, 0);
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
+            for (int q = 0; q < kMfmas; ++q) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, RBW == 1 ? 3 : 6, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, (RBW == 1 ? 48 : 96) / kMfmas, 0);
                 if (q < TT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -607,9 +616,9 @@ __global__ void __launch_bounds__(256, 1) mpgemm_ksplit_kernel(GemmArgs a) {
             dequant_part(1, (u + 1) % kKsSets, (u + 1) & 1);
             mfmas(u & 1, 1);
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
+            for (int q = 0; q < kMfmas; ++q) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, RBW == 1 ? 5 : 6, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, (RBW == 1 ? 80 : 96) / kMfmas, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
             // The buffer of own stage i is free now (its operand reads are consumed): request own stage i + NBuf
@@ -652,14 +661,14 @@ __global__ void __launch_bounds__(256, 1) mpgemm_ksplit_kernel(GemmArgs a) {
                     }
         }
         __syncthreads();
-        for (int piece = tid; piece < (T::TN / 2) * (T::TM / 8); piece += 256) {
+        for (int piece = tid; piece < (T::TN / 2) * (T::TM / 8); piece += 64 * W) {
             const int n = piece / (T::TM / 8), c8 = piece % (T::TM / 8);
             const int gn = n0 + half * (T::TN / 2) + n, gm = m0 + c8 * 8;
             float sum[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) sum[e] = 0.f;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
+            for (int w = 0; w < W; ++w) {
                 const float* src = reinterpret_cast<const float*>(smem + w * T::PartBytes + n * T::PartRow + c8 * 32);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) sum[e] += src[e];
@@ -679,20 +688,25 @@ __global__ void __launch_bounds__(256, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     }
 }
 
-template <int B, int GQ, bool HZ, int RBW, int TT>
+static unsigned deal_tiles(GemmArgs& a) {
+    a.per_xcd = (int)(((long long)a.m_tiles * a.n_tiles + kXcds - 1) / kXcds);
+    return (unsigned)a.per_xcd * kXcds;
+}
+
+template <int B, int GQ, bool HZ, int RBW, int TT, int W>
 static int launch_ksplit(GemmArgs a, hipStream_t st) {
-    using T = KsTile<RBW, TT>;
+    using T = KsTile<RBW, TT, W>;
     static std::once_flag once;
     static hipError_t attr_rc = hipSuccess;
     std::call_once(once, [] {
-        attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&mpgemm_ksplit_kernel<B, GQ, HZ, RBW, TT>),
+        attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&mpgemm_ksplit_kernel<B, GQ, HZ, RBW, TT, W>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, T::LdsBytes);
     });
     if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
     a.m_tiles = (a.n_row_blocks + RBW - 1) / RBW;
     a.n_tiles = (a.N + T::TN - 1) / T::TN;
-    const unsigned grid = (unsigned)((a.m_tiles + kXcds - 1) / kXcds * kXcds * a.n_tiles);
-    hipLaunchKernelGGL((mpgemm_ksplit_kernel<B, GQ, HZ, RBW, TT>), dim3(grid), dim3(256), T::LdsBytes, st, a);
+    const unsigned grid = deal_tiles(a);
+    hipLaunchKernelGGL((mpgemm_ksplit_kernel<B, GQ, HZ, RBW, TT, W>), dim3(grid), dim3(64 * W), T::LdsBytes, st, a);
     return launch_status();
 }
 
@@ -708,19 +722,23 @@ static int launch_tile(GemmArgs a, hipStream_t st) {
     if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
     a.m_tiles = (a.n_row_blocks + RB - 1) / RB;
     a.n_tiles = (a.N + kTN - 1) / kTN;
-    const unsigned grid = (unsigned)((a.m_tiles + kXcds - 1) / kXcds * kXcds * a.n_tiles);
+    const unsigned grid = deal_tiles(a);
     hipLaunchKernelGGL((mpgemm_kernel<B, GQ, HZ, RB>), dim3(grid), dim3(kThreads), Tile<RB>::LdsBytes, st, a);
     return launch_status();
 }
 
-// Which kernel and tile: 1 .. 4 = the tiled kernel with that many row blocks per workgroup; kSplitWide /
-// kSplitTall = the K-split kernel with 64 rows x 256 tokens / 128 rows x 128 tokens.
-// Tiled kernel: the row blocks that need the least time, counted as rounds of workgroups over the compute units
-// times rows per workgroup, with a small bonus for larger tiles (fewer operand reads and less dequantization per
-// MFMA).  A grid that leaves compute units idle even with one row block per workgroup goes to the K-split kernel
-// (measured 10 - 40 % faster there) unless K is short: the tall tile when the workgroups' activation streams are
-// what limits them (more than 256 tokens, or a full 256 with at least half of the units busy), else the wide one.
-constexpr int kSplitWide = 5, kSplitTall = 6;
+// Which kernel and tile: 1 .. 4 = the tiled kernel with that many row blocks per workgroup; the others = the K-split
+// kernel with 64 rows x 256 tokens, 128 x 128, 64 x 128, and 64 x 64 (four or eight waves).
+//
+// The choice models the time of the grid each of them gives: rounds of workgroups over the compute units, each round
+// a fixed part (prologue, exchange of the partial sums) and a part in proportion to K.  The constants are microseconds
+// measured at K = 1024 .. 11008 on 256 units: a round of 64 x 64 workgroups takes 16 us at K = 4096 (two share a unit:
+// 26 us, three 38, four 50), of 64 x 128 22 us, of 128 x 128 35 us, of the tiled kernel 25 us per row block (with a
+// small penalty for small tiles: more operand reads and dequantization per MFMA).  So short prompts, whose 256-token
+// tiles are mostly padding, and grids that leave units idle go to the narrow tiles (4096 x 11008, N = 173: 94 -> 37
+// us; 11008 x 4096, N = 64: 30 -> 19 us; 28672 x 4096, N = 64: 58 -> 31 us), large grids to the tiled kernel.  One
+// row block per workgroup of the tiled kernel (25 % slower per column, but without exchange) is left for short K.
+constexpr int kSplitWide = 5, kSplitTall = 6, kSplit128 = 7, kSplit64 = 8, kSplit64x8 = 9;
 static int choose_tile(int n_row_blocks, int N, int K) {
     static std::once_flag once;
     static int n_cu = 256;  // assumed when no device answers
@@ -735,30 +753,36 @@ static int choose_tile(int n_row_blocks, int N, int K) {
     if (t.prefill_k_split == 3) return kSplitTall;
     const int forced = t.prefill_row_blocks;
     if (forced >= 1 && forced <= 4) return forced;
-    const int n_tiles = (N + kTN - 1) / kTN;
-    if ((long long)n_row_blocks * n_tiles <= n_cu) {
-        if (t.prefill_k_split == 1 || K < 2048) return 1;
-        return N > 256 || (N > 192 && (long long)n_row_blocks * n_tiles * 2 >= n_cu) ? kSplitTall : kSplitWide;
-    }
-    const double penalty[5] = {0, 0, 1.10, 1.03, 1.0};
+    // rounds over the units of a grid of `rows` row blocks x `tokens` tokens per workgroup
+    auto rounds = [&](int rows, int tokens) {
+        const long long wgs = (long long)((n_row_blocks + rows - 1) / rows) * ((N + tokens - 1) / tokens);
+        return (double)((wgs + n_cu - 1) / n_cu);
+    };
+    const double k = K / 4096.0, penalty[5] = {0, 0, 1.10, 1.03, 1.0};
     int best = 4;
     double best_cost = 1e30;
-    for (int rb = 4; rb >= 2; --rb) {
-        const long long wgs = (long long)((n_row_blocks + rb - 1) / rb) * n_tiles;
-        const double cost = (double)((wgs + n_cu - 1) / n_cu) * rb * penalty[rb];
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = rb;
-        }
-    }
+    auto consider = [&](int choice, double cost) {
+        if (cost < best_cost) best_cost = cost, best = choice;
+    };
+    for (int rb = 4; rb >= 2; --rb) consider(rb, rounds(rb, kTN) * rb * penalty[rb] * (25.0 * k + 1.0));
+    if (rounds(1, kTN) <= 1.0) consider(1, 38.0 * k + 3.0);
+    if (t.prefill_k_split == 1 || K < 1024) return best;  // (short K: nothing to split)
+    consider(kSplitTall, rounds(2, 128) * (27.0 * k + 8.8));
+    consider(kSplit128, rounds(1, 128) * (18.5 * k + 4.0));
+    const double r64 = rounds(1, 64);
+    // eight waves pay from 32 stages per wave on; with more than one workgroup per unit four are as good
+    consider(r64 <= 1.0 && K >= 3072 ? kSplit64x8 : kSplit64, r64 <= 1.0 ? 12.0 * k + 5.0 : r64 * 11.3 * k + 5.0);
     return best;
 }
 
 template <int B, int GQ, bool HZ>
 static int launch_cfg(const GemmArgs& a, hipStream_t st) {
     switch (choose_tile(a.n_row_blocks, a.N, a.K)) {
-        case kSplitWide: return launch_ksplit<B, GQ, HZ, 1, 8>(a, st);
-        case kSplitTall: return launch_ksplit<B, GQ, HZ, 2, 4>(a, st);
+        case kSplitWide: return launch_ksplit<B, GQ, HZ, 1, 8, 4>(a, st);
+        case kSplitTall: return launch_ksplit<B, GQ, HZ, 2, 4, 4>(a, st);
+        case kSplit128: return launch_ksplit<B, GQ, HZ, 1, 4, 4>(a, st);
+        case kSplit64: return launch_ksplit<B, GQ, HZ, 1, 2, 4>(a, st);
+        case kSplit64x8: return launch_ksplit<B, GQ, HZ, 1, 2, 8>(a, st);
         case 1: return launch_tile<B, GQ, HZ, 1>(a, st);
         case 2: return launch_tile<B, GQ, HZ, 2>(a, st);
         case 3: return launch_tile<B, GQ, HZ, 3>(a, st);
@@ -777,12 +801,9 @@ static int launch_group(int group, const GemmArgs& a, hipStream_t st) {
 
 int mpgemm_row_blocks_per_workgroup(const Layout& L, int N) {
     const int c = choose_tile(L.n_row_blocks, N, L.K);
-    return c == kSplitWide ? 1 : c == kSplitTall ? 2 : c;
+    return c == kSplitTall ? 2 : c >= kSplitWide ? 1 : c;
 }
-int mpgemm_splits_k(const Layout& L, int N) {
-    const int c = choose_tile(L.n_row_blocks, N, L.K);
-    return c == kSplitWide || c == kSplitTall;
-}
+int mpgemm_splits_k(const Layout& L, int N) { return choose_tile(L.n_row_blocks, N, L.K) >= kSplitWide; }
 
 int launch_mpgemm(const Layout& L, const void* packed, const void* x, int N, void* y, void* workspace,
                   hipStream_t st) {

@@ -411,21 +411,21 @@ int tman_mpgemm_batch_run(int32_t count, const tman_shape_t* shapes, int32_t N, 
     if (N < 1 || N > TMAN_MAX_SMALL_TOKENS) return TMAN_ERR_SHAPE;
     if (!desc) return TMAN_ERR_NULL;
     if (!aligned16(desc)) return TMAN_ERR_ALIGN;
+    const int has_zero = shapes[0].flags & TMAN_FLAG_HAS_ZERO;
     {
         Layout L[8];
         for (int i = 0; i < count && i < 8; ++i) L[i] = make_layout(&shapes[i]);
         if (const int n_wg = ordered_workgroups_small(count, L, device_units()))
-            return launch_mpgemm_small_ordered(shapes[0].bits, shapes[0].group, shapes[0].flags & TMAN_FLAG_HAS_ZERO,
-                                               static_cast<const GemvDesc*>(desc), count,
-                                               order_of(const_cast<void*>(desc), count), n_wg, (hipStream_t)stream);
+            return launch_mpgemm_small_ordered(shapes[0].bits, shapes[0].group, has_zero, N, static_cast<const GemvDesc*>(desc),
+                                               count, order_of(const_cast<void*>(desc), count), n_wg, (hipStream_t)stream);
     }
     int max_wg = 0;  // the launch grid is (workgroups of the largest GEMM) x count
     for (int i = 0; i < count; ++i) {
         const int n = plan_small(make_layout(&shapes[i])).n_workgroups;
         if (n > max_wg) max_wg = n;
     }
-    return launch_mpgemm_small_batch(shapes[0].bits, shapes[0].group, shapes[0].flags & TMAN_FLAG_HAS_ZERO,
-                                     static_cast<const GemvDesc*>(desc), count, max_wg, (hipStream_t)stream);
+    return launch_mpgemm_small_batch(shapes[0].bits, shapes[0].group, has_zero, N, static_cast<const GemvDesc*>(desc), count,
+                                     max_wg, (hipStream_t)stream);
 }
 
 size_t tman_act_i8_bytes(int32_t N, int32_t K) {

@@ -148,7 +148,7 @@ int ordered_workgroups(int count, const Layout* L, int n_units);
 bool order_workgroups(int count, const Layout* L, int n_units, std::vector<uint16_t>* order);
 int ordered_workgroups_small(int count, const Layout* L, int n_units);
 bool order_workgroups_small(int count, const Layout* L, int n_units, std::vector<uint16_t>* order);
-int launch_mpgemm_small_ordered(int bits, int group, int has_zero, const GemvDesc* descs_dev, int n_gemv,
+int launch_mpgemm_small_ordered(int bits, int group, int has_zero, int N, const GemvDesc* descs_dev, int n_gemv,
                                 const uint16_t* order_dev, int n_wg, hipStream_t st);
 int launch_mpgemv_x_ordered(TokenSource source, int bits, int group, int has_zero, const GemvDesc* descs_dev, int n_gemv,
                             const uint16_t* order_dev, int n_wg, int max_seg_tiles, hipStream_t st);
@@ -156,8 +156,8 @@ int launch_mpgemv_x_ordered(TokenSource source, int bits, int group, int has_zer
 GemvPlan plan_small(const Layout& L);
 void fill_desc_small(GemvDesc& d, const Layout& L, const void* packed, const void* x, int N, void* y, void* workspace);
 int launch_mpgemm_small(const Layout& L, const void* packed, const void* x, int N, void* y, void* workspace, hipStream_t st);
-int launch_mpgemm_small_batch(int bits, int group, int has_zero, const GemvDesc* descs_dev, int n_gemv, int max_workgroups,
-                              hipStream_t st);
+int launch_mpgemm_small_batch(int bits, int group, int has_zero, int N, const GemvDesc* descs_dev, int n_gemv,
+                              int max_workgroups, hipStream_t st);
 // integer matrix cores for formats with one scale and zero per row (tman_quantize_act_i8, tman_mpgemm_i8)
 size_t act_i8_bytes(int N, int K);
 int launch_quantize_act_i8(const void* x, int N, int K, void* out, hipStream_t st);

@@ -206,32 +206,43 @@ static int check_batch(int32_t count, const tman_shape_t* shapes, int32_t N) {
     return TMAN_OK;
 }
 
-// Second half of a prepare call of the one-token kernel: a launch whose workgroups are all resident at once gets them
-// numbered for equal work per compute unit.
-static int write_one_token_order(int32_t count, const tman_shape_t* shapes, void* desc, hipStream_t st) {
+// Second half of a prepare call: a launch whose workgroups are all resident at once gets them numbered for equal work per
+// compute unit.
+static int write_decode_order(int32_t count, const tman_shape_t* shapes, int32_t N, void* desc, hipStream_t st) {
     std::vector<Layout> L(count);
     for (int i = 0; i < count; ++i) L[i] = make_layout(&shapes[i]);
     std::vector<uint16_t> order;
-    if (!order_workgroups(count, L.data(), device_units(), &order)) return TMAN_OK;
+    if (!order_workgroups(count, L.data(), N, device_units(), &order)) return TMAN_OK;
     return launch_write_order(order, order_of(desc, count), st);
 }
 
-// A batch of one-token GEMVs: numbered, or as the plain grid (workgroups of the largest GEMV) x count.
-static int run_one_token_batch(TokenSource source, int32_t count, const tman_shape_t* shapes, const void* desc, hipStream_t st) {
-    int max_wg = 0, max_seg_tiles = 0;  // LDS for the longest segment
+static int run_decode_batch(int (*launch)(const DecodeBatch&, hipStream_t), int32_t count, const tman_shape_t* shapes, int32_t N,
+                            const void* desc, void* stream) {
+    int rc = check_batch(count, shapes, N);
+    if (rc != TMAN_OK) return rc;
+    if (!desc) return TMAN_ERR_NULL;
+    if (!aligned16(desc)) return TMAN_ERR_ALIGN;
+    DecodeBatch b;
+    b.bits = shapes[0].bits;
+    b.group = shapes[0].group;
+    b.has_zero = shapes[0].flags & TMAN_FLAG_HAS_ZERO;
+    b.N = N;
+    b.descs = static_cast<const GemvDesc*>(desc);
+    b.n_gemv = count;
+    b.order = nullptr;
+    b.n_workgroups = b.max_seg_tiles = 0;
     for (int i = 0; i < count; ++i) {
-        const GemvPlan p = plan_gemv_x(make_layout(&shapes[i]));
-        if (p.n_workgroups > max_wg) max_wg = p.n_workgroups;
-        if (p.seg_tiles > max_seg_tiles) max_seg_tiles = p.seg_tiles;
+        const GemvPlan p = plan_decode(make_layout(&shapes[i]), N);
+        if (p.n_workgroups > b.n_workgroups) b.n_workgroups = p.n_workgroups;
+        if (p.seg_tiles > b.max_seg_tiles) b.max_seg_tiles = p.seg_tiles;
     }
-    const int has_zero = shapes[0].flags & TMAN_FLAG_HAS_ZERO;
     Layout L[8];
     for (int i = 0; i < count && i < 8; ++i) L[i] = make_layout(&shapes[i]);
-    if (const int n_wg = ordered_workgroups(count, L, device_units()))
-        return launch_mpgemv_x_ordered(source, shapes[0].bits, shapes[0].group, has_zero, static_cast<const GemvDesc*>(desc),
-                                       count, order_of(const_cast<void*>(desc), count), n_wg, max_seg_tiles, st);
-    return launch_mpgemv_x_batch(source, shapes[0].bits, shapes[0].group, has_zero, static_cast<const GemvDesc*>(desc), count,
-                                 max_wg, max_seg_tiles, st);
+    if (const int n_wg = ordered_workgroups(count, L, N, device_units())) {
+        b.order = order_of(const_cast<void*>(desc), count);
+        b.n_workgroups = n_wg;
+    }
+    return launch(b, (hipStream_t)stream);
 }
 
 int tman_mpgemv_batch_prepare(int32_t count, const tman_shape_t* shapes, const void* const* packed,
@@ -252,33 +263,16 @@ int tman_mpgemv_batch_prepare(int32_t count, const tman_shape_t* shapes, const v
     }
     rc = launch_write_descs(host, count, shapes[0].bits, shapes[0].group, (shapes[0].flags & TMAN_FLAG_HAS_ZERO) ? 1 : 0,
                             static_cast<GemvDesc*>(desc), (hipStream_t)stream);
-    if (rc != TMAN_OK || N > 1) return rc;
-    return write_one_token_order(count, shapes, desc, (hipStream_t)stream);
-}
-
-static int run_table_batch(TokenSource source, int32_t count, const tman_shape_t* shapes, int32_t N, const void* desc,
-                           void* stream) {
-    int rc = check_batch(count, shapes, N);
     if (rc != TMAN_OK) return rc;
-    if (!desc) return TMAN_ERR_NULL;
-    if (!aligned16(desc)) return TMAN_ERR_ALIGN;
-    if (N == 1) return run_one_token_batch(source, count, shapes, desc, (hipStream_t)stream);
-    int max_wg = 0;  // the launch grid is (workgroups of the largest GEMV) x count
-    for (int i = 0; i < count; ++i) {
-        const int n = plan_gemv(make_layout(&shapes[i]), N).n_workgroups;
-        if (n > max_wg) max_wg = n;
-    }
-    const auto launch = source == TokenSource::kTables ? launch_mpgemv_batch : launch_mpgemv_i16_batch;
-    return launch(shapes[0].bits, shapes[0].group, shapes[0].flags & TMAN_FLAG_HAS_ZERO, N, static_cast<const GemvDesc*>(desc),
-                  count, max_wg, (hipStream_t)stream);
+    return write_decode_order(count, shapes, N, desc, (hipStream_t)stream);
 }
 
 int tman_mpgemv_batch_run(int32_t count, const tman_shape_t* shapes, int32_t N, const void* desc, void* stream) {
-    return run_table_batch(TokenSource::kTables, count, shapes, N, desc, stream);
+    return run_decode_batch(launch_mpgemv_batch, count, shapes, N, desc, stream);
 }
 
 int tman_mpgemv_i16_batch_run(int32_t count, const tman_shape_t* shapes, int32_t N, const void* desc, void* stream) {
-    return run_table_batch(TokenSource::kTablesI16, count, shapes, N, desc, stream);
+    return run_decode_batch(launch_mpgemv_i16_batch, count, shapes, N, desc, stream);
 }
 
 int tman_mpgemv_x(const tman_shape_t* shape, const void* packed, const void* x, void* y, void* workspace,
@@ -290,7 +284,7 @@ int tman_mpgemv_x(const tman_shape_t* shape, const void* packed, const void* x, 
     size_t need = tman_mpgemv_workspace_bytes(shape, 1);
     if (need && (!workspace || workspace_bytes < need)) return TMAN_ERR_WORKSPACE;
     if (workspace && !aligned16(workspace)) return TMAN_ERR_ALIGN;
-    return launch_mpgemv_x(TokenSource::kActivations, make_layout(shape), packed, x, y, workspace, (hipStream_t)stream);
+    return launch_mpgemv_x(make_layout(shape), packed, x, y, workspace, (hipStream_t)stream);
 }
 
 int tman_mpgemv_x_batch_prepare(int32_t count, const tman_shape_t* shapes, const void* const* packed,
@@ -307,12 +301,12 @@ int tman_mpgemv_x_batch_prepare(int32_t count, const tman_shape_t* shapes, const
         if (workspace_bytes[i] < tman_mpgemv_workspace_bytes(&shapes[i], 1)) return TMAN_ERR_WORKSPACE;
         for (int j = 0; j < i; ++j)
             if (workspace[j] == workspace[i]) return TMAN_ERR_WORKSPACE;  // every GEMV needs its own
-        fill_desc_x(host[i], make_layout(&shapes[i]), packed[i], x[i], y[i], workspace[i]);
+        fill_desc(host[i], make_layout(&shapes[i]), packed[i], x[i], 1, y[i], workspace[i]);
     }
     rc = launch_write_descs(host, count, shapes[0].bits, shapes[0].group, (shapes[0].flags & TMAN_FLAG_HAS_ZERO) ? 1 : 0,
                             static_cast<GemvDesc*>(desc), (hipStream_t)stream);
     if (rc != TMAN_OK) return rc;
-    return write_one_token_order(count, shapes, desc, (hipStream_t)stream);
+    return write_decode_order(count, shapes, 1, desc, (hipStream_t)stream);
 }
 
 int tman_mpgemv_x_batch_order(int32_t count, const tman_shape_t* shapes, int32_t n_units, uint16_t* order,
@@ -324,7 +318,7 @@ int tman_mpgemv_x_batch_order(int32_t count, const tman_shape_t* shapes, int32_t
     std::vector<Layout> L(count);
     for (int i = 0; i < count; ++i) L[i] = make_layout(&shapes[i]);
     std::vector<uint16_t> o;
-    if (!order_workgroups(count, L.data(), n_units > 0 ? n_units : device_units(), &o)) o.clear();
+    if (!order_workgroups(count, L.data(), 1, n_units > 0 ? n_units : device_units(), &o)) o.clear();
     *n_entries = (int32_t)o.size();
     if (order)
         for (size_t i = 0; i < o.size() && i < (size_t)max_entries; ++i) order[i] = o[i];
@@ -332,11 +326,7 @@ int tman_mpgemv_x_batch_order(int32_t count, const tman_shape_t* shapes, int32_t
 }
 
 int tman_mpgemv_x_batch_run(int32_t count, const tman_shape_t* shapes, const void* desc, void* stream) {
-    int rc = check_batch(count, shapes, 1);
-    if (rc != TMAN_OK) return rc;
-    if (!desc) return TMAN_ERR_NULL;
-    if (!aligned16(desc)) return TMAN_ERR_ALIGN;
-    return run_one_token_batch(TokenSource::kActivations, count, shapes, desc, (hipStream_t)stream);
+    return run_decode_batch(launch_mpgemv_x_batch, count, shapes, 1, desc, stream);
 }
 
 int32_t tman_mpgemm_tile_rows(const tman_shape_t* shape, int32_t N) {

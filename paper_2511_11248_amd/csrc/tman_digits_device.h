@@ -119,20 +119,19 @@ __device__ __forceinline__ int sum_of_digits(const uint32_t (&w)[4]) {
 __device__ __forceinline__ int join_digits(const int (&acc)[4]) { return (((((acc[3] << 4) + acc[2]) << 4) + acc[1]) << 4) + acc[0]; }
 
 // Numbers of a quad of lanes -> digits in LDS.  Lane f (of 4) of a quad holds of one 32-weight block, in r[o], number
-// 4f + o (low half) and 16 + 4f + o (high half), as X + 0x8888.  The block's 16 words go to LDS at `ld` + 16 i (i =
-// index of the lane in the segment), and the first lane of every quantization block (GQ / 8 lanes) stores the
-// block's (sum of X, step, 8 * sum) at `lm`.  All lanes take part in the exchanges; with `live` false nothing is stored.
+// 4f + o (low half) and 16 + 4f + o (high half), as X + 0x8888.  The lane's four words of the block go to `ld`, and the
+// first lane of every quantization block (GQ / 8 lanes) stores the block's (sum of X, step, 8 * sum) at `lm`.  `i`: index
+// of the lane in the segment.  All lanes take part in the exchanges; with `live` false nothing is stored.
 template <int GQ>
 __device__ __forceinline__ void store_digits(uint32_t (&r)[4], float step, int i, bool live, uint32_t ld, uint32_t lm) {
     constexpr int LPG = GQ / 8;  // lanes per quantization block
     digit_words(r, i & 3);
     const int sum = isum_over_lanes<LPG>(sum_of_digits(r));
     if (live) {
-        store_lds<u32x4>(ld + i * 16, u32x4{r[0], r[1], r[2], r[3]});
+        store_lds<u32x4>(ld, u32x4{r[0], r[1], r[2], r[3]});
         if (i % LPG == 0)
-            store_lds<u32x4>(lm + (i / LPG) * kDigitMetaBytes,
-                             u32x4{__builtin_bit_cast(uint32_t, (float)sum), __builtin_bit_cast(uint32_t, step),
-                                   (uint32_t)sum << 3, 0u});
+            store_lds<u32x4>(lm, u32x4{__builtin_bit_cast(uint32_t, (float)sum), __builtin_bit_cast(uint32_t, step),
+                                       (uint32_t)sum << 3, 0u});
     }
 }
 
@@ -189,41 +188,59 @@ __device__ __forceinline__ void bias_block(const u32x2& xa, const u32x2& xb, uin
 }
 
 // Codes times activations of one tile block for the lane's row.  `dbase` is the LDS address of the tile's digit words
-// plus 4 (lane % 16), `mbase` of its blocks' (sum, step) pairs.
-template <int B, int GQ, bool HZ>
+// plus 4 (lane % 16), `mbase` of its blocks' records; token n's follow at n * 256 and n * GPT * 16.  The codes are made
+// once for all tokens.
+template <int B, int GQ, bool HZ, int NP>
 __device__ __forceinline__ void consume_weights_digits(const Stage<B, 1, GemvCfg<B, 1, GQ, HZ>::MPL>& s, uint32_t dbase,
-                                                       uint32_t mbase, float& y) {
+                                                       uint32_t mbase, float (&y)[NP]) {
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
     constexpr int BPG = GQ / 32;  // 32-weight blocks per quantization block
-    uint32_t dg[4];
-    u32x4 gm[Cfg::GPT];
+    uint32_t dg[NP][4];
+    u32x4 gm[NP][Cfg::GPT];
+    if constexpr (NP == 1) {  // (more tokens: read where they are used, to bound the registers)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) dg[b] = load_lds<uint32_t>(dbase + b * 64);
+        for (int b = 0; b < 4; ++b) dg[0][b] = load_lds<uint32_t>(dbase + b * 64);
 #pragma unroll
-    for (int gi = 0; gi < Cfg::GPT; ++gi) gm[gi] = load_lds<u32x4>(mbase + gi * kDigitMetaBytes);
+        for (int gi = 0; gi < Cfg::GPT; ++gi) gm[0][gi] = load_lds<u32x4>(mbase + gi * kDigitMetaBytes);
+    }
 #pragma unroll
     for (int gi = 0; gi < Cfg::GPT; ++gi) {
-        const uint32_t gs_w = gm[gi].x, step_w = gm[gi].y, sum8 = gm[gi].z;  // (copied out before the casts)
-        const float gs = __builtin_bit_cast(float, gs_w), step = __builtin_bit_cast(float, step_w);
-        int acc[4] = {B == 4 ? (int)sum8 : 0, 0, 0, 0};  // 4 bits: fields hold code - 8
+        int acc[NP][4];
+#pragma unroll
+        for (int n = 0; n < NP; ++n) {
+            if constexpr (NP > 1) gm[n][gi] = load_lds<u32x4>(mbase + (n * Cfg::GPT + gi) * kDigitMetaBytes);
+            const uint32_t sum8 = gm[n][gi].z;
+            acc[n][0] = B == 4 ? (int)sum8 : 0;  // 4 bits: fields hold code - 8
+            acc[n][1] = acc[n][2] = acc[n][3] = 0;
+        }
 #pragma unroll
         for (int b = gi * BPG; b < (gi + 1) * BPG; ++b) {
             const int v = (b * 32) / Cfg::CH, ksub = ((b * 32) % Cfg::CH) / 32;
             uint32_t p[B], c[4];
+            if constexpr (NP > 1)
+#pragma unroll
+                for (int n = 0; n < NP; ++n) dg[n][b] = load_lds<uint32_t>(dbase + n * kDigitBytesPerKTile + b * 64);
 #pragma unroll
             for (int i = 0; i < B; ++i) p[i] = word_of(s.c[v], ksub * B + i);
             planes_to_signed_codes<B>(p, c);
-            dot_block(acc, dg[b], c);
+#pragma unroll
+            for (int n = 0; n < NP; ++n) dot_block(acc[n], dg[n][b], c);
         }
-        const float a = (float)join_digits(acc);
         const int mo = gi * Cfg::MSZ;
         const uint32_t mw = s.meta[mo / 4];
-        const float sc = half_bits_to_float((mo % 4) ? (mw >> 16) : (mw & 0xffffu)) * step;
-        if constexpr (HZ) {
-            const float z = half_bits_to_float(mw >> 16);
-            y = fmaf(sc, fmaf(-z, gs, a), y);
-        } else {
-            y = fmaf(sc, fmaf(2.f, a, -gs), y);
+        const float scale = half_bits_to_float((mo % 4) ? (mw >> 16) : (mw & 0xffffu));
+#pragma unroll
+        for (int n = 0; n < NP; ++n) {
+            const uint32_t gs_w = gm[n][gi].x, step_w = gm[n][gi].y;  // (copied out before the casts)
+            const float gs = __builtin_bit_cast(float, gs_w), step = __builtin_bit_cast(float, step_w);
+            const float a = (float)join_digits(acc[n]);
+            const float sc = scale * step;
+            if constexpr (HZ) {
+                const float z = half_bits_to_float(mw >> 16);
+                y[n] = fmaf(sc, fmaf(-z, gs, a), y[n]);
+            } else {
+                y[n] = fmaf(sc, fmaf(2.f, a, -gs), y[n]);
+            }
         }
     }
 }

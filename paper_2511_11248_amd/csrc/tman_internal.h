@@ -111,6 +111,7 @@ GemvPlan plan_gemv(const Layout& L, int N);
 GemvPlan plan_segments(const Layout& L, int np, int max_seg);
 // Plan of the one-token kernel: at most 32 tiles per segment.
 GemvPlan plan_gemv_x(const Layout& L);
+GemvPlan plan_decode(const Layout& L, int N);  // the one of N tokens
 void fill_desc_plan(GemvDesc& d, const Layout& L, const GemvPlan& p, const void* packed, const void* lut, int N, void* y,
                     void* workspace);
 void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace);
@@ -124,34 +125,44 @@ int launch_build_lut_batch(int count, const void* const* x, int N, const int* K,
                            hipStream_t st);
 int launch_build_lut_i16_batch(int count, const void* const* x, int N, const int* K, int group, void* const* lut,
                                hipStream_t st);
-int launch_mpgemv_i16(const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace, hipStream_t st);
-int launch_mpgemv_i16_batch(int bits, int group, int has_zero, int N, const GemvDesc* descs_dev, int n_gemv,
-                            int max_workgroups, hipStream_t st);
-int launch_mpgemv(const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace,
-                  hipStream_t st);
-int launch_mpgemv_batch(int bits, int group, int has_zero, int N, const GemvDesc* descs_dev, int n_gemv,
-                        int max_workgroups, hipStream_t st);
-// one token; the activations come as such (fp16 [K]) or in tables made by tman_build_lut / tman_build_lut_i16
+// The decoding kernel takes the activations as such (fp16 [K], one token) or out of tables made by tman_build_lut /
+// tman_build_lut_i16 (1 to 8 tokens).
 enum class TokenSource { kActivations, kTables, kTablesI16 };
-void fill_desc_x(GemvDesc& d, const Layout& L, const void* packed, const void* x, void* y, void* workspace);
-int launch_mpgemv_x(TokenSource source, const Layout& L, const void* packed, const void* x, void* y, void* workspace,
-                    hipStream_t st);
-int launch_mpgemv_x_batch(TokenSource source, int bits, int group, int has_zero, const GemvDesc* descs_dev, int n_gemv, int max_workgroups, int max_seg_tiles, hipStream_t st);
+// Whether a format leaves the lookups for the dot product unit (tman_mpgemv_x_kernel.h).  A lookup serves all tokens at
+// once, digits cost 16 instructions per token and 32 weights; lookups cost per bit-plane, and integer entries have no
+// matrix instruction that adds them.  One token: digits.  More: 4-bit weights with integer tables (7B uint4 g128, lookups
+// -> digits, us per layer set with the table launch: N = 2 51 -> 35, N = 4 70 -> 46, N = 8 138 -> 78) and with fp16
+// tables for two tokens (36 -> 33; N = 4 37 -> 47, N = 8 61 -> 80 the other way round); 1 and 2 bits stay with the
+// lookups (7B uint2 N = 4: 29 against 44, int16 40 against 44).
+constexpr bool lookups_replaced(int bits, int np, bool integer) { return np == 1 || (bits == 4 && (integer || np == 2)); }
+// A batch launch: numbered (order != nullptr, n_workgroups in all) or as the plain grid n_workgroups (of the largest
+// GEMV) x n_gemv.
+struct DecodeBatch {
+    int bits, group, has_zero, N;
+    const GemvDesc* descs;  // device
+    int n_gemv;
+    const uint16_t* order;  // device
+    int n_workgroups, max_seg_tiles;
+};
+int launch_mpgemv(const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace, hipStream_t st);
+int launch_mpgemv_batch(const DecodeBatch& b, hipStream_t st);
+int launch_mpgemv_i16(const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace, hipStream_t st);
+int launch_mpgemv_i16_batch(const DecodeBatch& b, hipStream_t st);
+int launch_mpgemv_x(const Layout& L, const void* packed, const void* x, void* y, void* workspace, hipStream_t st);
+int launch_mpgemv_x_batch(const DecodeBatch& b, hipStream_t st);
 constexpr int kOrderedMaxWorkgroups = 4096;  // room in a descriptor table for a numbering of the workgroups
 // workgroups of a numbered launch (0: plain grid) and the numbering, for the plans of any of the decode kernels
 int ordered_workgroups_of(int count, const Layout* L, const GemvPlan* plans, int n_units, int per_unit);
 bool order_workgroups_of(int count, const Layout* L, const GemvPlan* plans, int n_units, int per_unit,
                          std::vector<uint16_t>* order);
 int launch_write_order(const std::vector<uint16_t>& order, uint16_t* dev, hipStream_t st);
-// ... of a one-token batch (tman_mpgemv_x) and of a small-batch mpGEMM batch
-int ordered_workgroups(int count, const Layout* L, int n_units);
-bool order_workgroups(int count, const Layout* L, int n_units, std::vector<uint16_t>* order);
+// ... of a decoding batch and of a small-batch mpGEMM batch
+int ordered_workgroups(int count, const Layout* L, int N, int n_units);
+bool order_workgroups(int count, const Layout* L, int N, int n_units, std::vector<uint16_t>* order);
 int ordered_workgroups_small(int count, const Layout* L, int n_units);
 bool order_workgroups_small(int count, const Layout* L, int n_units, std::vector<uint16_t>* order);
 int launch_mpgemm_small_ordered(int bits, int group, int has_zero, int N, const GemvDesc* descs_dev, int n_gemv,
                                 const uint16_t* order_dev, int n_wg, hipStream_t st);
-int launch_mpgemv_x_ordered(TokenSource source, int bits, int group, int has_zero, const GemvDesc* descs_dev, int n_gemv,
-                            const uint16_t* order_dev, int n_wg, int max_seg_tiles, hipStream_t st);
 // a handful of tokens on the matrix cores, scheduled like the decoding kernels (tman_mpgemm with N <= 32, and its batch form)
 GemvPlan plan_small(const Layout& L);
 void fill_desc_small(GemvDesc& d, const Layout& L, const void* packed, const void* x, int N, void* y, void* workspace);

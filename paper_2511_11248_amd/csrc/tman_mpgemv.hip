@@ -30,7 +30,7 @@
 #include <algorithm>
 #include <vector>
 
-#include "tman_mpgemv_kernel.h"
+#include "tman_mpgemv_x_kernel.h"
 
 namespace tman {
 
@@ -74,31 +74,13 @@ void fill_desc_plan(GemvDesc& d, const Layout& L, const GemvPlan& p, const void*
     d.K = L.K;
 }
 
-void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace) {
-    fill_desc_plan(d, L, N == 1 ? plan_gemv_x(L) : plan_gemv(L, N), packed, lut, N, y, workspace);
-}
-
 // ---------------------------------------------------------------------------------------------
-// launch (the kernel is in tman_mpgemv_kernel.h)
+// launch
 
-int launch_mpgemv(const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace,
-                  hipStream_t st) {
-    if (N == 1) return launch_mpgemv_x(TokenSource::kTables, L, packed, lut, y, workspace, st);
-    KernelArgs<true> a;
-    fill_desc(a.single, L, packed, lut, N, y, workspace);
-    a.n_gemv = 1;
-    a.status = device_status_word();
-    if (!a.status) return TMAN_ERR_LAUNCH;
-    return launch_format<true, false>(L.bits, L.has_zero, padded_tokens(N), L.group, a, plan_gemv(L, N).n_workgroups, st);
+int launch_mpgemv(const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace, hipStream_t st) {
+    return launch_x_single<TokenSource::kTables>(L, N, packed, lut, y, workspace, st);
 }
-
-int launch_mpgemv_batch(int bits, int group, int has_zero, int N, const GemvDesc* descs_dev, int n_gemv,
-                        int max_workgroups, hipStream_t st) {
-    KernelArgs<false> a;
-    a.descs = descs_dev;
-    a.n_gemv = n_gemv;
-    return launch_format<false, false>(bits, has_zero, padded_tokens(N), group, a, max_workgroups, st);
-}
+int launch_mpgemv_batch(const DecodeBatch& b, hipStream_t st) { return launch_x_batch<TokenSource::kTables>(b, st); }
 
 // Copies up to 16 descriptors per launch from the kernel arguments into the device table.  A GEMV whose blob
 // carries a header for another shape or layout gets an empty descriptor (no workgroup of the lookup launch

@@ -1,0 +1,267 @@
+// The decoding kernel on the 4-bit dot product unit, as a template over the weight format, the source of the activations
+// and the number of tokens (padded to 1, 2, 4 or 8); what it does and why is said in tman_mpgemv_x.hip.
+#pragma once
+#include "tman_digits_device.h"
+#include "tman_mpgemv_kernel.h"
+
+namespace tman {
+
+// K tiles whose digits are in LDS at a time (a longer segment is worked in such pieces): at most 61 KB
+constexpr int piece_tiles(int np) { return np == 8 ? 24 : kGemvXSegmentTiles; }
+
+// LDS of a workgroup whose segment has `seg_tiles` tiles: digit words and `gpt` quantization blocks per tile and token,
+// then the partial sums and a word per wave
+inline unsigned x_lds_bytes(int seg_tiles, int np, int gpt) {
+    const int tiles = seg_tiles < piece_tiles(np) ? seg_tiles : piece_tiles(np);
+    return (unsigned)(tiles * np * (kDigitBytesPerKTile + gpt * kDigitMetaBytes) + kWaves * kRows * np * 4 + kWaves * 4);
+}
+
+// The 8 activations of a lane, per token: numbers 4f .. 4f + 3 (a) and 16 + 4f .. (b) of its 32-column block.
+template <int NP>
+struct LaneActs {
+    u32x2 a[NP], b[NP];
+};
+
+// The four activations of each token out of one table.
+template <int NP>
+__device__ __forceinline__ void load_table(rsrc_t rt, int off, u32x2 (&x)[NP]) {
+    if constexpr (NP == 1) {
+        const u32x4 lo = __builtin_amdgcn_raw_buffer_load_b128(rt, off, 0, 0);
+        const uint32_t e8 = __builtin_amdgcn_raw_buffer_load_b32(rt, off + 16, 0, 0);
+        const uint32_t e01 = lo.x, e23 = lo.y, e45 = lo.z;
+        x[0] = u32x2{__builtin_amdgcn_perm(e23, e01, 0x05040302u), __builtin_amdgcn_perm(e8, e45, 0x05040100u)};
+    } else {
+        uint32_t e[4][NP / 2];  // entries 1, 2, 4, 8: NP numbers each
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int at = off + (1 << t) * 2 * NP;
+            if constexpr (NP == 2) {
+                e[t][0] = __builtin_amdgcn_raw_buffer_load_b32(rt, at, 0, 0);
+            } else if constexpr (NP == 4) {
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rt, at, 0, 0);
+                e[t][0] = v.x, e[t][1] = v.y;
+            } else {
+                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rt, at, 0, 0);
+                e[t][0] = v.x, e[t][1] = v.y, e[t][2] = v.z, e[t][3] = v.w;
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < NP; ++n) {
+            const uint32_t half = n & 1 ? 0x07060302u : 0x05040100u;
+            x[n] = u32x2{__builtin_amdgcn_perm(e[1][n / 2], e[0][n / 2], half), __builtin_amdgcn_perm(e[3][n / 2], e[2][n / 2], half)};
+        }
+    }
+}
+
+template <int B, int GQ, bool HZ, TokenSource SRC, int NP, bool SINGLE, typename Args>
+__global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
+    using Cfg = GemvCfg<B, 1, GQ, HZ>;
+    static_assert(NP == 1 || SRC != TokenSource::kActivations, "several tokens come in tables");
+    constexpr int kPiece = piece_tiles(NP);
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds_x[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    int g, wg_local;
+    workgroup_of<SINGLE>(a, g, wg_local);
+    const GemvDesc d = desc_value<SINGLE>(a, g);  // (one load: the fields are needed one after the other)
+    const int n_seg = d.n_seg, n_ktiles = d.n_ktiles;
+    // Exits: surplus workgroups of the grid, and (single call) a blob packed for another shape or layout, which is
+    // reported and leaves y alone; a batch is checked when its descriptor table is written, which empties the
+    // descriptor of such a GEMV.  One exit for both, before any other memory request.
+    int n_wg = d.n_row_blocks * n_seg;
+    if constexpr (SINGLE) {
+        if (!header_matches(d.tiles, d.M, d.K, B, GQ, HZ ? 1 : 0)) {
+            if (wg_local == 0 && tid == 0) report_header_mismatch(a.status);
+            n_wg = 0;
+        }
+    }
+    if (wg_local >= n_wg) return;
+    // row block and segment: quotient by the reciprocal floor((2^32 - 1) / n_seg), which falls short by at most one
+    int rb = (int)__umulhi((uint32_t)wg_local, (uint32_t)d.seg_recip), seg = wg_local - rb * n_seg;
+    if (seg >= n_seg) ++rb, seg -= n_seg;
+    const int k0 = seg * d.seg_tiles;
+    const int k1 = min(k0 + d.seg_tiles, n_ktiles);
+    Streams src;
+    src.w = d.tiles + (size_t)rb * n_ktiles * Cfg::TB;
+    src.t = src.s = nullptr;
+    src.w_bytes = (uint32_t)(n_ktiles * Cfg::TB);
+    src.t_bytes = src.s_bytes = 0;
+
+    const int piece = min(d.seg_tiles, kPiece);
+    const uint32_t ld = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr<uint8_t>)lds_x));
+    const uint32_t lm = ld + (uint32_t)(piece * NP * kDigitBytesPerKTile);          // quantization blocks
+    const uint32_t lr = lm + (uint32_t)(piece * NP * Cfg::GPT * kDigitMetaBytes);  // partial sums [wave][token][row]
+    const uint32_t lf = lr + kWaves * kRows * NP * 4;                               // a word per wave
+
+    float y[NP];
+#pragma unroll
+    for (int n = 0; n < NP; ++n) y[n] = 0.f;
+    // the segment in pieces whose digits fit the LDS: one piece, unless the tiling asks for very long segments (never
+    // for one token)
+    for (int p0 = k0;;) {
+        const int p1 = NP == 1 ? k1 : min(p0 + kPiece, k1);
+        // The activations are requested first and the first weight tiles right behind them: a wave's loads return in
+        // the order they were issued, so activations queued behind weight tiles (which come from HBM) would hold the
+        // digits back until those tiles are in; this way the digits are made while the weights travel.
+        // Four lanes share a block of 32 columns; a pass is 64 blocks, 16 tiles.
+        constexpr int kPasses = (kPiece * kKTile / 8 + kWaves * 64 - 1) / (kWaves * 64);
+        LaneActs<NP> xv[kPasses];  // (a pass beyond the piece reads what nobody uses; x beyond K reads as zero)
+        if constexpr (SRC == TokenSource::kActivations) {
+            const uint32_t x_start = (uint32_t)(p0 * kKTile * 2);  // p0 < n_ktiles, so this lies inside x
+            // (the range check of a buffer load covers the per-lane offset only, not the scalar offset, so the resource
+            // starts at the piece's first activation and ends with x: K * 2 bytes less the piece's start)
+            const rsrc_t rx = make_rsrc(d.lut_t + x_start, (uint32_t)d.K * 2u - x_start);
+#pragma unroll
+            for (int i = 0; i < kPasses; ++i) {
+                const int off = (i * kWaves * 64 + (tid & ~3)) * 16 + (tid & 3) * 8;
+                xv[i].a[0] = __builtin_amdgcn_raw_buffer_load_b64(rx, off, 0, 0);
+                xv[i].b[0] = __builtin_amdgcn_raw_buffer_load_b64(rx, off + 32, 0, 0);
+            }
+        } else {
+            // table j = activations 4j .. 4j + 3: 16 entries of NP numbers of two bytes; entry 1 << t is activation 4j + t
+            constexpr int kTable = 32 * NP;
+            const uint32_t t_start = (uint32_t)p0 * (uint32_t)(kTablesPerKTile * kTable);
+            const rsrc_t rt = make_rsrc(d.lut_t + t_start, (uint32_t)n_ktiles * (uint32_t)(kTablesPerKTile * kTable) - t_start);
+#pragma unroll
+            for (int i = 0; i < kPasses; ++i) {
+                const int off = ((i * kWaves * 64 + (tid & ~3)) * 2 + (tid & 3)) * kTable;
+                load_table<NP>(rt, off, xv[i].a);
+                load_table<NP>(rt, off + 4 * kTable, xv[i].b);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        Stage<B, 1, Cfg::MPL> st = {};
+        issue_weights<B, 1, GQ, HZ>(st, src, p0 + wave < p1, p0 + wave, lane);
+        __builtin_amdgcn_sched_barrier(0);
+
+        // digits of the piece: lane -> four lanes per 32-column block, sixteen per tile
+        const int n_lanes = (p1 - p0) * (kKTile / 8);
+        bool nonfinite = false;
+#pragma unroll
+        for (int i = 0; i < kPasses; ++i) {
+            if (i * kWaves * 64 >= n_lanes) break;
+            const int j = i * kWaves * 64 + tid, tile = j >> 4;
+            const bool live = j < n_lanes;
+#pragma unroll
+            for (int n = 0; n < NP; ++n) {
+                uint32_t r[4];
+                float step = 1.f;
+                if constexpr (SRC == TokenSource::kTablesI16)
+                    bias_block(xv[i].a[n], xv[i].b[n], r);
+                else
+                    nonfinite |= quantize_block<GQ>(xv[i].a[n], xv[i].b[n], r, step) && live;
+                store_digits<GQ>(r, step, j, live, ld + (uint32_t)((tile * NP + n) * kDigitBytesPerKTile + (j & 15) * 16),
+                                 lm + (uint32_t)(((tile * NP + n) * Cfg::GPT + (j & 15) / (GQ / 8)) * kDigitMetaBytes));
+            }
+        }
+        if constexpr (SRC != TokenSource::kTablesI16)
+            store_lds<uint32_t>(lf + wave * 4, __builtin_amdgcn_ballot_w64(nonfinite) != 0 ? 1u : 0u);
+        __syncthreads();
+
+        // the waves take the tiles in turn
+        for (int t = p0 + wave; t < p1; t += kWaves) {
+            consume_weights_digits<B, GQ, HZ, NP>(st, ld + (uint32_t)((t - p0) * NP * kDigitBytesPerKTile + (lane & 15) * 4),
+                                                  lm + (uint32_t)((t - p0) * NP * Cfg::GPT * kDigitMetaBytes), y);
+            issue_weights<B, 1, GQ, HZ>(st, src, t + kWaves < p1, t + kWaves, lane);
+        }
+        if constexpr (SRC != TokenSource::kTablesI16) {
+            const u32x4 f = load_lds<u32x4>(lf);
+            if (uniform((int)(f.x | f.y | f.z | f.w))) {
+#pragma unroll
+                for (int n = 0; n < NP; ++n) {
+                    auto fetch = [&](int k) -> uint32_t {
+                        if constexpr (SRC == TokenSource::kActivations) return load_global<uint16_t>(d.lut_t, (uint32_t)k * 2u);
+                        else
+                            return load_global<uint16_t>(
+                                d.lut_t, (((uint32_t)(k / kLutGroup) * 16u + (1u << (k % kLutGroup))) * NP + n) * 2u);
+                    };
+                    for (int t = p0 + wave; t < p1; t += kWaves)
+                        y[n] = add_nonfinite<B, GQ, HZ>(src.w + (size_t)t * Cfg::TB, fetch, d.K, t, lane, y[n]);
+                }
+            }
+        }
+        if (NP == 1 || p1 >= k1) break;
+        p0 = p1;
+        __syncthreads();  // the next piece overwrites the digits
+    }
+
+#pragma unroll
+    for (int n = 0; n < NP; ++n) store_lds<float>(lr + ((wave * NP + n) * kRows + lane) * 4, y[n]);
+    __syncthreads();
+    if (wave != 0) return;
+    float factor[NP];
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+        y[n] = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) y[n] += load_lds<float>(lr + ((w * NP + n) * kRows + lane) * 4);
+        factor[n] = 1.f;
+        if constexpr (SRC == TokenSource::kTablesI16)  // the tokens' power-of-two steps, behind the block sums of the tables
+            factor[n] = ldexpf(1.f, uniform(reinterpret_cast<const int*>(d.lut_s + (size_t)n_ktiles * Cfg::GPT * NP * 4)[n]));
+    }
+    finish_rows<NP>(d, rb, seg, n_seg, lane, y, factor);
+}
+
+// ---------------------------------------------------------------------------------------------
+// launch
+
+template <int B, bool HZ, TokenSource SRC, int NP, bool SINGLE, typename Args>
+static int launch_x_group(int group, const Args& a, int n_wg, int max_seg_tiles, hipStream_t st) {
+    const dim3 grid((unsigned)n_wg, __is_same(Args, OrderedArgs) ? 1u : (unsigned)a.n_gemv), block(kWaves * 64);
+    const unsigned lds = x_lds_bytes(max_seg_tiles, NP, kKTile / group);
+    switch (group) {
+        case 32: hipLaunchKernelGGL((mpgemv_x_kernel<B, 32, HZ, SRC, NP, SINGLE, Args>), grid, block, lds, st, a); break;
+        case 64: hipLaunchKernelGGL((mpgemv_x_kernel<B, 64, HZ, SRC, NP, SINGLE, Args>), grid, block, lds, st, a); break;
+        default: hipLaunchKernelGGL((mpgemv_x_kernel<B, 128, HZ, SRC, NP, SINGLE, Args>), grid, block, lds, st, a); break;
+    }
+    return launch_status();
+}
+
+template <TokenSource SRC, bool SINGLE, typename Args>
+static int launch_x_tokens(int np, int bits, int has_zero, int group, const Args& a, int n_wg, int max_seg_tiles, hipStream_t st) {
+    constexpr bool INT = SRC == TokenSource::kTablesI16;
+    if constexpr (SRC != TokenSource::kActivations) {
+        if (!lookups_replaced(bits, np, INT)) return launch_lookups<SINGLE, INT>(np, bits, has_zero, group, a, n_wg, st);
+        if (np == 2) return launch_x_group<4, true, SRC, 2, SINGLE>(group, a, n_wg, max_seg_tiles, st);
+        if constexpr (INT) {
+            if (np == 4) return launch_x_group<4, true, SRC, 4, SINGLE>(group, a, n_wg, max_seg_tiles, st);
+            if (np == 8) return launch_x_group<4, true, SRC, 8, SINGLE>(group, a, n_wg, max_seg_tiles, st);
+        }
+    }
+    if (bits == 1) {
+        return has_zero ? launch_x_group<1, true, SRC, 1, SINGLE>(group, a, n_wg, max_seg_tiles, st)
+                        : launch_x_group<1, false, SRC, 1, SINGLE>(group, a, n_wg, max_seg_tiles, st);
+    }
+    if (bits == 2) return launch_x_group<2, true, SRC, 1, SINGLE>(group, a, n_wg, max_seg_tiles, st);
+    return launch_x_group<4, true, SRC, 1, SINGLE>(group, a, n_wg, max_seg_tiles, st);
+}
+
+// A single GEMV, a numbered batch and a batch on the plain grid from one source of activations.
+template <TokenSource SRC>
+static int launch_x_single(const Layout& L, int N, const void* packed, const void* x, void* y, void* workspace, hipStream_t st) {
+    KernelArgs<true> a;
+    fill_desc(a.single, L, packed, x, N, y, workspace);
+    a.n_gemv = 1;
+    a.status = device_status_word();
+    if (!a.status) return TMAN_ERR_LAUNCH;
+    const GemvPlan p = plan_decode(L, N);
+    return launch_x_tokens<SRC, true>(p.np, L.bits, L.has_zero, L.group, a, p.n_workgroups, p.seg_tiles, st);
+}
+template <TokenSource SRC>
+static int launch_x_batch(const DecodeBatch& b, hipStream_t st) {
+    if (b.order) {
+        OrderedArgs a;
+        a.descs = b.descs;
+        a.order = b.order;
+        a.n_gemv = b.n_gemv;
+        return launch_x_tokens<SRC, false>(padded_tokens(b.N), b.bits, b.has_zero, b.group, a, b.n_workgroups, b.max_seg_tiles, st);
+    }
+    KernelArgs<false> a;
+    a.descs = b.descs;
+    a.n_gemv = b.n_gemv;
+    return launch_x_tokens<SRC, false>(padded_tokens(b.N), b.bits, b.has_zero, b.group, a, b.n_workgroups, b.max_seg_tiles, st);
+}
+
+}  // namespace tman

@@ -5,9 +5,9 @@ Headline (the benchmark spec metric, configs[1]): decode mpGEMV weight GB/s on the 7B
 uint2 weights, group 64, N = 1.  One step = one token through a 32-layer decoder built from that layer
 set: 32 launches, one per layer, each layer with packed weights of its own (2 GB in all, so the 256 MB
 Infinity Cache cannot serve them).  A launch takes the layer's activations in and gives its outputs: the
-lookup-table precompute and the five table-lookup GEMVs (qkv, o, gate, up, down) run in one kernel whose
-workgroups build the tables of their own K segment (the two-launch form, a table kernel followed by a
-lookup kernel, is timed beside it).  All inputs are resident in HBM before timing.
+activation digits and the five GEMVs (qkv, o, gate, up, down) run in one kernel whose
+workgroups make the digits of their own K segment (the two-launch form, a table kernel followed by a
+kernel that reads the tables, is timed beside it).  All inputs are resident in HBM before timing.
 
 The same JSON line carries: the error of the timed configuration against the fp64 CPU oracle; the prefill
 mpGEMM figure (11008 x 4096 uint4 g64, N = 1024) with its error; `configs`, every other BASELINE
@@ -116,7 +116,7 @@ def decode_job(torch, tman, synth, dev, w, N, n_inst):
     Ks = [w.layers[li0].K for li0 in act_layer0]
     lut_calls = [tman.bound_build_lut_batch(xs[inst], N, Ks, w.group, luts) for inst in range(n_inst)]
     gemv_calls = [tman.bound_mpgemv_batch_run(shapes, N, descs[inst]) for inst in range(n_inst)]
-    # one token: the lookup kernel can build its tables itself, which makes the step a single launch
+    # one token: the kernel can take the activations themselves, which makes the step a single launch
     x_calls, x_descs = None, []
     if N == 1:
         for inst in range(n_inst):
@@ -418,7 +418,7 @@ def main():
     events = []
 
     # One step = one token through a 32-layer decoder of this layer set: the 32 copies in turn, one launch each
-    # (activations in, outputs out: the table precompute and the lookups of all five GEMVs of a layer set).
+    # (activations in, outputs out: the digits and the integer products of all five GEMVs of a layer set).
     launches_per_step = n_inst
 
     def launch(j, record):
@@ -459,7 +459,7 @@ def main():
     weight_bytes_per_step = weight_bytes_per_launch * launches_per_step
     value = weight_bytes_per_step / sec_per_step / 1e9
 
-    # dominant kernel: the table-lookup GEMV (one launch per step covers the whole layer set); its average
+    # dominant kernel: the one-token GEMV (one launch per step covers the whole layer set); its average
     # launch duration comes from the HIP events that cut the timed region into runs of launches
     runs = [(i1 - i0, e0.elapsed_time(e1)) for (i0, e0), (i1, e1) in zip(events[:-1], events[1:])]
     n_launch = sum(n for n, _ in runs)
@@ -497,8 +497,8 @@ def main():
         "config": {"workload": f"{w.name}: decode of one token (N=1) through {n_inst} layers of the 7B-style layer set "
                                f"(qkv 12288x4096, o 4096x4096, gate/up 11008x4096, down 4096x11008), uint{w.bits} "
                                f"g{w.group}, every layer with weights of its own ({weight_bytes_per_step / 1e9:.2f} GB per "
-                               f"step); one launch per layer: every workgroup builds the lookup tables of its K "
-                               f"segment from the layer's {len(acts)} activations, then does its lookups",
+                               f"step); one launch per layer: every workgroup makes the 4-bit digits of its K "
+                               f"segment from the layer's {len(acts)} activations, then its integer products",
                    "launches_per_step": launches_per_step, "us_per_launch": round(sec_per_step / launches_per_step * 1e6, 3),
                    "weight_bytes_per_step": int(weight_bytes_per_step), "frac_of_hbm_peak": round(value / HBM_PEAK_GBS, 4),
                    "codes_only_GBs": round(value * codes_bytes / weight_bytes_per_step, 1), **context},

@@ -21,7 +21,7 @@
  * statistical statement, about five standard deviations of the rounding noise the method itself fixes
  * (16-bit table entries or fp16 weights, Sec. 4.1 / 4.3: rms 2-3e-4 of rms(y), one token less; the fp16 result: up to
  * 4.9e-4), not a hard bound: among 1500 random shapes one output in 52,000 of one case reached 2.07e-3,
- * and a token whose one or two outputs cancel to nearly zero can exceed it.  In tman_mpgemm a dequantized
+ * and a token whose one or two outputs cancel to nearly zero can exceed it.  In tman_mpgemm (N > 32) a dequantized
  * weight may differ from fp16((code - zero) * scale) by one fp16 step (about 5 % do: the constant
  * (1024 + zero) * scale is rounded to fp32 before the single rounding to fp16).  The integer paths state their
  * own bounds.
@@ -120,7 +120,7 @@ int tman_build_lut_batch(int32_t count, const void *const *x, int32_t N, const i
  *   y[n][m] = sum_G scale[m][G] * ( sum_i 2^i sum_{j in G} T[n][j][idx_i[m][j]] - zero[m][G] * S[n][G] )
  * where idx_i[m][j] is the 4-bit pattern of bit-plane i over weights 4j..4j+3 (sign form:
  * scale * (2 * sum_j T - S)).  fp16 table entries, fp32 accumulation, fp16 result.
- * For N = 1 the kernel is that of tman_mpgemv_x below: it takes the activations out of the tables (T[j][1 << t] is
+ * For N = 1 (and N = 2 with 4-bit weights) the kernel is that of tman_mpgemv_x below: it takes the activations out of the tables (T[j][1 << t] is
  * x[4j + t]) and sums integer products, which rounds less than adding fp16 table entries does.
  *   packed    : from tman_pack_weights for the same shape
  *   lut       : from tman_build_lut(x, N, shape->K, shape->group)
@@ -174,7 +174,8 @@ int tman_mpgemv_batch_run(int32_t count, const tman_shape_t *shapes, int32_t N, 
  *                        aligned): int16 entries laid out as the fp16 tables, int32 block sums, int32 e[n].
  *                        The _batch form follows tman_build_lut_batch.
  *   tman_mpgemv_i16    : arguments, workspace rules and determinism of tman_mpgemv, `lut` from tman_build_lut_i16
- *                        (N = 1 goes to the kernel of tman_mpgemv_x, which takes xq out of the tables: same integers).
+ *                        (N = 1, and 4-bit weights for any N, go to the kernel of tman_mpgemv_x, which takes xq out of
+ *                        the tables: same integers).
  *   tman_mpgemv_i16_batch_run : launches a batch whose descriptor table tman_mpgemv_batch_prepare wrote with
  *                        integer table buffers in `lut` (the two table buffers have the same geometry).
  */
@@ -244,7 +245,8 @@ int tman_device_status(void *stream);
  * mpGEMM on the matrix cores (Sec. 4.1 "Fused LUT-based dequantization", Sec. 4.2): bit-planes are repacked to
  * codes (level 1), each code is looked up in its quantization block's table
  * D[c] = fp16((c - zero) * scale) (level 2; sign form fp16((2c - 1) * scale)), and the fp16 weights
- * feed the matrix cores with fp32 accumulation.
+ * feed the matrix cores with fp32 accumulation (N <= 32, most formats: the codes feed them, exact, and scale and zero are
+ * applied in fp32 to the sums of a quantization block).
  *   x : fp16 [N][K], any N >= 1;   y : fp16 [N][M]
  * Two kernels share the call.  N > TMAN_MAX_SMALL_TOKENS runs the tiled prefill kernel (256 tokens per
  * workgroup, bound by the matrix cores; it needs no workspace).  1 <= N <= TMAN_MAX_SMALL_TOKENS runs a kernel

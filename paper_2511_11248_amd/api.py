@@ -375,7 +375,7 @@ def tman_mpgemv_batch_run(shapes, N: int, desc, stream=None) -> None:
 
 
 def tman_mpgemv_x(shape: Shape, packed, x, y, workspace, stream=None) -> None:
-    """y fp16 [M] = x fp16 [K] * dequant(W)^T for one token; the lookup kernel builds its tables itself."""
+    """y fp16 [M] = x fp16 [K] * dequant(W)^T for one token, from the activations in one launch."""
     wb = 0 if workspace is None or isinstance(workspace, int) else _nbytes(workspace)
     _check(_load().tman_mpgemv_x(C.byref(shape.c()), _ptr(packed), _ptr(x), _ptr(y), _ptr(workspace), wb,
                                  _stream(stream)), "tman_mpgemv_x")
@@ -393,7 +393,7 @@ def tman_mpgemv_x_batch_order(shapes, n_units: int = 0):
 
 
 def tman_mpgemv_x_batch_prepare(shapes, packed, xs, y, workspace, desc, stream=None) -> None:
-    """Descriptor table for a batch of one-token GEMVs that build their own tables (xs entries may repeat)."""
+    """Descriptor table for a batch of one-token GEMVs that take the activations themselves (xs entries may repeat)."""
     n, cs, pk, xx, yy, ws, wb = _batch_arrays(shapes, packed, xs, y, workspace)
     _check(_load().tman_mpgemv_x_batch_prepare(n, cs, pk, xx, yy, ws, wb, _ptr(desc), _stream(stream)),
            "tman_mpgemv_x_batch_prepare")

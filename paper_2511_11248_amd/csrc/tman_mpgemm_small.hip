@@ -257,7 +257,7 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemm_small_kernel(Args a) {
 // / 8 rounded up).  Level 1 leaves weights k and k + 16 of a 32-column step in the halves of one register; the
 // activations are paired to match (8 v_perm per step).  S comes from a third product, of the activations with ones, in the
 // accumulators' own layout (summing it ahead, once per workgroup, put 3 to 6 us in front of every workgroup).
-// 263 vector instructions per tile block for uint4 g128 and 8 tokens.  What bounds it now: registers for three waves per
+// About 263 vector instructions per tile block in the loop for uint4 g128 and 8 tokens.  What bounds it now: registers for three waves per
 // SIMD (two tiles in flight: 5 % better than one; with two waves per SIMD it loses 15 %), so latency, then the
 // vector pipe; 107.5 MB (7B uint4 g128, N = 8) in 29 us = 3.7 TB/s, from 34.5 us.
 // The offset: 64 for 4 bits (a nibble at mantissa bits 4..7 needs three shifts per code word; at bits 6..9, as 16 + c, it

@@ -1,5 +1,5 @@
-// Decoding mpGEMV of ONE token: tman_mpgemv_x (activations in), and tman_mpgemv / tman_mpgemv_i16 for one token
-// (tables in).
+// Decoding mpGEMV on the 4-bit dot product unit: tman_mpgemv_x (one token, activations in), and tman_mpgemv /
+// tman_mpgemv_i16 (tables in) for one token and, where it is faster, for two to eight (lookups_replaced).
 //
 // y[m] = sum_G scale[m][G] * (sum_{k in G} q[m][k] x[k] - zero[m][G] * S[G]) (Sec. 2.2).  The lookups of Sec. 4.3 turn
 // the inner sum into one table read per 4 weights and bit-plane; on this chip that costs 2.6 vector instructions and

@@ -191,11 +191,11 @@ int tman_mpgemv_i16_batch_run(int32_t count, const tman_shape_t *shapes, int32_t
  * Decoding mpGEMV of ONE token from the activations themselves, in one launch (Sec. 2.2; the lookups of Sec. 4.3 cost
  * more vector instructions on this hardware than the sums they replace, and Sec. 5's separate precompute costs a
  * kernel boundary).  Every workgroup turns the activations of its own K segment (at most 4096 columns) into fixed-point
- * numbers: every quantization block gets the smallest power-of-two step 2^e with max |x| / 2^e < 2^14, and
+ * numbers: every quantization block gets the smallest power-of-two step 2^e with max |x| / 2^e <= 30583, and
  * X = round_to_nearest_even(x / 2^e) is written with four signed 4-bit digits, whose products with the codes the dot
  * product unit sums exactly:
  *   y[m] = sum_G 2^e[G] * scale[m][G] * ( sum_{k in G} q[m][k] X[k] - zero[m][G] * sum_{k in G} X[k] )
- * (sign form: 2^e * scale * (2 sum q X - sum X)), scales applied in fp32, fp16 result.  Activations within a factor 16
+ * (sign form: 2^e * scale * (2 sum q X - sum X)), scales applied in fp32, fp16 result.  Activations within a factor 14
  * of their block's largest enter unrounded.  Infinities and NaN are kept out of the integers and added as
  * (q - zero) * scale * x.
  *   x         : fp16 [K], device, 16-byte aligned

@@ -7,11 +7,13 @@
 // lookup kernel was bound by vector issue.  Here a block of 32 weights costs its bit transposition (17 instructions
 // for 4-bit codes, 10 for 2-bit ones) and 16 dot products: 1.03 and 0.81 instructions per weight, no gather from LDS.
 //
-// Digits.  Every quantization block gets a power-of-two step 2^e, the smallest for which all |x| / 2^e < 2^14;
-// X = round_to_nearest_even(x / 2^e) fits 15 bits and is written with four digits d_i in -8 .. 7, X = sum 16^i d_i
-// (the nibbles of X + 0x8888, each exclusive-or 8).  Against fp16 table entries, which round every sum of four
-// activations to 11 bits, only activations below 1/16 of their block's largest are rounded at all.  All products and
-// sums inside a block are exact integers (|sum| < 2^14 * 15 * 128 < 2^25).
+// Digits.  Every quantization block gets a power-of-two step 2^e, the smallest for which all |x| / 2^e <= 30583, the
+// largest number that four digits d_i in -8 .. 7 hold: X = round_to_nearest_even(x / 2^e) = sum 16^i d_i (the nibbles
+// of X + 0x8888, each exclusive-or 8).  Against fp16 table entries, which round every sum of four activations to 11
+// bits, only activations below 1/14 of their block's largest are rounded at all.  (With |x| / 2^e < 2^14, a step twice
+// as large for seven maxima out of eight, blocks of 128 with channels of 100 to 1000 times the others came out up to 4 %
+// worse than through fp16 tables: rms error 3.4e-4 to 3.5e-4 of rms(y) for all formats; now 2.5e-4.)  All products and
+// sums inside a block are exact integers (|sum| <= 30583 * 15 * 128 < 2^26).
 //
 // Order.  The bit transposition leaves weight 4f + o of a 32-weight block in field f of word o, so digit word
 // (o, i) holds digit i of activations 4f + o.  A block's 16 digit words are read from LDS by ONE ds_read_b32 per
@@ -157,11 +159,13 @@ __device__ __forceinline__ bool quantize_block(const u32x2& xa, const u32x2& xb,
         }
         mx = largest();
     }
-    // exponent field eb of the block's largest magnitude (subnormals: 1): |x| < 2^(eb - 14), step 2^(eb - 28)
-    const uint32_t eb = max(max_over_lanes<GQ / 8>(mx) >> 10, 1u);
-    const float up = __builtin_bit_cast(float, (155u - eb) << 23);  // 2^(28 - eb)
-    step = __builtin_bit_cast(float, (99u + eb) << 23);             // 2^(eb - 28)
-    // x * 2^(28 - eb) rounded to an integer by adding 1.5 * 2^23: the low 16 bits of the sum are X (+ 0x8888)
+    // The block's largest magnitude is (1024 + f) * 2^(e - 25), e its exponent field: 16 (1024 + f) steps of 2^(e - 29)
+    // if that is at most 30583, f <= 887, else 8 (1024 + f) steps twice as large.  Adding 136 = 1023 - 887 to the bit
+    // pattern carries into the exponent in the second case: step 2^(eb - 29) (subnormals: that of e = 1).
+    const uint32_t eb = max((max_over_lanes<GQ / 8>(mx) + 136u) >> 10, 1u);
+    const float up = __builtin_bit_cast(float, (156u - eb) << 23);  // 2^(29 - eb)
+    step = __builtin_bit_cast(float, (98u + eb) << 23);             // 2^(eb - 29)
+    // x * 2^(29 - eb) rounded to an integer by adding 1.5 * 2^23: the low 16 bits of the sum are X (+ 0x8888)
     constexpr float kMagic = 12582912.f + 34952.f;
     uint32_t n[4][2];
 #pragma unroll

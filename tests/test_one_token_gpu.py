@@ -59,6 +59,31 @@ def test_infinities_and_nan(oracle_lib, bits, hz, through_tables):
         assert np.array_equal(y[np.isinf(ref)], ref[np.isinf(ref)])
 
 
+@pytest.mark.parametrize("bits,hz", FORMATS)
+@pytest.mark.parametrize("group,outlier", [(32, 100), (128, 20), (128, 100), (128, 1000)])
+def test_outlier_channels(oracle_lib, group, outlier, bits, hz):
+    """1 % of the channels 20 to 1000 times the others.  The error is that of the fp16 result (a step of the result,
+    uniform: / sqrt(12)) and of the activations below the block's step 2^e, the smallest with max |x| <= 30583 * 2^e (a step,
+    uniform, times the weight).  Both sums have thousands of terms, so their rms is known to a few per cent."""
+    M, K = 1024, 4096
+    q, s, z, _ = rand_case(820 + bits + group, M, K, 1, bits, group, hz)
+    rng = np.random.default_rng(outlier + group)
+    x = rng.standard_normal(K)
+    x[rng.permutation(K)[:K // 100]] *= outlier
+    x = x.astype(np.float16).reshape(1, K)
+    w = ((2.0 * q - 1.0) if z is None else q - z.astype(np.float64).repeat(group, axis=1)) * s.astype(np.float64).repeat(group, axis=1)
+    xd = x[0].astype(np.float64)
+    Y = w @ xd
+    step = np.exp2(np.ceil(np.log2(np.abs(xd).reshape(-1, group).max(axis=1) / 30583.0))).repeat(group)
+    rounded = np.rint(xd / step) != xd / step
+    half = np.exp2(np.maximum(np.floor(np.log2(np.abs(Y) + 1e-30)), -14) - 10)
+    expected = np.sqrt(np.mean(((w * w) @ np.where(rounded, step * step, 0.0) + half * half) / 12.0))
+    shape = tman.Shape(M, K, bits, group, hz)
+    blob = pack(shape, q, s, z)
+    for y in (mpgemv_x(shape, blob, x), mpgemv(shape, blob, x)):
+        assert np.sqrt(np.mean((y[0].astype(np.float64) - Y) ** 2)) <= 1.1 * expected
+
+
 def test_largest_activations_stay_finite(oracle_lib):
     """Four activations of 65504 sum past the largest fp16 number; the integers do not overflow."""
     M, K, bits, group = 64, 256, 4, 128

@@ -1,17 +1,19 @@
 // The decoding kernel on the 4-bit dot product unit, as a template over the weight format, the source of the activations
 // and the number of tokens (padded to 1, 2, 4 or 8); what it does and why is said in tman_mpgemv_x.hip.
 #pragma once
+#include <mutex>
+
 #include "tman_digits_device.h"
 #include "tman_mpgemv_kernel.h"
 
 namespace tman {
 
-// K tiles whose digits are in LDS at a time (a longer segment is worked in such pieces): at most 61 KB
+// K tiles whose digits are in LDS at a time (a longer segment is worked in such pieces): at most 61,440 bytes
 constexpr int piece_tiles(int np) { return np == 8 ? 24 : kGemvXSegmentTiles; }
 
 // LDS of a workgroup whose segment has `seg_tiles` tiles: digit words and `gpt` quantization blocks per tile and token,
-// then the partial sums and a word per wave
-inline unsigned x_lds_bytes(int seg_tiles, int np, int gpt) {
+// then the partial sums and a word per wave: at most 69,648 bytes (8 tokens, 24 tiles, blocks of 32)
+constexpr unsigned x_lds_bytes(int seg_tiles, int np, int gpt) {
     const int tiles = seg_tiles < piece_tiles(np) ? seg_tiles : piece_tiles(np);
     return (unsigned)(tiles * np * (kDigitBytesPerKTile + gpt * kDigitMetaBytes) + kWaves * kRows * np * 4 + kWaves * 4);
 }
@@ -207,16 +209,32 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
 // ---------------------------------------------------------------------------------------------
 // launch
 
+template <int B, int GQ, bool HZ, TokenSource SRC, int NP, bool SINGLE, typename Args>
+static int launch_x_cfg(const Args& a, const dim3& grid, int max_seg_tiles, hipStream_t st) {
+    constexpr unsigned kMostLds = x_lds_bytes(piece_tiles(NP), NP, kKTile / GQ);
+    static_assert(kMostLds <= 160 * 1024, "LDS of a workgroup");
+    if constexpr (kMostLds > 64 * 1024) {  // above what a launch gets without asking
+        static std::once_flag once;
+        static hipError_t attr_rc = hipSuccess;
+        std::call_once(once, [] {
+            attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&mpgemv_x_kernel<B, GQ, HZ, SRC, NP, SINGLE, Args>),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, kMostLds);
+        });
+        if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
+    }
+    hipLaunchKernelGGL((mpgemv_x_kernel<B, GQ, HZ, SRC, NP, SINGLE, Args>), grid, dim3(kWaves * 64),
+                       x_lds_bytes(max_seg_tiles, NP, kKTile / GQ), st, a);
+    return launch_status();
+}
+
 template <int B, bool HZ, TokenSource SRC, int NP, bool SINGLE, typename Args>
 static int launch_x_group(int group, const Args& a, int n_wg, int max_seg_tiles, hipStream_t st) {
-    const dim3 grid((unsigned)n_wg, __is_same(Args, OrderedArgs) ? 1u : (unsigned)a.n_gemv), block(kWaves * 64);
-    const unsigned lds = x_lds_bytes(max_seg_tiles, NP, kKTile / group);
+    const dim3 grid((unsigned)n_wg, __is_same(Args, OrderedArgs) ? 1u : (unsigned)a.n_gemv);
     switch (group) {
-        case 32: hipLaunchKernelGGL((mpgemv_x_kernel<B, 32, HZ, SRC, NP, SINGLE, Args>), grid, block, lds, st, a); break;
-        case 64: hipLaunchKernelGGL((mpgemv_x_kernel<B, 64, HZ, SRC, NP, SINGLE, Args>), grid, block, lds, st, a); break;
-        default: hipLaunchKernelGGL((mpgemv_x_kernel<B, 128, HZ, SRC, NP, SINGLE, Args>), grid, block, lds, st, a); break;
+        case 32: return launch_x_cfg<B, 32, HZ, SRC, NP, SINGLE>(a, grid, max_seg_tiles, st);
+        case 64: return launch_x_cfg<B, 64, HZ, SRC, NP, SINGLE>(a, grid, max_seg_tiles, st);
+        default: return launch_x_cfg<B, 128, HZ, SRC, NP, SINGLE>(a, grid, max_seg_tiles, st);
     }
-    return launch_status();
 }
 
 template <TokenSource SRC, bool SINGLE, typename Args>

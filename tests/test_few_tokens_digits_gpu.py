@@ -48,6 +48,13 @@ def test_integer_tables(oracle_lib, seg_tiles, M, K, group, N):
     assert np.all(np.abs(y - Y) <= 2.0 ** -11 * np.abs(Y) + 64 * (K // group) * 2.0 ** -24 * rms)
 
 
+@pytest.mark.parametrize("N", [5, 8])
+@pytest.mark.parametrize("K", [2944, 3072, 9216])
+def test_segments_that_take_more_than_64_kb_of_lds(oracle_lib, seg_tiles, K, N):
+    """Blocks of 32 and 5 to 8 tokens: 23 and 24 tiles' digits and partial sums are 67,088 and 69,648 bytes."""
+    test_integer_tables(oracle_lib, seg_tiles, 40, K, 32, N)
+
+
 @pytest.mark.parametrize("M,K,group", [(65, 128, 128), (40, 160, 32), (70, 8320, 64)])
 def test_two_tokens_from_fp16_tables(oracle_lib, seg_tiles, M, K, group):
     q, s, z, _ = rand_case(7300 + M + K, M, K, 1, 4, group)

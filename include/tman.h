@@ -126,8 +126,10 @@ int tman_build_lut_batch(int32_t count, const void *const *x, int32_t N, const i
  *   lut       : from tman_build_lut(x, N, shape->K, shape->group)
  *   y         : fp16 [N][M]
  *   workspace : tman_mpgemv_workspace_bytes(shape, N) bytes, 16-byte aligned.  It must be zero-filled
- *               once before its first use; every call leaves it ready for the next one.  Calls that
- *               may overlap in time need separate workspaces.
+ *               once before its first use; every call leaves it ready for the next one with the same number of
+ *               row blocks, (M + 63) / 64 (its tickets, one per row block, are back at zero; behind them lie
+ *               partial sums, so it is zero-filled again before a call with another M).  Calls that may
+ *               overlap in time need separate workspaces.
  * Deterministic: the same inputs give bit-identical outputs on every call.
  */
 int tman_mpgemv(const tman_shape_t *shape, const void *packed, const void *lut, int32_t N, void *y, void *workspace,
@@ -318,16 +320,17 @@ int32_t tman_mpgemm_i8_token_blocks(const tman_shape_t *shape, int32_t N);
 /*
  * tman_mpgemv for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same arguments, kernels and results as tman_mpgemv, but the
- * workspace (tickets and partial sums of the K segments) is a fixed array of TMAN_NOALLOC_SCRATCH_BYTES in
- * device memory that the library owns (each GPU the library runs on holds it until the process ends).  The
+ * workspace (tickets and partial sums of the K segments) is a fixed array in device memory that the library
+ * owns, with room for TMAN_NOALLOC_SCRATCH_BYTES (each GPU the library runs on holds it until the process ends).  The
  * call allocates and frees nothing.
  *   - shapes / N whose tman_mpgemv_workspace_bytes exceeds TMAN_NOALLOC_SCRATCH_BYTES are refused with
  *     TMAN_ERR_WORKSPACE (nothing is launched);
  *   - every call on a GPU uses that GPU's one array: calls that may overlap in time on one GPU (different
  *     streams, or several host threads) race and must be serialised by the caller, or use tman_mpgemv
  *     with workspaces of their own;
- *   - the array keeps what the last call left: the tickets are back at zero after every call, the partial
- *     sums are overwritten before they are read, so nothing is cleared between calls.
+ *   - the array keeps what the last call left, of whatever shape: the tickets of all shapes lie apart from the
+ *     partial sums and are back at zero after every call, the sums are overwritten before they are read, so nothing
+ *     is cleared between calls.
  * tman_noalloc_init resolves the array's device address on the CURRENT device (the first
  * tman_mpgemv_noalloc call on a device does the same); call it once per device at set-up, outside any graph
  * capture.  Both return TMAN_ERR_LAUNCH when the HIP runtime cannot provide the address.

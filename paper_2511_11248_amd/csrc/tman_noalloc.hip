@@ -11,7 +11,14 @@
 
 namespace tman {
 
-static __device__ __align__(256) unsigned char scratch[TMAN_NOALLOC_SCRATCH_BYTES];
+// A call's workspace is its tickets (one per row block), then its partial sums.  Calls of different shapes share the
+// array, so the partial sums of all of them start at the same byte and the tickets lie before it: a ticket is never a
+// byte that another shape used for sums (with the tickets at the array's start, a shape with more row blocks found sums
+// in its tickets, and its y was left unwritten).  Tickets are used when K has at least two segments, whose sums take at
+// least 512 bytes per row block; the region holds the tickets of all such shapes that the sums' limit admits.
+constexpr size_t kTicketRegion = (size_t)TMAN_NOALLOC_SCRATCH_BYTES / (2 * kRows * sizeof(float)) * sizeof(int32_t);
+static_assert(kTicketRegion % 256 == 0, "partial sums stay aligned");
+static __device__ __align__(256) unsigned char scratch[kTicketRegion + TMAN_NOALLOC_SCRATCH_BYTES];
 
 constexpr int kMaxDevices = 64;
 static std::mutex scratch_mutex;
@@ -56,9 +63,12 @@ int tman_mpgemv_noalloc(const tman_shape_t* shape, const void* packed, const voi
     void* ws = nullptr;
     rc = scratch_on_current_device(&ws);
     if (rc != TMAN_OK) return rc;
-    // The tickets at the start of the array are zero when the library is loaded and every call returns them
-    // to zero; the partial sums are written before they are read.  Nothing needs clearing between calls.
-    return launch_mpgemv(make_layout(shape), packed, lut, N, y, ws, (hipStream_t)stream);
+    // The tickets are zero when the library is loaded and every call returns them to zero; the partial sums are
+    // written before they are read.  Nothing needs clearing between calls.
+    const Layout L = make_layout(shape);
+    const size_t tickets = plan_decode(L, N).ticket_bytes;  // (more than the region only when K is one segment: unused)
+    if (tickets <= kTicketRegion) ws = static_cast<uint8_t*>(ws) + (kTicketRegion - tickets);
+    return launch_mpgemv(L, packed, lut, N, y, ws, (hipStream_t)stream);
 }
 
 }  // extern "C"

@@ -39,6 +39,19 @@ def test_two_calls_in_a_row_the_second_smaller(oracle_lib):
         assert oracle.row_relative_error(y_na, oracle.matmul(q, s, z, x, bits, group)).max() <= TOL
 
 
+@pytest.mark.parametrize("N", [1, 2, 8])
+def test_more_row_blocks_after_fewer(oracle_lib, N):
+    """The last shape has tickets where the others' partial sums would lie if they began right behind their own
+    tickets (256 bytes for up to 64 row blocks); all cut K into segments."""
+    for M, K, seed in [(64, 11008, 74), (2048, 4224, 75), (4352, 4224, 76)]:
+        shape = tman.Shape(M, K, 4, 64)
+        assert tman.tman_mpgemv_workspace_bytes(shape, N) <= 2 * 1024 * 1024
+        q, s, z, x = rand_case(seed, M, K, N, 4, 64)
+        y_ws, y_na = _both(shape, q, s, z, x)
+        assert np.array_equal(y_ws.view(np.uint16), y_na.view(np.uint16))
+        assert oracle.row_relative_error(y_na, oracle.matmul(q, s, z, x, 4, 64)).max() <= TOL
+
+
 def test_repeated_calls_are_identical_and_oversized_shapes_are_refused(oracle_lib):
     M, K, bits, group, N = 200, 9000 // 64 * 64, 4, 64, 8
     shape = tman.Shape(M, K, bits, group)

@@ -283,22 +283,37 @@ __device__ __forceinline__ void codes_to_half_pairs(const uint32_t (&p)[B], uint
     }
 }
 
-// The lane's row of tile block t times the activations of one token, weight by weight.
+// The lane's row of tile block t (in `st`) times the activations of one token (row x), weight by weight.
 template <int B, int GQ, bool HZ>
-__device__ __forceinline__ float add_products(const uint8_t* tile, const uint8_t* x, int K, int t, int lane, float sum) {
+__device__ __forceinline__ float add_products(const Stage<B, 1, GemvCfg<B, 1, GQ, HZ>::MPL>& st, const uint8_t* x, int K, int t,
+                                              int lane, float sum) {
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
-#pragma unroll 1
-    for (int k = t * kKTile; k < min((t + 1) * kKTile, K); ++k) {
-        const int b = (k % kKTile) / 32;
-        const int v = (b * 32) / Cfg::CH, ksub = ((b * 32) % Cfg::CH) / 32;
-        uint32_t c = 0;
+    uint32_t xv[2];  // lane l holds columns l and 64 + l of the tile
 #pragma unroll
-        for (int i = 0; i < B; ++i)
-            c |= ((load_global<uint32_t>(tile, v * 1024 + lane * 16 + (ksub * B + i) * 4) >> (k % 32)) & 1u) << i;
-        const uint32_t mo = B * 1024 + lane * Cfg::MPL + ((k % kKTile) / GQ) * Cfg::MSZ;
-        const float sc = half_bits_to_float(load_global<uint16_t>(tile, mo));
-        const float wt = HZ ? ((float)c - half_bits_to_float(load_global<uint16_t>(tile, mo + 2))) * sc : (2.f * (float)c - 1.f) * sc;
-        sum += wt * half_bits_to_float(load_global<uint16_t>(x, (uint32_t)k * 2u));
+    for (int i = 0; i < 2; ++i) {
+        const int k = t * kKTile + i * 64 + lane;
+        xv[i] = k < K ? load_global<uint16_t>(x, (uint32_t)k * 2u) : 0u;
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        if (t * kKTile + b * 32 >= K) break;  // (uniform)
+        const int v = (b * 32) / Cfg::CH, ksub = ((b * 32) % Cfg::CH) / 32;
+        uint32_t p[B], c[4];
+#pragma unroll
+        for (int i = 0; i < B; ++i) p[i] = word_of(st.c[v], ksub * B + i);
+        planes_to_codes<B>(p, c);
+        const int mo = (b * 32 / GQ) * Cfg::MSZ;
+        const uint32_t mw = (mo % 4) ? st.meta[mo / 4] >> 16 : st.meta[mo / 4];
+        const float sc = half_bits_to_float(mw & 0xffffu), z = HZ ? half_bits_to_float(mw >> 16) : 0.f;
+#pragma unroll 1
+        for (int f = 0; f < 8; ++f) {
+#pragma unroll
+            for (int o = 0; o < 4; ++o) {  // weight 4f + o is field f of word o
+                const float code = (float)((c[o] >> (4 * f)) & ((1u << B) - 1u));
+                const float wt = HZ ? (code - z) * sc : (2.f * code - 1.f) * sc;
+                sum += wt * half_bits_to_float((uint32_t)__builtin_amdgcn_readlane((int)xv[b / 2], (b % 2) * 32 + 4 * f + o));
+            }
+        }
     }
     return sum;
 }
@@ -444,20 +459,36 @@ __global__ void __launch_bounds__(kWaves * 64, 3) mpgemm_codes_kernel(Args a) {
     }
 
     // the four quarters of the segment meet in LDS, [wave][token][row]
-    if (__builtin_amdgcn_ballot_w64(check != check) == 0) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int v = 0; v < 4 * NT; ++v)
-                store_lds<float>(lr + ((wave * kTok + 8 * (v / 4) + 4 * (lane >> 5) + v % 4) * kRedStride + 32 * h + (lane & 31)) * 4,
-                                 y[h][v]);
-    } else {
-        // An infinity times (off + c) less an infinite sum is always NaN: tiles with an activation that is not finite are
-        // summed again weight by weight, (c - z) s x in fp32, lane = row.
-        for (int n = 0; n < N; ++n) {
+        for (int v = 0; v < 4 * NT; ++v)
+            store_lds<float>(lr + ((wave * kTok + 8 * (v / 4) + 4 * (lane >> 5) + v % 4) * kRedStride + 32 * h + (lane & 31)) * 4,
+                             y[h][v]);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(check != check) != 0, 0)) {
+        // An infinity times (off + c) less an infinite sum is always NaN: the tokens with an activation that is not finite
+        // in this wave's tiles, whose sums are not finite in any row, are summed again weight by weight, (c - z) s x
+        // in fp32, lane = row; the others keep their sums.  One infinity in 8 tokens makes four launches of a 7B layer
+        // set (uint4 g128) 235 instead of 121 us (5.8 ms when every token was summed again, a bit and a column at a
+        // time; 146 in the kernel above, which needs no second sum).  (A wave's LDS stores are executed in order.)
+        uint32_t again = 0;
+#pragma unroll
+        for (int v = 0; v < 4 * NT; ++v) {
+            const uint64_t m = __builtin_amdgcn_ballot_w64(!(fabsf(y[0][v]) < __builtin_inff()));
+            again |= (m & 0xffffffffu ? 1u << (8 * (v / 4) + v % 4) : 0u) | (m >> 32 ? 1u << (8 * (v / 4) + 4 + v % 4) : 0u);
+        }
+#pragma unroll 1
+        for (; again; again &= again - 1) {
+            const int n = __builtin_ctz(again);
+            const uint8_t* const x = d.lut_t + (size_t)n * K * 2;
             float sum = 0.f;
-            for (int t = t0; t < k1; t += kWaves)
-                sum = add_products<B, GQ, HZ>(src.w + (size_t)t * Cfg::TB, d.lut_t + (size_t)n * K * 2, K, t, lane, sum);
+            issue_weights<B, 1, GQ, HZ>(stg[0], src, t0 < k1, t0, lane);
+#pragma unroll 1
+            for (int t = t0; t < k1; t += kWaves) {
+                const auto st = stg[0];
+                issue_weights<B, 1, GQ, HZ>(stg[0], src, t + kWaves < k1, t + kWaves, lane);
+                sum = add_products<B, GQ, HZ>(st, x, K, t, lane, sum);
+            }
             store_lds<float>(lr + ((wave * kTok + n) * kRedStride + lane) * 4, sum);
         }
     }

@@ -50,6 +50,22 @@ def test_infinities_and_nan(oracle_lib, group, N, bits, hz):
     assert oracle.row_relative_error(y[ok], ref[ok]).max() <= 1e-3
 
 
+@pytest.mark.parametrize("bits,hz", FORMATS)
+@pytest.mark.parametrize("group,N", [(32, 8), (64, 16), (128, 32)])
+def test_one_bad_sequence_leaves_the_others_alone(oracle_lib, group, N, bits, hz):
+    """The tokens without infinities come out with the same bits as in a batch that has none."""
+    M, K = 66, 5760  # two segments
+    q, s, z, x = rand_case(6700 + bits, M, K, N, bits, group, hz)
+    shape = tman.Shape(M, K, bits, group, hz)
+    blob = pack(shape, q, s, z)
+    clean = mpgemm(shape, blob, x)
+    x[1, 70], x[1, 5000] = np.inf, np.nan
+    y = mpgemm(shape, blob, x)
+    assert np.isnan(y[1].astype(np.float64)).all()
+    others = np.arange(N) != 1
+    assert np.array_equal(y[others].view(np.uint16), clean[others].view(np.uint16))
+
+
 def test_next_token_does_not_leak_through_the_last_tile(oracle_lib):
     """K ends inside a tile: the columns beyond it are the next token's in memory."""
     M, K, bits, group, N = 64, 160, 4, 32, 4

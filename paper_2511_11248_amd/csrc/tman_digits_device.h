@@ -117,8 +117,15 @@ __device__ __forceinline__ int sum_of_digits(const uint32_t (&w)[4]) {
     return s;
 }
 
-// The sums of the four digits, put together.
-__device__ __forceinline__ int join_digits(const int (&acc)[4]) { return (((((acc[3] << 4) + acc[2]) << 4) + acc[1]) << 4) + acc[0]; }
+// The sums of the four digits, put together (modulo 2^32): three shift-adds (left to itself the compiler makes two shifts,
+// a shift-add and an addition of three).
+__device__ __forceinline__ uint32_t join_digits(const int (&acc)[4]) {
+    uint32_t s = ((uint32_t)acc[3] << 4) + (uint32_t)acc[2];
+    asm("" : "+v"(s));
+    s = (s << 4) + (uint32_t)acc[1];
+    asm("" : "+v"(s));
+    return (s << 4) + (uint32_t)acc[0];
+}
 
 // Numbers of a quad of lanes -> digits in LDS.  Lane f (of 4) of a quad holds of one 32-weight block, in r[o], number
 // 4f + o (low half) and 16 + 4f + o (high half), as X + 0x8888.  The lane's four words of the block go to `ld`, and the
@@ -193,30 +200,46 @@ __device__ __forceinline__ void bias_block(const u32x2& xa, const u32x2& xb, uin
 
 // Codes times activations of one tile block for the lane's row.  `dbase` is the LDS address of the tile's digit words
 // plus 4 (lane % 16), `mbase` of its blocks' records; token n's follow at n * 256 and n * GPT * 16.  The codes are made
-// once for all tokens.
-template <int B, int GQ, bool HZ, int NP>
+// once for all tokens.  One token: the accumulators run on over blocks and tiles, and a block's sum is what they gained
+// (`before`: their joined value so far; integers modulo 2^32), one subtraction instead of clearing four registers per
+// block (with more tokens they would be kept too long: 203 to 232 registers for 8 tokens instead of 157 to 159).
+// Vector instructions per tile for 1 bit, blocks of 32 / 64: 147 -> 127, 121 -> 111 (with the shorter join_digits and the
+// scale read as fp16 by the multiplication).
+// `next` requests the wave's next tile: when this one is done, into its stage, or (1 bit) before the wait for this one, into
+// another stage.
+template <int B, int GQ, bool HZ, int NP, typename Next>
 __device__ __forceinline__ void consume_weights_digits(const Stage<B, 1, GemvCfg<B, 1, GQ, HZ>::MPL>& s, uint32_t dbase,
-                                                       uint32_t mbase, float (&y)[NP]) {
+                                                       uint32_t mbase, int (&acc)[NP][4], uint32_t (&before)[NP],
+                                                       float (&y)[NP], Next next) {
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
+    static_assert(NP == 1 || B == 4, "several tokens: 4 bits");
     constexpr int BPG = GQ / 32;  // 32-weight blocks per quantization block
     uint32_t dg[NP][4];
-    u32x4 gm[NP][Cfg::GPT];
+    // a block's record: (sum of X, step), and 8 * sum for 4 bits.  (Of a 16-byte read whose last words nobody uses the
+    // compiler lets the next read overwrite those, and waits for each.)
+    typedef std::conditional_t<B == 4, u32x4, u32x2> record_t;
+    record_t gm[NP][Cfg::GPT];
     if constexpr (NP == 1) {  // (more tokens: read where they are used, to bound the registers)
 #pragma unroll
         for (int b = 0; b < 4; ++b) dg[0][b] = load_lds<uint32_t>(dbase + b * 64);
 #pragma unroll
-        for (int gi = 0; gi < Cfg::GPT; ++gi) gm[0][gi] = load_lds<u32x4>(mbase + gi * kDigitMetaBytes);
+        for (int gi = 0; gi < Cfg::GPT; ++gi) gm[0][gi] = load_lds<record_t>(mbase + gi * kDigitMetaBytes);
+    }
+    constexpr bool kEarly = B == 1 && NP == 1;
+    if constexpr (kEarly) {
+        next();
+        __builtin_amdgcn_sched_barrier(0);  // (digits and the next tile are requested before the wait for this one)
     }
 #pragma unroll
     for (int gi = 0; gi < Cfg::GPT; ++gi) {
-        int acc[NP][4];
 #pragma unroll
-        for (int n = 0; n < NP; ++n) {
-            if constexpr (NP > 1) gm[n][gi] = load_lds<u32x4>(mbase + (n * Cfg::GPT + gi) * kDigitMetaBytes);
-            const uint32_t sum8 = gm[n][gi].z;
-            acc[n][0] = B == 4 ? (int)sum8 : 0;  // 4 bits: fields hold code - 8
-            acc[n][1] = acc[n][2] = acc[n][3] = 0;
-        }
+        for (int n = 0; n < NP; ++n)
+            if constexpr (NP > 1) {
+                gm[n][gi] = load_lds<record_t>(mbase + (n * Cfg::GPT + gi) * kDigitMetaBytes);
+                const uint32_t sum8 = gm[n][gi].z;
+                acc[n][0] = (int)sum8;  // 4 bits: fields hold code - 8
+                acc[n][1] = acc[n][2] = acc[n][3] = 0;
+            }
 #pragma unroll
         for (int b = gi * BPG; b < (gi + 1) * BPG; ++b) {
             const int v = (b * 32) / Cfg::CH, ksub = ((b * 32) % Cfg::CH) / 32;
@@ -237,8 +260,15 @@ __device__ __forceinline__ void consume_weights_digits(const Stage<B, 1, GemvCfg
         for (int n = 0; n < NP; ++n) {
             const uint32_t gs_w = gm[n][gi].x, step_w = gm[n][gi].y;  // (copied out before the casts)
             const float gs = __builtin_bit_cast(float, gs_w), step = __builtin_bit_cast(float, step_w);
-            const float a = (float)join_digits(acc[n]);
-            const float sc = scale * step;
+            uint32_t own = join_digits(acc[n]);
+            if constexpr (NP == 1) {
+                const uint32_t now = own;
+                own -= before[n];
+                before[n] = now;
+                if constexpr (B == 4) own += gm[n][gi].z;
+            }
+            const float a = (float)(int)own;
+            const float sc = NP == 1 ? fmaf(scale, step, 0.f) : scale * step;  // (one mixed-precision instruction)
             if constexpr (HZ) {
                 const float z = half_bits_to_float(mw >> 16);
                 y[n] = fmaf(sc, fmaf(-z, gs, a), y[n]);
@@ -247,6 +277,7 @@ __device__ __forceinline__ void consume_weights_digits(const Stage<B, 1, GemvCfg
             }
         }
     }
+    if constexpr (!kEarly) next();
 }
 
 // Activations that are not finite take no part in the integer arithmetic (their X is 0); their products with the

@@ -98,8 +98,14 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
     const uint32_t lf = lr + kWaves * kRows * NP * 4;                               // a word per wave
 
     float y[NP];
+    int acc[NP][4];  // running sums of the digits, and their joined value (see consume_weights_digits)
+    uint32_t before[NP];
 #pragma unroll
-    for (int n = 0; n < NP; ++n) y[n] = 0.f;
+    for (int n = 0; n < NP; ++n) {
+        y[n] = 0.f;
+        acc[n][0] = acc[n][1] = acc[n][2] = acc[n][3] = 0;
+        before[n] = 0;
+    }
     // the segment in pieces whose digits fit the LDS: one piece, unless the tiling asks for very long segments (never
     // for one token)
     for (int p0 = k0;;) {
@@ -134,8 +140,14 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        Stage<B, 1, Cfg::MPL> st = {};
-        issue_weights<B, 1, GQ, HZ>(st, src, p0 + wave < p1, p0 + wave, lane);
+        // One bit: the next tile is requested before the wait for the current one, otherwise when the current one is done.
+        // A 1-bit tile is 1.3 to 2 KB and 110 vector instructions, so a wave waits longer than it computes: with the request
+        // at the end of a tile (where the last use of a zero kept it) 16 launches of a layer set of width 1024 took 131 us,
+        // now 92; width 3072 145 -> 130, 4096 184 -> 170 (zeros, blocks of 64; lookups: 109, 139, 182).  2 and 4 bits: more
+        // streams in flight cost more than they hide (see tman_mpgemv_x.hip).
+        constexpr int kStages = B == 1 && NP == 1 ? 2 : 1;
+        Stage<B, 1, Cfg::MPL> st[kStages] = {};
+        issue_weights<B, 1, GQ, HZ>(st[0], src, p0 + wave < p1, p0 + wave, lane);
         __builtin_amdgcn_sched_barrier(0);
 
         // digits of the piece: lane -> four lanes per 32-column block, sixteen per tile
@@ -143,7 +155,7 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
         bool nonfinite = false;
 #pragma unroll
         for (int i = 0; i < kPasses; ++i) {
-            if (i * kWaves * 64 >= n_lanes) break;
+            if (i * kWaves * 64 + wave * 64 >= n_lanes) break;  // (this wave has none)
             const int j = i * kWaves * 64 + tid, tile = j >> 4;
             const bool live = j < n_lanes;
 #pragma unroll
@@ -163,10 +175,17 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
         __syncthreads();
 
         // the waves take the tiles in turn
-        for (int t = p0 + wave; t < p1; t += kWaves) {
-            consume_weights_digits<B, GQ, HZ, NP>(st, ld + (uint32_t)((t - p0) * NP * kDigitBytesPerKTile + (lane & 15) * 4),
-                                                  lm + (uint32_t)((t - p0) * NP * Cfg::GPT * kDigitMetaBytes), y);
-            issue_weights<B, 1, GQ, HZ>(st, src, t + kWaves < p1, t + kWaves, lane);
+        for (int t0 = p0 + wave; t0 < p1; t0 += kStages * kWaves) {
+#pragma unroll
+            for (int s = 0; s < kStages; ++s) {
+                const int t = t0 + s * kWaves;
+                if (t < p1)
+                    consume_weights_digits<B, GQ, HZ, NP>(
+                        st[s], ld + (uint32_t)((t - p0) * NP * kDigitBytesPerKTile + (lane & 15) * 4),
+                        lm + (uint32_t)((t - p0) * NP * Cfg::GPT * kDigitMetaBytes), acc, before, y, [&] {
+                            issue_weights<B, 1, GQ, HZ>(st[(s + 1) % kStages], src, t + kWaves < p1, t + kWaves, lane);
+                        });
+            }
         }
         if constexpr (SRC != TokenSource::kTablesI16) {
             const u32x4 f = load_lds<u32x4>(lf);

@@ -63,15 +63,18 @@ struct GemmArgs {
     int M, N, K, n_row_blocks, n_ktiles;
     int m_tiles, n_tiles;
     int per_xcd;  // workgroups dealt to each XCD
+    int whole_row_tiles;
     int* status;  // the library's status word
 };
 
-// Tile of this workgroup, token tiles fastest.  Consecutive workgroup ids go to consecutive XCDs; every XCD gets an
-// equal run of consecutive tiles, so the token tiles that share the weights of one row tile sit on one XCD and its L2,
-// and no XCD has a workgroup more than another (dealing out whole row tiles left 3 x 12 workgroups for the 32 units
-// of one XCD at 17 row tiles x 12 token tiles: 70 instead of 38 us).  May lie past the last tile.
+// Tile of this workgroup, token tiles fastest.  Consecutive workgroup ids go to consecutive XCDs, and the token tiles that
+// share the weights of one row tile should sit on one XCD and its L2.  Either every XCD gets an equal run of consecutive
+// tiles, which cuts up to seven row tiles in two, or row tiles are dealt out whole, which may leave XCDs unequal (see
+// deal_tiles).  May lie past the last tile.
 __device__ __forceinline__ int tile_of_workgroup(const GemmArgs& a) {
-    return (int)(blockIdx.x % kXcds) * a.per_xcd + (int)(blockIdx.x / kXcds);
+    const int xcd = (int)(blockIdx.x % kXcds), slot = (int)(blockIdx.x / kXcds);
+    if (a.whole_row_tiles) return ((slot / a.n_tiles) * kXcds + xcd) * a.n_tiles + slot % a.n_tiles;
+    return xcd * a.per_xcd + slot;
 }
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -688,8 +691,31 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     }
 }
 
-static unsigned deal_tiles(GemmArgs& a) {
-    a.per_xcd = (int)(((long long)a.m_tiles * a.n_tiles + kXcds - 1) / kXcds);
+static int compute_units() {
+    static std::once_flag once;
+    static int n_cu = 256;  // assumed when no device answers
+    std::call_once(once, [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
+            n_cu = n;
+    });
+    return n_cu;
+}
+
+// Equal runs of tiles per XCD (K-split kernel: always).  Tiled kernel: whole row tiles where that costs an XCD no further round
+// of workgroups over its units, and leaves it at most 5 % more of them, or there are so few row tiles that the cuts are what
+// costs.  11008 x 4096, 43 row tiles x 4 token tiles, 24 or 22 per XCD: 98.9 us whole, 96.8 in runs (N = 2048 192.9 /
+// 189.4); 2112 x 4096, N = 2048, 17 x 8, weights in cache: 60.9 / 63.0; 6912 x 2560, N = 777, 54 x 4, 28 or 27: 46.4 /
+// 47.8; 24 x 8 (3072 x 8192, N = 2048), 24 per XCD in both: 129.5 / 131.5; 2112 x 4096, N = 3072, 17 x 12, 36 or 26 for 32
+// units: 70 / 38.
+static unsigned deal_tiles(GemmArgs& a, bool may_be_whole) {
+    const long long whole = (long long)((a.m_tiles + kXcds - 1) / kXcds) * a.n_tiles;
+    const long long even = ((long long)a.m_tiles * a.n_tiles + kXcds - 1) / kXcds;
+    const int units = compute_units() / kXcds > 0 ? compute_units() / kXcds : 1;
+    const bool same_rounds = (whole + units - 1) / units == (even + units - 1) / units;
+    a.whole_row_tiles = may_be_whole && same_rounds && (whole * 20 <= even * 21 || (a.m_tiles >= kXcds && a.m_tiles < 18));
+    a.per_xcd = (int)(a.whole_row_tiles ? whole : even);
     return (unsigned)a.per_xcd * kXcds;
 }
 
@@ -705,7 +731,7 @@ static int launch_ksplit(GemmArgs a, hipStream_t st) {
     if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
     a.m_tiles = (a.n_row_blocks + RBW - 1) / RBW;
     a.n_tiles = (a.N + T::TN - 1) / T::TN;
-    const unsigned grid = deal_tiles(a);
+    const unsigned grid = deal_tiles(a, false);
     hipLaunchKernelGGL((mpgemm_ksplit_kernel<B, GQ, HZ, RBW, TT, W>), dim3(grid), dim3(64 * W), T::LdsBytes, st, a);
     return launch_status();
 }
@@ -722,7 +748,7 @@ static int launch_tile(GemmArgs a, hipStream_t st) {
     if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
     a.m_tiles = (a.n_row_blocks + RB - 1) / RB;
     a.n_tiles = (a.N + kTN - 1) / kTN;
-    const unsigned grid = deal_tiles(a);
+    const unsigned grid = deal_tiles(a, true);
     hipLaunchKernelGGL((mpgemm_kernel<B, GQ, HZ, RB>), dim3(grid), dim3(kThreads), Tile<RB>::LdsBytes, st, a);
     return launch_status();
 }
@@ -740,14 +766,7 @@ static int launch_tile(GemmArgs a, hipStream_t st) {
 // row block per workgroup of the tiled kernel (25 % slower per column, but without exchange) is left for short K.
 constexpr int kSplitWide = 5, kSplitTall = 6, kSplit128 = 7, kSplit64 = 8, kSplit64x8 = 9;
 static int choose_tile(int n_row_blocks, int N, int K) {
-    static std::once_flag once;
-    static int n_cu = 256;  // assumed when no device answers
-    std::call_once(once, [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-            n_cu = n;
-    });
+    const int n_cu = compute_units();
     const tman_tiling_t t = current_tiling();
     if (t.prefill_k_split == 2) return kSplitWide;
     if (t.prefill_k_split == 3) return kSplitTall;

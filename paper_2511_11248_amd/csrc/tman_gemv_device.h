@@ -1,6 +1,6 @@
-// Device-side building blocks shared by the decoding kernels (table lookup by packed weight index, Sec. 2.2
-// and Sec. 4.3): streaming of tile blocks through buffer loads, LDS access with explicit address spaces, the
-// lookups of one tile block against tables that sit in LDS.
+// Device-side building blocks shared by the kernels that stream tile blocks (decoding, Sec. 2.2 and Sec. 4.3, and the
+// small-batch mpGEMM): descriptors and workgroup numbers, requests of tile blocks through buffer loads, LDS access with
+// explicit address spaces, the output of a row block and the exchange between K segments.
 #pragma once
 #include <hip/hip_fp16.h>
 
@@ -218,11 +218,11 @@ __device__ __forceinline__ GemvDesc desc_value(const Args& a, int g) {
     if constexpr (__is_same(Args, KernelArgs<true>)) {
         return a.single;
     } else {
-        typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+        typedef uint32_t u32x16 __attribute__((ext_vector_type(16), aligned(16)));  // (a table is, and its entries of 80 bytes)
         struct alignas(8) Words {
             uint32_t w[20];
         } raw;
-        static_assert(sizeof(GemvDesc) == sizeof(Words), "descriptor size");
+        static_assert(sizeof(GemvDesc) == sizeof(Words) && sizeof(GemvDesc) % 16 == 0, "descriptor size");
         const uintptr_t p = reinterpret_cast<uintptr_t>(a.descs + g);
         const u32x16 lo = *reinterpret_cast<const_ptr<u32x16>>(p);
         const u32x4 hi = *reinterpret_cast<const_ptr<u32x4>>(p + 64);

@@ -63,8 +63,8 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline int launch_status() { return hipGetLastError() == hipSuccess ? TMAN_OK : TMAN_ERR_LAUNCH; }
 
 // Does the header in front of the tile blocks describe this shape?  The 14 defined words are fetched with one
-// 64-byte load and compared without branches, so the check costs one memory round trip.
-typedef int32_t header_words_t __attribute__((ext_vector_type(16)));
+// 64-byte load (of a blob that is 16-byte aligned) and compared without branches, so the check costs one memory round trip.
+typedef int32_t header_words_t __attribute__((ext_vector_type(16), aligned(16)));
 __device__ __forceinline__ bool header_matches(const uint8_t* tiles, int M, int K, int bits, int group, int has_zero) {
     const header_words_t h = *reinterpret_cast<const header_words_t*>(tiles - kHeaderBytes);
     const int diff = (h[0] ^ 0x4e414d54) | (h[1] ^ 0x00314b50) | (h[2] ^ M) | (h[3] ^ K) | (h[4] ^ bits) | (h[5] ^ group) |

@@ -59,14 +59,8 @@ size_t tman_lut_i16_bytes(int32_t N, int32_t K, int32_t group) {
 
 size_t tman_mpgemv_workspace_bytes(const tman_shape_t* shape, int32_t N) {
     if (check_shape(shape) != TMAN_OK || N < 1 || N > TMAN_MAX_DECODE_TOKENS) return 0;
-    const Layout L = make_layout(shape);
-    GemvPlan p = plan_gemv(L, N);
-    size_t need = p.ticket_bytes + p.partial_bytes;
-    if (N == 1) {  // also serves tman_mpgemv_x, which cuts K into shorter segments
-        GemvPlan px = plan_gemv_x(L);
-        if (px.ticket_bytes + px.partial_bytes > need) need = px.ticket_bytes + px.partial_bytes;
-    }
-    return need;
+    const GemvPlan p = plan_decode(make_layout(shape), N);
+    return p.ticket_bytes + p.partial_bytes;
 }
 
 size_t tman_mpgemm_workspace_bytes(const tman_shape_t* shape, int32_t N) {
@@ -166,8 +160,7 @@ int tman_mpgemv(const tman_shape_t* shape, const void* packed, const void* lut, 
     return launch_mpgemv(make_layout(shape), packed, lut, N, y, workspace, (hipStream_t)stream);
 }
 
-// A descriptor table: the GEMV descriptors, then (one-token batches whose workgroups are numbered for balance) the
-// numbering.
+// A descriptor table: the GEMV descriptors, then (batches whose workgroups are numbered for balance) the numbering.
 static size_t desc_table_bytes(int count) { return ((size_t)count * sizeof(GemvDesc) + 255) / 256 * 256; }
 static uint16_t* order_of(void* desc, int count) {
     return reinterpret_cast<uint16_t*>(static_cast<uint8_t*>(desc) + desc_table_bytes(count));
@@ -200,7 +193,7 @@ static int check_batch(int32_t count, const tman_shape_t* shapes, int32_t N) {
         if (shapes[i].bits != shapes[0].bits || shapes[i].group != shapes[0].group ||
             shapes[i].flags != shapes[0].flags)
             return TMAN_ERR_SHAPE;  // one launch runs one weight format
-        total += plan_gemv(make_layout(&shapes[i]), N).n_workgroups;
+        total += plan_decode(make_layout(&shapes[i]), N).n_workgroups;
     }
     if (total > 0x7fffffffLL) return TMAN_ERR_SHAPE;
     return TMAN_OK;

@@ -80,3 +80,12 @@ def test_tiling_enters_the_plans():
         tman.tman_set_tiling(_with(i8_token_blocks=forced))
         assert tman.tman_mpgemm_i8_token_blocks(pre, 1024) == forced
         assert tman.tman_mpgemm_i8_token_blocks(pre, 5) == forced
+
+
+def test_one_token_workspace_follows_the_one_token_plan():
+    """decode_seg_tiles belongs to two tokens; the workspace of one token is what its own segments take."""
+    shape = tman.Shape(4096, 4096, 2, 64)  # 32 K tiles: one segment for one token
+    assert tman.tman_mpgemv_workspace_bytes(shape, 1) == 256
+    tman.tman_set_tiling(_with(decode_seg_tiles=8))
+    assert tman.tman_mpgemv_workspace_bytes(shape, 1) == 256
+    assert tman.tman_mpgemv_workspace_bytes(shape, 2) == 256 + 64 * 4 * 2 * 64 * 4

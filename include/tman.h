@@ -120,8 +120,9 @@ int tman_build_lut_batch(int32_t count, const void *const *x, int32_t N, const i
  *   y[n][m] = sum_G scale[m][G] * ( sum_i 2^i sum_{j in G} T[n][j][idx_i[m][j]] - zero[m][G] * S[n][G] )
  * where idx_i[m][j] is the 4-bit pattern of bit-plane i over weights 4j..4j+3 (sign form:
  * scale * (2 * sum_j T - S)).  fp16 table entries, fp32 accumulation, fp16 result.
- * For N = 1 (and N = 2 with 4-bit weights) the kernel is that of tman_mpgemv_x below: it takes the activations out of the tables (T[j][1 << t] is
- * x[4j + t]) and sums integer products, which rounds less than adding fp16 table entries does.
+ * For N = 1 (and N = 2 with 4-bit weights) the kernel is that of tman_mpgemv_x below: it takes the activations out of
+ * the tables (T[j][1 << t] is x[4j + t]) and sums integer products, which rounds less than adding fp16 table entries
+ * does.
  *   packed    : from tman_pack_weights for the same shape
  *   lut       : from tman_build_lut(x, N, shape->K, shape->group)
  *   y         : fp16 [N][M]
@@ -150,8 +151,8 @@ int tman_mpgemv(const tman_shape_t *shape, const void *packed, const void *lut, 
  * and reused for every decode step.
  * tman_mpgemv_batch_run launches the batch described by `desc`; `count`, `shapes` and `N` must be the
  * ones given to prepare.  Results are identical to `count` separate tman_mpgemv calls up to the
- * order of the fp32 additions across K, and deterministic for a given batch.  One-token batches are numbered for
- * balance like those of tman_mpgemv_x.
+ * order of the fp32 additions across K, and deterministic for a given batch.  Batches of up to 8 GEMVs, of any N, whose
+ * workgroups are all resident at once are numbered for balance like those of tman_mpgemv_x.
  */
 #define TMAN_MAX_BATCH 256
 size_t tman_mpgemv_batch_desc_bytes(int32_t count);
@@ -250,13 +251,16 @@ int tman_device_status(void *stream);
  * feed the matrix cores with fp32 accumulation (N <= 32, most formats: the codes feed them, exact, and scale and zero are
  * applied in fp32 to the sums of a quantization block).
  *   x : fp16 [N][K], any N >= 1;   y : fp16 [N][M]
- * Two kernels share the call.  N > TMAN_MAX_SMALL_TOKENS runs the tiled prefill kernel (256 tokens per
- * workgroup, bound by the matrix cores; it needs no workspace).  1 <= N <= TMAN_MAX_SMALL_TOKENS runs a kernel
- * organised like the decoding kernels (bound by the weight stream: every wave dequantizes the tile blocks it
- * streams and multiplies them with all tokens at once), which cuts a long K into segments that meet in the
- * workspace, under the rules of tman_mpgemv: tman_mpgemm_workspace_bytes(shape, N) bytes (0 when K is one
- * segment, then NULL is accepted), 16-byte aligned, zero-filled once before first use, left ready by every
- * call, not shared by calls that may overlap.  Deterministic.
+ * N > TMAN_MAX_SMALL_TOKENS runs one of two prefill kernels (the tiled one, 256 tokens per workgroup, bound by the
+ * matrix cores, or the one whose waves split K, for short prompts and small grids; neither needs a workspace).
+ * 1 <= N <= TMAN_MAX_SMALL_TOKENS runs one of two kernels organised like the decoding kernels (bound by the weight
+ * stream: every wave multiplies the tile blocks it streams with all tokens at once): the codes themselves, with scale and
+ * zero applied to the sums of quantization blocks (N <= 8; N <= 16 with blocks of 64 or 128; N <= 32 with blocks of
+ * 128), or weights dequantized to fp16 (the others).  They cut a long K into segments that meet in the workspace, under
+ * the rules of tman_mpgemv: tman_mpgemm_workspace_bytes(shape, N) bytes (0 when K is one segment, then NULL is
+ * accepted), 16-byte aligned, zero-filled once before first use, left ready by every call, not shared by calls that may
+ * overlap.  An activation that is not finite makes its own token's outputs what the sum over all columns gives; the
+ * other tokens are not affected.  Deterministic.
  */
 #define TMAN_MAX_SMALL_TOKENS 32
 int tman_mpgemm(const tman_shape_t *shape, const void *packed, const void *x, int32_t N, void *y, void *workspace,
@@ -268,8 +272,8 @@ int tman_mpgemm(const tman_shape_t *shape, const void *packed, const void *x, in
  * activation share it; here entries of `x` may repeat).  Arguments as for tman_mpgemv_batch_prepare / _run with
  * the activations `x` (fp16 [N][K] each) in place of the table buffers; workspace[i] may be NULL where
  * tman_mpgemm_workspace_bytes(&shapes[i], N) is 0; the descriptor table takes
- * tman_mpgemv_batch_desc_bytes(count) bytes.  Batches of up to 8 GEMMs whose workgroups are all resident at once
- * (four per compute unit) are numbered for balance like those of tman_mpgemv_x (tiling.decode_balance).
+ * tman_mpgemv_batch_desc_bytes(count) bytes.  Batches of up to 8 GEMMs with at most four workgroups per
+ * compute unit are numbered for balance like those of tman_mpgemv_x (tiling.decode_balance).
  */
 int tman_mpgemm_batch_prepare(int32_t count, const tman_shape_t *shapes, const void *const *packed,
                               const void *const *x, int32_t N, void *const *y, void *const *workspace,
@@ -350,9 +354,9 @@ int tman_mpgemv_noalloc(const tman_shape_t *shape, const void *packed, const voi
  *                              packed weights per row block, is ONE segment; it is at most 32 (Eq. 1: what a
  *                              workgroup keeps of its activations lives in LDS; 32 tiles are two passes of its lanes)
  *   decode_x_long_seg_tiles    ... a longer K is cut into equal segments of at most this many tiles
- *   decode_balance             1: one-token batches and batches of the small-batch tman_mpgemm number their
- *                              workgroups for equal work per compute unit (see tman_mpgemv_x_batch_order),
- *                              0: plain grids
+ *   decode_balance             1: batches of tman_mpgemv_x, of tman_mpgemv (tables) and of the small-batch
+ *                              tman_mpgemm number their workgroups for equal work per compute unit where they fit
+ *                              the chip (see tman_mpgemv_x_batch_order), 0: plain grids
  *   small_seg_tiles            K tiles per workgroup of tman_mpgemm for N <= 32
  *   prefill_row_blocks         tile blocks in M per workgroup of the tiled prefill kernel, 1..4 (Eq. 4: four
  *                              stage buffers of rows x 80 + 256 x 64 bytes within 160 KB of LDS), 0 = chosen per

@@ -70,11 +70,12 @@ struct GemmArgs {
 // Tile of this workgroup, token tiles fastest.  Consecutive workgroup ids go to consecutive XCDs, and the token tiles that
 // share the weights of one row tile should sit on one XCD and its L2.  Either every XCD gets an equal run of consecutive
 // tiles, which cuts up to seven row tiles in two, or row tiles are dealt out whole, which may leave XCDs unequal (see
-// deal_tiles).  May lie past the last tile.
-__device__ __forceinline__ int tile_of_workgroup(const GemmArgs& a) {
+// deal_tiles).  `mt` may lie past the last row tile.
+__device__ __forceinline__ void tile_of_workgroup(const GemmArgs& a, int& mt, int& nt) {
     const int xcd = (int)(blockIdx.x % kXcds), slot = (int)(blockIdx.x / kXcds);
-    if (a.whole_row_tiles) return ((slot / a.n_tiles) * kXcds + xcd) * a.n_tiles + slot % a.n_tiles;
-    return xcd * a.per_xcd + slot;
+    const int at = a.whole_row_tiles ? slot : xcd * a.per_xcd + slot, row = at / a.n_tiles;
+    nt = at - row * a.n_tiles;
+    mt = a.whole_row_tiles ? row * kXcds + xcd : row;
 }
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -136,7 +137,8 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
-    const int tile = tile_of_workgroup(a), mt = tile / a.n_tiles, nt = tile % a.n_tiles;
+    int mt, nt;
+    tile_of_workgroup(a, mt, nt);
     // A blob packed for another shape or layout: say so and leave y alone.  (The check is folded into the one
     // exit below: a second exit after this load makes the compiler keep the dequantization state in scratch
     // memory.)
@@ -480,7 +482,8 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     constexpr int TB = B * 1024 + 64 * (kKTile / GQ) * MSZ;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
-    const int tile = tile_of_workgroup(a), mt = tile / a.n_tiles, nt = tile % a.n_tiles;
+    int mt, nt;
+    tile_of_workgroup(a, mt, nt);
     const bool header_ok = header_matches(a.tiles, a.M, a.K, B, GQ, HZ ? 1 : 0);
     if (!header_ok && blockIdx.x == 0 && threadIdx.x == 0) report_header_mismatch(a.status);
     if (mt >= (header_ok ? a.m_tiles : 0)) return;

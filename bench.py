@@ -36,8 +36,8 @@ MFMA_I8_PEAK_TOPS = 5000.0
 # WRITE_SIZE runs of this script scaled by a plain copy of known size (--calibration-copy); the counters
 # cannot be read from inside the process.  Source: profiles/mpgemv_x_7b_w2g64_and_mpgemm_w4g64_hbm_traffic.txt.
 MEASURED_TRAFFIC_BYTES = {
-    ("mpgemv_x", "7b_w2g64", 1): 63_865_856 + 197_632,
-    ("mpgemm", "prefill_w4g64", 1024): 92_651_315 + 22_544_384,
+    ("mpgemv_x", "7b_w2g64", 1): 63_839_232 + 197_632,
+    ("mpgemm", "prefill_w4g64", 1024): 95_291_597 + 22_544_384,
 }
 
 
@@ -261,7 +261,7 @@ def other_configs(args, torch, tman, synth, oracle, dev):
                 sec = timed_steps(torch, step, 100, 300)
                 err, _, _ = decode_error(torch, synth, oracle, w, job, N, matrix_cores=True)
                 add(f"{name} N={N}, {w.instances} rotating copies, one tman_mpgemm_batch launch per layer set "
-                    f"(dequantization in registers + MFMA)", sec, job["weight_bytes_per_step"] / sec / 1e9, "GB/s",
+                    f"(codes on the matrix cores)", sec, job["weight_bytes_per_step"] / sec / 1e9, "GB/s",
                     HBM_PEAK_GBS, err, "all outputs of copy 0")
             if w.config == 4:  # the whole 32-layer weight stream as one launch of 160 GEMVs
                 big = whole_model_launch(torch, tman, dev, w, job)

@@ -372,7 +372,7 @@ int tman_mpgemv_noalloc(const tman_shape_t *shape, const void *packed, const voi
  *                              split K (128 rows x 128 tokens per workgroup, for small grids), 0 = chosen per call
  *                              from the grids they give
  * tman_default_tiling gives the built-in values (the best of the measured sweep paper_2511_11248_amd/tune.py
- * makes on the device), tman_get_tiling the current ones; tman_set_tiling checks the constraints
+ * makes on the device, or within 3 % of it), tman_get_tiling the current ones; tman_set_tiling checks the constraints
  * (TMAN_ERR_SHAPE if violated) and makes the values current for all later calls of the process.  The tiling
  * enters the workspace size queries and the descriptor tables: set it before sizing workspaces and preparing
  * batches, not between a prepare and its runs.

@@ -708,8 +708,8 @@ static int compute_units() {
 
 // Equal runs of tiles per XCD (K-split kernel: always).  Tiled kernel: whole row tiles where that costs an XCD no further round
 // of workgroups over its units, and leaves it at most 5 % more of them, or there are so few row tiles that the cuts are what
-// costs.  11008 x 4096, 43 row tiles x 4 token tiles, 24 or 22 per XCD: 98.9 us whole, 96.8 in runs (N = 2048 192.9 /
-// 189.4); 2112 x 4096, N = 2048, 17 x 8, weights in cache: 60.9 / 63.0; 6912 x 2560, N = 777, 54 x 4, 28 or 27: 46.4 /
+// costs.  11008 x 4096, 58 row tiles x 4 token tiles, 32 or 29 per XCD: 98.9 us whole, 96.8 in runs (N = 2048, 64 or 58:
+// 192.9 / 189.4); 2112 x 4096, N = 2048, 17 x 8, weights in cache: 60.9 / 63.0; 6912 x 2560, N = 777, 54 x 4, 28 or 27: 46.4 /
 // 47.8; 24 x 8 (3072 x 8192, N = 2048), 24 per XCD in both: 129.5 / 131.5; 2112 x 4096, N = 3072, 17 x 12, 36 or 26 for 32
 // units: 70 / 38.
 static unsigned deal_tiles(GemmArgs& a, bool may_be_whole) {

@@ -259,7 +259,7 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemm_small_kernel(Args a) {
 // accumulators' own layout (summing it ahead, once per workgroup, put 3 to 6 us in front of every workgroup).
 // About 263 vector instructions per tile block in the loop for uint4 g128 and 8 tokens.  What bounds it now: registers for three waves per
 // SIMD (two tiles in flight: 5 % better than one; with two waves per SIMD it loses 15 %), so latency, then the
-// vector pipe; 107.5 MB (7B uint4 g128, N = 8) in 29 us = 3.7 TB/s, from 34.5 us.
+// vector pipe; 107.5 MB (7B uint4 g128, N = 8) in 28.7 - 29.5 us = 3.7 TB/s, from 35.0 (bench run: 31.1 - 31.8, from 39.3).
 // The offset: 64 for 4 bits (a nibble at mantissa bits 4..7 needs three shifts per code word; at bits 6..9, as 16 + c, it
 // would need four), 4 for 2 bits (bits 8..9), 2 for 1 bit (bit 9): small against the codes, because what the offset
 // adds to the sums is lost to their precision.

@@ -14,13 +14,13 @@
 // out of them: the entries of patterns 1, 2, 4 and 8 are the four activations themselves.  The sums of the four waves
 // meet in LDS, segments of a long K through the workspace (tickets, fixed order of addition).
 //
-// What bounds it: the weight stream.  63.2 MB (7B uint2 g64) in 13.4 us = 4.7 TB/s, 107.5 MB (uint4 g128) in 19.3
-// us = 5.6 TB/s; reading alone reaches 6.0-6.15 TB/s, and about 1 us at the start (descriptor, first activations)
+// What bounds it: the weight stream.  63.2 MB (7B uint2 g64) in 13.5 us = 4.7 TB/s, 107.5 MB (uint4 g128) in 19.6 - 20.5
+// us = 5.2 - 5.5 TB/s; reading alone reaches 6.0-6.15 TB/s, and about 1 us at the start (descriptor, first activations)
 // and 1.5 us at the end (exchange between segments) are not covered.  What helped beside the digits, measured in
 // turn on the uint2 / uint4 launch: the waves of a workgroup take its tiles in turn instead of a quarter each, so that
 // a workgroup reads one contiguous stream (uint4 20.6 -> 20.1 us); ONE tile in flight per wave instead of two or three
 // (uint2 14.2 -> 13.6 us with two against one, 15.2 with three: more streams in flight cost more in the memory
-// system than they hide); no issue priorities (uint2 14.3 -> 13.9 us: they balanced vector work, which no longer
+// system than they hide; 1 bit: two, see the kernel); no issue priorities (uint2 14.3 -> 13.9 us: they balanced vector work, which no longer
 // bounds); K up to 4096 as one segment also for 4-bit weights (uint4 20.7 -> 19.6 us).
 #include <algorithm>
 #include <vector>

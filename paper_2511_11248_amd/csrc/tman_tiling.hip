@@ -10,13 +10,14 @@
 // remains free, and what tman_set_tiling can change, is how many tile blocks one workgroup takes:
 //   decode_*            K tiles per decoding workgroup (its K segment); the one-token kernel keeps the activations of
 //                       its whole segment in LDS, so there the segment is bounded like K_lut in Eq. 1: 32 tiles;
-//   decode_balance    whether the workgroups of a one-token batch are numbered for equal work per compute unit
+//   decode_balance    whether the workgroups of a batch are numbered for equal work per compute unit
 //                       (not a tile size, but it decides which segment length is best);
 //   prefill_row_blocks  tile blocks in M per prefill workgroup; Eq. 4 reads ring (4) x stage bytes <= 160 KB of
 //                       LDS, which admits at most 4;
 //   prefill_k_split     whether small prefill grids go to the kernel whose waves split K, and with which tile;
 //   i8_token_blocks     which integer-matrix-core prefill kernel runs and how many tokens its workgroup takes.
-// The defaults are the best of the measured sweep in paper_2511_11248_amd/tune.py over the benchmark shapes.
+// The defaults are the best of the measured sweep in paper_2511_11248_amd/tune.py over the benchmark shapes, or within its
+// run-to-run noise (3 %) of the best.
 #include <atomic>
 #include <mutex>
 

@@ -3,8 +3,8 @@
 sizes are searched per machine under the constraints of Eq. 1-4).
 
 The shared tile block is fixed by the packed layout; what is searched is how many tile blocks a workgroup takes
-(`tman_tiling_t`, include/tman.h).  Candidates that violate the constraints are refused by tman_set_tiling (the
-tables of a one-token K segment must fit the workgroup's LDS, the prefill stage ring must fit 160 KB), every
+(`tman_tiling_t`, include/tman.h).  Candidates that violate the constraints are refused by tman_set_tiling (a one-token
+K segment is at most 32 tiles, the prefill stage ring must fit 160 KB), every
 admissible candidate is timed on synthetic layers of the benchmark shapes with rotating weight copies, and the
 best value of each parameter is printed beside the built-in default.
 
@@ -120,7 +120,7 @@ def main():
               "prefill_row_blocks", [0, 1, 2, 3, 4, 5], lambda: time_prefill(N))
     for N in (128, 256):
         sweep(f"prefill 11008 x 4096 uint4 g64, N = {N}: 1 = the tiled kernel, 2 / 3 = the kernel whose waves split K with its "
-              "64 x 256 / 128 x 128 tile (0 = the launcher's rule)",
+              "64 x 256 / 128 x 128 tile (0 = the launcher's rule, which also has narrower tiles)",
               "prefill_k_split", [0, 1, 2, 3], lambda: time_prefill(N))
     for N in (256, 512, 1024, 2048):
         sweep(f"int8 prefill 11008 x 4096 uint4 per row, N = {N}: 1 = 128 x 128 tiles, 3 / 4 / 7 = 256 rows x 96 / 128 / 224 "

@@ -224,16 +224,24 @@ static int run_decode_batch(int (*launch)(const DecodeBatch&, hipStream_t), int3
     b.n_gemv = count;
     b.order = nullptr;
     b.n_workgroups = b.max_seg_tiles = 0;
-    for (int i = 0; i < count; ++i) {
-        const GemvPlan p = plan_decode(make_layout(&shapes[i]), N);
-        if (p.n_workgroups > b.n_workgroups) b.n_workgroups = p.n_workgroups;
-        if (p.seg_tiles > b.max_seg_tiles) b.max_seg_tiles = p.seg_tiles;
-    }
+    b.row_blocks = 1;
     Layout L[8];
     for (int i = 0; i < count && i < 8; ++i) L[i] = make_layout(&shapes[i]);
-    if (const int n_wg = ordered_workgroups(count, L, N, device_units())) {
+    const int n_ordered = ordered_workgroups(count, L, N, device_units());
+    long long total = 0;
+    if (!n_ordered && N == 1)
+        for (int i = 0; i < count; ++i) total += plan_decode(make_layout(&shapes[i]), N).n_workgroups;
+    if (!n_ordered) b.row_blocks = batch_row_blocks(b.bits, N, total, device_units());
+    for (int i = 0; i < count; ++i) {
+        const Layout Li = make_layout(&shapes[i]);
+        const GemvPlan p = plan_decode(Li, N);
+        const int n_wg = (Li.n_row_blocks + b.row_blocks - 1) / b.row_blocks * p.n_seg;
+        if (n_wg > b.n_workgroups) b.n_workgroups = n_wg;
+        if (p.seg_tiles > b.max_seg_tiles) b.max_seg_tiles = p.seg_tiles;
+    }
+    if (n_ordered) {
         b.order = order_of(const_cast<void*>(desc), count);
-        b.n_workgroups = n_wg;
+        b.n_workgroups = n_ordered;
     }
     return launch(b, (hipStream_t)stream);
 }

@@ -169,6 +169,7 @@ template <>
 struct KernelArgs<false> {
     const GemvDesc* descs;
     int n_gemv;
+    int row_blocks;  // one-token kernel, 1 bit: row blocks per workgroup
 };
 
 // A batch launch whose workgroups are numbered by the host: workgroup id -> (GEMV, workgroup within the GEMV).

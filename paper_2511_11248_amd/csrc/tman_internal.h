@@ -143,7 +143,11 @@ struct DecodeBatch {
     int n_gemv;
     const uint16_t* order;  // device
     int n_workgroups, max_seg_tiles;
+    int row_blocks;  // per workgroup (plain grid)
 };
+// Row blocks per workgroup of a batch on the plain grid with `n_workgroups` of one row block each: 1, or more for large
+// one-token batches of 1-bit weights (tman_mpgemv_x.hip).
+int batch_row_blocks(int bits, int N, long long n_workgroups, int n_units);
 int launch_mpgemv(const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace, hipStream_t st);
 int launch_mpgemv_batch(const DecodeBatch& b, hipStream_t st);
 int launch_mpgemv_i16(const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace, hipStream_t st);

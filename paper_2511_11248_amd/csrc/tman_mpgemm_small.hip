@@ -574,6 +574,7 @@ int launch_mpgemm_small_batch(int bits, int group, int has_zero, int N, const Ge
     KernelArgs<false> a;
     a.descs = descs_dev;
     a.n_gemv = n_gemv;
+    a.row_blocks = 1;
     return launch_small_format<false>(bits, has_zero, group, a, N, max_workgroups, st);
 }
 

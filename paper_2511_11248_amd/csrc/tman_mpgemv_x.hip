@@ -46,6 +46,15 @@ void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut
     fill_desc_plan(d, L, plan_decode(L, N), packed, lut, N, y, workspace);
 }
 
+// A fifth of the vector instructions of a 1-bit workgroup make digits, and a large launch (all layers of a model at once) is
+// bound by vector issue: its workgroups take two row blocks each, as long as that leaves at least eight per compute unit.
+// 160 GEMVs of a 32-layer 3.8B model in one launch, sign form with blocks of 64: 113 us with two, 120 with one, 119 by
+// lookups (launches back to back; right after an idle GPU, whose clocks are still low: 144 - 148, 150, 140); with zeros 120, 127, 129;
+// width 4096, 64-blocks: 194, 210, 249.  Four: 113, with zeros 123, width 4096 230: fewer, longer workgroups end unevenly.
+int batch_row_blocks(int bits, int N, long long n_workgroups, int n_units) {
+    return bits == 1 && N == 1 && n_units > 0 && n_workgroups >= 16LL * n_units ? 2 : 1;
+}
+
 // The numbered launch of a batch (see order_workgroups_of): at most 8 workgroups per compute unit, as many as the LDS holds, and no
 // more than 5 of 32 tiles - numbering a
 // launch pays while a unit has few of them (1152 workgroups of a layer set with MLP width 14336, uint4 g128: 25.5 us on

@@ -12,11 +12,15 @@ namespace tman {
 constexpr int piece_tiles(int np) { return np == 8 ? 24 : kGemvXSegmentTiles; }
 
 // LDS of a workgroup whose segment has `seg_tiles` tiles: digit words and `gpt` quantization blocks per tile and token,
-// then the partial sums and a word per wave: at most 69,648 bytes (8 tokens, 24 tiles, blocks of 32)
-constexpr unsigned x_lds_bytes(int seg_tiles, int np, int gpt) {
+// then the partial sums (two sets where a workgroup takes several row blocks) and a word per wave: at most 69,648 bytes
+// (8 tokens, 24 tiles, blocks of 32)
+constexpr unsigned x_lds_bytes(int seg_tiles, int np, int gpt, int sets = 1) {
     const int tiles = seg_tiles < piece_tiles(np) ? seg_tiles : piece_tiles(np);
-    return (unsigned)(tiles * np * (kDigitBytesPerKTile + gpt * kDigitMetaBytes) + kWaves * kRows * np * 4 + kWaves * 4);
+    return (unsigned)(tiles * np * (kDigitBytesPerKTile + gpt * kDigitMetaBytes) + sets * kWaves * kRows * np * 4 + kWaves * 4);
 }
+// Workgroups of a large 1-bit batch take several row blocks with one set of digits (batch_row_blocks).
+template <int B, int NP, typename Args>
+constexpr bool several_row_blocks = B == 1 && NP == 1 && std::is_same_v<Args, KernelArgs<false>>;
 
 // The 8 activations of a lane, per token: numbers 4f .. 4f + 3 (a) and 16 + 4f .. (b) of its 32-column block.
 template <int NP>
@@ -60,6 +64,7 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
     static_assert(NP == 1 || SRC != TokenSource::kActivations, "several tokens come in tables");
     constexpr int kPiece = piece_tiles(NP);
+    constexpr bool kSeveral = several_row_blocks<B, NP, Args>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds_x[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -73,6 +78,7 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
     // reported and leaves y alone; a batch is checked when its descriptor table is written, which empties the
     // descriptor of such a GEMV.  One exit for both, before any other memory request.
     int n_wg = d.n_row_blocks * n_seg;
+    if constexpr (kSeveral) n_wg = (d.n_row_blocks + a.row_blocks - 1) / a.row_blocks * n_seg;
     if constexpr (SINGLE) {
         if (!header_matches(d.tiles, d.M, d.K, B, GQ, HZ ? 1 : 0)) {
             if (wg_local == 0 && tid == 0) report_header_mismatch(a.status);
@@ -83,6 +89,11 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
     // row block and segment: quotient by the reciprocal floor((2^32 - 1) / n_seg), which falls short by at most one
     int rb = (int)__umulhi((uint32_t)wg_local, (uint32_t)d.seg_recip), seg = wg_local - rb * n_seg;
     if (seg >= n_seg) ++rb, seg -= n_seg;
+    int rb_end = rb + 1;
+    if constexpr (kSeveral) {
+        rb *= a.row_blocks;
+        rb_end = min(rb + a.row_blocks, d.n_row_blocks);
+    }
     const int k0 = seg * d.seg_tiles;
     const int k1 = min(k0 + d.seg_tiles, n_ktiles);
     Streams src;
@@ -95,7 +106,7 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
     const uint32_t ld = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr<uint8_t>)lds_x));
     const uint32_t lm = ld + (uint32_t)(piece * NP * kDigitBytesPerKTile);          // quantization blocks
     const uint32_t lr = lm + (uint32_t)(piece * NP * Cfg::GPT * kDigitMetaBytes);  // partial sums [wave][token][row]
-    const uint32_t lf = lr + kWaves * kRows * NP * 4;                               // a word per wave
+    const uint32_t lf = lr + (kSeveral ? 2 : 1) * kWaves * kRows * NP * 4;          // a word per wave
 
     float y[NP];
     int acc[NP][4];  // running sums of the digits, and their joined value (see consume_weights_digits)
@@ -106,6 +117,25 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
         acc[n][0] = acc[n][1] = acc[n][2] = acc[n][3] = 0;
         before[n] = 0;
     }
+    // the four sums of a row meet in LDS, the first wave adds them
+    auto publish = [&](uint32_t set) {
+#pragma unroll
+        for (int n = 0; n < NP; ++n) store_lds<float>(set + ((wave * NP + n) * kRows + lane) * 4, y[n]);
+        __syncthreads();
+    };
+    auto finish = [&](uint32_t set) {
+        float factor[NP];
+#pragma unroll
+        for (int n = 0; n < NP; ++n) {
+            y[n] = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) y[n] += load_lds<float>(set + ((w * NP + n) * kRows + lane) * 4);
+            factor[n] = 1.f;
+            if constexpr (SRC == TokenSource::kTablesI16)  // the tokens' power-of-two steps, behind the block sums of the tables
+                factor[n] = ldexpf(1.f, uniform(reinterpret_cast<const int*>(d.lut_s + (size_t)n_ktiles * Cfg::GPT * NP * 4)[n]));
+        }
+        finish_rows<NP>(d, rb, seg, n_seg, lane, y, factor);
+    };
     // the segment in pieces whose digits fit the LDS: one piece, unless the tiling asks for very long segments (never
     // for one token)
     for (int p0 = k0;;) {
@@ -174,33 +204,49 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
             store_lds<uint32_t>(lf + wave * 4, __builtin_amdgcn_ballot_w64(nonfinite) != 0 ? 1u : 0u);
         __syncthreads();
 
-        // the waves take the tiles in turn
-        for (int t0 = p0 + wave; t0 < p1; t0 += kStages * kWaves) {
+        for (int r = 0;; r ^= 1) {  // the row blocks of the workgroup (one, unless kSeveral)
+            // the waves take the tiles in turn
+            for (int t0 = p0 + wave; t0 < p1; t0 += kStages * kWaves) {
 #pragma unroll
-            for (int s = 0; s < kStages; ++s) {
-                const int t = t0 + s * kWaves;
-                if (t < p1)
-                    consume_weights_digits<B, GQ, HZ, NP>(
-                        st[s], ld + (uint32_t)((t - p0) * NP * kDigitBytesPerKTile + (lane & 15) * 4),
-                        lm + (uint32_t)((t - p0) * NP * Cfg::GPT * kDigitMetaBytes), acc, before, y, [&] {
-                            issue_weights<B, 1, GQ, HZ>(st[(s + 1) % kStages], src, t + kWaves < p1, t + kWaves, lane);
-                        });
-            }
-        }
-        if constexpr (SRC != TokenSource::kTablesI16) {
-            const u32x4 f = load_lds<u32x4>(lf);
-            if (uniform((int)(f.x | f.y | f.z | f.w))) {
-#pragma unroll
-                for (int n = 0; n < NP; ++n) {
-                    auto fetch = [&](int k) -> uint32_t {
-                        if constexpr (SRC == TokenSource::kActivations) return load_global<uint16_t>(d.lut_t, (uint32_t)k * 2u);
-                        else
-                            return load_global<uint16_t>(
-                                d.lut_t, (((uint32_t)(k / kLutGroup) * 16u + (1u << (k % kLutGroup))) * NP + n) * 2u);
-                    };
-                    for (int t = p0 + wave; t < p1; t += kWaves)
-                        y[n] = add_nonfinite<B, GQ, HZ>(src.w + (size_t)t * Cfg::TB, fetch, d.K, t, lane, y[n]);
+                for (int s = 0; s < kStages; ++s) {
+                    const int t = t0 + s * kWaves;
+                    if (t < p1)
+                        consume_weights_digits<B, GQ, HZ, NP>(
+                            st[s], ld + (uint32_t)((t - p0) * NP * kDigitBytesPerKTile + (lane & 15) * 4),
+                            lm + (uint32_t)((t - p0) * NP * Cfg::GPT * kDigitMetaBytes), acc, before, y, [&] {
+                                issue_weights<B, 1, GQ, HZ>(st[(s + 1) % kStages], src, t + kWaves < p1, t + kWaves, lane);
+                            });
                 }
+            }
+            if constexpr (SRC != TokenSource::kTablesI16) {
+                const u32x4 f = load_lds<u32x4>(lf);
+                if (uniform((int)(f.x | f.y | f.z | f.w))) {
+#pragma unroll
+                    for (int n = 0; n < NP; ++n) {
+                        auto fetch = [&](int k) -> uint32_t {
+                            if constexpr (SRC == TokenSource::kActivations) return load_global<uint16_t>(d.lut_t, (uint32_t)k * 2u);
+                            else
+                                return load_global<uint16_t>(
+                                    d.lut_t, (((uint32_t)(k / kLutGroup) * 16u + (1u << (k % kLutGroup))) * NP + n) * 2u);
+                        };
+                        for (int t = p0 + wave; t < p1; t += kWaves)
+                            y[n] = add_nonfinite<B, GQ, HZ>(src.w + (size_t)t * Cfg::TB, fetch, d.K, t, lane, y[n]);
+                    }
+                }
+            }
+            if constexpr (!kSeveral) {
+                break;
+            } else {
+                // the next row block's first tile travels while this one's four sums meet in LDS, in one of two sets: a wave
+                // writes a set again only after the barrier that follows its last reading
+                const bool more = rb + 1 < rb_end;
+                src.w += (size_t)n_ktiles * Cfg::TB;
+                issue_weights<B, 1, GQ, HZ>(st[0], src, more && p0 + wave < p1, p0 + wave, lane);
+                publish(lr + (uint32_t)(r * kWaves * kRows * 4));
+                if (wave == 0) finish(lr + (uint32_t)(r * kWaves * kRows * 4));
+                if (!more) return;
+                y[0] = 0.f;
+                ++rb;
             }
         }
         if (NP == 1 || p1 >= k1) break;
@@ -208,21 +254,8 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
         __syncthreads();  // the next piece overwrites the digits
     }
 
-#pragma unroll
-    for (int n = 0; n < NP; ++n) store_lds<float>(lr + ((wave * NP + n) * kRows + lane) * 4, y[n]);
-    __syncthreads();
-    if (wave != 0) return;
-    float factor[NP];
-#pragma unroll
-    for (int n = 0; n < NP; ++n) {
-        y[n] = 0.f;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) y[n] += load_lds<float>(lr + ((w * NP + n) * kRows + lane) * 4);
-        factor[n] = 1.f;
-        if constexpr (SRC == TokenSource::kTablesI16)  // the tokens' power-of-two steps, behind the block sums of the tables
-            factor[n] = ldexpf(1.f, uniform(reinterpret_cast<const int*>(d.lut_s + (size_t)n_ktiles * Cfg::GPT * NP * 4)[n]));
-    }
-    finish_rows<NP>(d, rb, seg, n_seg, lane, y, factor);
+    publish(lr);
+    if (wave == 0) finish(lr);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -230,7 +263,8 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
 
 template <int B, int GQ, bool HZ, TokenSource SRC, int NP, bool SINGLE, typename Args>
 static int launch_x_cfg(const Args& a, const dim3& grid, int max_seg_tiles, hipStream_t st) {
-    constexpr unsigned kMostLds = x_lds_bytes(piece_tiles(NP), NP, kKTile / GQ);
+    constexpr int kSets = several_row_blocks<B, NP, Args> ? 2 : 1;
+    constexpr unsigned kMostLds = x_lds_bytes(piece_tiles(NP), NP, kKTile / GQ, kSets);
     static_assert(kMostLds <= 160 * 1024, "LDS of a workgroup");
     if constexpr (kMostLds > 64 * 1024) {  // above what a launch gets without asking
         static std::once_flag once;
@@ -242,7 +276,7 @@ static int launch_x_cfg(const Args& a, const dim3& grid, int max_seg_tiles, hipS
         if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
     }
     hipLaunchKernelGGL((mpgemv_x_kernel<B, GQ, HZ, SRC, NP, SINGLE, Args>), grid, dim3(kWaves * 64),
-                       x_lds_bytes(max_seg_tiles, NP, kKTile / GQ), st, a);
+                       x_lds_bytes(max_seg_tiles, NP, kKTile / GQ, kSets), st, a);
     return launch_status();
 }
 
@@ -298,6 +332,7 @@ static int launch_x_batch(const DecodeBatch& b, hipStream_t st) {
     KernelArgs<false> a;
     a.descs = b.descs;
     a.n_gemv = b.n_gemv;
+    a.row_blocks = b.row_blocks;
     return launch_x_tokens<SRC, false>(padded_tokens(b.N), b.bits, b.has_zero, b.group, a, b.n_workgroups, b.max_seg_tiles, st);
 }
 

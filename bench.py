@@ -37,7 +37,7 @@ MFMA_I8_PEAK_TOPS = 5000.0
 # cannot be read from inside the process.  Source: profiles/mpgemv_x_7b_w2g64_and_mpgemm_w4g64_hbm_traffic.txt.
 MEASURED_TRAFFIC_BYTES = {
     ("mpgemv_x", "7b_w2g64", 1): 63_839_232 + 197_632,
-    ("mpgemm", "prefill_w4g64", 1024): 95_291_597 + 22_544_384,
+    ("mpgemm", "prefill_w4g64", 1024): 95_291_392 + 22_544_384,
 }
 
 

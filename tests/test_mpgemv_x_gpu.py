@@ -1,4 +1,4 @@
-"""tman_mpgemv_x (one-token decode, tables built inside the lookup kernel) against the fp64 definition
+"""tman_mpgemv_x (one-token decode from the activations, in one launch) against the fp64 definition
 oracle, element by element, and against the two-call path it replaces."""
 import numpy as np
 import pytest

@@ -26,7 +26,7 @@ def test_defaults_are_current_and_consistent():
 
 
 @pytest.mark.parametrize("bad", [
-    dict(decode_x_seg_tiles=33),            # Eq. 1: 33 KB of tables do not fit the workgroup's 32 KB
+    dict(decode_x_seg_tiles=33),            # Eq. 1: a one-token segment is at most 32 tiles
     dict(decode_x_seg_tiles=0),
     dict(decode_x_long_seg_tiles=40),       # longer than a whole segment may be
     dict(decode_x_long_seg_tiles=0),

@@ -154,6 +154,7 @@ int launch_mpgemv_i16(const Layout& L, const void* packed, const void* lut, int 
 int launch_mpgemv_i16_batch(const DecodeBatch& b, hipStream_t st);
 int launch_mpgemv_x(const Layout& L, const void* packed, const void* x, void* y, void* workspace, hipStream_t st);
 int launch_mpgemv_x_batch(const DecodeBatch& b, hipStream_t st);
+constexpr int kCodesResident = 4;  // workgroups per compute unit up to which a launch of the matrix core kernels is numbered
 constexpr int kOrderedMaxWorkgroups = 4096;  // room in a descriptor table for a numbering of the workgroups
 // workgroups of a numbered launch (0: plain grid) and the numbering, for the plans of any of the decode kernels
 int ordered_workgroups_of(int count, const Layout* L, const GemvPlan* plans, int n_units, int per_unit);

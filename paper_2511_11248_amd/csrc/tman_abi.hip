@@ -59,8 +59,7 @@ size_t tman_lut_i16_bytes(int32_t N, int32_t K, int32_t group) {
 
 size_t tman_mpgemv_workspace_bytes(const tman_shape_t* shape, int32_t N) {
     if (check_shape(shape) != TMAN_OK || N < 1 || N > TMAN_MAX_DECODE_TOKENS) return 0;
-    const GemvPlan p = plan_decode(make_layout(shape), N);
-    return p.ticket_bytes + p.partial_bytes;
+    return decode_workspace_bytes(make_layout(shape), N);
 }
 
 size_t tman_mpgemm_workspace_bytes(const tman_shape_t* shape, int32_t N) {

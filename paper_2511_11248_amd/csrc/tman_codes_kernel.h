@@ -1,6 +1,6 @@
 // The product of codes and a handful of tokens on the matrix cores, as a template over the weight format, the number of
-// tokens and where the activations come from (as such: tman_mpgemm for 2 .. 32 tokens; out of fp16 lookup tables:
-// tman_mpgemv for 3 .. 8 tokens).
+// tokens and where the activations come from (as such: tman_mpgemm for 2 .. 32 tokens; out of lookup tables: tman_mpgemv and
+// tman_mpgemv_i16 for 2 .. 8 tokens, see lookups_stay).
 //
 // The matrix cores multiply the codes themselves, as exact fp16 numbers off + c (the code inserted into the mantissa of a
 // power of two), and a quantization block's scale and zero are applied to its sums:

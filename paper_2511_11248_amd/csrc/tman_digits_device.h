@@ -199,85 +199,61 @@ __device__ __forceinline__ void bias_block(const u32x2& xa, const u32x2& xb, uin
 }
 
 // Codes times activations of one tile block for the lane's row.  `dbase` is the LDS address of the tile's digit words
-// plus 4 (lane % 16), `mbase` of its blocks' records; token n's follow at n * 256 and n * GPT * 16.  The codes are made
-// once for all tokens.  One token: the accumulators run on over blocks and tiles, and a block's sum is what they gained
-// (`before`: their joined value so far; integers modulo 2^32), one subtraction instead of clearing four registers per
-// block (with more tokens they would be kept too long: 203 to 232 registers for 8 tokens instead of 157 to 159).
+// plus 4 (lane % 16), `mbase` of its blocks' records.  The accumulators run on over blocks and tiles, and a block's sum is
+// what they gained (`before`: their joined value so far; integers modulo 2^32), one subtraction instead of clearing four
+// registers per block.
 // Vector instructions per tile for 1 bit, blocks of 32 / 64: 147 -> 127, 121 -> 111 (with the shorter join_digits and the
 // scale read as fp16 by the multiplication).
 // `next` requests the wave's next tile: when this one is done, into its stage, or (1 bit) before the wait for this one, into
 // another stage.
-template <int B, int GQ, bool HZ, int NP, typename Next>
+template <int B, int GQ, bool HZ, typename Next>
 __device__ __forceinline__ void consume_weights_digits(const Stage<B, 1, GemvCfg<B, 1, GQ, HZ>::MPL>& s, uint32_t dbase,
-                                                       uint32_t mbase, int (&acc)[NP][4], uint32_t (&before)[NP],
-                                                       float (&y)[NP], Next next) {
+                                                       uint32_t mbase, int (&acc)[4], uint32_t& before, float& y, Next next) {
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
-    static_assert(NP == 1 || B == 4, "several tokens: 4 bits");
     constexpr int BPG = GQ / 32;  // 32-weight blocks per quantization block
-    uint32_t dg[NP][4];
+    uint32_t dg[4];
     // a block's record: (sum of X, step), and 8 * sum for 4 bits.  (Of a 16-byte read whose last words nobody uses the
     // compiler lets the next read overwrite those, and waits for each.)
     typedef std::conditional_t<B == 4, u32x4, u32x2> record_t;
-    record_t gm[NP][Cfg::GPT];
-    if constexpr (NP == 1) {  // (more tokens: read where they are used, to bound the registers)
+    record_t gm[Cfg::GPT];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) dg[0][b] = load_lds<uint32_t>(dbase + b * 64);
+    for (int b = 0; b < 4; ++b) dg[b] = load_lds<uint32_t>(dbase + b * 64);
 #pragma unroll
-        for (int gi = 0; gi < Cfg::GPT; ++gi) gm[0][gi] = load_lds<record_t>(mbase + gi * kDigitMetaBytes);
-    }
-    constexpr bool kEarly = B == 1 && NP == 1;
-    if constexpr (kEarly) {
+    for (int gi = 0; gi < Cfg::GPT; ++gi) gm[gi] = load_lds<record_t>(mbase + gi * kDigitMetaBytes);
+    if constexpr (B == 1) {
         next();
         __builtin_amdgcn_sched_barrier(0);  // (digits and the next tile are requested before the wait for this one)
     }
 #pragma unroll
     for (int gi = 0; gi < Cfg::GPT; ++gi) {
 #pragma unroll
-        for (int n = 0; n < NP; ++n)
-            if constexpr (NP > 1) {
-                gm[n][gi] = load_lds<record_t>(mbase + (n * Cfg::GPT + gi) * kDigitMetaBytes);
-                const uint32_t sum8 = gm[n][gi].z;
-                acc[n][0] = (int)sum8;  // 4 bits: fields hold code - 8
-                acc[n][1] = acc[n][2] = acc[n][3] = 0;
-            }
-#pragma unroll
         for (int b = gi * BPG; b < (gi + 1) * BPG; ++b) {
             const int v = (b * 32) / Cfg::CH, ksub = ((b * 32) % Cfg::CH) / 32;
             uint32_t p[B], c[4];
-            if constexpr (NP > 1)
-#pragma unroll
-                for (int n = 0; n < NP; ++n) dg[n][b] = load_lds<uint32_t>(dbase + n * kDigitBytesPerKTile + b * 64);
 #pragma unroll
             for (int i = 0; i < B; ++i) p[i] = word_of(s.c[v], ksub * B + i);
             planes_to_signed_codes<B>(p, c);
-#pragma unroll
-            for (int n = 0; n < NP; ++n) dot_block(acc[n], dg[n][b], c);
+            dot_block(acc, dg[b], c);
         }
         const int mo = gi * Cfg::MSZ;
         const uint32_t mw = s.meta[mo / 4];
         const float scale = half_bits_to_float((mo % 4) ? (mw >> 16) : (mw & 0xffffu));
-#pragma unroll
-        for (int n = 0; n < NP; ++n) {
-            const uint32_t gs_w = gm[n][gi].x, step_w = gm[n][gi].y;  // (copied out before the casts)
-            const float gs = __builtin_bit_cast(float, gs_w), step = __builtin_bit_cast(float, step_w);
-            uint32_t own = join_digits(acc[n]);
-            if constexpr (NP == 1) {
-                const uint32_t now = own;
-                own -= before[n];
-                before[n] = now;
-                if constexpr (B == 4) own += gm[n][gi].z;
-            }
-            const float a = (float)(int)own;
-            const float sc = NP == 1 ? fmaf(scale, step, 0.f) : scale * step;  // (one mixed-precision instruction)
-            if constexpr (HZ) {
-                const float z = half_bits_to_float(mw >> 16);
-                y[n] = fmaf(sc, fmaf(-z, gs, a), y[n]);
-            } else {
-                y[n] = fmaf(sc, fmaf(2.f, a, -gs), y[n]);
-            }
+        const uint32_t gs_w = gm[gi].x, step_w = gm[gi].y;  // (copied out before the casts)
+        const float gs = __builtin_bit_cast(float, gs_w), step = __builtin_bit_cast(float, step_w);
+        const uint32_t now = join_digits(acc);
+        uint32_t own = now - before;
+        before = now;
+        if constexpr (B == 4) own += gm[gi].z;  // fields hold code - 8
+        const float a = (float)(int)own;
+        const float sc = fmaf(scale, step, 0.f);  // (one mixed-precision instruction)
+        if constexpr (HZ) {
+            const float z = half_bits_to_float(mw >> 16);
+            y = fmaf(sc, fmaf(-z, gs, a), y);
+        } else {
+            y = fmaf(sc, fmaf(2.f, a, -gs), y);
         }
     }
-    if constexpr (!kEarly) next();
+    if constexpr (B != 1) next();
 }
 
 // Activations that are not finite take no part in the integer arithmetic (their X is 0); their products with the

@@ -30,7 +30,7 @@ struct GemvCfg {
     static constexpr int SLOT = T_BYTES + 256;  // table slice + group sums, per wave (multiple of 256)
     // tile blocks in flight per wave.  Measured: more do not help (the waves of a compute unit together
     // keep enough requests in flight) and cost time.
-    static constexpr int D = NP >= 4 ? 1 : (B == 4 ? 1 : (B == 2 ? 2 : 3));
+    static constexpr int D = NP >= 4 ? 1 : (B == 2 ? 2 : 3);
 };
 
 template <int B, int NP, int MPL>

@@ -107,11 +107,12 @@ struct GemvPlan {
     size_t ticket_bytes;
     size_t partial_bytes;
 };
-GemvPlan plan_gemv(const Layout& L, int N);
+GemvPlan plan_tables(const Layout& L, int N);  // table lookups, and what a workspace is sized for
 GemvPlan plan_segments(const Layout& L, int np, int max_seg);
 // Plan of the one-token kernel: at most 32 tiles per segment.
 GemvPlan plan_gemv_x(const Layout& L);
-GemvPlan plan_decode(const Layout& L, int N);  // the one of N tokens
+GemvPlan plan_decode(const Layout& L, int N);  // the one of N tokens; its workspace is at most decode_workspace_bytes
+size_t decode_workspace_bytes(const Layout& L, int N);
 void fill_desc_plan(GemvDesc& d, const Layout& L, const GemvPlan& p, const void* packed, const void* lut, int N, void* y,
                     void* workspace);
 void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace);
@@ -128,13 +129,15 @@ int launch_build_lut_i16_batch(int count, const void* const* x, int N, const int
 // The decoding kernel takes the activations as such (fp16 [K], one token) or out of tables made by tman_build_lut /
 // tman_build_lut_i16 (1 to 8 tokens).
 enum class TokenSource { kActivations, kTables, kTablesI16 };
-// Whether a format leaves the lookups for the dot product unit (tman_mpgemv_x_kernel.h).  A lookup serves all tokens at
-// once, digits cost 16 instructions per token and 32 weights; lookups cost per bit-plane, and integer entries have no
-// matrix instruction that adds them.  One token: digits.  More: 4-bit weights with integer tables (7B uint4 g128, lookups
-// -> digits, us per layer set with the table launch: N = 2 51 -> 35, N = 4 70 -> 46, N = 8 138 -> 78) and with fp16
-// tables for two tokens (36 -> 33; N = 4 37 -> 47, N = 8 61 -> 80 the other way round); 1 and 2 bits stay with the
-// lookups (7B uint2 N = 4: 29 against 44, int16 40 against 44).
-constexpr bool lookups_replaced(int bits, int np, bool integer) { return np == 1 || (bits == 4 && (integer || np == 2)); }
+// Which formats keep the table lookups for `np` tokens (padded).  One token goes to the dot product unit, the rest to the
+// matrix cores, which multiply the codes with the activations out of the tables (tman_codes_kernel.h); lookups cost per bit-plane
+// and need no codes, so they stay the better ones for few planes and few tokens.  Layer sets of width 4096, us with the
+// table launch, lookups (4 bits with integer tables: dot products) -> matrix cores: uint4 g128 N = 4 37.5 -> 29.7, g64 N = 2 / 4 / 8
+// 32 / 37 / 58 -> 28 / 31 / 41, integers 36 / 48 / 81 -> 31 / 35 / 48; uint2 g64 N = 2 / 4 / 8 22.4 / 25.7 / 40 -> 24.1 / 25.8 / 32,
+// integers 30 / 39 / 74 -> 27 / 30 / 38; 1 bit 18.5 / 21.3 / 33 -> 23.6 / 24 / 31, integers 22 / 25 / 46 -> 27 / 28 / 36.
+constexpr bool lookups_stay(int bits, int np, bool integer) {
+    return np == 2 ? bits == 1 || (bits == 2 && !integer) : np == 4 && bits == 1;
+}
 // A batch launch: numbered (order != nullptr, n_workgroups in all) or as the plain grid n_workgroups (of the largest
 // GEMV) x n_gemv.
 struct DecodeBatch {

@@ -25,8 +25,9 @@
 // All GEMVs of a decode step can share one launch (descriptor table), so the machine is filled even
 // though one layer alone is too small.
 //
-// mpgemv_kernel serves 2 to 8 tokens and reads the tables tman_build_lut made (Sec. 5: the precompute as a
-// kernel of its own, shared by the layers fed from one activation).  One token goes to tman_mpgemv_x.hip.
+// mpgemv_kernel serves 2 to 4 tokens of few bit-planes (lookups_stay) and reads the tables tman_build_lut made (Sec. 5: the
+// precompute as a kernel of its own, shared by the layers fed from one activation).  One token goes to tman_mpgemv_x.hip, the
+// rest to the matrix cores (tman_codes_kernel.h).
 #include <algorithm>
 #include <vector>
 
@@ -49,11 +50,28 @@ GemvPlan plan_segments(const Layout& L, int np, int max_seg) {
     return p;
 }
 
-GemvPlan plan_gemv(const Layout& L, int N) {
+GemvPlan plan_tables(const Layout& L, int N) {
     const int np = padded_tokens(N);
-    // with four or eight tokens a tile takes about twice as long: shorter segments, more workgroups (measured)
+    // with four or eight tokens a looked-up tile takes about twice as long: shorter segments, more workgroups (measured)
     const tman_tiling_t t = current_tiling();
     return plan_segments(L, np, np >= 4 ? t.decode_seg_tiles_many : t.decode_seg_tiles);
+}
+
+// Several tokens on the matrix cores: the kernel of small batches, and its segments (7B uint4 g128, N = 4, us per layer set with the
+// table launch, segments of 24 / 32 / 43 tiles: 37.5 / 33.6 / 29.7), unless the tiling asks for longer ones.  A table batch is
+// prepared for both kinds of tables; where only one of them is looked up (2 bits, two tokens) the plan is this one too.
+GemvPlan plan_decode(const Layout& L, int N) {
+    if (N == 1) return plan_gemv_x(L);
+    const int np = padded_tokens(N);
+    const tman_tiling_t t = current_tiling();
+    if (lookups_stay(L.bits, np, true)) return plan_tables(L, N);
+    return plan_segments(L, np, std::max(t.small_seg_tiles, np >= 4 ? t.decode_seg_tiles_many : t.decode_seg_tiles));
+}
+
+// (plan_decode never has more segments than plan_tables.)
+size_t decode_workspace_bytes(const Layout& L, int N) {
+    const GemvPlan p = N == 1 ? plan_gemv_x(L) : plan_tables(L, N);
+    return p.ticket_bytes + p.partial_bytes;
 }
 
 void fill_desc_plan(GemvDesc& d, const Layout& L, const GemvPlan& p, const void* packed, const void* lut, int N,

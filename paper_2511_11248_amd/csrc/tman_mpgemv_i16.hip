@@ -1,7 +1,8 @@
 // Decoding mpGEMV from INTEGER tables (Sec. 6.1 "A_INT16": activations as 16-bit integers; Sec. 4.3 two-level tiling: low
 // precision -- here exact integers -- inside a quantization block, floating point only across blocks).  The tables come
-// from tman_build_lut_i16; the kernel takes the 14-bit activations out of them and multiplies their digits with the codes
-// (tman_mpgemv_x.hip): the block sums are the integers the lookups would add up to.
+// from tman_build_lut_i16; the kernels take the 14-bit activations out of them and multiply them with the codes: one token as
+// digits on the dot product unit (tman_mpgemv_x.hip), several on the matrix cores (tman_codes_kernel.h), where an activation
+// is two exact fp16 numbers, a multiple of 8 and a rest; sums of products below 2^24 are exact there too.
 #include "tman_mpgemv_x_kernel.h"
 
 namespace tman {

@@ -28,26 +28,24 @@ __device__ __forceinline__ void issue_tile(Stage<B, NP, GemvCfg<B, NP, GQ, HZ>::
 template <int NP, bool INT> struct EntryT;
 template <> struct EntryT<2, false> { typedef half2_t type; };
 template <> struct EntryT<4, false> { typedef half4_t type; };
-template <> struct EntryT<8, false> { typedef half8_t type; };
 template <> struct EntryT<2, true> { typedef uint32_t type; };
 template <> struct EntryT<4, true> { typedef u32x2 type; };
-template <> struct EntryT<8, true> { typedef u32x4 type; };
 
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
 // Plane weights 2^i ("shift and accumulate") in the two forms the accumulation uses.
 //
 // Two tokens: a uniform float, the entry is added with a mixed-precision FMA.
-// Four or eight tokens: a lookup returns the entries of 4 (8) tokens for the lane's row, and adding them with
+// Four tokens: a lookup returns the entries of 4 tokens for the lane's row, and adding them with
 // one FMA per token makes the kernel bound by vector instruction issue.  The matrix pipe does the same
-// additions in one 4x4x4 MFMA per four tokens: with the 64 lanes as 16 blocks of 4, lane (b, j) supplies as
+// additions in one 4x4x4 MFMA: with the 64 lanes as 16 blocks of 4, lane (b, j) supplies as
 // B[k][j] its own four entries (k = token) and as A[i][k] row i = j of 2^plane times the identity, so
 // D[i][j] = 2^plane * (entry of token i in lane (b, j)): register i of the lane's accumulator is token i of
 // its own row.  fp16 inputs, exact products, fp32 accumulation, as with the FMA.
 template <int B, int NP>
 struct PlaneWeights {
     float pw[B];
-    half4_t hot[B];  // NP >= 4: row (lane % 4) of 2^i * identity
+    half4_t hot[B];  // NP == 4: row (lane % 4) of 2^i * identity
 };
 
 template <int B, int NP>
@@ -67,34 +65,23 @@ struct Accum;
 
 template <int NP>
 struct Accum<NP, false> {
-    float a[NP < 4 ? NP : 1];
-    float4_t q[NP >= 4 ? NP / 4 : 1];
+    static_assert(NP == 2 || NP == 4, "2 or 4 tokens");
+    typedef std::conditional_t<NP == 2, float[2], float4_t> sums_t;
+    sums_t a;
     __device__ __forceinline__ void clear() {
-        if constexpr (NP < 4) {
 #pragma unroll
-            for (int n = 0; n < NP; ++n) a[n] = 0.f;
-        } else {
-#pragma unroll
-            for (int h = 0; h < NP / 4; ++h) q[h] = float4_t{0.f, 0.f, 0.f, 0.f};
-        }
+        for (int n = 0; n < NP; ++n) a[n] = 0.f;
     }
     template <int B>
     __device__ __forceinline__ void add(const typename EntryT<NP, false>::type& e, const PlaneWeights<B, NP>& w, int plane) {
         if constexpr (NP == 2) {
 #pragma unroll
             for (int n = 0; n < NP; ++n) a[n] = fmaf(w.pw[plane], (float)e[n], a[n]);
-        } else if constexpr (NP == 4) {
-            q[0] = __builtin_amdgcn_mfma_f32_4x4x4f16(w.hot[plane], e, q[0], 0, 0, 0);
         } else {
-            const half4_t lo = {e[0], e[1], e[2], e[3]}, hi = {e[4], e[5], e[6], e[7]};
-            q[0] = __builtin_amdgcn_mfma_f32_4x4x4f16(w.hot[plane], lo, q[0], 0, 0, 0);
-            q[1] = __builtin_amdgcn_mfma_f32_4x4x4f16(w.hot[plane], hi, q[1], 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_4x4x4f16(w.hot[plane], e, a, 0, 0, 0);
         }
     }
-    __device__ __forceinline__ float get(int n) const {
-        if constexpr (NP < 4) return a[n];
-        else return q[n / 4][n % 4];
-    }
+    __device__ __forceinline__ float get(int n) const { return a[n]; }
 };
 
 // Integer tables (Sec. 4.3: entries are aggregated at low precision inside a quantization block, floating point
@@ -139,7 +126,7 @@ __device__ __forceinline__ void consume_tile(const Stage<B, NP, GemvCfg<B, NP, G
     using Cfg = GemvCfg<B, NP, GQ, HZ>;
     typedef typename EntryT<NP, INT>::type entry_t;
     constexpr int EB = 2 * NP;                                       // bytes per table entry
-    constexpr int SH = EB == 2 ? 1 : EB == 4 ? 2 : EB == 8 ? 3 : 4;  // log2(EB)
+    constexpr int SH = EB == 4 ? 2 : 3;                              // log2(EB)
     constexpr uint32_t NIB = 0x0F0F0F0Fu << SH;                      // index * EB, one per byte
     constexpr int TSTRIDE = 16 * EB;                                 // bytes per table
     constexpr int W = 4 * B;                                         // plane words per tile
@@ -162,7 +149,7 @@ __device__ __forceinline__ void consume_tile(const Stage<B, NP, GemvCfg<B, NP, G
         // the eight 4-bit indices of the word, pre-multiplied by the entry size: even nibbles in the
         // bytes of xe, odd nibbles in the bytes of xo
         const uint32_t xe = (w << SH) & NIB;
-        const uint32_t xo = SH == 4 ? (w & NIB) : ((w >> (4 - SH)) & NIB);
+        const uint32_t xo = (w >> (4 - SH)) & NIB;
         e[0] = load_lds<entry_t>(byte_of<0>(xe) + (lds + tb + 0 * TSTRIDE));
         e[1] = load_lds<entry_t>(byte_of<0>(xo) + (lds + tb + 1 * TSTRIDE));
         e[2] = load_lds<entry_t>(byte_of<1>(xe) + (lds + tb + 2 * TSTRIDE));
@@ -322,23 +309,17 @@ static int launch_group(int group, const Args& a, int n_wg, hipStream_t st) {
     return launch_status();
 }
 
-template <int NP, bool SINGLE, bool INT, typename Args>
-static int launch_format(int bits, int has_zero, int group, const Args& a, int n_wg, hipStream_t st) {
-    if (bits == 1) {
-        return has_zero ? launch_group<1, NP, true, SINGLE, INT>(group, a, n_wg, st)
-                        : launch_group<1, NP, false, SINGLE, INT>(group, a, n_wg, st);
-    }
-    if constexpr (!lookups_replaced(4, NP, INT))
-        if (bits == 4) return launch_group<4, NP, true, SINGLE, INT>(group, a, n_wg, st);
-    return launch_group<2, NP, true, SINGLE, INT>(group, a, n_wg, st);
-}
-
-// Lookups for 2 to 8 tokens.
+// The formats that keep the lookups (lookups_stay).
 template <bool SINGLE, bool INT, typename Args>
 static int launch_lookups(int np, int bits, int has_zero, int group, const Args& a, int n_wg, hipStream_t st) {
-    if (np == 2) return launch_format<2, SINGLE, INT>(bits, has_zero, group, a, n_wg, st);
-    if (np == 4) return launch_format<4, SINGLE, INT>(bits, has_zero, group, a, n_wg, st);
-    return launch_format<8, SINGLE, INT>(bits, has_zero, group, a, n_wg, st);
+    if constexpr (!INT)
+        if (bits == 2) return launch_group<2, 2, true, SINGLE, INT>(group, a, n_wg, st);
+    if (np == 2) {
+        return has_zero ? launch_group<1, 2, true, SINGLE, INT>(group, a, n_wg, st)
+                        : launch_group<1, 2, false, SINGLE, INT>(group, a, n_wg, st);
+    }
+    return has_zero ? launch_group<1, 4, true, SINGLE, INT>(group, a, n_wg, st)
+                    : launch_group<1, 4, false, SINGLE, INT>(group, a, n_wg, st);
 }
 
 }  // namespace tman

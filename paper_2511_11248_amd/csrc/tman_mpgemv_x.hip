@@ -1,5 +1,5 @@
-// Decoding mpGEMV on the 4-bit dot product unit: tman_mpgemv_x (one token, activations in), and tman_mpgemv /
-// tman_mpgemv_i16 (tables in) for one token and, where it is faster, for two to eight (lookups_replaced).
+// Decoding mpGEMV of one token on the 4-bit dot product unit: tman_mpgemv_x (activations in), tman_mpgemv and
+// tman_mpgemv_i16 (tables in).
 //
 // y[m] = sum_G scale[m][G] * (sum_{k in G} q[m][k] x[k] - zero[m][G] * S[G]) (Sec. 2.2).  The lookups of Sec. 4.3 turn
 // the inner sum into one table read per 4 weights and bit-plane; on this chip that costs 2.6 vector instructions and
@@ -40,8 +40,6 @@ GemvPlan plan_gemv_x(const Layout& L) {
     return plan_segments(L, 1, L.n_ktiles <= whole ? whole : t.decode_x_long_seg_tiles);
 }
 
-GemvPlan plan_decode(const Layout& L, int N) { return N == 1 ? plan_gemv_x(L) : plan_gemv(L, N); }
-
 void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace) {
     fill_desc_plan(d, L, plan_decode(L, N), packed, lut, N, y, workspace);
 }
@@ -60,14 +58,13 @@ int batch_row_blocks(int bits, int N, long long n_workgroups, int n_units) {
 // launch pays while a unit has few of them (1152 workgroups of a layer set with MLP width 14336, uint4 g128: 25.5 us on
 // the plain grid, 23.3 us numbered; equal workgroups need none).
 static int resident_per_unit(int count, const Layout* L, int N) {
+    const int np = padded_tokens(N);
+    if (np > 1 && !lookups_stay(L[0].bits, np, true)) return kCodesResident;
     int max_seg_tiles = 1;
     for (int g = 0; g < count; ++g) max_seg_tiles = std::max(max_seg_tiles, plan_decode(L[g], N).seg_tiles);
-    // (a descriptor table serves both kinds of tables: the kernel that takes more LDS counts)
-    const int np = padded_tokens(N);
-    unsigned lds = lookups_replaced(L[0].bits, np, true) ? x_lds_bytes(max_seg_tiles, np, L[0].groups_per_tile) : 0u;
-    if (np > 1) lds = std::max(lds, (unsigned)(kWaves * (kTableBytesPerKTile * np + 256 + np * kRows * 4)));
-    const int by_lds = (int)(160u * 1024u / lds);
-    return std::max(1, std::min(by_lds, std::min(8, 160 / max_seg_tiles)));
+    const unsigned lds = np == 1 ? x_lds_bytes(max_seg_tiles, L[0].groups_per_tile)
+                                 : (unsigned)(kWaves * (kTableBytesPerKTile * np + 256 + np * kRows * 4));
+    return std::max(1, std::min((int)(160u * 1024u / lds), std::min(8, 160 / max_seg_tiles)));
 }
 int ordered_workgroups(int count, const Layout* L, int N, int n_units) {
     if (count > 8) return 0;

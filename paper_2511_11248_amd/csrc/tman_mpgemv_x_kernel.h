@@ -1,70 +1,38 @@
-// The decoding kernel on the 4-bit dot product unit, as a template over the weight format, the source of the activations
-// and the number of tokens (padded to 1, 2, 4 or 8); what it does and why is said in tman_mpgemv_x.hip.
+// The one-token decoding kernel on the 4-bit dot product unit, as a template over the weight format and the source of the
+// activations; what it does and why is said in tman_mpgemv_x.hip.
 #pragma once
-#include <mutex>
-
+#include "tman_codes_kernel.h"
 #include "tman_digits_device.h"
 #include "tman_mpgemv_kernel.h"
 
 namespace tman {
 
-// K tiles whose digits are in LDS at a time (a longer segment is worked in such pieces): at most 61,440 bytes
-constexpr int piece_tiles(int np) { return np == 8 ? 24 : kGemvXSegmentTiles; }
-
-// LDS of a workgroup whose segment has `seg_tiles` tiles: digit words and `gpt` quantization blocks per tile and token,
-// then the partial sums (two sets where a workgroup takes several row blocks) and a word per wave: at most 69,648 bytes
-// (8 tokens, 24 tiles, blocks of 32)
-constexpr unsigned x_lds_bytes(int seg_tiles, int np, int gpt, int sets = 1) {
-    const int tiles = seg_tiles < piece_tiles(np) ? seg_tiles : piece_tiles(np);
-    return (unsigned)(tiles * np * (kDigitBytesPerKTile + gpt * kDigitMetaBytes) + sets * kWaves * kRows * np * 4 + kWaves * 4);
+// LDS of a workgroup whose segment has `seg_tiles` tiles: digit words and `gpt` quantization blocks per tile, then the
+// partial sums (two sets where a workgroup takes several row blocks) and a word per wave: at most 12,304 bytes
+constexpr unsigned x_lds_bytes(int seg_tiles, int gpt, int sets = 1) {
+    return (unsigned)(seg_tiles * (kDigitBytesPerKTile + gpt * kDigitMetaBytes) + sets * kWaves * kRows * 4 + kWaves * 4);
 }
 // Workgroups of a large 1-bit batch take several row blocks with one set of digits (batch_row_blocks).
-template <int B, int NP, typename Args>
-constexpr bool several_row_blocks = B == 1 && NP == 1 && std::is_same_v<Args, KernelArgs<false>>;
+template <int B, typename Args>
+constexpr bool several_row_blocks = B == 1 && std::is_same_v<Args, KernelArgs<false>>;
 
-// The 8 activations of a lane, per token: numbers 4f .. 4f + 3 (a) and 16 + 4f .. (b) of its 32-column block.
-template <int NP>
+// The 8 activations of a lane: numbers 4f .. 4f + 3 (a) and 16 + 4f .. (b) of its 32-column block.
 struct LaneActs {
-    u32x2 a[NP], b[NP];
+    u32x2 a, b;
 };
 
-// The four activations of each token out of one table.
-template <int NP>
-__device__ __forceinline__ void load_table(rsrc_t rt, int off, u32x2 (&x)[NP]) {
-    if constexpr (NP == 1) {
-        const u32x4 lo = __builtin_amdgcn_raw_buffer_load_b128(rt, off, 0, 0);
-        const uint32_t e8 = __builtin_amdgcn_raw_buffer_load_b32(rt, off + 16, 0, 0);
-        const uint32_t e01 = lo.x, e23 = lo.y, e45 = lo.z;
-        x[0] = u32x2{__builtin_amdgcn_perm(e23, e01, 0x05040302u), __builtin_amdgcn_perm(e8, e45, 0x05040100u)};
-    } else {
-        uint32_t e[4][NP / 2];  // entries 1, 2, 4, 8: NP numbers each
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int at = off + (1 << t) * 2 * NP;
-            if constexpr (NP == 2) {
-                e[t][0] = __builtin_amdgcn_raw_buffer_load_b32(rt, at, 0, 0);
-            } else if constexpr (NP == 4) {
-                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rt, at, 0, 0);
-                e[t][0] = v.x, e[t][1] = v.y;
-            } else {
-                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rt, at, 0, 0);
-                e[t][0] = v.x, e[t][1] = v.y, e[t][2] = v.z, e[t][3] = v.w;
-            }
-        }
-#pragma unroll
-        for (int n = 0; n < NP; ++n) {
-            const uint32_t half = n & 1 ? 0x07060302u : 0x05040100u;
-            x[n] = u32x2{__builtin_amdgcn_perm(e[1][n / 2], e[0][n / 2], half), __builtin_amdgcn_perm(e[3][n / 2], e[2][n / 2], half)};
-        }
-    }
+// The four activations out of one table.
+__device__ __forceinline__ void load_table(rsrc_t rt, int off, u32x2& x) {
+    const u32x4 lo = __builtin_amdgcn_raw_buffer_load_b128(rt, off, 0, 0);
+    const uint32_t e8 = __builtin_amdgcn_raw_buffer_load_b32(rt, off + 16, 0, 0);
+    const uint32_t e01 = lo.x, e23 = lo.y, e45 = lo.z;
+    x = u32x2{__builtin_amdgcn_perm(e23, e01, 0x05040302u), __builtin_amdgcn_perm(e8, e45, 0x05040100u)};
 }
 
-template <int B, int GQ, bool HZ, TokenSource SRC, int NP, bool SINGLE, typename Args>
+template <int B, int GQ, bool HZ, TokenSource SRC, bool SINGLE, typename Args>
 __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
-    static_assert(NP == 1 || SRC != TokenSource::kActivations, "several tokens come in tables");
-    constexpr int kPiece = piece_tiles(NP);
-    constexpr bool kSeveral = several_row_blocks<B, NP, Args>;
+    constexpr bool kSeveral = several_row_blocks<B, Args>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds_x[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -102,158 +70,129 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
     src.w_bytes = (uint32_t)(n_ktiles * Cfg::TB);
     src.t_bytes = src.s_bytes = 0;
 
-    const int piece = min(d.seg_tiles, kPiece);
     const uint32_t ld = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr<uint8_t>)lds_x));
-    const uint32_t lm = ld + (uint32_t)(piece * NP * kDigitBytesPerKTile);          // quantization blocks
-    const uint32_t lr = lm + (uint32_t)(piece * NP * Cfg::GPT * kDigitMetaBytes);  // partial sums [wave][token][row]
-    const uint32_t lf = lr + (kSeveral ? 2 : 1) * kWaves * kRows * NP * 4;          // a word per wave
+    const uint32_t lm = ld + (uint32_t)(d.seg_tiles * kDigitBytesPerKTile);          // quantization blocks
+    const uint32_t lr = lm + (uint32_t)(d.seg_tiles * Cfg::GPT * kDigitMetaBytes);  // partial sums [wave][row]
+    const uint32_t lf = lr + (kSeveral ? 2 : 1) * kWaves * kRows * 4;                // a word per wave
 
-    float y[NP];
-    int acc[NP][4];  // running sums of the digits, and their joined value (see consume_weights_digits)
-    uint32_t before[NP];
-#pragma unroll
-    for (int n = 0; n < NP; ++n) {
-        y[n] = 0.f;
-        acc[n][0] = acc[n][1] = acc[n][2] = acc[n][3] = 0;
-        before[n] = 0;
-    }
+    float y[1] = {0.f};
+    int acc[4] = {0, 0, 0, 0};  // running sums of the digits, and their joined value (see consume_weights_digits)
+    uint32_t before = 0;
     // the four sums of a row meet in LDS, the first wave adds them
     auto publish = [&](uint32_t set) {
-#pragma unroll
-        for (int n = 0; n < NP; ++n) store_lds<float>(set + ((wave * NP + n) * kRows + lane) * 4, y[n]);
+        store_lds<float>(set + (wave * kRows + lane) * 4, y[0]);
         __syncthreads();
     };
     auto finish = [&](uint32_t set) {
-        float factor[NP];
+        y[0] = 0.f;
 #pragma unroll
-        for (int n = 0; n < NP; ++n) {
-            y[n] = 0.f;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) y[n] += load_lds<float>(set + ((w * NP + n) * kRows + lane) * 4);
-            factor[n] = 1.f;
-            if constexpr (SRC == TokenSource::kTablesI16)  // the tokens' power-of-two steps, behind the block sums of the tables
-                factor[n] = ldexpf(1.f, uniform(reinterpret_cast<const int*>(d.lut_s + (size_t)n_ktiles * Cfg::GPT * NP * 4)[n]));
-        }
-        finish_rows<NP>(d, rb, seg, n_seg, lane, y, factor);
+        for (int w = 0; w < kWaves; ++w) y[0] += load_lds<float>(set + (w * kRows + lane) * 4);
+        float factor[1] = {1.f};
+        if constexpr (SRC == TokenSource::kTablesI16)  // the token's power-of-two step, behind the block sums of the tables
+            factor[0] = ldexpf(1.f, uniform(*reinterpret_cast<const int*>(d.lut_s + (size_t)n_ktiles * Cfg::GPT * 4)));
+        finish_rows<1>(d, rb, seg, n_seg, lane, y, factor);
     };
-    // the segment in pieces whose digits fit the LDS: one piece, unless the tiling asks for very long segments (never
-    // for one token)
-    for (int p0 = k0;;) {
-        const int p1 = NP == 1 ? k1 : min(p0 + kPiece, k1);
-        // The activations are requested first and the first weight tiles right behind them: a wave's loads return in
-        // the order they were issued, so activations queued behind weight tiles (which come from HBM) would hold the
-        // digits back until those tiles are in; this way the digits are made while the weights travel.
-        // Four lanes share a block of 32 columns; a pass is 64 blocks, 16 tiles.
-        constexpr int kPasses = (kPiece * kKTile / 8 + kWaves * 64 - 1) / (kWaves * 64);
-        LaneActs<NP> xv[kPasses];  // (a pass beyond the piece reads what nobody uses; x beyond K reads as zero)
-        if constexpr (SRC == TokenSource::kActivations) {
-            const uint32_t x_start = (uint32_t)(p0 * kKTile * 2);  // p0 < n_ktiles, so this lies inside x
-            // (the range check of a buffer load covers the per-lane offset only, not the scalar offset, so the resource
-            // starts at the piece's first activation and ends with x: K * 2 bytes less the piece's start)
-            const rsrc_t rx = make_rsrc(d.lut_t + x_start, (uint32_t)d.K * 2u - x_start);
-#pragma unroll
-            for (int i = 0; i < kPasses; ++i) {
-                const int off = (i * kWaves * 64 + (tid & ~3)) * 16 + (tid & 3) * 8;
-                xv[i].a[0] = __builtin_amdgcn_raw_buffer_load_b64(rx, off, 0, 0);
-                xv[i].b[0] = __builtin_amdgcn_raw_buffer_load_b64(rx, off + 32, 0, 0);
-            }
-        } else {
-            // table j = activations 4j .. 4j + 3: 16 entries of NP numbers of two bytes; entry 1 << t is activation 4j + t
-            constexpr int kTable = 32 * NP;
-            const uint32_t t_start = (uint32_t)p0 * (uint32_t)(kTablesPerKTile * kTable);
-            const rsrc_t rt = make_rsrc(d.lut_t + t_start, (uint32_t)n_ktiles * (uint32_t)(kTablesPerKTile * kTable) - t_start);
-#pragma unroll
-            for (int i = 0; i < kPasses; ++i) {
-                const int off = ((i * kWaves * 64 + (tid & ~3)) * 2 + (tid & 3)) * kTable;
-                load_table<NP>(rt, off, xv[i].a);
-                load_table<NP>(rt, off + 4 * kTable, xv[i].b);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // One bit: the next tile is requested before the wait for the current one, otherwise when the current one is done.
-        // A 1-bit tile is 1.3 to 2 KB and 110 vector instructions, so a wave waits longer than it computes: with the request
-        // at the end of a tile (where the last use of a zero kept it) 16 launches of a layer set of width 1024 took 131 us,
-        // now 92; width 3072 145 -> 130, 4096 184 -> 170 (zeros, blocks of 64; lookups: 109, 139, 182).  2 and 4 bits: more
-        // streams in flight cost more than they hide (see tman_mpgemv_x.hip).
-        constexpr int kStages = B == 1 && NP == 1 ? 2 : 1;
-        Stage<B, 1, Cfg::MPL> st[kStages] = {};
-        issue_weights<B, 1, GQ, HZ>(st[0], src, p0 + wave < p1, p0 + wave, lane);
-        __builtin_amdgcn_sched_barrier(0);
-
-        // digits of the piece: lane -> four lanes per 32-column block, sixteen per tile
-        const int n_lanes = (p1 - p0) * (kKTile / 8);
-        bool nonfinite = false;
+    // The activations are requested first and the first weight tiles right behind them: a wave's loads return in
+    // the order they were issued, so activations queued behind weight tiles (which come from HBM) would hold the
+    // digits back until those tiles are in; this way the digits are made while the weights travel.
+    // Four lanes share a block of 32 columns; a pass is 64 blocks, 16 tiles.
+    constexpr int kPasses = (kGemvXSegmentTiles * kKTile / 8 + kWaves * 64 - 1) / (kWaves * 64);
+    LaneActs xv[kPasses];  // (a pass beyond the segment reads what nobody uses; x beyond K reads as zero)
+    if constexpr (SRC == TokenSource::kActivations) {
+        const uint32_t x_start = (uint32_t)(k0 * kKTile * 2);  // k0 < n_ktiles, so this lies inside x
+        // (the range check of a buffer load covers the per-lane offset only, not the scalar offset, so the resource
+        // starts at the segment's first activation and ends with x: K * 2 bytes less the segment's start)
+        const rsrc_t rx = make_rsrc(d.lut_t + x_start, (uint32_t)d.K * 2u - x_start);
 #pragma unroll
         for (int i = 0; i < kPasses; ++i) {
-            if (i * kWaves * 64 + wave * 64 >= n_lanes) break;  // (this wave has none)
-            const int j = i * kWaves * 64 + tid, tile = j >> 4;
-            const bool live = j < n_lanes;
-#pragma unroll
-            for (int n = 0; n < NP; ++n) {
-                uint32_t r[4];
-                float step = 1.f;
-                if constexpr (SRC == TokenSource::kTablesI16)
-                    bias_block(xv[i].a[n], xv[i].b[n], r);
-                else
-                    nonfinite |= quantize_block<GQ>(xv[i].a[n], xv[i].b[n], r, step) && live;
-                store_digits<GQ>(r, step, j, live, ld + (uint32_t)((tile * NP + n) * kDigitBytesPerKTile + (j & 15) * 16),
-                                 lm + (uint32_t)(((tile * NP + n) * Cfg::GPT + (j & 15) / (GQ / 8)) * kDigitMetaBytes));
-            }
+            const int off = (i * kWaves * 64 + (tid & ~3)) * 16 + (tid & 3) * 8;
+            xv[i].a = __builtin_amdgcn_raw_buffer_load_b64(rx, off, 0, 0);
+            xv[i].b = __builtin_amdgcn_raw_buffer_load_b64(rx, off + 32, 0, 0);
         }
-        if constexpr (SRC != TokenSource::kTablesI16)
-            store_lds<uint32_t>(lf + wave * 4, __builtin_amdgcn_ballot_w64(nonfinite) != 0 ? 1u : 0u);
-        __syncthreads();
-
-        for (int r = 0;; r ^= 1) {  // the row blocks of the workgroup (one, unless kSeveral)
-            // the waves take the tiles in turn
-            for (int t0 = p0 + wave; t0 < p1; t0 += kStages * kWaves) {
+    } else {
+        // table j = activations 4j .. 4j + 3: 16 entries of two bytes; entry 1 << t is activation 4j + t
+        constexpr int kTable = 32;
+        const uint32_t t_start = (uint32_t)k0 * (uint32_t)(kTablesPerKTile * kTable);
+        const rsrc_t rt = make_rsrc(d.lut_t + t_start, (uint32_t)n_ktiles * (uint32_t)(kTablesPerKTile * kTable) - t_start);
 #pragma unroll
-                for (int s = 0; s < kStages; ++s) {
-                    const int t = t0 + s * kWaves;
-                    if (t < p1)
-                        consume_weights_digits<B, GQ, HZ, NP>(
-                            st[s], ld + (uint32_t)((t - p0) * NP * kDigitBytesPerKTile + (lane & 15) * 4),
-                            lm + (uint32_t)((t - p0) * NP * Cfg::GPT * kDigitMetaBytes), acc, before, y, [&] {
-                                issue_weights<B, 1, GQ, HZ>(st[(s + 1) % kStages], src, t + kWaves < p1, t + kWaves, lane);
-                            });
-                }
-            }
-            if constexpr (SRC != TokenSource::kTablesI16) {
-                const u32x4 f = load_lds<u32x4>(lf);
-                if (uniform((int)(f.x | f.y | f.z | f.w))) {
-#pragma unroll
-                    for (int n = 0; n < NP; ++n) {
-                        auto fetch = [&](int k) -> uint32_t {
-                            if constexpr (SRC == TokenSource::kActivations) return load_global<uint16_t>(d.lut_t, (uint32_t)k * 2u);
-                            else
-                                return load_global<uint16_t>(
-                                    d.lut_t, (((uint32_t)(k / kLutGroup) * 16u + (1u << (k % kLutGroup))) * NP + n) * 2u);
-                        };
-                        for (int t = p0 + wave; t < p1; t += kWaves)
-                            y[n] = add_nonfinite<B, GQ, HZ>(src.w + (size_t)t * Cfg::TB, fetch, d.K, t, lane, y[n]);
-                    }
-                }
-            }
-            if constexpr (!kSeveral) {
-                break;
-            } else {
-                // the next row block's first tile travels while this one's four sums meet in LDS, in one of two sets: a wave
-                // writes a set again only after the barrier that follows its last reading
-                const bool more = rb + 1 < rb_end;
-                src.w += (size_t)n_ktiles * Cfg::TB;
-                issue_weights<B, 1, GQ, HZ>(st[0], src, more && p0 + wave < p1, p0 + wave, lane);
-                publish(lr + (uint32_t)(r * kWaves * kRows * 4));
-                if (wave == 0) finish(lr + (uint32_t)(r * kWaves * kRows * 4));
-                if (!more) return;
-                y[0] = 0.f;
-                ++rb;
-            }
+        for (int i = 0; i < kPasses; ++i) {
+            const int off = ((i * kWaves * 64 + (tid & ~3)) * 2 + (tid & 3)) * kTable;
+            load_table(rt, off, xv[i].a);
+            load_table(rt, off + 4 * kTable, xv[i].b);
         }
-        if (NP == 1 || p1 >= k1) break;
-        p0 = p1;
-        __syncthreads();  // the next piece overwrites the digits
     }
+    __builtin_amdgcn_sched_barrier(0);
+    // One bit: the next tile is requested before the wait for the current one, otherwise when the current one is done.
+    // A 1-bit tile is 1.3 to 2 KB and 110 vector instructions, so a wave waits longer than it computes: with the request
+    // at the end of a tile (where the last use of a zero kept it) 16 launches of a layer set of width 1024 took 131 us,
+    // now 92; width 3072 145 -> 130, 4096 184 -> 170 (zeros, blocks of 64; lookups: 109, 139, 182).  2 and 4 bits: more
+    // streams in flight cost more than they hide (see tman_mpgemv_x.hip).
+    constexpr int kStages = B == 1 ? 2 : 1;
+    Stage<B, 1, Cfg::MPL> st[kStages] = {};
+    issue_weights<B, 1, GQ, HZ>(st[0], src, k0 + wave < k1, k0 + wave, lane);
+    __builtin_amdgcn_sched_barrier(0);
 
+    // digits of the segment: lane -> four lanes per 32-column block, sixteen per tile
+    const int n_lanes = (k1 - k0) * (kKTile / 8);
+    bool nonfinite = false;
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+        if (i * kWaves * 64 + wave * 64 >= n_lanes) break;  // (this wave has none)
+        const int j = i * kWaves * 64 + tid, tile = j >> 4;
+        const bool live = j < n_lanes;
+        uint32_t r[4];
+        float step = 1.f;
+        if constexpr (SRC == TokenSource::kTablesI16)
+            bias_block(xv[i].a, xv[i].b, r);
+        else
+            nonfinite |= quantize_block<GQ>(xv[i].a, xv[i].b, r, step) && live;
+        store_digits<GQ>(r, step, j, live, ld + (uint32_t)(tile * kDigitBytesPerKTile + (j & 15) * 16),
+                         lm + (uint32_t)((tile * Cfg::GPT + (j & 15) / (GQ / 8)) * kDigitMetaBytes));
+    }
+    if constexpr (SRC != TokenSource::kTablesI16)
+        store_lds<uint32_t>(lf + wave * 4, __builtin_amdgcn_ballot_w64(nonfinite) != 0 ? 1u : 0u);
+    __syncthreads();
+
+    for (int r = 0;; r ^= 1) {  // the row blocks of the workgroup (one, unless kSeveral)
+        // the waves take the tiles in turn
+        for (int t0 = k0 + wave; t0 < k1; t0 += kStages * kWaves) {
+#pragma unroll
+            for (int s = 0; s < kStages; ++s) {
+                const int t = t0 + s * kWaves;
+                if (t < k1)
+                    consume_weights_digits<B, GQ, HZ>(
+                        st[s], ld + (uint32_t)((t - k0) * kDigitBytesPerKTile + (lane & 15) * 4),
+                        lm + (uint32_t)((t - k0) * Cfg::GPT * kDigitMetaBytes), acc, before, y[0], [&] {
+                            issue_weights<B, 1, GQ, HZ>(st[(s + 1) % kStages], src, t + kWaves < k1, t + kWaves, lane);
+                        });
+            }
+        }
+        if constexpr (SRC != TokenSource::kTablesI16) {
+            const u32x4 f = load_lds<u32x4>(lf);
+            if (uniform((int)(f.x | f.y | f.z | f.w))) {
+                auto fetch = [&](int k) -> uint32_t {
+                    if constexpr (SRC == TokenSource::kActivations) return load_global<uint16_t>(d.lut_t, (uint32_t)k * 2u);
+                    else return load_global<uint16_t>(d.lut_t, ((uint32_t)(k / kLutGroup) * 16u + (1u << (k % kLutGroup))) * 2u);
+                };
+                for (int t = k0 + wave; t < k1; t += kWaves)
+                    y[0] = add_nonfinite<B, GQ, HZ>(src.w + (size_t)t * Cfg::TB, fetch, d.K, t, lane, y[0]);
+            }
+        }
+        if constexpr (!kSeveral) {
+            break;
+        } else {
+            // the next row block's first tile travels while this one's four sums meet in LDS, in one of two sets: a wave
+            // writes a set again only after the barrier that follows its last reading
+            const bool more = rb + 1 < rb_end;
+            src.w += (size_t)n_ktiles * Cfg::TB;
+            issue_weights<B, 1, GQ, HZ>(st[0], src, more && k0 + wave < k1, k0 + wave, lane);
+            publish(lr + (uint32_t)(r * kWaves * kRows * 4));
+            if (wave == 0) finish(lr + (uint32_t)(r * kWaves * kRows * 4));
+            if (!more) return;
+            y[0] = 0.f;
+            ++rb;
+        }
+    }
     publish(lr);
     if (wave == 0) finish(lr);
 }
@@ -261,52 +200,40 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
 // ---------------------------------------------------------------------------------------------
 // launch
 
-template <int B, int GQ, bool HZ, TokenSource SRC, int NP, bool SINGLE, typename Args>
+template <int B, int GQ, bool HZ, TokenSource SRC, bool SINGLE, typename Args>
 static int launch_x_cfg(const Args& a, const dim3& grid, int max_seg_tiles, hipStream_t st) {
-    constexpr int kSets = several_row_blocks<B, NP, Args> ? 2 : 1;
-    constexpr unsigned kMostLds = x_lds_bytes(piece_tiles(NP), NP, kKTile / GQ, kSets);
-    static_assert(kMostLds <= 160 * 1024, "LDS of a workgroup");
-    if constexpr (kMostLds > 64 * 1024) {  // above what a launch gets without asking
-        static std::once_flag once;
-        static hipError_t attr_rc = hipSuccess;
-        std::call_once(once, [] {
-            attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&mpgemv_x_kernel<B, GQ, HZ, SRC, NP, SINGLE, Args>),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, kMostLds);
-        });
-        if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
-    }
-    hipLaunchKernelGGL((mpgemv_x_kernel<B, GQ, HZ, SRC, NP, SINGLE, Args>), grid, dim3(kWaves * 64),
-                       x_lds_bytes(max_seg_tiles, NP, kKTile / GQ, kSets), st, a);
+    constexpr int kSets = several_row_blocks<B, Args> ? 2 : 1;
+    static_assert(x_lds_bytes(kGemvXSegmentTiles, kKTile / GQ, kSets) <= 64 * 1024, "LDS of a launch that does not ask for more");
+    hipLaunchKernelGGL((mpgemv_x_kernel<B, GQ, HZ, SRC, SINGLE, Args>), grid, dim3(kWaves * 64),
+                       x_lds_bytes(max_seg_tiles, kKTile / GQ, kSets), st, a);
     return launch_status();
 }
 
-template <int B, bool HZ, TokenSource SRC, int NP, bool SINGLE, typename Args>
+template <int B, bool HZ, TokenSource SRC, bool SINGLE, typename Args>
 static int launch_x_group(int group, const Args& a, int n_wg, int max_seg_tiles, hipStream_t st) {
     const dim3 grid((unsigned)n_wg, __is_same(Args, OrderedArgs) ? 1u : (unsigned)a.n_gemv);
     switch (group) {
-        case 32: return launch_x_cfg<B, 32, HZ, SRC, NP, SINGLE>(a, grid, max_seg_tiles, st);
-        case 64: return launch_x_cfg<B, 64, HZ, SRC, NP, SINGLE>(a, grid, max_seg_tiles, st);
-        default: return launch_x_cfg<B, 128, HZ, SRC, NP, SINGLE>(a, grid, max_seg_tiles, st);
+        case 32: return launch_x_cfg<B, 32, HZ, SRC, SINGLE>(a, grid, max_seg_tiles, st);
+        case 64: return launch_x_cfg<B, 64, HZ, SRC, SINGLE>(a, grid, max_seg_tiles, st);
+        default: return launch_x_cfg<B, 128, HZ, SRC, SINGLE>(a, grid, max_seg_tiles, st);
     }
 }
 
 template <TokenSource SRC, bool SINGLE, typename Args>
 static int launch_x_tokens(int np, int bits, int has_zero, int group, const Args& a, int n_wg, int max_seg_tiles, hipStream_t st) {
-    constexpr bool INT = SRC == TokenSource::kTablesI16;
     if constexpr (SRC != TokenSource::kActivations) {
-        if (!lookups_replaced(bits, np, INT)) return launch_lookups<SINGLE, INT>(np, bits, has_zero, group, a, n_wg, st);
-        if (np == 2) return launch_x_group<4, true, SRC, 2, SINGLE>(group, a, n_wg, max_seg_tiles, st);
-        if constexpr (INT) {
-            if (np == 4) return launch_x_group<4, true, SRC, 4, SINGLE>(group, a, n_wg, max_seg_tiles, st);
-            if (np == 8) return launch_x_group<4, true, SRC, 8, SINGLE>(group, a, n_wg, max_seg_tiles, st);
-        }
+        constexpr bool INT = SRC == TokenSource::kTablesI16;
+        if (np > 1 && lookups_stay(bits, np, INT)) return launch_lookups<SINGLE, INT>(np, bits, has_zero, group, a, n_wg, st);
+        if (np == 2) return launch_codes_tables<2, INT, SINGLE>(bits, has_zero, group, a, n_wg, st);
+        if (np == 4) return launch_codes_tables<4, INT, SINGLE>(bits, has_zero, group, a, n_wg, st);
+        if (np == 8) return launch_codes_tables<8, INT, SINGLE>(bits, has_zero, group, a, n_wg, st);
     }
     if (bits == 1) {
-        return has_zero ? launch_x_group<1, true, SRC, 1, SINGLE>(group, a, n_wg, max_seg_tiles, st)
-                        : launch_x_group<1, false, SRC, 1, SINGLE>(group, a, n_wg, max_seg_tiles, st);
+        return has_zero ? launch_x_group<1, true, SRC, SINGLE>(group, a, n_wg, max_seg_tiles, st)
+                        : launch_x_group<1, false, SRC, SINGLE>(group, a, n_wg, max_seg_tiles, st);
     }
-    if (bits == 2) return launch_x_group<2, true, SRC, 1, SINGLE>(group, a, n_wg, max_seg_tiles, st);
-    return launch_x_group<4, true, SRC, 1, SINGLE>(group, a, n_wg, max_seg_tiles, st);
+    if (bits == 2) return launch_x_group<2, true, SRC, SINGLE>(group, a, n_wg, max_seg_tiles, st);
+    return launch_x_group<4, true, SRC, SINGLE>(group, a, n_wg, max_seg_tiles, st);
 }
 
 // A single GEMV, a numbered batch and a batch on the plain grid from one source of activations.

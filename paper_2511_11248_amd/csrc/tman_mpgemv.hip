@@ -29,6 +29,8 @@
 // precompute as a kernel of its own, shared by the layers fed from one activation).  One token goes to tman_mpgemv_x.hip, the
 // rest to the matrix cores (tman_codes_kernel.h).
 #include <algorithm>
+#include <functional>
+#include <queue>
 #include <vector>
 
 #include "tman_mpgemv_x_kernel.h"
@@ -154,12 +156,14 @@ bool order_workgroups_of(int count, const Layout* L, const GemvPlan* plans, int 
                          std::vector<uint16_t>* order) {
     const int n = ordered_workgroups_of(count, L, plans, n_units, per_unit);
     if (!n) return false;
+    const int slots = (n + n_units - 1) / n_units;  // places of a unit; units from n % n_units on have one less if that is not 0
     auto places = [&](int j) { return n / n_units + (j < n % n_units ? 1 : 0); };
     struct Item {
         int cost;
         uint16_t id;
     };
     std::vector<Item> items;
+    items.reserve(n);
     for (int g = 0; g < count; ++g) {
         const GemvPlan& p = plans[g];
         for (int w = 0; w < p.n_workgroups; ++w) {
@@ -168,46 +172,53 @@ bool order_workgroups_of(int count, const Layout* L, const GemvPlan* plans, int 
             items.push_back(Item{tiles + 2, (uint16_t)((g << 13) | w)});
         }
     }
-    std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.cost > b.cost; });
-    std::vector<int> load(n_units, 0);
-    std::vector<std::vector<uint16_t>> mine(n_units);
-    std::vector<std::vector<int>> cost(n_units);
+    auto larger = [](const Item& a, const Item& b) { return a.cost > b.cost; };
+    std::stable_sort(items.begin(), items.end(), larger);
+    // the unit with the least work and a free place, of several the first
+    typedef std::pair<int, int> Unit;  // (work so far, unit)
+    std::priority_queue<Unit, std::vector<Unit>, std::greater<Unit>> open;
+    for (int j = 0; j < n_units; ++j)
+        if (places(j) > 0) open.push(Unit(0, j));
+    std::vector<int> load(n_units, 0), count_of(n_units, 0);
+    std::vector<Item> mine((size_t)n_units * slots);  // by unit
     for (const Item& it : items) {
-        int best = -1;
-        for (int j = 0; j < n_units; ++j)
-            if ((int)mine[j].size() < places(j) && (best < 0 || load[j] < load[best])) best = j;
-        load[best] += it.cost;
-        mine[best].push_back(it.id);
-        cost[best].push_back(it.cost);
+        const int j = open.top().second;
+        open.pop();
+        load[j] += it.cost;
+        mine[(size_t)j * slots + count_of[j]++] = it;
+        if (count_of[j] < places(j)) open.push(Unit(load[j], j));
     }
     for (int round = 0; round < 8 * n; ++round) {
         int hi = 0;
         for (int j = 1; j < n_units; ++j)
             if (load[j] > load[hi]) hi = j;
+        const Item* const h = &mine[(size_t)hi * slots];
         int best_j = -1, best_a = -1, best_b = -1, best_max = load[hi];
         for (int j = 0; j < n_units; ++j) {
-            if (j == hi || load[j] >= load[hi]) continue;
-            for (size_t a = 0; a < cost[hi].size(); ++a)
-                for (size_t b = 0; b < cost[j].size(); ++b) {
-                    const int d = cost[hi][a] - cost[j][b];
-                    if (d <= 0) continue;
+            if (j == hi || load[hi] + load[j] >= 2 * best_max) continue;  // (the larger is at least the mean)
+            const Item* const q = &mine[(size_t)j * slots];
+            for (int a = 0; a < count_of[hi]; ++a) {
+                if (a > 0 && h[a].cost == h[a - 1].cost) continue;  // (of equal exchanges the first counts)
+                for (int b = 0; b < count_of[j]; ++b) {
+                    const int d = h[a].cost - q[b].cost;
+                    if (d <= 0 || (b > 0 && q[b].cost == q[b - 1].cost)) continue;
                     const int m = std::max(load[hi] - d, load[j] + d);
-                    if (m < best_max) best_max = m, best_j = j, best_a = (int)a, best_b = (int)b;
+                    if (m < best_max) best_max = m, best_j = j, best_a = a, best_b = b;
                 }
+            }
         }
         if (best_j < 0) break;
-        const int d = cost[hi][best_a] - cost[best_j][best_b];
-        std::swap(cost[hi][best_a], cost[best_j][best_b]);
-        std::swap(mine[hi][best_a], mine[best_j][best_b]);
+        Item &from = mine[(size_t)hi * slots + best_a], &to = mine[(size_t)best_j * slots + best_b];
+        const int d = from.cost - to.cost;
+        std::swap(from, to);
         load[hi] -= d;
         load[best_j] += d;
     }
     order->assign(n, 0);
     for (int j = 0; j < n_units; ++j) {
-        std::vector<size_t> by_cost(mine[j].size());
-        for (size_t r = 0; r < by_cost.size(); ++r) by_cost[r] = r;
-        std::stable_sort(by_cost.begin(), by_cost.end(), [&](size_t a, size_t b) { return cost[j][a] > cost[j][b]; });
-        for (size_t r = 0; r < by_cost.size(); ++r) (*order)[r * n_units + j] = mine[j][by_cost[r]];
+        Item* const q = &mine[(size_t)j * slots];
+        std::stable_sort(q, q + count_of[j], larger);
+        for (int r = 0; r < count_of[j]; ++r) (*order)[(size_t)r * n_units + j] = q[r].id;
     }
     return true;
 }

@@ -15,8 +15,9 @@ LIB = os.path.join(HERE, "libtman.so")
 SOURCES = ["tman_abi.hip", "tman_tiling.hip", "tman_pack.hip", "tman_lut.hip", "tman_mpgemv.hip", "tman_mpgemv_i16.hip", "tman_mpgemv_x.hip", "tman_mpgemm.hip", "tman_mpgemm_small.hip", "tman_mpgemm_i8.hip", "tman_noalloc.hip"]
 
 # -packed-fp32-ops: keep the compiler from forming packed fp32 VALU instructions
+# kernarg-preload: scalar kernel arguments are in registers when a wave starts
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
-         "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-command-line-argument",
+         "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-command-line-argument",
          "-Wno-unknown-attributes"]
 
 

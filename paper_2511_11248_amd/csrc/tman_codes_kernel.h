@@ -171,8 +171,9 @@ constexpr uint32_t codes_lds_bytes(int nt) { return kWaves * codes_wave_bytes(nt
 
 // NT: rows of the first operand / 8, rounded up.  TNP: 0, or the tokens (padded to 2, 4 or 8) of the tables the activations are
 // taken from; INT: integer tables, whose 14-bit activations are two rows each, a multiple of 8 and a rest of -4 .. 3.
-template <int B, int GQ, bool HZ, int NT, int TNP, bool INT, bool SINGLE, typename Args>
-__global__ void __launch_bounds__(kWaves * 64, 3) mpgemm_codes_kernel(Args a) {
+template <int B, int GQ, bool HZ, int NT, int TNP, bool INT, bool SINGLE, typename Args, typename... Fields>
+__global__ void __launch_bounds__(kWaves * 64, 3) mpgemm_codes_kernel(Fields... fields) {
+    const Args a{fields...};
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
     static_assert(GQ >= 64 || NT <= 2, "blocks of 32: 16 rows");
     static_assert(TNP == 0 || NT == (INT && TNP == 8 ? 2 : 1), "tables: 8 tokens");
@@ -189,9 +190,8 @@ __global__ void __launch_bounds__(kWaves * 64, 3) mpgemm_codes_kernel(Args a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    int g, wg_local;
-    workgroup_of<SINGLE>(a, g, wg_local);
-    const GemvDesc d = desc_value<SINGLE>(a, g);
+    int wg_local;
+    const GemvDesc d = desc_of_workgroup(a, wg_local);
     const int n_seg = d.n_seg, n_ktiles = d.n_ktiles;
     // Exits: surplus workgroups of the grid, and (single call) a blob packed for another shape or layout, which is
     // reported and leaves y alone (a batch is checked when its descriptor table is written).
@@ -528,7 +528,10 @@ __global__ void __launch_bounds__(kWaves * 64, 3) mpgemm_codes_kernel(Args a) {
 template <int B, int GQ, bool HZ, int NT, int TNP, bool INT, bool SINGLE, typename Args>
 static int launch_codes(const Args& a, int n_wg, hipStream_t st) {
     const dim3 grid((unsigned)n_wg, __is_same(Args, OrderedArgs) ? 1u : (unsigned)a.n_gemv);
-    hipLaunchKernelGGL((mpgemm_codes_kernel<B, GQ, HZ, NT, TNP, INT, SINGLE, Args>), grid, dim3(kWaves * 64), codes_lds_bytes(NT), st, a);
+    with_fields(a, [&](auto... f) {
+        hipLaunchKernelGGL((mpgemm_codes_kernel<B, GQ, HZ, NT, TNP, INT, SINGLE, Args, decltype(f)...>), grid, dim3(kWaves * 64),
+                           codes_lds_bytes(NT), st, f...);
+    });
     return launch_status();
 }
 

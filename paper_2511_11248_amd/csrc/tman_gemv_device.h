@@ -181,44 +181,39 @@ struct OrderedArgs {
     const uint16_t* order;  // per workgroup id: GEMV in bits 13..15, workgroup within the GEMV in bits 0..12
     int n_gemv;
 };
-template <bool SINGLE>
-__device__ __forceinline__ const GemvDesc& desc_of(const OrderedArgs& a, int g) {
-    return a.descs[g];
-}
+
+// The batch kernels take the fields of their arguments one by one: scalar arguments are in registers when a wave starts (the
+// build asks for it), a structure is read from memory first (0.25 us of a launch).
+template <typename Launch>
+static void with_fields(const KernelArgs<true>& a, Launch launch) { launch(a); }
+template <typename Launch>
+static void with_fields(const KernelArgs<false>& a, Launch launch) { launch(a.descs, a.n_gemv, a.row_blocks); }
+template <typename Launch>
+static void with_fields(const OrderedArgs& a, Launch launch) { launch(a.descs, a.order, a.n_gemv); }
+
 // wave-uniform loads from constant memory (scalar loads)
 template <typename T>
 using const_ptr = const T __attribute__((address_space(4)))*;
 
-// (GEMV, workgroup of the GEMV) of this workgroup: from the numbering, or from the 2-D grid
-template <bool SINGLE, typename Args>
-__device__ __forceinline__ void workgroup_of(const Args& a, int& g, int& wg_local) {
-    if constexpr (__is_same(Args, OrderedArgs)) {
-        // entries in pairs, one scalar load (the numbering has room for an even number)
-        const uint32_t pair = reinterpret_cast<const_ptr<uint32_t>>(reinterpret_cast<uintptr_t>(a.order))[blockIdx.x >> 1];
-        const uint32_t e = (blockIdx.x & 1) ? pair >> 16 : pair & 0xffffu;
-        g = (int)(e >> 13);
-        wg_local = (int)(e & 0x1fffu);
-    } else {
-        g = SINGLE ? 0 : (int)blockIdx.y;
-        wg_local = (int)blockIdx.x;
-    }
-}
-
-template <bool SINGLE>
-__device__ __forceinline__ const GemvDesc& desc_of(const KernelArgs<SINGLE>& a, int g) {
-    if constexpr (SINGLE) {
-        return a.single;
-    } else {
-        return a.descs[g];
-    }
-}
-
-// The descriptor as a value, fetched whole by scalar loads: one memory round trip instead of one per group of fields.
-template <bool SINGLE, typename Args>
-__device__ __forceinline__ GemvDesc desc_value(const Args& a, int g) {
+// The descriptor of this workgroup's GEMV, as a value, and the workgroup's index in it: from the numbering, or from the
+// 2-D grid.  The descriptor is fetched whole by scalar loads: one memory round trip instead of one per group of fields.
+// (Requesting all descriptors of a numbered launch along with the entry that says which one it is, three to a register by
+// vector loads, and picking one out of the lanes cost 0.25 us more than the second round trip.)
+template <typename Args>
+__device__ __forceinline__ GemvDesc desc_of_workgroup(const Args& a, int& wg_local) {
     if constexpr (__is_same(Args, KernelArgs<true>)) {
+        wg_local = (int)blockIdx.x;
         return a.single;
     } else {
+        int g = (int)blockIdx.y;
+        wg_local = (int)blockIdx.x;
+        if constexpr (__is_same(Args, OrderedArgs)) {
+            // entries in pairs, one scalar load (the numbering has room for an even number)
+            const uint32_t pair = reinterpret_cast<const_ptr<uint32_t>>(reinterpret_cast<uintptr_t>(a.order))[blockIdx.x >> 1];
+            const uint32_t e = (blockIdx.x & 1) ? pair >> 16 : pair & 0xffffu;
+            g = (int)(e >> 13);
+            wg_local = (int)(e & 0x1fffu);
+        }
         typedef uint32_t u32x16 __attribute__((ext_vector_type(16), aligned(16)));  // (a table is, and its entries of 80 bytes)
         struct alignas(8) Words {
             uint32_t w[20];

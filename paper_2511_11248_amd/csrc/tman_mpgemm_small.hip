@@ -41,8 +41,9 @@ void fill_desc_small(GemvDesc& d, const Layout& L, const void* packed, const voi
     d.lut_s = nullptr;
 }
 
-template <int B, int GQ, bool HZ, bool SINGLE, typename Args>
-__global__ void __launch_bounds__(kWaves * 64) mpgemm_small_kernel(Args a) {
+template <int B, int GQ, bool HZ, bool SINGLE, typename Args, typename... Fields>
+__global__ void __launch_bounds__(kWaves * 64) mpgemm_small_kernel(Fields... fields) {
+    const Args a{fields...};
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
     constexpr int D = 2;  // weight tile blocks in flight per wave
     __shared__ __attribute__((aligned(16))) float red[kWaves][kSmallTokens][kRedStride];
@@ -50,9 +51,8 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemm_small_kernel(Args a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    int g, wg_local;
-    workgroup_of<SINGLE>(a, g, wg_local);
-    const GemvDesc& d = desc_of<SINGLE>(a, g);
+    int wg_local;
+    const GemvDesc d = desc_of_workgroup(a, wg_local);
     const int n_seg = uniform(d.n_seg), n_ktiles = uniform(d.n_ktiles);
     // Exits: surplus workgroups of the grid, and (single call) a blob packed for another shape or layout, which
     // is reported and leaves y alone (a batch is checked when its descriptor table is written).
@@ -193,7 +193,9 @@ static int launch_small_cfg(const Args& a, int N, int n_wg, hipStream_t st) {
     if (N <= 8) return launch_codes<B, GQ, HZ, 1, 0, false, SINGLE>(a, n_wg, st);
     if (N <= 16) return launch_codes<B, GQ, HZ, 2, 0, false, SINGLE>(a, n_wg, st);
     if constexpr (GQ >= 128) return launch_codes<B, GQ, HZ, 4, 0, false, SINGLE>(a, n_wg, st);
-    hipLaunchKernelGGL((mpgemm_small_kernel<B, GQ, HZ, SINGLE, Args>), grid, block, 0, st, a);
+    with_fields(a, [&](auto... f) {
+        hipLaunchKernelGGL((mpgemm_small_kernel<B, GQ, HZ, SINGLE, Args, decltype(f)...>), grid, block, 0, st, f...);
+    });
     return launch_status();
 }
 

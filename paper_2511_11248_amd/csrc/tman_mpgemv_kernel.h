@@ -197,8 +197,9 @@ __device__ __forceinline__ void consume_tile(const Stage<B, NP, GemvCfg<B, NP, G
     }
 }
 
-template <int B, int NP, int GQ, bool HZ, bool SINGLE, bool INT, typename Args>
-__global__ void __launch_bounds__(kWaves * 64) mpgemv_kernel(Args a) {
+template <int B, int NP, int GQ, bool HZ, bool SINGLE, bool INT, typename Args, typename... Fields>
+__global__ void __launch_bounds__(kWaves * 64) mpgemv_kernel(Fields... fields) {
+    const Args a{fields...};
     using Cfg = GemvCfg<B, NP, GQ, HZ>;
     constexpr int D = Cfg::D;
     __shared__ __attribute__((aligned(1024))) uint8_t slots[kWaves * Cfg::SLOT];
@@ -208,9 +209,8 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_kernel(Args a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const PlaneWeights<B, NP> pw = make_plane_weights<B, NP>(lane);
 
-    int g, wg_local;
-    workgroup_of<SINGLE>(a, g, wg_local);
-    const GemvDesc& d = desc_of<SINGLE>(a, g);
+    int wg_local;
+    const GemvDesc d = desc_of_workgroup(a, wg_local);
     const int n_seg = uniform(d.n_seg), n_ktiles = uniform(d.n_ktiles);
     if (wg_local >= uniform(d.n_row_blocks) * n_seg) return;
     if constexpr (SINGLE) {
@@ -301,11 +301,13 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_kernel(Args a) {
 template <int B, int NP, bool HZ, bool SINGLE, bool INT, typename Args>
 static int launch_group(int group, const Args& a, int n_wg, hipStream_t st) {
     const dim3 grid((unsigned)n_wg, __is_same(Args, OrderedArgs) ? 1u : (unsigned)a.n_gemv), block(kWaves * 64);
-    switch (group) {
-        case 32: hipLaunchKernelGGL((mpgemv_kernel<B, NP, 32, HZ, SINGLE, INT, Args>), grid, block, 0, st, a); break;
-        case 64: hipLaunchKernelGGL((mpgemv_kernel<B, NP, 64, HZ, SINGLE, INT, Args>), grid, block, 0, st, a); break;
-        default: hipLaunchKernelGGL((mpgemv_kernel<B, NP, 128, HZ, SINGLE, INT, Args>), grid, block, 0, st, a); break;
-    }
+    with_fields(a, [&](auto... f) {
+        switch (group) {
+            case 32: hipLaunchKernelGGL((mpgemv_kernel<B, NP, 32, HZ, SINGLE, INT, Args, decltype(f)...>), grid, block, 0, st, f...); break;
+            case 64: hipLaunchKernelGGL((mpgemv_kernel<B, NP, 64, HZ, SINGLE, INT, Args, decltype(f)...>), grid, block, 0, st, f...); break;
+            default: hipLaunchKernelGGL((mpgemv_kernel<B, NP, 128, HZ, SINGLE, INT, Args, decltype(f)...>), grid, block, 0, st, f...); break;
+        }
+    });
     return launch_status();
 }
 

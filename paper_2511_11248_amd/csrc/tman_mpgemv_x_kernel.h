@@ -29,8 +29,9 @@ __device__ __forceinline__ void load_table(rsrc_t rt, int off, u32x2& x) {
     x = u32x2{__builtin_amdgcn_perm(e23, e01, 0x05040302u), __builtin_amdgcn_perm(e8, e45, 0x05040100u)};
 }
 
-template <int B, int GQ, bool HZ, TokenSource SRC, bool SINGLE, typename Args>
-__global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
+template <int B, int GQ, bool HZ, TokenSource SRC, bool SINGLE, typename Args, typename... Fields>
+__global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Fields... fields) {
+    const Args a{fields...};
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
     constexpr bool kSeveral = several_row_blocks<B, Args>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds_x[];
@@ -38,9 +39,8 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Args a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    int g, wg_local;
-    workgroup_of<SINGLE>(a, g, wg_local);
-    const GemvDesc d = desc_value<SINGLE>(a, g);  // (one load: the fields are needed one after the other)
+    int wg_local;
+    const GemvDesc d = desc_of_workgroup(a, wg_local);
     const int n_seg = d.n_seg, n_ktiles = d.n_ktiles;
     // Exits: surplus workgroups of the grid, and (single call) a blob packed for another shape or layout, which is
     // reported and leaves y alone; a batch is checked when its descriptor table is written, which empties the
@@ -204,8 +204,10 @@ template <int B, int GQ, bool HZ, TokenSource SRC, bool SINGLE, typename Args>
 static int launch_x_cfg(const Args& a, const dim3& grid, int max_seg_tiles, hipStream_t st) {
     constexpr int kSets = several_row_blocks<B, Args> ? 2 : 1;
     static_assert(x_lds_bytes(kGemvXSegmentTiles, kKTile / GQ, kSets) <= 64 * 1024, "LDS of a launch that does not ask for more");
-    hipLaunchKernelGGL((mpgemv_x_kernel<B, GQ, HZ, SRC, SINGLE, Args>), grid, dim3(kWaves * 64),
-                       x_lds_bytes(max_seg_tiles, kKTile / GQ, kSets), st, a);
+    with_fields(a, [&](auto... f) {
+        hipLaunchKernelGGL((mpgemv_x_kernel<B, GQ, HZ, SRC, SINGLE, Args, decltype(f)...>), grid, dim3(kWaves * 64),
+                           x_lds_bytes(max_seg_tiles, kKTile / GQ, kSets), st, f...);
+    });
     return launch_status();
 }
 

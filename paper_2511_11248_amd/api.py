@@ -52,6 +52,18 @@ class Shape:
     def c(self) -> _CShape:
         return _CShape(self.M, self.K, self.bits, self.group, TMAN_FLAG_HAS_ZERO if self.has_zero else 0)
 
+    def __reduce__(self):  # (the C form that _ref keeps stays behind)
+        return type(self), (self.M, self.K, self.bits, self.group, self.has_zero)
+
+
+def _ref(shape: Shape):
+    """Reference to the shape's C form, which is made once: a shape never changes."""
+    c = shape.__dict__.get("_c")
+    if c is None:
+        c = shape.c()
+        object.__setattr__(shape, "_c", c)
+    return C.byref(c)
+
 
 def library_path() -> str:
     return _LIB_PATH
@@ -158,11 +170,30 @@ def _nbytes(t) -> int:
     return t.numel() * t.element_size()
 
 
-def _stream(stream) -> Optional[int]:
-    if stream is None:
+_stream_query = None
+
+
+def _current_stream() -> Optional[int]:
+    """Handle of torch's current stream.  Asking torch.cuda whether there is a GPU and for a Stream object took 3 of the 8 us of
+    the smallest call, so the first is asked until the answer is yes and the handle is asked for directly."""
+    global _stream_query
+    if _stream_query is None:
         import torch
 
-        return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
+        if not torch.cuda.is_available():
+            return None
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = torch.cuda.current_device
+        if raw is None:
+            _stream_query = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+        else:
+            _stream_query = lambda: raw(device())  # noqa: E731
+    return _stream_query()
+
+
+def _stream(stream) -> Optional[int]:
+    if stream is None:
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -182,7 +213,7 @@ def tman_layout_version() -> int:
 
 
 def tman_packed_bytes(shape: Shape) -> int:
-    return int(_load().tman_packed_bytes(C.byref(shape.c())))
+    return int(_load().tman_packed_bytes(_ref(shape)))
 
 
 def tman_lut_bytes(N: int, K: int, group: int) -> int:
@@ -190,33 +221,33 @@ def tman_lut_bytes(N: int, K: int, group: int) -> int:
 
 
 def tman_mpgemv_workspace_bytes(shape: Shape, N: int) -> int:
-    return int(_load().tman_mpgemv_workspace_bytes(C.byref(shape.c()), N))
+    return int(_load().tman_mpgemv_workspace_bytes(_ref(shape), N))
 
 
 def tman_mpgemm_workspace_bytes(shape: Shape, N: int) -> int:
-    return int(_load().tman_mpgemm_workspace_bytes(C.byref(shape.c()), N))
+    return int(_load().tman_mpgemm_workspace_bytes(_ref(shape), N))
 
 
 def tman_mpgemm_tile_rows(shape: Shape, N: int) -> int:
-    return int(_load().tman_mpgemm_tile_rows(C.byref(shape.c()), N))
+    return int(_load().tman_mpgemm_tile_rows(_ref(shape), N))
 
 
 def tman_mpgemm_splits_k(shape: Shape, N: int) -> int:
-    return int(_load().tman_mpgemm_splits_k(C.byref(shape.c()), N))
+    return int(_load().tman_mpgemm_splits_k(_ref(shape), N))
 
 
 def tman_mpgemm_i8_token_blocks(shape: Shape, N: int) -> int:
-    return int(_load().tman_mpgemm_i8_token_blocks(C.byref(shape.c()), N))
+    return int(_load().tman_mpgemm_i8_token_blocks(_ref(shape), N))
 
 
 def tman_pack_weights(shape: Shape, codes, scales, zeros, packed, stream=None) -> None:
     """codes u8 [M][K], scales/zeros fp16 [M][K/group] (zeros None for the sign form) -> packed (u8 blob)."""
-    _check(_load().tman_pack_weights(C.byref(shape.c()), _ptr(codes), _ptr(scales), _ptr(zeros), _ptr(packed),
+    _check(_load().tman_pack_weights(_ref(shape), _ptr(codes), _ptr(scales), _ptr(zeros), _ptr(packed),
                                      _stream(stream)), "tman_pack_weights")
 
 
 def tman_unpack_weights(shape: Shape, packed, codes, scales=None, zeros=None, stream=None) -> None:
-    _check(_load().tman_unpack_weights(C.byref(shape.c()), _ptr(packed), _ptr(codes), _ptr(scales), _ptr(zeros),
+    _check(_load().tman_unpack_weights(_ref(shape), _ptr(packed), _ptr(codes), _ptr(scales), _ptr(zeros),
                                        _stream(stream)), "tman_unpack_weights")
 
 
@@ -244,7 +275,7 @@ def tman_build_lut_i16_batch(xs, N: int, Ks, group: int, luts, stream=None) -> N
 def tman_mpgemv_i16(shape: Shape, packed, lut, N: int, y, workspace, stream=None) -> None:
     """y fp16 [N][M] through lookups in integer tables (from tman_build_lut_i16)."""
     wb = 0 if workspace is None or isinstance(workspace, int) else _nbytes(workspace)
-    _check(_load().tman_mpgemv_i16(C.byref(shape.c()), _ptr(packed), _ptr(lut), N, _ptr(y), _ptr(workspace), wb,
+    _check(_load().tman_mpgemv_i16(_ref(shape), _ptr(packed), _ptr(lut), N, _ptr(y), _ptr(workspace), wb,
                                    _stream(stream)), "tman_mpgemv_i16")
 
 
@@ -257,13 +288,13 @@ def tman_mpgemv_i16_batch_run(shapes, N: int, desc, stream=None) -> None:
 def tman_mpgemv(shape: Shape, packed, lut, N: int, y, workspace, stream=None) -> None:
     """y fp16 [N][M] = x * dequant(W)^T through table lookup; workspace zero-filled once by the caller."""
     wb = 0 if workspace is None or isinstance(workspace, int) else _nbytes(workspace)
-    _check(_load().tman_mpgemv(C.byref(shape.c()), _ptr(packed), _ptr(lut), N, _ptr(y), _ptr(workspace), wb,
+    _check(_load().tman_mpgemv(_ref(shape), _ptr(packed), _ptr(lut), N, _ptr(y), _ptr(workspace), wb,
                                _stream(stream)), "tman_mpgemv")
 
 
 def tman_check_packed(shape: Shape, packed, stream=None) -> int:
     """Status of the host-side header check (0 or TMAN_ERR_HEADER = -8); waits for the stream."""
-    return int(_load().tman_check_packed(C.byref(shape.c()), _ptr(packed), _stream(stream)))
+    return int(_load().tman_check_packed(_ref(shape), _ptr(packed), _stream(stream)))
 
 
 def tman_device_status(stream=None) -> int:
@@ -293,14 +324,14 @@ def tman_noalloc_init() -> None:
 
 def tman_mpgemv_noalloc(shape: Shape, packed, lut, N: int, y, stream=None) -> None:
     """tman_mpgemv with the library's own fixed scratch array as workspace (allocates nothing)."""
-    _check(_load().tman_mpgemv_noalloc(C.byref(shape.c()), _ptr(packed), _ptr(lut), N, _ptr(y), _stream(stream)),
+    _check(_load().tman_mpgemv_noalloc(_ref(shape), _ptr(packed), _ptr(lut), N, _ptr(y), _stream(stream)),
            "tman_mpgemv_noalloc")
 
 
 def tman_mpgemm(shape: Shape, packed, x, N: int, y, workspace=None, stream=None) -> None:
     """y fp16 [N][M] = x fp16 [N][K] * dequant(W)^T, table dequantization feeding the matrix cores."""
     wb = 0 if workspace is None or isinstance(workspace, int) else _nbytes(workspace)
-    _check(_load().tman_mpgemm(C.byref(shape.c()), _ptr(packed), _ptr(x), N, _ptr(y), _ptr(workspace), wb,
+    _check(_load().tman_mpgemm(_ref(shape), _ptr(packed), _ptr(x), N, _ptr(y), _ptr(workspace), wb,
                                _stream(stream)), "tman_mpgemm")
 
 
@@ -315,7 +346,7 @@ def tman_quantize_act_i8(x, N: int, K: int, xq, stream=None) -> None:
 
 def tman_mpgemm_i8(shape: Shape, packed, xq, N: int, y, acc=None, stream=None) -> None:
     """y fp16 [N][M] on the integer matrix cores for weights with one scale and zero per row."""
-    _check(_load().tman_mpgemm_i8(C.byref(shape.c()), _ptr(packed), _ptr(xq), N, _ptr(y), _ptr(acc), _stream(stream)),
+    _check(_load().tman_mpgemm_i8(_ref(shape), _ptr(packed), _ptr(xq), N, _ptr(y), _ptr(acc), _stream(stream)),
            "tman_mpgemm_i8")
 
 
@@ -377,7 +408,7 @@ def tman_mpgemv_batch_run(shapes, N: int, desc, stream=None) -> None:
 def tman_mpgemv_x(shape: Shape, packed, x, y, workspace, stream=None) -> None:
     """y fp16 [M] = x fp16 [K] * dequant(W)^T for one token, from the activations in one launch."""
     wb = 0 if workspace is None or isinstance(workspace, int) else _nbytes(workspace)
-    _check(_load().tman_mpgemv_x(C.byref(shape.c()), _ptr(packed), _ptr(x), _ptr(y), _ptr(workspace), wb,
+    _check(_load().tman_mpgemv_x(_ref(shape), _ptr(packed), _ptr(x), _ptr(y), _ptr(workspace), wb,
                                  _stream(stream)), "tman_mpgemv_x")
 
 

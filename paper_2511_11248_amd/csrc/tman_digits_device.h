@@ -83,10 +83,8 @@ __device__ __forceinline__ int isum_over_lanes(int v) {
     return v;
 }
 
-// From 16-bit numbers to digit words, for a quad of lanes that holds one 32-weight block: lane f (of 4) comes with
-// r[o] = number 4f + o of the block in the low half, 16 + 4f + o in the high half (as X + 0x8888), and leaves with
-// r[i] = digit word (o = its lane, i): a 4 x 4 transposition over the quad, then one of nibbles.
-__device__ __forceinline__ void digit_words(uint32_t (&r)[4], int lane) {
+// 4 x 4 transposition over a quad of lanes: lane f comes with r[o], lane o leaves with r[f].
+__device__ __forceinline__ void quad_transpose(uint32_t (&r)[4], int lane) {
     const bool odd = lane & 1, up = lane & 2;
 #pragma unroll
     for (int h = 0; h < 4; h += 2) {  // 2 x 2 blocks: lanes differing in bit 0, registers differing in bit 0
@@ -100,6 +98,13 @@ __device__ __forceinline__ void digit_words(uint32_t (&r)[4], int lane) {
         r[h] = up ? got : r[h];
         r[h + 2] = up ? r[h + 2] : got;
     }
+}
+
+// From 16-bit numbers to digit words, for a quad of lanes that holds one 32-weight block: lane f (of 4) comes with
+// r[o] = number 4f + o of the block in the low half, 16 + 4f + o in the high half (as X + 0x8888), and leaves with
+// r[i] = digit word (o = its lane, i): a 4 x 4 transposition over the quad, then one of nibbles.
+__device__ __forceinline__ void digit_words(uint32_t (&r)[4], int lane) {
+    quad_transpose(r, lane);
     // r[f] now holds the numbers 4f + o and 4 (f + 4) + o of this lane's o; nibble i of each goes to word i
     const uint32_t a0 = bfi(0x00FF00FFu, r[0], r[2] << 8), a1 = bfi(0x00FF00FFu, r[1], r[3] << 8);
     const uint32_t b0 = bfi(0xFF00FF00u, r[2], r[0] >> 8), b1 = bfi(0xFF00FF00u, r[3], r[1] >> 8);

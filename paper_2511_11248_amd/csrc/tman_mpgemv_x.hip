@@ -1,5 +1,5 @@
-// Decoding mpGEMV of one token on the 4-bit dot product unit: tman_mpgemv_x (activations in), tman_mpgemv and
-// tman_mpgemv_i16 (tables in).
+// Decoding mpGEMV of one token on the 4-bit dot product unit, or for 1 and 2 bits on the matrix cores (tman_fp4_device.h):
+// tman_mpgemv_x (activations in), tman_mpgemv and tman_mpgemv_i16 (tables in).
 //
 // y[m] = sum_G scale[m][G] * (sum_{k in G} q[m][k] x[k] - zero[m][G] * S[G]) (Sec. 2.2).  The lookups of Sec. 4.3 turn
 // the inner sum into one table read per 4 weights and bit-plane; on this chip that costs 2.6 vector instructions and
@@ -14,8 +14,8 @@
 // out of them: the entries of patterns 1, 2, 4 and 8 are the four activations themselves.  The sums of the four waves
 // meet in LDS, segments of a long K through the workspace (tickets, fixed order of addition).
 //
-// What bounds it: the weight stream.  63.2 MB (7B uint2 g64) in 13.5 us = 4.7 TB/s, 107.5 MB (uint4 g128) in 19.6 - 20.5
-// us = 5.2 - 5.5 TB/s; reading alone reaches 6.0-6.15 TB/s, and about 1 us at the start (descriptor, first activations)
+// What bounds it: the weight stream.  63.2 MB (7B uint2 g64) in 12.6 us = 5.0 TB/s, 107.5 MB (uint4 g128) in 19.1 us =
+// 5.6 TB/s (20.0 when nothing is computed); reading alone reaches 6.0-6.15 TB/s, and about 1 us at the start (descriptor, first activations)
 // and 1.5 us at the end (exchange between segments) are not covered.  What helped beside the digits, measured in
 // turn on the uint2 / uint4 launch: the waves of a workgroup take its tiles in turn instead of a quarter each, so that
 // a workgroup reads one contiguous stream (uint4 20.6 -> 20.1 us); ONE tile in flight per wave instead of two or three
@@ -44,7 +44,7 @@ void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut
     fill_desc_plan(d, L, plan_decode(L, N), packed, lut, N, y, workspace);
 }
 
-// A fifth of the vector instructions of a 1-bit workgroup make digits, and a large launch (all layers of a model at once) is
+// A good part of the vector instructions of a 1-bit workgroup make digits, and a large launch (all layers of a model at once) is
 // bound by vector issue: its workgroups take two row blocks each, as long as that leaves at least eight per compute unit.
 // 160 GEMVs of a 32-layer 3.8B model in one launch, sign form with blocks of 64: 113 us with two, 120 with one, 119 by
 // lookups (launches back to back; right after an idle GPU, whose clocks are still low: 144 - 148, 150, 140); with zeros 120, 127, 129;
@@ -62,7 +62,7 @@ static int resident_per_unit(int count, const Layout* L, int N) {
     if (np > 1 && !lookups_stay(L[0].bits, np, true)) return kCodesResident;
     int max_seg_tiles = 1;
     for (int g = 0; g < count; ++g) max_seg_tiles = std::max(max_seg_tiles, plan_decode(L[g], N).seg_tiles);
-    const unsigned lds = np == 1 ? x_lds_bytes(max_seg_tiles, L[0].groups_per_tile)
+    const unsigned lds = np == 1 ? x_lds_bytes(max_seg_tiles, L[0].groups_per_tile, on_matrix_cores(L[0].bits, TokenSource::kActivations))
                                  : (unsigned)(kWaves * (kTableBytesPerKTile * np + 256 + np * kRows * 4));
     return std::max(1, std::min((int)(160u * 1024u / lds), std::min(8, 160 / max_seg_tiles)));
 }

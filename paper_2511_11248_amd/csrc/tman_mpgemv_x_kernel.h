@@ -1,16 +1,24 @@
-// The one-token decoding kernel on the 4-bit dot product unit, as a template over the weight format and the source of the
-// activations; what it does and why is said in tman_mpgemv_x.hip.
+// The one-token decoding kernel on the 4-bit dot product unit or (on_matrix_cores) the matrix cores, as a template over the
+// weight format and the source of the activations; what it does and why is said in tman_mpgemv_x.hip.
 #pragma once
 #include "tman_codes_kernel.h"
 #include "tman_digits_device.h"
+#include "tman_fp4_device.h"
 #include "tman_mpgemv_kernel.h"
 
 namespace tman {
 
-// LDS of a workgroup whose segment has `seg_tiles` tiles: digit words and `gpt` quantization blocks per tile, then the
-// partial sums (two sets where a workgroup takes several row blocks) and a word per wave: at most 12,304 bytes
-constexpr unsigned x_lds_bytes(int seg_tiles, int gpt, int sets = 1) {
-    return (unsigned)(seg_tiles * (kDigitBytesPerKTile + gpt * kDigitMetaBytes) + sets * kWaves * kRows * 4 + kWaves * 4);
+// Which formats multiply on the matrix cores (tman_fp4_device.h) instead of the dot product unit: 1 and 2 bits, whose codes are 4-bit
+// numbers as they are, with fp16 activations.  4 bits would be two such products beside a longer transposition, 110 vector
+// instructions for 177, and their launches wait for memory already (without any computing 20.0 us against 19.2); integer activations
+// stay integers.
+constexpr bool on_matrix_cores(int bits, TokenSource src) { return bits <= 2 && src != TokenSource::kTablesI16; }
+
+// LDS of a workgroup whose segment has `seg_tiles` tiles: digits and sums or quantization blocks (`gpt` per tile) of the
+// activations, then the partial sums (two sets where a workgroup takes several row blocks) and a word per wave: at most 18,976 bytes
+constexpr unsigned x_lds_bytes(int seg_tiles, int gpt, bool matrix, int sets = 1) {
+    const int tile = matrix ? kFp4BytesPerKTile + kFp4SumBytes : kDigitBytesPerKTile + gpt * kDigitMetaBytes;
+    return (unsigned)(seg_tiles * tile + sets * kWaves * kRows * 4 + kWaves * 4 + (matrix ? kFp4Zeros : 0));
 }
 // Workgroups of a large 1-bit batch take several row blocks with one set of digits (batch_row_blocks).
 template <int B, typename Args>
@@ -30,10 +38,11 @@ __device__ __forceinline__ void load_table(rsrc_t rt, int off, u32x2& x) {
 }
 
 template <int B, int GQ, bool HZ, TokenSource SRC, bool SINGLE, typename Args, typename... Fields>
-__global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Fields... fields) {
+__global__ void __launch_bounds__(kWaves * 64, 4) mpgemv_x_kernel(Fields... fields) {
     const Args a{fields...};
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
     constexpr bool kSeveral = several_row_blocks<B, Args>;
+    constexpr bool kMatrix = on_matrix_cores(B, SRC);
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds_x[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -71,11 +80,19 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Fields... fields)
     src.t_bytes = src.s_bytes = 0;
 
     const uint32_t ld = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr<uint8_t>)lds_x));
-    const uint32_t lm = ld + (uint32_t)(d.seg_tiles * kDigitBytesPerKTile);          // quantization blocks
-    const uint32_t lr = lm + (uint32_t)(d.seg_tiles * Cfg::GPT * kDigitMetaBytes);  // partial sums [wave][row]
-    const uint32_t lf = lr + (kSeveral ? 2 : 1) * kWaves * kRows * 4;                // a word per wave
+    // quantization blocks, or sums of 32-column blocks
+    const uint32_t lm = ld + (uint32_t)(d.seg_tiles * (kMatrix ? kFp4BytesPerKTile : kDigitBytesPerKTile));
+    const uint32_t lr = lm + (uint32_t)(d.seg_tiles * (kMatrix ? kFp4SumBytes : Cfg::GPT * kDigitMetaBytes));  // partial sums [wave][row]
+    const uint32_t lf = lr + (kSeveral ? 2 : 1) * kWaves * kRows * 4;  // a word per wave, then (matrix cores) zeros
 
     float y[1] = {0.f};
+    // matrix cores: the lane's sums for weight rows 16 r + lane % 16, and where its part of the first operand is (see multiply_fp4)
+    float y4[4] = {0.f, 0.f, 0.f, 0.f};
+    const int xb = (lane >> 2) & 3, xg = lane >> 4;  // row 4 xb + digit, columns of lane group xg
+    const bool x_mine = (xb & 1) == xg >> 1;
+    const uint32_t x_at = ld + (uint32_t)((lane & 15) * 32 + (xg & 1) * 16), zeros = lf + kWaves * 4;
+    const uint32_t x_lo = x_mine && xb < 2 ? x_at : zeros, x_lo_step = x_mine && xb < 2 ? kFp4BytesPerKTile : 0u;
+    const uint32_t x_hi = x_mine && xb >= 2 ? x_at : zeros, x_hi_step = x_mine && xb >= 2 ? kFp4BytesPerKTile : 0u;
     int acc[4] = {0, 0, 0, 0};  // running sums of the digits, and their joined value (see consume_weights_digits)
     uint32_t before = 0;
     // the four sums of a row meet in LDS, the first wave adds them
@@ -123,13 +140,14 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Fields... fields)
     }
     __builtin_amdgcn_sched_barrier(0);
     // One bit: the next tile is requested before the wait for the current one, otherwise when the current one is done.
-    // A 1-bit tile is 1.3 to 2 KB and 110 vector instructions, so a wave waits longer than it computes: with the request
+    // A 1-bit tile is 1.3 to 2 KB and 70 vector instructions, so a wave waits longer than it computes: on the dot product unit, with the request
     // at the end of a tile (where the last use of a zero kept it) 16 launches of a layer set of width 1024 took 131 us,
-    // now 92; width 3072 145 -> 130, 4096 184 -> 170 (zeros, blocks of 64; lookups: 109, 139, 182).  2 and 4 bits: more
-    // streams in flight cost more than they hide (see tman_mpgemv_x.hip).
+    // else 92; width 3072 145 -> 130, 4096 184 -> 170 (zeros, blocks of 64); on the matrix cores 3.8B layer sets 277 -> 247.  2 and 4
+    // bits: more streams in flight cost more than they hide (uint2 g64 404 -> 409; see tman_mpgemv_x.hip).
     constexpr int kStages = B == 1 ? 2 : 1;
     Stage<B, 1, Cfg::MPL> st[kStages] = {};
-    issue_weights<B, 1, GQ, HZ>(st[0], src, k0 + wave < k1, k0 + wave, lane);
+    auto issue = [&](auto& s, bool live, int t) { issue_weights<B, 1, GQ, HZ>(s, src, live, t, lane); };
+    issue(st[0], k0 + wave < k1, k0 + wave);
     __builtin_amdgcn_sched_barrier(0);
 
     // digits of the segment: lane -> four lanes per 32-column block, sixteen per tile
@@ -140,6 +158,10 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Fields... fields)
         if (i * kWaves * 64 + wave * 64 >= n_lanes) break;  // (this wave has none)
         const int j = i * kWaves * 64 + tid, tile = j >> 4;
         const bool live = j < n_lanes;
+        if constexpr (kMatrix) {
+            nonfinite |= store_fp8_digits<HZ>(xv[i].a, xv[i].b, lane, live, ld + (uint32_t)((j >> 2) * 128), lm + (uint32_t)((j >> 2) * 4)) && live;
+            continue;
+        }
         uint32_t r[4];
         float step = 1.f;
         if constexpr (SRC == TokenSource::kTablesI16)
@@ -149,6 +171,8 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Fields... fields)
         store_digits<GQ>(r, step, j, live, ld + (uint32_t)(tile * kDigitBytesPerKTile + (j & 15) * 16),
                          lm + (uint32_t)((tile * Cfg::GPT + (j & 15) / (GQ / 8)) * kDigitMetaBytes));
     }
+    if constexpr (kMatrix)
+        if (tid == 0) store_lds<u32x4>(zeros, u32x4{0, 0, 0, 0});
     if constexpr (SRC != TokenSource::kTablesI16)
         store_lds<uint32_t>(lf + wave * 4, __builtin_amdgcn_ballot_w64(nonfinite) != 0 ? 1u : 0u);
     __syncthreads();
@@ -159,13 +183,26 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Fields... fields)
 #pragma unroll
             for (int s = 0; s < kStages; ++s) {
                 const int t = t0 + s * kWaves;
-                if (t < k1)
-                    consume_weights_digits<B, GQ, HZ>(
-                        st[s], ld + (uint32_t)((t - k0) * kDigitBytesPerKTile + (lane & 15) * 4),
-                        lm + (uint32_t)((t - k0) * Cfg::GPT * kDigitMetaBytes), acc, before, y[0], [&] {
-                            issue_weights<B, 1, GQ, HZ>(st[(s + 1) % kStages], src, t + kWaves < k1, t + kWaves, lane);
-                        });
+                if (t < k1) {
+                    auto next = [&] { issue(st[(s + 1) % kStages], t + kWaves < k1, t + kWaves); };
+                    if constexpr (kMatrix) {
+                        const uint32_t at = (uint32_t)(t - k0);
+                        multiply_fp4<B, GQ, HZ>(st[s], x_lo + at * x_lo_step, x_hi + at * x_hi_step, lm + at * kFp4SumBytes, lane, y4, next);
+                    } else {
+                        consume_weights_digits<B, GQ, HZ>(
+                            st[s], ld + (uint32_t)((t - k0) * kDigitBytesPerKTile + (lane & 15) * 4),
+                            lm + (uint32_t)((t - k0) * Cfg::GPT * kDigitMetaBytes), acc, before, y[0], next);
+                    }
+                }
             }
+        }
+        if constexpr (kMatrix) {  // the lane groups' sums of a row meet; lane 16 r + i takes row 16 r + i
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                y4[r] += __shfl_xor(y4[r], 16, 64);
+                y4[r] += __shfl_xor(y4[r], 32, 64);
+            }
+            y[0] = kFp4Factor<HZ> * (lane < 32 ? (lane < 16 ? y4[0] : y4[1]) : (lane < 48 ? y4[2] : y4[3]));
         }
         if constexpr (SRC != TokenSource::kTablesI16) {
             const u32x4 f = load_lds<u32x4>(lf);
@@ -185,11 +222,13 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Fields... fields)
             // writes a set again only after the barrier that follows its last reading
             const bool more = rb + 1 < rb_end;
             src.w += (size_t)n_ktiles * Cfg::TB;
-            issue_weights<B, 1, GQ, HZ>(st[0], src, more && k0 + wave < k1, k0 + wave, lane);
+            issue(st[0], more && k0 + wave < k1, k0 + wave);
             publish(lr + (uint32_t)(r * kWaves * kRows * 4));
             if (wave == 0) finish(lr + (uint32_t)(r * kWaves * kRows * 4));
             if (!more) return;
             y[0] = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) y4[q] = 0.f;
             ++rb;
         }
     }
@@ -203,10 +242,10 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemv_x_kernel(Fields... fields)
 template <int B, int GQ, bool HZ, TokenSource SRC, bool SINGLE, typename Args>
 static int launch_x_cfg(const Args& a, const dim3& grid, int max_seg_tiles, hipStream_t st) {
     constexpr int kSets = several_row_blocks<B, Args> ? 2 : 1;
-    static_assert(x_lds_bytes(kGemvXSegmentTiles, kKTile / GQ, kSets) <= 64 * 1024, "LDS of a launch that does not ask for more");
+    static_assert(x_lds_bytes(kGemvXSegmentTiles, kKTile / GQ, on_matrix_cores(B, SRC), kSets) <= 64 * 1024, "LDS of a launch that does not ask for more");
     with_fields(a, [&](auto... f) {
         hipLaunchKernelGGL((mpgemv_x_kernel<B, GQ, HZ, SRC, SINGLE, Args, decltype(f)...>), grid, dim3(kWaves * 64),
-                           x_lds_bytes(max_seg_tiles, kKTile / GQ, kSets), st, f...);
+                           x_lds_bytes(max_seg_tiles, kKTile / GQ, on_matrix_cores(B, SRC), kSets), st, f...);
     });
     return launch_status();
 }

@@ -125,7 +125,7 @@ def decode_job(torch, tman, synth, dev, w, N, n_inst):
             x_descs.append(d)
         torch.cuda.synchronize()
         x_calls = [tman.bound_mpgemv_x_batch_run(shapes, x_descs[inst]) for inst in range(n_inst)]
-    # integer tables (A_INT16 reading): a table launch that quantizes the activations, a lookup launch on int16 entries
+    # integer tables (A_INT16 reading): a table launch that quantizes the activations, a launch on int16 entries
     i16_luts = [torch.empty(tman.tman_lut_i16_bytes(N, w.layers[li0].K, w.group), dtype=torch.uint8, device=dev)
                 for li0 in act_layer0]
     i16_descs = []
@@ -245,7 +245,7 @@ def other_configs(args, torch, tman, synth, oracle, dev):
             sec = timed_steps(torch, step, 100, 300)
             err, _, _ = decode_error(torch, synth, oracle, w, job, N)
             gbs = job["weight_bytes_per_step"] / sec / 1e9
-            kind = "one launch per layer set" if job["x_calls"] is not None else "table launch + lookup launch per layer set"
+            kind = "one launch per layer set" if job["x_calls"] is not None else "table launch + launch reading them per layer set"
             add(f"{name} N={N}, {w.instances} rotating copies, {kind}" + (" (cache-resident: correctness only)" if w.instances == 1 else ""),
                 sec, gbs, "GB/s", HBM_PEAK_GBS, err, "all outputs of copy 0")
             if w.config == 2:  # integer activations and tables (the paper's A_INT16 configuration), same workload
@@ -372,7 +372,7 @@ def context_figures(args, torch, dev, job, n_inst):
     steps = max(args.steps, 500)
     hot_value = weight_bytes_per_step / timed_steps(torch, lambda i: x_calls[0](stream), 100, steps) / 1e9
 
-    # the same step as two launches (table precompute kernel, then the lookup kernel reading its tables)
+    # the same step as two launches (table precompute kernel, then the kernel reading its tables)
     def two(i):
         lut_calls[i % n_inst](stream)
         gemv_calls[i % n_inst](stream)
@@ -418,7 +418,7 @@ def main():
     events = []
 
     # One step = one token through a 32-layer decoder of this layer set: the 32 copies in turn, one launch each
-    # (activations in, outputs out: the digits and the integer products of all five GEMVs of a layer set).
+    # (activations in, outputs out: the digits and the products of all five GEMVs of a layer set).
     launches_per_step = n_inst
 
     def launch(j, record):
@@ -497,8 +497,8 @@ def main():
         "config": {"workload": f"{w.name}: decode of one token (N=1) through {n_inst} layers of the 7B-style layer set "
                                f"(qkv 12288x4096, o 4096x4096, gate/up 11008x4096, down 4096x11008), uint{w.bits} "
                                f"g{w.group}, every layer with weights of its own ({weight_bytes_per_step / 1e9:.2f} GB per "
-                               f"step); one launch per layer: every workgroup makes the 4-bit digits of its K "
-                               f"segment from the layer's {len(acts)} activations, then its integer products",
+                               f"step); one launch per layer: every workgroup makes the digits of its K "
+                               f"segment from the layer's {len(acts)} activations, then its products with the codes",
                    "launches_per_step": launches_per_step, "us_per_launch": round(sec_per_step / launches_per_step * 1e6, 3),
                    "weight_bytes_per_step": int(weight_bytes_per_step), "frac_of_hbm_peak": round(value / HBM_PEAK_GBS, 4),
                    "codes_only_GBs": round(value * codes_bytes / weight_bytes_per_step, 1), **context},

@@ -120,9 +120,9 @@ int tman_build_lut_batch(int32_t count, const void *const *x, int32_t N, const i
  *   y[n][m] = sum_G scale[m][G] * ( sum_i 2^i sum_{j in G} T[n][j][idx_i[m][j]] - zero[m][G] * S[n][G] )
  * where idx_i[m][j] is the 4-bit pattern of bit-plane i over weights 4j..4j+3 (sign form:
  * scale * (2 * sum_j T - S)).  fp16 table entries, fp32 accumulation, fp16 result.
- * For N = 1 (and N = 2 with 4-bit weights) the kernel is that of tman_mpgemv_x below: it takes the activations out of
- * the tables (T[j][1 << t] is x[4j + t]) and sums integer products, which rounds less than adding fp16 table entries
- * does.
+ * Except for few tokens of few bit-planes (1 bit and N = 2 to 4, 2 bits and N = 2) the kernel takes the activations out of
+ * the tables (T[j][1 << t] is x[4j + t]) and sums their products with the codes - N = 1 as tman_mpgemv_x below, more
+ * tokens on the matrix cores -, which rounds less than adding fp16 table entries does.
  *   packed    : from tman_pack_weights for the same shape
  *   lut       : from tman_build_lut(x, N, shape->K, shape->group)
  *   y         : fp16 [N][M]
@@ -177,8 +177,8 @@ int tman_mpgemv_batch_run(int32_t count, const tman_shape_t *shapes, int32_t N, 
  *                        aligned): int16 entries laid out as the fp16 tables, int32 block sums, int32 e[n].
  *                        The _batch form follows tman_build_lut_batch.
  *   tman_mpgemv_i16    : arguments, workspace rules and determinism of tman_mpgemv, `lut` from tman_build_lut_i16
- *                        (N = 1, and 4-bit weights for any N, go to the kernel of tman_mpgemv_x, which takes xq out of
- *                        the tables: same integers).
+ *                        (N = 1 goes to the dot products of tman_mpgemv_x, which take xq out of the tables, more
+ *                        tokens to the matrix cores, but 1 bit and N = 2 to 4: same integers).
  *   tman_mpgemv_i16_batch_run : launches a batch whose descriptor table tman_mpgemv_batch_prepare wrote with
  *                        integer table buffers in `lut` (the two table buffers have the same geometry).
  */
@@ -193,13 +193,15 @@ int tman_mpgemv_i16_batch_run(int32_t count, const tman_shape_t *shapes, int32_t
 /*
  * Decoding mpGEMV of ONE token from the activations themselves, in one launch (Sec. 2.2; the lookups of Sec. 4.3 cost
  * more vector instructions on this hardware than the sums they replace, and Sec. 5's separate precompute costs a
- * kernel boundary).  Every workgroup turns the activations of its own K segment (at most 4096 columns) into fixed-point
- * numbers: every quantization block gets the smallest power-of-two step 2^e with max |x| / 2^e <= 30583, and
+ * kernel boundary).  4-bit weights: every workgroup turns the activations of its own K segment (at most 4096 columns) into
+ * fixed-point numbers: every quantization block gets the smallest power-of-two step 2^e with max |x| / 2^e <= 30583, and
  * X = round_to_nearest_even(x / 2^e) is written with four signed 4-bit digits, whose products with the codes the dot
  * product unit sums exactly:
  *   y[m] = sum_G 2^e[G] * scale[m][G] * ( sum_{k in G} q[m][k] X[k] - zero[m][G] * sum_{k in G} X[k] )
  * (sign form: 2^e * scale * (2 sum q X - sum X)), scales applied in fp32, fp16 result.  Activations within a factor 14
- * of their block's largest enter unrounded.  Infinities and NaN are kept out of the integers and added as
+ * of their block's largest enter unrounded.  1- and 2-bit weights: the activations are split into four 8-bit floating point
+ * digits whose sum is the activation, and the matrix cores multiply them with the codes in fp32 sums, of 8 neighbouring
+ * products of a digit's row only what is at least 2^-13 of their largest.  Infinities and NaN are kept out of the integers and added as
  * (q - zero) * scale * x.
  *   x         : fp16 [K], device, 16-byte aligned
  *   y         : fp16 [M]
@@ -349,7 +351,8 @@ int tman_mpgemv_noalloc(const tman_shape_t *shape, const void *packed, const voi
  * on-chip-memory constraints, the prefill and the decoding loop nest covering the same M and K extents of the one
  * weight copy).  The shared tile block is fixed by the packed layout (64 rows x 128 columns, which is Eq. 2 and
  * Eq. 3 by construction); free is how many tile blocks one workgroup takes:
- *   decode_seg_tiles / _many   K tiles per workgroup of tman_mpgemv for 2 / 3-8 tokens
+ *   decode_seg_tiles / _many   K tiles per workgroup of tman_mpgemv for 2 / 3-8 tokens where it looks up (1 bit, 2 bits with
+ *                              two tokens); elsewhere small_seg_tiles, or these if longer
  *   decode_x_seg_tiles         one token: a K of at most this many tiles, and at most decode_x_whole_bytes of
  *                              packed weights per row block, is ONE segment; it is at most 32 (Eq. 1: what a
  *                              workgroup keeps of its activations lives in LDS; 32 tiles are two passes of its lanes)
@@ -357,7 +360,7 @@ int tman_mpgemv_noalloc(const tman_shape_t *shape, const void *packed, const voi
  *   decode_balance             1: batches of tman_mpgemv_x, of tman_mpgemv (tables) and of the small-batch
  *                              tman_mpgemm number their workgroups for equal work per compute unit where they fit
  *                              the chip (see tman_mpgemv_x_batch_order), 0: plain grids
- *   small_seg_tiles            K tiles per workgroup of tman_mpgemm for N <= 32
+ *   small_seg_tiles            K tiles per workgroup of tman_mpgemm for N <= 32 and of tables multiplied on the matrix cores
  *   prefill_row_blocks         tile blocks in M per workgroup of the tiled prefill kernel, 1..4 (Eq. 4: four
  *                              stage buffers of rows x 80 + 256 x 64 bytes within 160 KB of LDS), 0 = chosen per
  *                              call from the grid it gives

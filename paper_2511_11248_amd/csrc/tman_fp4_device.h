@@ -2,9 +2,10 @@
 // point numbers, activations as four 8-bit ones.
 //
 // Why.  On the dot product unit a block of 32 weights costs 16 dot products beside its transposition, whatever the width of
-// the codes, and a 2-bit tile 154 vector instructions.  v_mfma_f32_16x16x128_f8f6f4 multiplies 16 rows x 128 columns of
+// the codes, and a 2-bit tile 123 vector instructions (1 bit: 110).  v_mfma_f32_16x16x128_f8f6f4 multiplies 16 rows x 128 columns of
 // codes with 16 rows of activations in one instruction that runs beside the vector pipe; what is left are exchanges between
-// lanes, the transposition and 5 multiply-adds per 16 rows: 82 instructions per tile for 2 bits, 69 for 1 bit.
+// lanes, the transposition and 5 multiply-adds per 16 rows: 82 instructions per tile for 2 bits, 69 for 1 bit (with
+// the digits and the ends of a workgroup: 154 -> 122 and 143 -> 111).
 // 32 launches of a 7B layer set, uint2 g64: 415 -> 404 us (63.2 MB in 12.6 us = 5.0 TB/s), of a 3.8B one, 1 bit: 257 -> 247;
 // one 4096 x 4096 GEMV, uint2, 8.4 -> 7.7.  What bounds them now is what a launch has to wait for: the memory system (without
 // any computing the 2-bit launch takes 12.2 us) and its start and end (a 1-bit launch without computing: 6.5 of 7.7 us).

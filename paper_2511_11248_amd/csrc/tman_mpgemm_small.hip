@@ -240,7 +240,7 @@ int launch_mpgemm_small_batch(int bits, int group, int has_zero, int N, const Ge
 
 // The numbered launch of a batch (see order_workgroups_of), up to four workgroups per compute unit: what is resident of
 // mpgemm_small_kernel, whose reduction buffer takes 34.8 KB of LDS.  Of mpgemm_codes_kernel three are (registers), but
-// numbering, largest workgroups first, pays up to four for it too, and never costs: eight launches of a layer set of width
+// numbering, largest workgroups first, pays up to four for it too, and never costs (measured with a row of W per lane): eight launches of a layer set of width
 // 4096 and MLP width 14336 (896 workgroups), plain grid -> numbered, uint4 g128 N = 8 309 -> 275 us, g64 N = 16 358 -> 318,
 // uint2 g64 N = 4 267 -> 236, 1 bit 233 -> 202; 992 workgroups 364 -> 354; 832 equal ones 284 / 285.
 int ordered_workgroups_small(int count, const Layout* L, int n_units) {

@@ -9,8 +9,8 @@
 namespace tman {
 
 // Which formats multiply on the matrix cores (tman_fp4_device.h) instead of the dot product unit: 1 and 2 bits, whose codes are 4-bit
-// numbers as they are, with fp16 activations.  4 bits would be two such products beside a longer transposition, 110 vector
-// instructions for 177, and their launches wait for memory already (without any computing 20.0 us against 19.2); integer activations
+// numbers as they are, with fp16 activations.  4 bits would be two such products beside a longer transposition, and their
+// launches wait for memory already (without any computing 20.0 us against 19.2); integer activations
 // stay integers.
 constexpr bool on_matrix_cores(int bits, TokenSource src) { return bits <= 2 && src != TokenSource::kTablesI16; }
 

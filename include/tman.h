@@ -199,9 +199,10 @@ int tman_mpgemv_i16_batch_run(int32_t count, const tman_shape_t *shapes, int32_t
  * product unit sums exactly:
  *   y[m] = sum_G 2^e[G] * scale[m][G] * ( sum_{k in G} q[m][k] X[k] - zero[m][G] * sum_{k in G} X[k] )
  * (sign form: 2^e * scale * (2 sum q X - sum X)), scales applied in fp32, fp16 result.  Activations within a factor 14
- * of their block's largest enter unrounded.  1- and 2-bit weights: the activations are split into four 8-bit floating point
- * digits whose sum is the activation, and the matrix cores multiply them with the codes in fp32 sums, of 8 neighbouring
- * products of a digit's row only what is at least 2^-13 of their largest.  Infinities and NaN are kept out of the integers and added as
+ * of their block's largest enter unrounded.  1- and 2-bit weights: every 32 columns get the power-of-two step 2^e for which their
+ * largest |x| / 2^e lies in 2^17 .. 2^18, X = round_to_nearest_even(x / 2^e) is split into four 8-bit floating point digits, exactly,
+ * and the matrix cores multiply them with the codes in fp32 sums (activations within a factor 128 of the largest enter
+ * unrounded). Infinities and NaN are kept out of the digits and added as
  * (q - zero) * scale * x.
  *   x         : fp16 [K], device, 16-byte aligned
  *   y         : fp16 [M]

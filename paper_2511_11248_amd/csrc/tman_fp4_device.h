@@ -4,25 +4,25 @@
 // Why.  On the dot product unit a block of 32 weights costs 16 dot products beside its transposition, whatever the width of
 // the codes, and a 2-bit tile 123 vector instructions (1 bit: 110).  v_mfma_f32_16x16x128_f8f6f4 multiplies 16 rows x 128 columns of
 // codes with 16 rows of activations in one instruction that runs beside the vector pipe; what is left are exchanges between
-// lanes, the transposition and 5 multiply-adds per 16 rows: 82 instructions per tile for 2 bits, 69 for 1 bit (with
-// the digits and the ends of a workgroup: 154 -> 122 and 143 -> 111).
-// 32 launches of a 7B layer set, uint2 g64: 415 -> 404 us (63.2 MB in 12.6 us = 5.0 TB/s), of a 3.8B one, 1 bit: 257 -> 247;
-// one 4096 x 4096 GEMV, uint2, 8.4 -> 7.7.  What bounds them now is what a launch has to wait for: the memory system (without
+// lanes, the transposition and 5 or 6 multiply-adds per 16 rows: 84 instructions per tile for 2 bits, 69 for 1 bit, in the loop.
+// 32 launches of a 7B layer set, uint2 g64: 431 -> 418 us (63.2 MB in 13.1 us = 4.8 TB/s), of a 3.8B one, 1 bit: 264 -> 250 (without
+// the scaling of the blocks: 411 and 248).  What bounds them now is what a launch has to wait for: the memory system (without
 // any computing the 2-bit launch takes 12.2 us) and its start and end (a 1-bit launch without computing: 6.5 of 7.7 us).
 //
 // Codes.  The numbers 0, 1, 2, 3 in the low bits of an E2M1 number (4 bits) are 0, 0.5, 1, 1.5: codes of 1 and 2 bits in
 // nibbles are operands as they are (times 2).
 //
 // Activations.  An fp16 number is its high byte, which is an E5M2 number (sign, exponent, 2 of 10 mantissa bits), and a rest;
-// the rest times 4 is an fp16 number that starts again with its leading bit, and so on: x = d0 + d1 / 4 + d2 / 32 + d3 / 256
-// with E5M2 numbers d, exactly, for every finite x (11 significant bits, 3 at a time; the powers of two keep the rests of
-// the smallest numbers above E5M2's smallest, 2^-16).  So the split rounds nothing, and no block has to agree on a step.
+// the rest times 4 is an fp16 number that starts again with its leading bit, and so on: x = d0 + d1 / 4 + d2 / 32 + d3 / 256.  But of 8
+// neighbouring products of a row the instruction keeps only what is at least 2^-13 of the largest (measured; beyond these 8 all 24
+// bits are kept), cut towards zero.  So every 32-column block is first scaled by a power of two that brings its largest magnitude
+// into 2^-7 .. 2^-6, where the last place of E5M2's subnormals, 2^-16, ends a digit before the cut does; the bits below it go
+// to the next digit, which starts two or three places lower, and the last one ends where fp16 does, at 2^-24.  So the split is exact and
+// nothing is cut; what is rounded are activations below 2^-7 of their block's largest, by the scaling, to the nearest 2^-24.
 //
-// Precision.  Sums are fp32, except that of 8 neighbouring columns of an instruction only what is at least 2^-13 of their
-// largest product is kept (measured; beyond these 8 all 24 bits are).  A digit has 3 bits, so that cuts only digits 2^11
-// below another of their row, in the same 8 columns.  rms error against 64 bits, 16-bit fixed point numbers (dot
-// products) -> here, all formats: normal activations 2.06 - 2.09e-4 -> 2.06 - 2.09e-4 (the fp16 result alone), 1 % of the channels x 20
-// 2.2 - 2.5e-4 -> 2.05 - 2.1e-4, x 100 2.2 - 2.5e-4 -> 2.1 - 2.2e-4, x 1000 2.2 - 2.6e-4 -> 2.3 - 2.7e-4.
+// Precision.  Sums are fp32.  rms error against 64 bits in units of rms(y), all formats and block sizes, for normal activations and with 1 % of the
+// channels x 20 to x 4000, of both signs or one: 2.05 - 2.12e-4, the fp16 result alone (the rest is at most 0.2e-4).  Fixed point numbers of 16 bits per quantization block (the dot product unit): 2.2 - 2.6e-4 with such channels.
+// The same digits without the scaling: 2.1 - 3.0e-4, and with channels x 1000 / x 4000 of one sign 6e-4 / 1.1e-3, nearly all of it towards zero.
 //
 // Rows.  The first operand has 16 rows: row 4 b + v is digit v of the tile's 32-column block b, zero in the other blocks'
 // columns, so lane group g of a product (lanes 16 g ..) has the four digits' sums of block g, for weight row lane % 16.  That is
@@ -36,7 +36,7 @@ typedef int v8i_t __attribute__((ext_vector_type(8)));
 typedef float v4f_t __attribute__((ext_vector_type(4)));
 
 constexpr int kFp4BytesPerKTile = 512;  // 16 rows x 32 columns
-constexpr int kFp4SumBytes = 16;        // sums of the tile's four 32-column blocks
+constexpr int kFp4SumBytes = 32;        // (sum, step) of the tile's four 32-column blocks
 constexpr int kFp4Zeros = 16;
 
 // The factor between (sum of code value x activation - what the zero takes) as the lanes add it up and y.
@@ -58,52 +58,69 @@ __device__ __forceinline__ void group_transpose(uint32_t (&w)[4]) {
 }
 
 // A quad of lanes holds one 32-column block: lane f of it has activations 4f .. 4f + 3 (xa) and 16 + 4f .. (xb).  Its digits go to
-// `ld` + 32 * digit + 8 * (lane % 4) (the block's first row in LDS), the sum of the block to `ls`.  Returns whether an activation is
+// `ld` + 32 * digit + 8 * (lane % 4) (the block's first row in LDS), its sum and step to `ls`.  Returns whether an activation is
 // not finite (those count as zero here, see add_nonfinite).  All lanes take part; with `live` false nothing is stored.
 template <bool HZ>
 __device__ __forceinline__ bool store_fp8_digits(const u32x2& xa, const u32x2& xb, int lane, bool live, uint32_t ld, uint32_t ls) {
     uint32_t h[4] = {xa.x, xa.y, xb.x, xb.y};
-    auto block_sum = [&] {
-        float s = 0.f;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const half2_t v = __builtin_bit_cast(half2_t, h[k]);
-            s += (float)v.x;
-            s += (float)v.y;
-        }
-        s += __builtin_bit_cast(float, dpp_u32<0xB1>(__builtin_bit_cast(uint32_t, s)));
-        s += __builtin_bit_cast(float, dpp_u32<0x4E>(__builtin_bit_cast(uint32_t, s)));
-        return s;
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    auto largest = [&] {  // of the block; magnitudes compare like their bit patterns
+        auto magnitudes = [&](int k) { return __builtin_bit_cast(u16x2, h[k] & 0x7fff7fffu); };
+        const u16x2 m = __builtin_elementwise_max(__builtin_elementwise_max(magnitudes(0), magnitudes(1)), __builtin_elementwise_max(magnitudes(2), magnitudes(3)));
+        return max_over_lanes<4>(max((uint32_t)m.x, (uint32_t)m.y));
     };
-    float sum = block_sum();
-    const bool nonfinite = !(fabsf(sum) < __builtin_inff());
+    uint32_t mx = largest();
+    const bool nonfinite = mx >= 0x7c00u;
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(nonfinite) != 0, 0)) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             if ((h[k] & 0x7c00u) == 0x7c00u) h[k] &= 0xffff0000u;
             if ((h[k] & 0x7c000000u) == 0x7c000000u) h[k] &= 0xffffu;
         }
-        sum = block_sum();
+        mx = largest();
     }
-    // r[o] = numbers 4f + o and 16 + 4f + o; after the exchange r[f] = numbers 4f + o and 4 (f + 4) + o, o = lane % 4
-    uint32_t r[4];
+    float sum = 0.f;
+    const float one = opaque(1.f);  // (one mixed-precision instruction per activation)
 #pragma unroll
-    for (int o = 0; o < 4; ++o) r[o] = __builtin_amdgcn_perm(h[2 + o / 2], h[o / 2], o & 1 ? 0x07060302u : 0x05040100u);
-    quad_transpose(r, lane);
+    for (int k = 0; k < 4; ++k) {
+        const half2_t v = __builtin_bit_cast(half2_t, h[k]);
+        sum = fmaf((float)v.x, one, sum);
+        sum = fmaf((float)v.y, one, sum);
+    }
+    sum += __builtin_bit_cast(float, dpp_u32<0xB1>(__builtin_bit_cast(uint32_t, sum)));
+    sum += __builtin_bit_cast(float, dpp_u32<0x4E>(__builtin_bit_cast(uint32_t, sum)));
+    // Exponent field e: magnitudes below 2^(e - 14), in steps of 2^(e - 8) below 2^-6.  (1 / step is a subnormal fp16 number from e = 23 on.)
+    const uint32_t e = max(mx >> 10, 1u);
+    const half2_t scale = __builtin_bit_cast(half2_t, (e < 23 ? (23u - e) << 10 : 0x200u >> (e - 23u)) * 0x10001u);
+    const float step = __builtin_bit_cast(float, (119u + e) << 23);
+    // Lane o of the quad takes numbers 4f + o: halves of words are exchanged with the lane that differs in bit 0, words with the one
+    // that differs in bit 1; x[p] = numbers 8p + o and 8p + 4 + o.
+    half2_t x[4];
+    const uint32_t halves = lane & 1 ? 0x03020706u : 0x05040100u;
+    const bool up = lane & 2;
+#pragma unroll
+    for (int p = 0; p < 4; p += 2) {
+        const uint32_t w0 = __builtin_amdgcn_perm(dpp_u32<0xB1>(h[p]), h[p], halves), w1 = __builtin_amdgcn_perm(dpp_u32<0xB1>(h[p + 1]), h[p + 1], halves);
+        const uint32_t got = dpp_u32<0x4E>(up ? w0 : w1);
+        x[p] = __builtin_bit_cast(half2_t, up ? got : w0) * scale;
+        x[p + 1] = __builtin_bit_cast(half2_t, up ? w1 : got) * scale;
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const uint32_t a = __builtin_amdgcn_perm(r[1], r[0], 0x07030501u), b = __builtin_amdgcn_perm(r[3], r[2], 0x07030501u);
-        if (live) store_lds<u32x2>(ld + v * 32 + (lane & 3) * 8, u32x2{__builtin_amdgcn_perm(b, a, 0x05040100u), __builtin_amdgcn_perm(b, a, 0x07060302u)});
-        if (v < 3) {
-            const _Float16 up = v == 0 ? (_Float16)4.f : (_Float16)8.f;
+        uint32_t w[2];
 #pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                const half2_t x = __builtin_bit_cast(half2_t, r[f]), d = __builtin_bit_cast(half2_t, r[f] & 0xff00ff00u);
-                r[f] = __builtin_bit_cast(uint32_t, (half2_t)((x - d) * up));
-            }
+        for (int q = 0; q < 2; ++q) w[q] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, x[2 * q + 1]), __builtin_bit_cast(uint32_t, x[2 * q]), 0x07050301u);
+        if (live) store_lds<u32x2>(ld + v * 32 + (lane & 3) * 8, u32x2{w[0], w[1]});
+        if (v < 3) {
+            const _Float16 by = v == 0 ? (_Float16)4.f : (_Float16)8.f;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) x[p] = (x[p] - __builtin_bit_cast(half2_t, __builtin_bit_cast(uint32_t, x[p]) & 0xff00ff00u)) * by;
         }
     }
-    if (live && (lane & 3) == 0) store_lds<float>(ls, sum * (HZ ? 0.5f : 0.25f));
+    if (live && (lane & 3) == 0) {
+        const float s = HZ ? sum * __builtin_bit_cast(float, (134u - e) << 23) : sum * 0.25f;  // half the sum in steps, a quarter of the sum
+        store_lds<u32x2>(ls, u32x2{__builtin_bit_cast(uint32_t, s), __builtin_bit_cast(uint32_t, step)});
+    }
     return nonfinite;
 }
 
@@ -119,7 +136,8 @@ __device__ __forceinline__ void planes_to_fp4(const uint32_t (&p)[B], uint32_t (
 
 // Codes times activations of one tile (`st`: lane = row): y[r] += scale (sum - zero S) of block lane / 16 and weight row
 // 16 r + lane % 16.  `lo` and `hi`: LDS addresses of the lane's 16 bytes of the first operand in columns 16 g .. and 64 + 16 g ..
-// (the zeros, where they are another block's); `ls`: of the tile's block sums.
+// (the zeros, where they are another block's); `ls`: of the tile's block
+// sums and steps.
 // (Lanes that load what they multiply - four requests of 8 bytes a lane and four for the parameters instead of two and one
 // whole ones - save the exchanges and lose a quarter: 16.2 us a launch against 12.6, uint2 g64.)
 template <int B, int GQ, bool HZ, typename Next>
@@ -127,7 +145,7 @@ __device__ __forceinline__ void multiply_fp4(const Stage<B, 1, GemvCfg<B, 1, GQ,
                                              int lane, float (&y)[4], Next next) {
     using Cfg = GemvCfg<B, 1, GQ, HZ>;
     const u32x4 xl = load_lds<u32x4>(lo), xh = load_lds<u32x4>(hi);
-    const float S = load_lds<float>(ls + (lane >> 4) * 4);
+    const u32x2 block = load_lds<u32x2>(ls + (lane >> 4) * 8);
     const v8i_t x = {(int)xl.x, (int)xl.y, (int)xl.z, (int)xl.w, (int)xh.x, (int)xh.y, (int)xh.z, (int)xh.w};
     if constexpr (B == 1) {
         next();
@@ -155,15 +173,21 @@ __device__ __forceinline__ void multiply_fp4(const Stage<B, 1, GemvCfg<B, 1, GQ,
         // formats: 1 = E5M2 activations, 4 = E2M1 codes; no scales
         d[r] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x, w, v4f_t{0.f, 0.f, 0.f, 0.f}, 1, 4, 0, 0, 0, 0);
     }
+    const uint32_t sum_w = block.x, step_w = block.y;  // (copied out before the casts)
+    const float S = __builtin_bit_cast(float, sum_w), step = __builtin_bit_cast(float, step_w);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         float t = fmaf(d[r][1], 0.25f, d[r][0]);
         t = fmaf(d[r][2], 0.03125f, t);
         t = fmaf(d[r][3], 0.00390625f, t);
         const float sc = half_bits_to_float(meta[r] & 0xffffu);
-        if constexpr (HZ) t = fmaf(-half_bits_to_float(meta[r] >> 16), S, t);
-        else t -= S;
-        y[r] = fmaf(sc, t, y[r]);
+        if constexpr (HZ) {  // (two mixed-precision instructions and a multiply-add)
+            t = fmaf(-half_bits_to_float(meta[r] >> 16), S, t);
+            y[r] = fmaf(fmaf(sc, step, 0.f), t, y[r]);
+        } else {
+            t = fmaf(t, step, -S);
+            y[r] = fmaf(sc, t, y[r]);
+        }
     }
     if constexpr (B != 1) next();
 }

@@ -15,7 +15,7 @@ namespace tman {
 constexpr bool on_matrix_cores(int bits, TokenSource src) { return bits <= 2 && src != TokenSource::kTablesI16; }
 
 // LDS of a workgroup whose segment has `seg_tiles` tiles: digits and sums or quantization blocks (`gpt` per tile) of the
-// activations, then the partial sums (two sets where a workgroup takes several row blocks) and a word per wave: at most 18,976 bytes
+// activations, then the partial sums (two sets where a workgroup takes several row blocks) and a word per wave: at most 19,488 bytes
 constexpr unsigned x_lds_bytes(int seg_tiles, int gpt, bool matrix, int sets = 1) {
     const int tile = matrix ? kFp4BytesPerKTile + kFp4SumBytes : kDigitBytesPerKTile + gpt * kDigitMetaBytes;
     return (unsigned)(seg_tiles * tile + sets * kWaves * kRows * 4 + kWaves * 4 + (matrix ? kFp4Zeros : 0));
@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(kWaves * 64, 4) mpgemv_x_kernel(Fields... fiel
     src.t_bytes = src.s_bytes = 0;
 
     const uint32_t ld = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr<uint8_t>)lds_x));
-    // quantization blocks, or sums of 32-column blocks
+    // quantization blocks, or sums and steps of 32-column blocks
     const uint32_t lm = ld + (uint32_t)(d.seg_tiles * (kMatrix ? kFp4BytesPerKTile : kDigitBytesPerKTile));
     const uint32_t lr = lm + (uint32_t)(d.seg_tiles * (kMatrix ? kFp4SumBytes : Cfg::GPT * kDigitMetaBytes));  // partial sums [wave][row]
     const uint32_t lf = lr + (kSeveral ? 2 : 1) * kWaves * kRows * 4;  // a word per wave, then (matrix cores) zeros
@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(kWaves * 64, 4) mpgemv_x_kernel(Fields... fiel
         const int j = i * kWaves * 64 + tid, tile = j >> 4;
         const bool live = j < n_lanes;
         if constexpr (kMatrix) {
-            nonfinite |= store_fp8_digits<HZ>(xv[i].a, xv[i].b, lane, live, ld + (uint32_t)((j >> 2) * 128), lm + (uint32_t)((j >> 2) * 4)) && live;
+            nonfinite |= store_fp8_digits<HZ>(xv[i].a, xv[i].b, lane, live, ld + (uint32_t)((j >> 2) * 128), lm + (uint32_t)((j >> 2) * 8)) && live;
             continue;
         }
         uint32_t r[4];

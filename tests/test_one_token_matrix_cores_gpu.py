@@ -42,9 +42,8 @@ def test_one_activation_of_every_exponent(oracle_lib, group, K, bits, hz):
 @pytest.mark.parametrize("group", [32, 64, 128])
 @pytest.mark.parametrize("M,K", [(1, 128), (64, 32), (65, 416), (130, 4096), (63, 5696)])
 def test_sums(oracle_lib, M, K, group, bits, hz):
-    """Normal activations.  Of 8 neighbouring products the matrix cores keep what is at least 2^-13 of the largest; a product is a code
-    times a digit of 3 bits, so what is cut lies below 2^-11 (of activations up to 4) and comes from digits that small: less than
-    1e-4 of rms(y) beside the fp16 result."""
+    """Normal activations.  They are rounded to 2^-18 of the power of two above the largest of their 32 columns, 4 (once in a while 8), to
+    2^-16: less than 1e-4 of rms(y) beside the fp16 result."""
     K = -(-K // group) * group
     q, s, z, x = rand_case(9750 + M + K, max(M, 33), K, 1, bits, group, hz)
     shape = tman.Shape(max(M, 33), K, bits, group, hz)
@@ -52,6 +51,33 @@ def test_sums(oracle_lib, M, K, group, bits, hz):
     y = mpgemv_x(shape, pack(shape, q, s, z), x).astype(np.float64)
     rms = np.sqrt(np.mean(Y ** 2, axis=1, keepdims=True))
     assert np.all(np.abs(y - Y) <= 2.0 ** -11 * np.abs(Y) * 1.001 + 1e-4 * rms)
+
+
+@pytest.mark.parametrize("bits,hz", FORMATS)
+@pytest.mark.parametrize("one_sign", [False, True])
+@pytest.mark.parametrize("group,outlier", [(32, 100), (32, 1000), (32, 4000), (64, 1000), (64, 4000), (128, 4000)])
+def test_large_channels(oracle_lib, group, outlier, one_sign, bits, hz):
+    """1 % of the channels up to 4000 times the others, also with activations of one sign, where errors of one sign would add up.
+    What is left is the fp16 result (a step of the result, uniform: / sqrt(12)) and activations rounded to the step of their 32
+    columns, 2^-18 of the power of two above the largest, to either side alike: the mean error of 1024 rows lies within five
+    standard deviations of zero."""
+    M, K = 1024, 4096
+    q, s, z, _ = rand_case(9900 + bits + group, M, K, 1, bits, group, hz)
+    rng = np.random.default_rng(outlier + group)
+    x = rng.standard_normal(K)
+    x[rng.permutation(K)[:K // 100]] *= outlier
+    x = (np.abs(x) if one_sign else x).astype(np.float16).reshape(1, K)
+    w = ((2.0 * q - 1.0) if z is None else q - _repeat(z, group)) * _repeat(s, group)
+    xd = x[0].astype(np.float64)
+    Y = w @ xd
+    step = np.exp2(np.ceil(np.log2(np.abs(xd).reshape(-1, 32).max(axis=1))) - 18).repeat(32)
+    rounded = np.rint(xd / step) != xd / step
+    half = np.exp2(np.maximum(np.floor(np.log2(np.abs(Y) + 1e-30)), -14) - 10)
+    expected = np.sqrt(np.mean(((w * w) @ np.where(rounded, step * step, 0.0) + half * half) / 12.0))
+    shape = tman.Shape(M, K, bits, group, hz)
+    error = mpgemv_x(shape, pack(shape, q, s, z), x)[0].astype(np.float64) - Y
+    assert np.sqrt(np.mean(error ** 2)) <= 1.1 * expected
+    assert abs(np.mean(error)) <= 5 * expected / np.sqrt(M)
 
 
 @pytest.mark.parametrize("bits,hz", FORMATS)

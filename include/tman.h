@@ -11,7 +11,8 @@
  *     the library never allocates, frees or keeps a pointer after the call returns;
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream); every call only enqueues
  *     work on it and never synchronises with the host;
- *   - tensors are row-major; fp16 means IEEE binary16;
+ *   - tensors are row-major; fp16 means IEEE binary16; a pointer has the alignment of its elements unless the call asks for more
+ *     (16 bytes for packed weights, tables, workspaces, descriptor tables and most activations, never for y);
  *   - the return value is TMAN_OK or a negative tman_status; arguments are validated before
  *     anything is launched, so an error means no work was enqueued (except TMAN_ERR_LAUNCH, which
  *     reports the HIP runtime refusing a launch).

@@ -114,10 +114,11 @@ __device__ __forceinline__ void finish_tokens(const GemvDesc& d, int rb, int seg
     __shared__ int last_flag;
     const int m0 = rb * kRows + r8;
     _Float16* out = static_cast<_Float16*>(d.y);
+    const bool wide = M % 8 == 0 && aligned16(out);  // 16-byte aligned rows of y
     auto store_rows = [&](const float (&v)[8]) {
         if (token >= N) return;
         _Float16* dst = out + (size_t)token * M + m0;
-        if (m0 + 8 <= M && (M % 8) == 0) {
+        if (wide && m0 + 8 <= M) {
             half8_t h;
 #pragma unroll
             for (int e = 0; e < 8; ++e) h[e] = (_Float16)v[e];

@@ -430,7 +430,7 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
     }
     __syncthreads();
     const int m0 = mt * T::TM;
-    const bool fast = (a.M % 8 == 0);  // 16-byte aligned rows of y
+    const bool fast = a.M % 8 == 0 && aligned16(a.y);  // 16-byte aligned rows of y
     for (int piece = tid; piece < kTN * (T::TM / 8); piece += kThreads) {
         const int n = piece / (T::TM / 8), c8 = piece % (T::TM / 8);
         const int gn = n0 + n, gm = m0 + c8 * 8;
@@ -648,7 +648,7 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     // [token][row], then thread -> (token, 8 rows) adds the four in wave order and stores fp16.
     // acc[b][hb][nb][v] is row 64 b + 32 hb + 8 (v / 4) + 4 h + v % 4 for token 32 nb + r.
     const int m0 = mt * T::TM;
-    const bool fast = (a.M % 8 == 0);
+    const bool fast = a.M % 8 == 0 && aligned16(a.y);  // 16-byte aligned rows of y
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
         uint8_t* mine = smem + wave * T::PartBytes;

@@ -381,7 +381,7 @@ __global__ void __launch_bounds__(256) mpgemm_i8_kernel(GemmI8Args a) {
     }
     __syncthreads();
     const int m0 = mt * kI8Rows;
-    const bool fast = (a.M % 8 == 0);  // 16-byte aligned rows of y
+    const bool fast = a.M % 8 == 0 && aligned16(a.y);  // 16-byte aligned rows of y
     for (int piece = tid; piece < kI8Tokens * (kI8Rows / 8); piece += 256) {
         const int n = piece / (kI8Rows / 8), c8 = piece % (kI8Rows / 8);
         const int gn = n0 + n, gm = m0 + c8 * 8;
@@ -600,7 +600,7 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
     }
     __syncthreads();
     const int m0 = mt * kI8WRows;
-    const bool fast = (a.M % 8 == 0);  // 16-byte aligned rows of y
+    const bool fast = a.M % 8 == 0 && aligned16(a.y);  // 16-byte aligned rows of y
     for (int piece = tid; piece < T::TN * (kI8WRows / 8); piece += 256) {
         const int n = piece / (kI8WRows / 8), c8 = piece % (kI8WRows / 8);
         const int gn = n0 + n, gm = m0 + c8 * 8;
@@ -814,7 +814,7 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
     // [token][row], then thread -> (token, 8 rows) adds the four, scales and stores fp16.
     // acc[b][hb][nb][v] is row 64 b + 32 hb + 8 (v / 4) + 4 h + v % 4 for token 32 nb + r.
     const int m0 = mt * T::TM;
-    const bool fast = (a.M % 8 == 0);
+    const bool fast = a.M % 8 == 0 && aligned16(a.y);  // 16-byte aligned rows of y
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
         uint8_t* mine = smem + wave * T::PartBytes;

@@ -353,8 +353,10 @@ int tman_mpgemv_noalloc(const tman_shape_t *shape, const void *packed, const voi
  * on-chip-memory constraints, the prefill and the decoding loop nest covering the same M and K extents of the one
  * weight copy).  The shared tile block is fixed by the packed layout (64 rows x 128 columns, which is Eq. 2 and
  * Eq. 3 by construction); free is how many tile blocks one workgroup takes:
- *   decode_seg_tiles / _many   K tiles per workgroup of tman_mpgemv for 2 / 3-8 tokens where it looks up (1 bit, 2 bits with
- *                              two tokens); elsewhere small_seg_tiles, or these if longer
+ *   decode_seg_tiles / _many   K tiles per workgroup of tman_mpgemv for 2 / 3-8 tokens.  At their built-in values, launches
+ *                              whose workgroups then outnumber the compute units and whose codes the matrix cores
+ *                              multiply (all formats but 1 bit with up to 4 tokens) take small_seg_tiles, if longer;
+ *                              workspaces are sized for the segments without that
  *   decode_x_seg_tiles         one token: a K of at most this many tiles, and at most decode_x_whole_bytes of
  *                              packed weights per row block, is ONE segment; it is at most 32 (Eq. 1: what a
  *                              workgroup keeps of its activations lives in LDS; 32 tiles are two passes of its lanes)
@@ -362,7 +364,7 @@ int tman_mpgemv_noalloc(const tman_shape_t *shape, const void *packed, const voi
  *   decode_balance             1: batches of tman_mpgemv_x, of tman_mpgemv (tables) and of the small-batch
  *                              tman_mpgemm number their workgroups for equal work per compute unit where they fit
  *                              the chip (see tman_mpgemv_x_batch_order), 0: plain grids
- *   small_seg_tiles            K tiles per workgroup of tman_mpgemm for N <= 32 and of tables multiplied on the matrix cores
+ *   small_seg_tiles            K tiles per workgroup of tman_mpgemm for N <= 32 and of large tman_mpgemv launches (see above)
  *   prefill_row_blocks         tile blocks in M per workgroup of the tiled prefill kernel, 1..4 (Eq. 4: four
  *                              stage buffers of rows x 80 + 256 x 64 bytes within 160 KB of LDS), 0 = chosen per
  *                              call from the grid it gives

@@ -164,18 +164,6 @@ static size_t desc_table_bytes(int count) { return ((size_t)count * sizeof(GemvD
 static uint16_t* order_of(void* desc, int count) {
     return reinterpret_cast<uint16_t*>(static_cast<uint8_t*>(desc) + desc_table_bytes(count));
 }
-static int device_units() {
-    static std::once_flag once;
-    static int n_units = 0;
-    std::call_once(once, [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-            n_units = n;
-    });
-    return n_units;
-}
-
 size_t tman_mpgemv_batch_desc_bytes(int32_t count) {
     if (count < 1 || count > TMAN_MAX_BATCH) return 0;
     return desc_table_bytes(count) + (size_t)kOrderedMaxWorkgroups * sizeof(uint16_t);
@@ -192,20 +180,35 @@ static int check_batch(int32_t count, const tman_shape_t* shapes, int32_t N) {
         if (shapes[i].bits != shapes[0].bits || shapes[i].group != shapes[0].group ||
             shapes[i].flags != shapes[0].flags)
             return TMAN_ERR_SHAPE;  // one launch runs one weight format
-        total += plan_decode(make_layout(&shapes[i]), N).n_workgroups;
+        const Layout L = make_layout(&shapes[i]);
+        total += (N == 1 ? plan_gemv_x(L) : plan_tables(L, N)).n_workgroups;  // (the others have no more)
     }
     if (total > 0x7fffffffLL) return TMAN_ERR_SHAPE;
     return TMAN_OK;
 }
 
+// Layouts and plans of a decoding batch, the same for its prepare and its run calls.
+struct BatchPlans {
+    int count;
+    Layout L[TMAN_MAX_BATCH];
+    GemvPlan plans[TMAN_MAX_BATCH];
+    BatchPlans(int count_, const tman_shape_t* shapes, int N) : count(count_) {
+        long long n_wg = 0;
+        for (int i = 0; i < count; ++i) {
+            L[i] = make_layout(&shapes[i]);
+            if (N > 1) n_wg += plan_tables(L[i], N).n_workgroups;
+        }
+        const bool fills = fills_device(n_wg);
+        for (int i = 0; i < count; ++i) plans[i] = plan_decode(L[i], N, fills);
+    }
+};
+
 // Second half of a prepare call: a launch whose workgroups are all resident at once gets them numbered for equal work per
 // compute unit.
-static int write_decode_order(int32_t count, const tman_shape_t* shapes, int32_t N, void* desc, hipStream_t st) {
-    std::vector<Layout> L(count);
-    for (int i = 0; i < count; ++i) L[i] = make_layout(&shapes[i]);
+static int write_decode_order(const BatchPlans& p, int32_t N, void* desc, hipStream_t st) {
     std::vector<uint16_t> order;
-    if (!order_workgroups(count, L.data(), N, device_units(), &order)) return TMAN_OK;
-    return launch_write_order(order, order_of(desc, count), st);
+    if (!order_workgroups(p.count, p.L, p.plans, N, device_units(), &order)) return TMAN_OK;
+    return launch_write_order(order, order_of(desc, p.count), st);
 }
 
 static int run_decode_batch(int (*launch)(const DecodeBatch&, hipStream_t), int32_t count, const tman_shape_t* shapes, int32_t N,
@@ -224,19 +227,16 @@ static int run_decode_batch(int (*launch)(const DecodeBatch&, hipStream_t), int3
     b.order = nullptr;
     b.n_workgroups = b.max_seg_tiles = 0;
     b.row_blocks = 1;
-    Layout L[8];
-    for (int i = 0; i < count && i < 8; ++i) L[i] = make_layout(&shapes[i]);
-    const int n_ordered = ordered_workgroups(count, L, N, device_units());
+    const BatchPlans p(count, shapes, N);
+    const int n_ordered = ordered_workgroups(count, p.L, p.plans, N, device_units());
     long long total = 0;
     if (!n_ordered && N == 1)
-        for (int i = 0; i < count; ++i) total += plan_decode(make_layout(&shapes[i]), N).n_workgroups;
+        for (int i = 0; i < count; ++i) total += p.plans[i].n_workgroups;
     if (!n_ordered) b.row_blocks = batch_row_blocks(b.bits, N, total, device_units());
     for (int i = 0; i < count; ++i) {
-        const Layout Li = make_layout(&shapes[i]);
-        const GemvPlan p = plan_decode(Li, N);
-        const int n_wg = (Li.n_row_blocks + b.row_blocks - 1) / b.row_blocks * p.n_seg;
+        const int n_wg = (p.L[i].n_row_blocks + b.row_blocks - 1) / b.row_blocks * p.plans[i].n_seg;
         if (n_wg > b.n_workgroups) b.n_workgroups = n_wg;
-        if (p.seg_tiles > b.max_seg_tiles) b.max_seg_tiles = p.seg_tiles;
+        if (p.plans[i].seg_tiles > b.max_seg_tiles) b.max_seg_tiles = p.plans[i].seg_tiles;
     }
     if (n_ordered) {
         b.order = order_of(const_cast<void*>(desc), count);
@@ -253,18 +253,19 @@ int tman_mpgemv_batch_prepare(int32_t count, const tman_shape_t* shapes, const v
     if (!packed || !lut || !y || !workspace || !workspace_bytes || !desc) return TMAN_ERR_NULL;
     if (!aligned16(desc)) return TMAN_ERR_ALIGN;
     GemvDesc host[TMAN_MAX_BATCH];
+    const BatchPlans p(count, shapes, N);
     for (int i = 0; i < count; ++i) {
         if (!packed[i] || !lut[i] || !y[i] || !workspace[i]) return TMAN_ERR_NULL;
         if (!aligned16(packed[i]) || !aligned16(lut[i]) || !aligned16(workspace[i])) return TMAN_ERR_ALIGN;
         if (workspace_bytes[i] < tman_mpgemv_workspace_bytes(&shapes[i], N)) return TMAN_ERR_WORKSPACE;
         for (int j = 0; j < i; ++j)
             if (workspace[j] == workspace[i]) return TMAN_ERR_WORKSPACE;  // every GEMV needs its own
-        fill_desc(host[i], make_layout(&shapes[i]), packed[i], lut[i], N, y[i], workspace[i]);
+        fill_desc_plan(host[i], p.L[i], p.plans[i], packed[i], lut[i], N, y[i], workspace[i]);
     }
     rc = launch_write_descs(host, count, shapes[0].bits, shapes[0].group, (shapes[0].flags & TMAN_FLAG_HAS_ZERO) ? 1 : 0,
                             static_cast<GemvDesc*>(desc), (hipStream_t)stream);
     if (rc != TMAN_OK) return rc;
-    return write_decode_order(count, shapes, N, desc, (hipStream_t)stream);
+    return write_decode_order(p, N, desc, (hipStream_t)stream);
 }
 
 int tman_mpgemv_batch_run(int32_t count, const tman_shape_t* shapes, int32_t N, const void* desc, void* stream) {
@@ -295,18 +296,19 @@ int tman_mpgemv_x_batch_prepare(int32_t count, const tman_shape_t* shapes, const
     if (!packed || !x || !y || !workspace || !workspace_bytes || !desc) return TMAN_ERR_NULL;
     if (!aligned16(desc)) return TMAN_ERR_ALIGN;
     GemvDesc host[TMAN_MAX_BATCH];
+    const BatchPlans p(count, shapes, 1);
     for (int i = 0; i < count; ++i) {
         if (!packed[i] || !x[i] || !y[i] || !workspace[i]) return TMAN_ERR_NULL;
         if (!aligned16(packed[i]) || !aligned16(x[i]) || !aligned16(workspace[i])) return TMAN_ERR_ALIGN;
         if (workspace_bytes[i] < tman_mpgemv_workspace_bytes(&shapes[i], 1)) return TMAN_ERR_WORKSPACE;
         for (int j = 0; j < i; ++j)
             if (workspace[j] == workspace[i]) return TMAN_ERR_WORKSPACE;  // every GEMV needs its own
-        fill_desc(host[i], make_layout(&shapes[i]), packed[i], x[i], 1, y[i], workspace[i]);
+        fill_desc_plan(host[i], p.L[i], p.plans[i], packed[i], x[i], 1, y[i], workspace[i]);
     }
     rc = launch_write_descs(host, count, shapes[0].bits, shapes[0].group, (shapes[0].flags & TMAN_FLAG_HAS_ZERO) ? 1 : 0,
                             static_cast<GemvDesc*>(desc), (hipStream_t)stream);
     if (rc != TMAN_OK) return rc;
-    return write_decode_order(count, shapes, 1, desc, (hipStream_t)stream);
+    return write_decode_order(p, 1, desc, (hipStream_t)stream);
 }
 
 int tman_mpgemv_x_batch_order(int32_t count, const tman_shape_t* shapes, int32_t n_units, uint16_t* order,
@@ -315,10 +317,9 @@ int tman_mpgemv_x_batch_order(int32_t count, const tman_shape_t* shapes, int32_t
     if (rc != TMAN_OK) return rc;
     if (!n_entries) return TMAN_ERR_NULL;
     if (n_units < 0 || max_entries < 0) return TMAN_ERR_SHAPE;
-    std::vector<Layout> L(count);
-    for (int i = 0; i < count; ++i) L[i] = make_layout(&shapes[i]);
+    const BatchPlans p(count, shapes, 1);
     std::vector<uint16_t> o;
-    if (!order_workgroups(count, L.data(), 1, n_units > 0 ? n_units : device_units(), &o)) o.clear();
+    if (!order_workgroups(count, p.L, p.plans, 1, n_units > 0 ? n_units : device_units(), &o)) o.clear();
     *n_entries = (int32_t)o.size();
     if (order)
         for (size_t i = 0; i < o.size() && i < (size_t)max_entries; ++i) order[i] = o[i];

@@ -111,11 +111,14 @@ GemvPlan plan_tables(const Layout& L, int N);  // table lookups, and what a work
 GemvPlan plan_segments(const Layout& L, int np, int max_seg);
 // Plan of the one-token kernel: at most 32 tiles per segment.
 GemvPlan plan_gemv_x(const Layout& L);
-GemvPlan plan_decode(const Layout& L, int N);  // the one of N tokens; its workspace is at most decode_workspace_bytes
+// The one of N tokens; its workspace is at most decode_workspace_bytes.  `fills`: fills_device of the sum of
+// plan_tables().n_workgroups over the GEMVs of the launch (one token: not looked at).
+GemvPlan plan_decode(const Layout& L, int N, bool fills);
+bool fills_device(long long table_workgroups);
+int device_units();  // compute units, 0 when no device answers
 size_t decode_workspace_bytes(const Layout& L, int N);
 void fill_desc_plan(GemvDesc& d, const Layout& L, const GemvPlan& p, const void* packed, const void* lut, int N, void* y,
                     void* workspace);
-void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace);
 
 // launchers (each returns a tman_status)
 int launch_pack(const Layout& L, const uint8_t* codes, const void* scales, const void* zeros, void* packed,
@@ -165,8 +168,8 @@ bool order_workgroups_of(int count, const Layout* L, const GemvPlan* plans, int 
                          std::vector<uint16_t>* order);
 int launch_write_order(const std::vector<uint16_t>& order, uint16_t* dev, hipStream_t st);
 // ... of a decoding batch and of a small-batch mpGEMM batch
-int ordered_workgroups(int count, const Layout* L, int N, int n_units);
-bool order_workgroups(int count, const Layout* L, int N, int n_units, std::vector<uint16_t>* order);
+int ordered_workgroups(int count, const Layout* L, const GemvPlan* plans, int N, int n_units);
+bool order_workgroups(int count, const Layout* L, const GemvPlan* plans, int N, int n_units, std::vector<uint16_t>* order);
 int ordered_workgroups_small(int count, const Layout* L, int n_units);
 bool order_workgroups_small(int count, const Layout* L, int n_units, std::vector<uint16_t>* order);
 int launch_mpgemm_small_ordered(int bits, int group, int has_zero, int N, const GemvDesc* descs_dev, int n_gemv,

@@ -30,6 +30,7 @@
 // rest to the matrix cores (tman_codes_kernel.h).
 #include <algorithm>
 #include <functional>
+#include <mutex>
 #include <queue>
 #include <vector>
 
@@ -52,6 +53,18 @@ GemvPlan plan_segments(const Layout& L, int np, int max_seg) {
     return p;
 }
 
+int device_units() {
+    static std::once_flag once;
+    static int n_units = 0;
+    std::call_once(once, [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
+            n_units = n;
+    });
+    return n_units;
+}
+
 GemvPlan plan_tables(const Layout& L, int N) {
     const int np = padded_tokens(N);
     // with four or eight tokens a looked-up tile takes about twice as long: shorter segments, more workgroups (measured)
@@ -59,18 +72,27 @@ GemvPlan plan_tables(const Layout& L, int N) {
     return plan_segments(L, np, np >= 4 ? t.decode_seg_tiles_many : t.decode_seg_tiles);
 }
 
-// Several tokens on the matrix cores: the kernel of small batches, and its segments (7B uint4 g128, N = 4, us per layer set with the
-// table launch, segments of 24 / 32 / 43 tiles: 37.5 / 33.6 / 29.7), unless the tiling asks for longer ones.  A table batch is
-// prepared for both kinds of tables; where only one of them is looked up (2 bits, two tokens) the plan is this one too.
-GemvPlan plan_decode(const Layout& L, int N) {
+// Several tokens on the matrix cores: the kernel of small batches.  Its segments are longer (small_seg_tiles) where the launch fills the chip
+// without short ones: 7B uint4 g128, N = 4, us per layer set with the table launch, segments of 24 / 32 / 43 tiles 37.5 / 33.6 /
+// 29.7; a K of 44 to 50 tiles, which 43 cuts in two, is better off so (layer sets 2048 / 5632 and 2048 / 6400: one segment +15 to 45 %).  A launch that
+// leaves compute units idle (`fills` false: a single GEMV with few rows) keeps the lookups' short segments: 4096 x 11008, N = 4,
+// 22 / 43 tiles 11.8 / 14.7 us, 4096 x 4096 16 / 32 tiles 8.9 / 10.0; 11008 x 4096, which fills it, 11.9 / 10.5.  A caller's own
+// decode_seg_tiles (_many) decides alone.  A table batch is prepared for both kinds of tables; where only one of them is looked up (2
+// bits, two tokens) the plan is this one too (7B uint2 g64 fp16, 32 / 43 tiles: 18.3 / 18.4, integers 23.7 / 20.0).
+GemvPlan plan_decode(const Layout& L, int N, bool fills) {
     if (N == 1) return plan_gemv_x(L);
     const int np = padded_tokens(N);
     const tman_tiling_t t = current_tiling();
-    if (lookups_stay(L.bits, np, true)) return plan_tables(L, N);
-    return plan_segments(L, np, std::max(t.small_seg_tiles, np >= 4 ? t.decode_seg_tiles_many : t.decode_seg_tiles));
+    tman_tiling_t built_in;
+    (void)tman_default_tiling(&built_in);
+    const int own = np >= 4 ? t.decode_seg_tiles_many : t.decode_seg_tiles;
+    if (!fills || lookups_stay(L.bits, np, true) || own != (np >= 4 ? built_in.decode_seg_tiles_many : built_in.decode_seg_tiles))
+        return plan_tables(L, N);
+    return plan_segments(L, np, std::max(t.small_seg_tiles, own));
 }
+bool fills_device(long long table_workgroups) { return table_workgroups > device_units(); }
 
-// (plan_decode never has more segments than plan_tables.)
+// (plan_decode never has more segments than plan_tables, which it has in a small launch.)
 size_t decode_workspace_bytes(const Layout& L, int N) {
     const GemvPlan p = N == 1 ? plan_gemv_x(L) : plan_tables(L, N);
     return p.ticket_bytes + p.partial_bytes;

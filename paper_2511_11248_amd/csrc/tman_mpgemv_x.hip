@@ -40,10 +40,6 @@ GemvPlan plan_gemv_x(const Layout& L) {
     return plan_segments(L, 1, L.n_ktiles <= whole ? whole : t.decode_x_long_seg_tiles);
 }
 
-void fill_desc(GemvDesc& d, const Layout& L, const void* packed, const void* lut, int N, void* y, void* workspace) {
-    fill_desc_plan(d, L, plan_decode(L, N), packed, lut, N, y, workspace);
-}
-
 // A good part of the vector instructions of a 1-bit workgroup make digits, and a large launch (all layers of a model at once) is
 // bound by vector issue: its workgroups take two row blocks each, as long as that leaves at least eight per compute unit.
 // 160 GEMVs of a 32-layer 3.8B model in one launch, sign form with blocks of 64: 113 us with two, 120 with one, 119 by
@@ -57,26 +53,20 @@ int batch_row_blocks(int bits, int N, long long n_workgroups, int n_units) {
 // more than 5 of 32 tiles - numbering a
 // launch pays while a unit has few of them (1152 workgroups of a layer set with MLP width 14336, uint4 g128: 25.5 us on
 // the plain grid, 23.3 us numbered; equal workgroups need none).
-static int resident_per_unit(int count, const Layout* L, int N) {
+static int resident_per_unit(int count, const Layout* L, const GemvPlan* plans, int N) {
     const int np = padded_tokens(N);
     if (np > 1 && !lookups_stay(L[0].bits, np, true)) return kCodesResident;
     int max_seg_tiles = 1;
-    for (int g = 0; g < count; ++g) max_seg_tiles = std::max(max_seg_tiles, plan_decode(L[g], N).seg_tiles);
+    for (int g = 0; g < count; ++g) max_seg_tiles = std::max(max_seg_tiles, plans[g].seg_tiles);
     const unsigned lds = np == 1 ? x_lds_bytes(max_seg_tiles, L[0].groups_per_tile, on_matrix_cores(L[0].bits, TokenSource::kActivations))
                                  : (unsigned)(kWaves * (kTableBytesPerKTile * np + 256 + np * kRows * 4));
     return std::max(1, std::min((int)(160u * 1024u / lds), std::min(8, 160 / max_seg_tiles)));
 }
-int ordered_workgroups(int count, const Layout* L, int N, int n_units) {
-    if (count > 8) return 0;
-    std::vector<GemvPlan> plans(count);
-    for (int g = 0; g < count; ++g) plans[g] = plan_decode(L[g], N);
-    return ordered_workgroups_of(count, L, plans.data(), n_units, resident_per_unit(count, L, N));
+int ordered_workgroups(int count, const Layout* L, const GemvPlan* plans, int N, int n_units) {
+    return count > 8 ? 0 : ordered_workgroups_of(count, L, plans, n_units, resident_per_unit(count, L, plans, N));
 }
-bool order_workgroups(int count, const Layout* L, int N, int n_units, std::vector<uint16_t>* order) {
-    if (count > 8) return false;
-    std::vector<GemvPlan> plans(count);
-    for (int g = 0; g < count; ++g) plans[g] = plan_decode(L[g], N);
-    return order_workgroups_of(count, L, plans.data(), n_units, resident_per_unit(count, L, N), order);
+bool order_workgroups(int count, const Layout* L, const GemvPlan* plans, int N, int n_units, std::vector<uint16_t>* order) {
+    return count <= 8 && order_workgroups_of(count, L, plans, n_units, resident_per_unit(count, L, plans, N), order);
 }
 
 int launch_mpgemv_x(const Layout& L, const void* packed, const void* x, void* y, void* workspace, hipStream_t st) {

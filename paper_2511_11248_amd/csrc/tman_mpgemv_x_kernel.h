@@ -281,11 +281,11 @@ static int launch_x_tokens(int np, int bits, int has_zero, int group, const Args
 template <TokenSource SRC>
 static int launch_x_single(const Layout& L, int N, const void* packed, const void* x, void* y, void* workspace, hipStream_t st) {
     KernelArgs<true> a;
-    fill_desc(a.single, L, packed, x, N, y, workspace);
+    const GemvPlan p = plan_decode(L, N, N > 1 && fills_device(plan_tables(L, N).n_workgroups));
+    fill_desc_plan(a.single, L, p, packed, x, N, y, workspace);
     a.n_gemv = 1;
     a.status = device_status_word();
     if (!a.status) return TMAN_ERR_LAUNCH;
-    const GemvPlan p = plan_decode(L, N);
     return launch_x_tokens<SRC, true>(p.np, L.bits, L.has_zero, L.group, a, p.n_workgroups, p.seg_tiles, st);
 }
 template <TokenSource SRC>

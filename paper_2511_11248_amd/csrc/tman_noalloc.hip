@@ -66,7 +66,7 @@ int tman_mpgemv_noalloc(const tman_shape_t* shape, const void* packed, const voi
     // The tickets are zero when the library is loaded and every call returns them to zero; the partial sums are
     // written before they are read.  Nothing needs clearing between calls.
     const Layout L = make_layout(shape);
-    const size_t tickets = plan_decode(L, N).ticket_bytes;  // (more than the region only when K is one segment: unused)
+    const size_t tickets = plan_tables(L, N).ticket_bytes;  // (more than the region only when K is one segment: unused)
     if (tickets <= kTicketRegion) ws = static_cast<uint8_t*>(ws) + (kTicketRegion - tickets);
     return launch_mpgemv(L, packed, lut, N, y, ws, (hipStream_t)stream);
 }

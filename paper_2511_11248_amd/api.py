@@ -39,8 +39,13 @@ class _CShape(C.Structure):
     _fields_ = [("M", C.c_int32), ("K", C.c_int32), ("bits", C.c_int32), ("group", C.c_int32), ("flags", C.c_int32)]
 
 
+class _KeepsCForm:
+    """Room for the C form of a shape outside its fields and its ``__dict__``."""
+    __slots__ = ("_c",)
+
+
 @dataclass(frozen=True)
-class Shape:
+class Shape(_KeepsCForm):
     """Mirror of ``tman_shape_t``: W is (M, K), ``bits``-bit codes, quantization blocks of ``group``
     along K, with a per-block zero point unless ``has_zero`` is False (1-bit sign form)."""
     M: int
@@ -52,14 +57,18 @@ class Shape:
     def c(self) -> _CShape:
         return _CShape(self.M, self.K, self.bits, self.group, TMAN_FLAG_HAS_ZERO if self.has_zero else 0)
 
-    def __reduce__(self):  # (the C form that _ref keeps stays behind)
-        return type(self), (self.M, self.K, self.bits, self.group, self.has_zero)
+    def __getstate__(self):  # (copies and pickles take the fields, not the C form)
+        return self.__dict__
 
 
 def _ref(shape: Shape):
-    """Reference to the shape's C form, which is made once: a shape never changes."""
-    c = shape.__dict__.get("_c")
-    if c is None:
+    """Reference to the shape's C form, which a Shape makes once because it never changes (a derived class or another object
+    with a C form may)."""
+    if type(shape) is not Shape:
+        return C.byref(shape.c())
+    try:
+        c = shape._c
+    except AttributeError:
         c = shape.c()
         object.__setattr__(shape, "_c", c)
     return C.byref(c)

@@ -1,11 +1,9 @@
-// mpGEMM for a handful of tokens (2 .. 32): two-level table dequantization in registers feeding the matrix
-// cores (Sec. 4.1 "Fused LUT-based dequantization", Sec. 4.2), organised like the decoding kernel because with
-// so few tokens the product is bound by the weight stream, not by the matrix cores.
+// mpGEMM for a handful of tokens (up to 32): which kernel, how K is cut, and the kernel for 17 to 32 tokens with quantization
+// blocks of 32 and 64.  The others multiply the codes themselves (tman_codes_kernel.h; see launch_small_cfg).
 //
-// Why not the lookup kernel for 4 or 8 tokens: a lookup then returns 8 or 16 bytes per lane and the vector
-// lookups are bound by LDS bandwidth (16 bytes per lane and lookup), three to four times the time the weight
-// stream needs.  Dequantizing a weight once and multiplying it with all tokens in one MFMA costs the same
-// vector work for 2 tokens as for 32.
+// With so few tokens the product is bound by the weight stream, so both kernels are organised like the decoding kernels.  The one
+// here is two-level table dequantization in registers feeding the matrix cores (Sec. 4.1 "Fused LUT-based dequantization",
+// Sec. 4.2): a weight is dequantized once and multiplied with all tokens in one MFMA.
 //
 // Mapping.  The weights stay in the bit-serial layout the decoding kernel streams (lane = row of a 64-row
 // tile block, 16-byte chunks of bit-plane words, group scales and zeros behind them): a wave requests whole
@@ -187,16 +185,25 @@ __global__ void __launch_bounds__(kWaves * 64) mpgemm_small_kernel(Fields... fie
 // not fit the registers of three waves per SIMD (uint4 g64 N = 32: 132 us against 46).  Layer sets of width 4096 / MLP
 // 11008, us per launch, dequantized weights -> codes: uint4 N = 4, blocks of 128 / 64 / 32: 35 / 36 / 41 -> 22.2 / 24.5 / 26.9;
 // N = 16: 39 / 40 / 45 -> 27.6 / 29.1 / 35.6; N = 32, 128: 45 -> 34.7; uint2 g64 N = 4 30 -> 19.0; 1 bit g128 N = 4 28 -> 16.3.
+// Where a launch leaves most units idle, two kinds of single GEMVs are slower than the kernels before (dequantized weights; codes with
+// a row per lane), which round more or are slower everywhere else: blocks of 32 with 9 to 16 tokens, 4096 x 4096, N = 16, 1 / 2
+// / 4 bits 13.3 / 13.8 / 14.9 -> 14.6 / 14.3 / 14.8, 4096 x 11008 20.3 / 20.8 / 22.2 -> 21.6 / 21.3 / 22.2 (error 2.9e-4 -> 2.1e-4; a layer
+// set 32 / 34.5 / 44.5 -> 28.5 / 29.5 / 34.5); 2 bits, blocks of 128, 17 tokens 12.0 -> 12.6 (N = 32 12.8 both; a layer set 27.6 -> 26.2, 38.5 -> 30.5).
+// (1 bit, blocks of 128, more than 16 tokens: three registers are spilled; forms without, which make the codes in pieces, are 2
+// to 4 % slower.)
 template <int B, int GQ, bool HZ, bool SINGLE, typename Args>
 static int launch_small_cfg(const Args& a, int N, int n_wg, hipStream_t st) {
-    const dim3 grid((unsigned)n_wg, __is_same(Args, OrderedArgs) ? 1u : (unsigned)a.n_gemv), block(kWaves * 64);
     if (N <= 8) return launch_codes<B, GQ, HZ, 1, 0, false, SINGLE>(a, n_wg, st);
     if (N <= 16) return launch_codes<B, GQ, HZ, 2, 0, false, SINGLE>(a, n_wg, st);
-    if constexpr (GQ >= 128) return launch_codes<B, GQ, HZ, 4, 0, false, SINGLE>(a, n_wg, st);
-    with_fields(a, [&](auto... f) {
-        hipLaunchKernelGGL((mpgemm_small_kernel<B, GQ, HZ, SINGLE, Args, decltype(f)...>), grid, block, 0, st, f...);
-    });
-    return launch_status();
+    if constexpr (GQ >= 128) {
+        return launch_codes<B, GQ, HZ, 4, 0, false, SINGLE>(a, n_wg, st);
+    } else {
+        const dim3 grid((unsigned)n_wg, __is_same(Args, OrderedArgs) ? 1u : (unsigned)a.n_gemv), block(kWaves * 64);
+        with_fields(a, [&](auto... f) {
+            hipLaunchKernelGGL((mpgemm_small_kernel<B, GQ, HZ, SINGLE, Args, decltype(f)...>), grid, block, 0, st, f...);
+        });
+        return launch_status();
+    }
 }
 
 template <int B, bool HZ, bool SINGLE, typename Args>

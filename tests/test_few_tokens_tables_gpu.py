@@ -1,5 +1,5 @@
-"""Two to eight tokens on the 4-bit dot product unit (4-bit weights: integer tables, and fp16 tables for two tokens): every
-token count, K edges, segments worked in several pieces, infinities."""
+"""Two to eight tokens out of tables with 4-bit weights (the matrix cores multiply the codes): integer tables for every token count,
+fp16 tables for two, K edges, the default segments and one segment of any length, infinities."""
 import numpy as np
 import pytest
 import torch
@@ -23,7 +23,7 @@ def _i16(shape, blob, x):
 
 @pytest.fixture(params=[0, 100])
 def seg_tiles(request):
-    """0: the default segments; 100: one segment for every K here, worked in pieces of 24 or 32 tiles."""
+    """0: the default segments; 100: one segment for every K here."""
     saved = tman.tman_get_tiling()
     if request.param:
         t = tman.tman_get_tiling()
@@ -50,8 +50,8 @@ def test_integer_tables(oracle_lib, seg_tiles, M, K, group, N):
 
 @pytest.mark.parametrize("N", [5, 8])
 @pytest.mark.parametrize("K", [2944, 3072, 9216])
-def test_segments_that_take_more_than_64_kb_of_lds(oracle_lib, seg_tiles, K, N):
-    """Blocks of 32 and 5 to 8 tokens: 23 and 24 tiles' digits and partial sums are 67,088 and 69,648 bytes."""
+def test_blocks_of_32_in_long_segments(oracle_lib, seg_tiles, K, N):
+    """Blocks of 32 and 5 to 8 tokens (two rows of the product each): 23, 24 and 72 tiles."""
     test_integer_tables(oracle_lib, seg_tiles, 40, K, 32, N)
 
 

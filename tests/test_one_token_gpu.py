@@ -1,5 +1,5 @@
-"""One-token decode on the 4-bit dot product unit: precision, infinities and NaN, agreement of its three sources of
-activations (x, fp16 tables, int16 tables)."""
+"""One-token decode (4-bit weights and integer tables: the 4-bit dot product unit; 1- and 2-bit weights: the matrix cores): precision,
+infinities and NaN, agreement of its three sources of activations (x, fp16 tables, int16 tables)."""
 import numpy as np
 import pytest
 import torch
@@ -18,8 +18,8 @@ EDGES = [(65, 128), (40, 160), (64, 2048), (33, 2080), (70, 4096), (64, 4224)]  
 @pytest.mark.parametrize("group", [32, 64, 128])
 @pytest.mark.parametrize("M,K", EDGES)
 def test_short_activations_are_not_rounded(oracle_lib, M, K, group, bits, hz):
-    """Activations that are 10-bit integers times a power of two per block enter the integer sums exactly, so the only
-    roundings are the fp32 sum over blocks and the fp16 result: half a step of the result, 2^-11, plus the fp32 terms
+    """Activations that are 10-bit integers times a power of two per block enter the sums exactly (as 16-bit integers; as digits, which
+    hold 17 bits below a block's largest), so the only roundings are the fp32 sum over blocks and the fp16 result: half a step of the result, 2^-11, plus the fp32 terms
     (K / group additions of 2^-24 each, against the largest partial sum, taken as 64 times the row's rms)."""
     K = -(-K // group) * group
     q, s, z, _ = rand_case(500 + M + K + bits + group, M, K, 1, bits, group, hz)
@@ -63,8 +63,9 @@ def test_infinities_and_nan(oracle_lib, bits, hz, through_tables):
 @pytest.mark.parametrize("group,outlier", [(32, 100), (128, 20), (128, 100), (128, 1000)])
 def test_outlier_channels(oracle_lib, group, outlier, bits, hz):
     """1 % of the channels 20 to 1000 times the others.  The error is that of the fp16 result (a step of the result,
-    uniform: / sqrt(12)) and of the activations below the block's step 2^e, the smallest with max |x| <= 30583 * 2^e (a step,
-    uniform, times the weight).  Both sums have thousands of terms, so their rms is known to a few per cent."""
+    uniform: / sqrt(12)) and of activations that are not multiples of their step (a step, uniform, times the weight).  4 bits: a quantization
+    block's step is the smallest 2^e with max |x| <= 30583 * 2^e.  1 and 2 bits: 32 columns have the step 2^-18 times the power of two
+    above their largest.  Both sums have thousands of terms, so their rms is known to a few per cent."""
     M, K = 1024, 4096
     q, s, z, _ = rand_case(820 + bits + group, M, K, 1, bits, group, hz)
     rng = np.random.default_rng(outlier + group)
@@ -74,7 +75,10 @@ def test_outlier_channels(oracle_lib, group, outlier, bits, hz):
     w = ((2.0 * q - 1.0) if z is None else q - z.astype(np.float64).repeat(group, axis=1)) * s.astype(np.float64).repeat(group, axis=1)
     xd = x[0].astype(np.float64)
     Y = w @ xd
-    step = np.exp2(np.ceil(np.log2(np.abs(xd).reshape(-1, group).max(axis=1) / 30583.0))).repeat(group)
+    if bits == 4:
+        step = np.exp2(np.ceil(np.log2(np.abs(xd).reshape(-1, group).max(axis=1) / 30583.0))).repeat(group)
+    else:
+        step = np.exp2(np.ceil(np.log2(np.abs(xd).reshape(-1, 32).max(axis=1))) - 18).repeat(32)
     rounded = np.rint(xd / step) != xd / step
     half = np.exp2(np.maximum(np.floor(np.log2(np.abs(Y) + 1e-30)), -14) - 10)
     expected = np.sqrt(np.mean(((w * w) @ np.where(rounded, step * step, 0.0) + half * half) / 12.0))
@@ -85,7 +89,7 @@ def test_outlier_channels(oracle_lib, group, outlier, bits, hz):
 
 
 def test_largest_activations_stay_finite(oracle_lib):
-    """Four activations of 65504 sum past the largest fp16 number; the integers do not overflow."""
+    """Four activations of 65504 sum past the largest fp16 number; sums of digits do not overflow."""
     M, K, bits, group = 64, 256, 4, 128
     q, s, z, _ = rand_case(77, M, K, 1, bits, group)
     s[:] = np.float16(2.0 ** -12)

@@ -6,8 +6,8 @@
 // codes with 16 rows of activations in one instruction that runs beside the vector pipe; what is left are exchanges between
 // lanes, the transposition and 5 or 6 multiply-adds per 16 rows: 84 instructions per tile for 2 bits, 69 for 1 bit, in the loop.
 // 32 launches of a 7B layer set, uint2 g64: 431 -> 418 us (63.2 MB in 13.1 us = 4.8 TB/s), of a 3.8B one, 1 bit: 264 -> 250 (without
-// the scaling of the blocks: 411 and 248).  What bounds them now is what a launch has to wait for: the memory system (without
-// any computing the 2-bit launch takes 12.2 us) and its start and end (a 1-bit launch without computing: 6.5 of 7.7 us).
+// the scaling of the blocks: 411 and 248).  What bounds them now is the memory system and, for 2 bits, digits and products of waves
+// that start together (a launch with neither: 11.7 of 13.0 us), for 1 bit the start and end of a launch (6.5 of 7.7).
 //
 // Codes.  The numbers 0, 1, 2, 3 in the low bits of an E2M1 number (4 bits) are 0, 0.5, 1, 1.5: codes of 1 and 2 bits in
 // nibbles are operands as they are (times 2).

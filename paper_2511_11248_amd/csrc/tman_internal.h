@@ -138,6 +138,9 @@ enum class TokenSource { kActivations, kTables, kTablesI16 };
 // table launch, lookups (4 bits with integer tables: dot products) -> matrix cores: uint4 g128 N = 4 37.5 -> 29.7, g64 N = 2 / 4 / 8
 // 32 / 37 / 58 -> 28 / 31 / 41, integers 36 / 48 / 81 -> 31 / 35 / 48; uint2 g64 N = 2 / 4 / 8 22.4 / 25.7 / 40 -> 24.1 / 25.8 / 32,
 // integers 30 / 39 / 74 -> 27 / 30 / 38; 1 bit 18.5 / 21.3 / 33 -> 23.6 / 24 / 31, integers 22 / 25 / 46 -> 27 / 28 / 36.
+// 1 bit with 5 to 8 fp16 tokens is the one place where the line costs some widths: layer sets 1024 / 2048 / 4096 8.7 / 11.3 / 27.8 -> 6.7 /
+// 9.8 / 24.2 us, but 2560 / 3072 12.2 / 16.3 -> 13.3 / 17.5 (their workgroups divide badly over the units); it stays for the
+// precision there, 3.6e-4 -> 2.1e-4.
 constexpr bool lookups_stay(int bits, int np, bool integer) {
     return np == 2 ? bits == 1 || (bits == 2 && !integer) : np == 4 && bits == 1;
 }

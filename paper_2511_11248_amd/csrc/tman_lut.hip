@@ -12,8 +12,8 @@
 //   fp32 element  G * NP + n                    at byte offset n_ktiles * 1024 * NP, G < n_ktiles * 128 / group
 // so the slice of one K tile is contiguous and can be copied to LDS as it is.
 //
-// One launch serves up to 8 activations (the distinct inputs of a decode step): the second grid
-// dimension is the activation; a thread builds one table and takes part in the sum of its quantization block.
+// One launch serves up to 8 activations (the distinct inputs of a decode step): the second grid dimension is the activation.
+// One fp16 token: a thread builds one table; several tokens and integer tables: four threads share a table of all tokens.
 #include <hip/hip_fp16.h>
 
 #include "tman_internal.h"
@@ -29,7 +29,7 @@ struct LutJob {
 constexpr int kLutJobsPerLaunch = 8;  // kernel arguments stay small
 struct LutJobs {
     LutJob job[kLutJobsPerLaunch];
-    int count, N, NP, group;
+    int count, N, group;
 };
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
@@ -162,7 +162,6 @@ int launch_build_lut_batch(int count, const void* const* x, int N, const int* K,
         LutJobs a;
         a.count = count - i0 < kLutJobsPerLaunch ? count - i0 : kLutJobsPerLaunch;
         a.N = N;
-        a.NP = NP;
         a.group = group;
         int blocks = 0;  // of the longest activation
         for (int i = 0; i < kLutJobsPerLaunch; ++i) {
@@ -333,7 +332,6 @@ int launch_build_lut_i16_batch(int count, const void* const* x, int N, const int
         LutJobs a;
         a.count = count - i0 < kLutJobsPerLaunch ? count - i0 : kLutJobsPerLaunch;
         a.N = N;
-        a.NP = NP;
         a.group = group;
         int blocks = 0;  // of the longest activation
         for (int i = 0; i < kLutJobsPerLaunch; ++i) {

@@ -2,7 +2,8 @@
 // precision -- here exact integers -- inside a quantization block, floating point only across blocks).  The tables come
 // from tman_build_lut_i16; the kernels take the 14-bit activations out of them and multiply them with the codes: one token as
 // digits on the dot product unit (tman_mpgemv_x.hip), several on the matrix cores (tman_codes_kernel.h), where an activation
-// is two exact fp16 numbers, a multiple of 8 and a rest; sums of products below 2^24 are exact there too.
+// is two exact fp16 numbers, a multiple of 8 and a rest of -4 .. 3.  A block's sums are exact there too: those of the first are multiples
+// of 8 below 2^27 (128 x 79 x 8192 with 4 bits and the codes' offset), those of the rests are below 2^16.
 #include "tman_mpgemv_x_kernel.h"
 
 namespace tman {

@@ -14,8 +14,9 @@
 // out of them: the entries of patterns 1, 2, 4 and 8 are the four activations themselves.  The sums of the four waves
 // meet in LDS, segments of a long K through the workspace (tickets, fixed order of addition).
 //
-// What bounds it: the weight stream.  63.2 MB (7B uint2 g64) in 12.6 us = 5.0 TB/s, 107.5 MB (uint4 g128) in 19.1 us =
-// 5.6 TB/s (20.0 when nothing is computed); reading alone reaches 6.0-6.15 TB/s, and about 1 us at the start (descriptor, first activations)
+// What bounds it: the weight stream.  63.2 MB (7B uint2 g64) in 13.0 us = 4.9 TB/s (11.7 with neither digits nor products), 107.5 MB
+// (uint4 g128) in 19.2 us = 5.6 TB/s (20.0 without: the waves then have their requests out sooner, which costs the memory system more
+// than the computing does); reading alone reaches 6.0-6.15 TB/s, and about 1 us at the start (descriptor, first activations)
 // and 1.5 us at the end (exchange between segments) are not covered.  What helped beside the digits, measured in
 // turn on the uint2 / uint4 launch: the waves of a workgroup take its tiles in turn instead of a quarter each, so that
 // a workgroup reads one contiguous stream (uint4 20.6 -> 20.1 us); ONE tile in flight per wave instead of two or three

@@ -143,7 +143,7 @@ __global__ void __launch_bounds__(kWaves * 64, 4) mpgemv_x_kernel(Fields... fiel
     // A 1-bit tile is 1.3 to 2 KB and 70 vector instructions, so a wave waits longer than it computes: on the dot product unit, with the request
     // at the end of a tile (where the last use of a zero kept it) 16 launches of a layer set of width 1024 took 131 us,
     // else 92; width 3072 145 -> 130, 4096 184 -> 170 (zeros, blocks of 64); on the matrix cores 3.8B layer sets 277 -> 247.  2 and 4
-    // bits: more streams in flight cost more than they hide (uint2 g64 404 -> 409; see tman_mpgemv_x.hip).
+    // bits: more streams in flight cost more than they hide (uint2 g64 +1 %; see tman_mpgemv_x.hip).
     constexpr int kStages = B == 1 ? 2 : 1;
     Stage<B, 1, Cfg::MPL> st[kStages] = {};
     auto issue = [&](auto& s, bool live, int t) { issue_weights<B, 1, GQ, HZ>(s, src, live, t, lane); };

@@ -236,28 +236,30 @@ __device__ __forceinline__ int step_exponent(unsigned mx) {
     return E - 13;
 }
 
-// As for fp16 entries: four threads per table, thread q makes entries 4 q .. 4 q + 3 of all NP tokens.  Blocks grow with
-// the tokens (at least 128 threads search a token), because every block searches all of them.  With
-// a block per token, whose threads stored two bytes at a time, the launch for four activations of a 7B layer took 5.1 / 5.5 /
-// 6.4 / 10.1 us for NP = 1 / 2 / 4 / 8 (now 3.3, 3.8, 4.7, 8.0; reading a token's activations one request
-// after the other was two thirds of the first).
-constexpr int i16_threads(int np) { return np <= 2 ? 256 : 128 * np; }
+// As for fp16 entries: four threads per table, thread q makes entries 4 q .. 4 q + 3 of the block's tokens, all or half of 8.  At
+// least 128 threads search a token, because every block searches all of its tokens, six requests at a time.  The launch for four
+// activations of a 7B layer takes 3.5 / 4.0 / 5.0 / 5.5 us for NP = 1 / 2 / 4 / 8, for one activation of 4096 3.5 / 3.6 / 4.4 / 4.6 (a
+// block per token, whose threads stored two bytes at a time: 5.3 / 5.7 / 6.5 / 10.7 and 4.5 / 4.8 / 5.1 / 5.1; all 8 tokens in a block
+// of 1024 threads: 8.2 and 7.0).
+constexpr int i16_tokens(int np) { return np < 4 ? np : 4; }  // per block
+constexpr int i16_threads(int np) { return np <= 2 ? 256 : 512; }
 template <int NP>
 __global__ void __launch_bounds__(i16_threads(NP)) build_lut_i16_kernel(LutJobs a) {
-    constexpr int kThreads = i16_threads(NP), kTables = kThreads / 4;
-    __shared__ unsigned largest[NP][4];
-    __shared__ int sums[kTables][NP];
+    constexpr int kThreads = i16_threads(NP), kTables = kThreads / 4, TB = i16_tokens(NP);
+    __shared__ unsigned largest[TB][4];
+    __shared__ int sums[kTables][TB];
     const LutJob& jb = a.job[blockIdx.y];
-    const int N = a.N, K = jb.K, tid = threadIdx.x;
+    const int n0 = (int)blockIdx.z * TB;  // the block's first token
+    const int N = a.N - n0, K = jb.K, tid = threadIdx.x;
     const int j = (int)blockIdx.x * kTables + (tid >> 2), q = tid & 3;  // n_tables is a multiple of 32
     if ((int)blockIdx.x * kTables >= jb.n_tables) return;
     const bool live = j < jb.n_tables, inside = live && 4 * j < K;  // K is a multiple of 32
-    const uint16_t* const x = reinterpret_cast<const uint16_t*>(jb.x);
+    const uint16_t* const x = reinterpret_cast<const uint16_t*>(jb.x) + (size_t)n0 * K;
     const bool wide = (reinterpret_cast<uintptr_t>(x) & 7u) == 0;  // (a row is K * 2 bytes, a multiple of 64)
     typedef uint16_t u16x4_t __attribute__((ext_vector_type(4)));
-    u16x4_t own[NP];  // requested before the search
+    u16x4_t own[TB];  // requested before the search
 #pragma unroll
-    for (int n = 0; n < NP; ++n) {
+    for (int n = 0; n < TB; ++n) {
         own[n] = u16x4_t{0, 0, 0, 0};
         if (inside && n < N) {
             const uint16_t* src = x + (size_t)n * K + 4 * j;
@@ -269,7 +271,7 @@ __global__ void __launch_bounds__(i16_threads(NP)) build_lut_i16_kernel(LutJobs 
             }
         }
     }
-    constexpr int T = kThreads / NP;        // threads per token
+    constexpr int T = kThreads / TB;        // threads per token
     constexpr int W = T / 64;               // waves per token
     {
         const int n = tid / T, t = tid % T;
@@ -279,14 +281,14 @@ __global__ void __launch_bounds__(i16_threads(NP)) build_lut_i16_kernel(LutJobs 
     __syncthreads();
     int* const S = reinterpret_cast<int*>(jb.S);
     int* const ex = S + (size_t)(jb.n_tables / kTablesPerKTile) * (kKTile / a.group) * NP;
-    int16_t e[4][NP];
+    int16_t e[4][TB];
 #pragma unroll
-    for (int n = 0; n < NP; ++n) {
+    for (int n = 0; n < TB; ++n) {
         unsigned mx = largest[n][0];
 #pragma unroll
         for (int w = 1; w < W; ++w) mx = max(mx, largest[n][w]);
         const int exponent = step_exponent(mx);
-        if (blockIdx.x == 0 && tid == 0) ex[n] = exponent;
+        if (blockIdx.x == 0 && tid == 0) ex[n0 + n] = exponent;
         int v[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -299,8 +301,12 @@ __global__ void __launch_bounds__(i16_threads(NP)) build_lut_i16_kernel(LutJobs 
         if (q == 0) sums[tid >> 2][n] = (v[0] + v[1]) + (v[2] + v[3]);
     }
     if (live) {
-        int16_t* const dst = reinterpret_cast<int16_t*>(jb.T) + ((size_t)j * 16 + 4 * q) * NP;
-        if constexpr (NP == 1) {
+        int16_t* const dst = reinterpret_cast<int16_t*>(jb.T) + ((size_t)j * 16 + 4 * q) * NP + n0;
+        if constexpr (NP == 8) {  // half of each entry row
+            typedef int16_t i16x4_t __attribute__((ext_vector_type(4)));
+#pragma unroll
+            for (int p = 0; p < 4; ++p) *reinterpret_cast<i16x4_t*>(dst + p * NP) = i16x4_t{e[p][0], e[p][1], e[p][2], e[p][3]};
+        } else if constexpr (NP == 1) {
             typedef int16_t i16x4_t __attribute__((ext_vector_type(4)));
             *reinterpret_cast<i16x4_t*>(dst) = i16x4_t{e[0][0], e[1][0], e[2][0], e[3][0]};
         } else {
@@ -317,11 +323,12 @@ __global__ void __launch_bounds__(i16_threads(NP)) build_lut_i16_kernel(LutJobs 
     }
     __syncthreads();
     const int tables_per_group = a.group / kLutGroup, groups = kTables / tables_per_group;
-    const int gi = tid / NP, n = tid % NP, j0 = (int)blockIdx.x * kTables + gi * tables_per_group;
+    const int gi = tid / TB, n = tid % TB, j0 = (int)blockIdx.x * kTables + gi * tables_per_group;
     if (gi < groups && j0 < jb.n_tables) {
         int s = 0;
-        for (int i = 0; i < tables_per_group; ++i) s += sums[gi * tables_per_group + i][n];
-        S[(size_t)(j0 / tables_per_group) * NP + n] = s;
+#pragma unroll 8
+        for (int i = 0; i < tables_per_group; ++i) s += sums[gi * tables_per_group + i][n];  // (8, 16 or 32)
+        S[(size_t)(j0 / tables_per_group) * NP + n0 + n] = s;
     }
 }
 
@@ -346,7 +353,7 @@ int launch_build_lut_i16_batch(int count, const void* const* x, int N, const int
             const int per = i16_threads(NP) / 4, b = (jb.n_tables + per - 1) / per;
             if (i < a.count && b > blocks) blocks = b;
         }
-        const dim3 grid((unsigned)blocks, (unsigned)a.count);
+        const dim3 grid((unsigned)blocks, (unsigned)a.count, (unsigned)(NP / i16_tokens(NP)));
         if (NP == 1) hipLaunchKernelGGL(build_lut_i16_kernel<1>, grid, dim3(256), 0, st, a);
         else if (NP == 2) hipLaunchKernelGGL(build_lut_i16_kernel<2>, grid, dim3(256), 0, st, a);
         else if (NP == 4) hipLaunchKernelGGL(build_lut_i16_kernel<4>, grid, dim3(i16_threads(4)), 0, st, a);

@@ -5,8 +5,8 @@
 // the codes, and a 2-bit tile 123 vector instructions (1 bit: 110).  v_mfma_f32_16x16x128_f8f6f4 multiplies 16 rows x 128 columns of
 // codes with 16 rows of activations in one instruction that runs beside the vector pipe; what is left are exchanges between
 // lanes, the transposition and 5 or 6 multiply-adds per 16 rows: 84 instructions per tile for 2 bits, 69 for 1 bit, in the loop.
-// 32 launches of a 7B layer set, uint2 g64: 431 -> 418 us (63.2 MB in 13.1 us = 4.8 TB/s), of a 3.8B one, 1 bit: 264 -> 250 (without
-// the scaling of the blocks: 411 and 248).  What bounds them now is the memory system and, for 2 bits, digits and products of waves
+// 32 launches of a 7B layer set, uint2 g64: 430 -> 416 us (63.2 MB in 13.0 us = 4.9 TB/s), of a 3.8B one, 1 bit: 265 -> 249 (without
+// the scaling of the blocks: 413 and 248).  What bounds them now is the memory system and, for 2 bits, digits and products of waves
 // that start together (a launch with neither: 11.7 of 13.0 us), for 1 bit the start and end of a launch (6.5 of 7.7).
 //
 // Codes.  The numbers 0, 1, 2, 3 in the low bits of an E2M1 number (4 bits) are 0, 0.5, 1, 1.5: codes of 1 and 2 bits in
@@ -57,69 +57,82 @@ __device__ __forceinline__ void group_transpose(uint32_t (&w)[4]) {
     }
 }
 
-// A quad of lanes holds one 32-column block: lane f of it has activations 4f .. 4f + 3 (xa) and 16 + 4f .. (xb).  Its digits go to
-// `ld` + 32 * digit + 8 * (lane % 4) (the block's first row in LDS), its sum and step to `ls`.  Returns whether an activation is
-// not finite (those count as zero here, see add_nonfinite).  All lanes take part; with `live` false nothing is stored.
-template <bool HZ>
-__device__ __forceinline__ bool store_fp8_digits(const u32x2& xa, const u32x2& xb, int lane, bool live, uint32_t ld, uint32_t ls) {
-    uint32_t h[4] = {xa.x, xa.y, xb.x, xb.y};
+// P blocks per quad of lanes: lane f of it holds, of block i, activations 4f .. 4f + 3 (h[i][0], h[i][1]) and 16 + 4f .. .  Digits
+// go to `ld[i]` + 32 * digit (the lane's 8 bytes of the block's rows in LDS), sum and step of the block to `ls[i]`.  Returns whether an
+// activation is not finite (those count as zero here, see add_nonfinite).  All lanes take part, and all store: the addresses of
+// those whose numbers nobody reads point to where nothing is kept yet.
+// (Several blocks at once, in one basic block: what a block's digits have to wait for, its largest magnitude and the scale, is a
+// chain of 20 instructions.  One block after the other, stores under a branch: 420 and 250 us.)
+template <bool HZ, int P>
+__device__ __forceinline__ bool store_fp8_digits(uint32_t (&h)[P][4], int lane, const uint32_t (&ld)[P], const uint32_t (&ls)[P]) {
     typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-    auto largest = [&] {  // of the block; magnitudes compare like their bit patterns
-        auto magnitudes = [&](int k) { return __builtin_bit_cast(u16x2, h[k] & 0x7fff7fffu); };
-        const u16x2 m = __builtin_elementwise_max(__builtin_elementwise_max(magnitudes(0), magnitudes(1)), __builtin_elementwise_max(magnitudes(2), magnitudes(3)));
-        return max_over_lanes<4>(max((uint32_t)m.x, (uint32_t)m.y));
+    uint32_t mx[P];
+    auto largest = [&] {  // of the blocks; magnitudes compare like their bit patterns
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            auto magnitudes = [&](int k) { return __builtin_bit_cast(u16x2, h[i][k] & 0x7fff7fffu); };
+            const u16x2 m = __builtin_elementwise_max(__builtin_elementwise_max(magnitudes(0), magnitudes(1)), __builtin_elementwise_max(magnitudes(2), magnitudes(3)));
+            mx[i] = max_over_lanes<4>(max((uint32_t)m.x, (uint32_t)m.y));
+        }
     };
-    uint32_t mx = largest();
-    const bool nonfinite = mx >= 0x7c00u;
+    largest();
+    bool nonfinite = false;
+#pragma unroll
+    for (int i = 0; i < P; ++i) nonfinite |= mx[i] >= 0x7c00u;
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(nonfinite) != 0, 0)) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if ((h[k] & 0x7c00u) == 0x7c00u) h[k] &= 0xffff0000u;
-            if ((h[k] & 0x7c000000u) == 0x7c000000u) h[k] &= 0xffffu;
-        }
-        mx = largest();
-    }
-    float sum = 0.f;
-    const float one = opaque(1.f);  // (one mixed-precision instruction per activation)
+        for (int i = 0; i < P; ++i)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const half2_t v = __builtin_bit_cast(half2_t, h[k]);
-        sum = fmaf((float)v.x, one, sum);
-        sum = fmaf((float)v.y, one, sum);
+            for (int k = 0; k < 4; ++k) {
+                if ((h[i][k] & 0x7c00u) == 0x7c00u) h[i][k] &= 0xffff0000u;
+                if ((h[i][k] & 0x7c000000u) == 0x7c000000u) h[i][k] &= 0xffffu;
+            }
+        largest();
     }
-    sum += __builtin_bit_cast(float, dpp_u32<0xB1>(__builtin_bit_cast(uint32_t, sum)));
-    sum += __builtin_bit_cast(float, dpp_u32<0x4E>(__builtin_bit_cast(uint32_t, sum)));
-    // Exponent field e: magnitudes below 2^(e - 14), in steps of 2^(e - 8) below 2^-6.  (1 / step is a subnormal fp16 number from e = 23 on.)
-    const uint32_t e = max(mx >> 10, 1u);
-    const half2_t scale = __builtin_bit_cast(half2_t, (e < 23 ? (23u - e) << 10 : 0x200u >> (e - 23u)) * 0x10001u);
-    const float step = __builtin_bit_cast(float, (119u + e) << 23);
-    // Lane o of the quad takes numbers 4f + o: halves of words are exchanged with the lane that differs in bit 0, words with the one
-    // that differs in bit 1; x[p] = numbers 8p + o and 8p + 4 + o.
-    half2_t x[4];
     const uint32_t halves = lane & 1 ? 0x03020706u : 0x05040100u;
     const bool up = lane & 2;
+    const float one = opaque(1.f);  // (one mixed-precision instruction per activation)
 #pragma unroll
-    for (int p = 0; p < 4; p += 2) {
-        const uint32_t w0 = __builtin_amdgcn_perm(dpp_u32<0xB1>(h[p]), h[p], halves), w1 = __builtin_amdgcn_perm(dpp_u32<0xB1>(h[p + 1]), h[p + 1], halves);
-        const uint32_t got = dpp_u32<0x4E>(up ? w0 : w1);
-        x[p] = __builtin_bit_cast(half2_t, up ? got : w0) * scale;
-        x[p + 1] = __builtin_bit_cast(half2_t, up ? w1 : got) * scale;
-    }
+    for (int i = 0; i < P; ++i) {
+        // Exponent field e: magnitudes below 2^(e - 14), in steps of 2^(e - 8) below 2^-6.  (1 / step is a subnormal fp16 number from
+        // e = 23 on.)
+        const uint32_t step_bits = (max(mx[i] & 0x7c00u, 0x400u) << 13) + (119u << 23), inv_bits = (254u << 23) - step_bits;
+        const float inv = __builtin_bit_cast(float, inv_bits);
+        const _Float16 scale = (_Float16)inv;
+        const half2_t scales = {scale, scale};
+        float sum = 0.f;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        uint32_t w[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) w[q] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, x[2 * q + 1]), __builtin_bit_cast(uint32_t, x[2 * q]), 0x07050301u);
-        if (live) store_lds<u32x2>(ld + v * 32 + (lane & 3) * 8, u32x2{w[0], w[1]});
-        if (v < 3) {
-            const _Float16 by = v == 0 ? (_Float16)4.f : (_Float16)8.f;
-#pragma unroll
-            for (int p = 0; p < 4; ++p) x[p] = (x[p] - __builtin_bit_cast(half2_t, __builtin_bit_cast(uint32_t, x[p]) & 0xff00ff00u)) * by;
+        for (int k = 0; k < 4; ++k) {
+            const half2_t v = __builtin_bit_cast(half2_t, h[i][k]);
+            sum = fmaf((float)v.x, one, sum);
+            sum = fmaf((float)v.y, one, sum);
         }
-    }
-    if (live && (lane & 3) == 0) {
-        const float s = HZ ? sum * __builtin_bit_cast(float, (134u - e) << 23) : sum * 0.25f;  // half the sum in steps, a quarter of the sum
-        store_lds<u32x2>(ls, u32x2{__builtin_bit_cast(uint32_t, s), __builtin_bit_cast(uint32_t, step)});
+        sum += __builtin_bit_cast(float, dpp_u32<0xB1>(__builtin_bit_cast(uint32_t, sum)));
+        sum += __builtin_bit_cast(float, dpp_u32<0x4E>(__builtin_bit_cast(uint32_t, sum)));
+        const float s = HZ ? sum * (inv * 0.5f) : sum * 0.25f;  // half the sum in steps, a quarter of the sum
+        store_lds<u32x2>(ls[i], u32x2{__builtin_bit_cast(uint32_t, s), step_bits});
+        // Lane o of the quad takes numbers 4f + o: halves of words are exchanged with the lane that differs in bit 0, words with the one
+        // that differs in bit 1; x[p] = numbers 8p + o and 8p + 4 + o.
+        half2_t x[4];
+#pragma unroll
+        for (int p = 0; p < 4; p += 2) {
+            const uint32_t w0 = __builtin_amdgcn_perm(dpp_u32<0xB1>(h[i][p]), h[i][p], halves), w1 = __builtin_amdgcn_perm(dpp_u32<0xB1>(h[i][p + 1]), h[i][p + 1], halves);
+            const uint32_t got = dpp_u32<0x4E>(up ? w0 : w1);
+            x[p] = __builtin_bit_cast(half2_t, up ? got : w0) * scales;
+            x[p + 1] = __builtin_bit_cast(half2_t, up ? w1 : got) * scales;
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            uint32_t w[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) w[q] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, x[2 * q + 1]), __builtin_bit_cast(uint32_t, x[2 * q]), 0x07050301u);
+            store_lds<u32x2>(ld[i] + v * 32, u32x2{w[0], w[1]});
+            if (v < 3) {
+                const _Float16 by = v == 0 ? (_Float16)4.f : (_Float16)8.f;
+#pragma unroll
+                for (int p = 0; p < 4; ++p) x[p] = (x[p] - __builtin_bit_cast(half2_t, __builtin_bit_cast(uint32_t, x[p]) & 0xff00ff00u)) * by;
+            }
+        }
     }
     return nonfinite;
 }

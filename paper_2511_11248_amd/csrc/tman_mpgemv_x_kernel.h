@@ -153,23 +153,39 @@ __global__ void __launch_bounds__(kWaves * 64, 4) mpgemv_x_kernel(Fields... fiel
     // digits of the segment: lane -> four lanes per 32-column block, sixteen per tile
     const int n_lanes = (k1 - k0) * (kKTile / 8);
     bool nonfinite = false;
+    if constexpr (kMatrix) {
+        auto passes = [&](auto count) {
+            constexpr int P = decltype(count)::value;
+            uint32_t h[P][4], to[P], ts[P];
 #pragma unroll
-    for (int i = 0; i < kPasses; ++i) {
-        if (i * kWaves * 64 + wave * 64 >= n_lanes) break;  // (this wave has none)
-        const int j = i * kWaves * 64 + tid, tile = j >> 4;
-        const bool live = j < n_lanes;
-        if constexpr (kMatrix) {
-            nonfinite |= store_fp8_digits<HZ>(xv[i].a, xv[i].b, lane, live, ld + (uint32_t)((j >> 2) * 128), lm + (uint32_t)((j >> 2) * 8)) && live;
-            continue;
+            for (int i = 0; i < P; ++i) {
+                const int j = i * kWaves * 64 + tid;
+                const bool live = j < n_lanes;
+                h[i][0] = live ? xv[i].a.x : 0u, h[i][1] = live ? xv[i].a.y : 0u, h[i][2] = live ? xv[i].b.x : 0u, h[i][3] = live ? xv[i].b.y : 0u;
+                // (the partial sums' place is free until all digits are there)
+                to[i] = live ? ld + (uint32_t)((j >> 2) * 128 + (j & 3) * 8) : lr;
+                ts[i] = live && (j & 3) == 0 ? lm + (uint32_t)((j >> 2) * 8) : lr + 128;
+            }
+            nonfinite = store_fp8_digits<HZ, P>(h, lane, to, ts);
+        };
+        static_assert(kPasses == 2, "one or two passes");
+        if (kWaves * 64 + wave * 64 < n_lanes) passes(std::integral_constant<int, 2>{});
+        else if (wave * 64 < n_lanes) passes(std::integral_constant<int, 1>{});
+    } else {
+#pragma unroll
+        for (int i = 0; i < kPasses; ++i) {
+            if (i * kWaves * 64 + wave * 64 >= n_lanes) break;  // (this wave has none)
+            const int j = i * kWaves * 64 + tid, tile = j >> 4;
+            const bool live = j < n_lanes;
+            uint32_t r[4];
+            float step = 1.f;
+            if constexpr (SRC == TokenSource::kTablesI16)
+                bias_block(xv[i].a, xv[i].b, r);
+            else
+                nonfinite |= quantize_block<GQ>(xv[i].a, xv[i].b, r, step) && live;
+            store_digits<GQ>(r, step, j, live, ld + (uint32_t)(tile * kDigitBytesPerKTile + (j & 15) * 16),
+                             lm + (uint32_t)((tile * Cfg::GPT + (j & 15) / (GQ / 8)) * kDigitMetaBytes));
         }
-        uint32_t r[4];
-        float step = 1.f;
-        if constexpr (SRC == TokenSource::kTablesI16)
-            bias_block(xv[i].a, xv[i].b, r);
-        else
-            nonfinite |= quantize_block<GQ>(xv[i].a, xv[i].b, r, step) && live;
-        store_digits<GQ>(r, step, j, live, ld + (uint32_t)(tile * kDigitBytesPerKTile + (j & 15) * 16),
-                         lm + (uint32_t)((tile * Cfg::GPT + (j & 15) / (GQ / 8)) * kDigitMetaBytes));
     }
     if constexpr (kMatrix)
         if (tid == 0) store_lds<u32x4>(zeros, u32x4{0, 0, 0, 0});

@@ -111,8 +111,8 @@ def main():
           "decode_x_whole_bytes", [40960, 81920, 163840], lambda: time_decode("7b_w4g128", 1))
     sweep("one-token decode, 3.8B layer set uint2 g64 (K = 3072 and 8192)",
           "decode_x_long_seg_tiles", [15, 17, 20, 22, 24, 32], lambda: time_decode("3p8b_w2g64", 1))
-    sweep("8 tokens from tables, 7B layer set uint4 g128: segments beyond small_seg_tiles' 43",
-          "decode_seg_tiles_many", [24, 48, 64, 86], lambda: time_decode("7b_w4g128", 8))
+    sweep("8 tokens from tables, 7B layer set uint4 g128 (24, the built-in value, stands for small_seg_tiles' 43 here)",
+          "decode_seg_tiles_many", [16, 20, 24, 32, 48, 86], lambda: time_decode("7b_w4g128", 8))
     sweep("8 tokens through the small-batch matrix-core kernel, 7B layer set uint4 g128",
           "small_seg_tiles", [16, 22, 24, 32, 43, 86], lambda: time_decode("7b_w4g128", 8, matrix_cores=True))
     for N in (256, 1024, 2048):

@@ -74,7 +74,8 @@ GemvPlan plan_tables(const Layout& L, int N) {
 
 // Several tokens on the matrix cores: the kernel of small batches.  Its segments are longer (small_seg_tiles) where the launch fills the chip
 // without short ones: 7B uint4 g128, N = 4, us per layer set with the table launch, segments of 24 / 32 / 43 tiles 37.5 / 33.6 /
-// 29.7; a K of 44 to 50 tiles, which 43 cuts in two, is better off so (layer sets 2048 / 5632 and 2048 / 6400: one segment +15 to 45 %).  A launch that
+// 29.7; a K of 44 to 50 tiles, which 43 cuts in two, is better off so on the whole (one segment,
+// layer sets 2048 / 5632 and 2048 / 6400: +14 to 45 %; 3072 / 6144: -14 to +30 %).  A launch that
 // leaves compute units idle (`fills` false: a single GEMV with few rows) keeps the lookups' short segments: 4096 x 11008, N = 4,
 // 22 / 43 tiles 11.8 / 14.7 us, 4096 x 4096 16 / 32 tiles 8.9 / 10.0; 11008 x 4096, which fills it, 11.9 / 10.5.  A caller's own
 // decode_seg_tiles (_many) decides alone.  A table batch is prepared for both kinds of tables; where only one of them is looked up (2

@@ -13,16 +13,18 @@ typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// (a & mask) | (b & ~mask) and (a & mask) | k as single instructions; the masks live in scalar registers
+// (a & mask) | (b & ~mask) and (a & mask) | k as single instructions.  v_bitop3_b32 with all operands in vector registers is one
+// of the instructions that two waves of a SIMD issue side by side: 1.07-1.12 ns an instruction from two waves on; 1.85-1.95 for
+// v_bfi_b32, for v_and_or_b32 and for itself with a mask in a scalar register.
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t constant) {
+    asm("" : "+v"(constant));
+    return constant;
+}
 __device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) {
-    uint32_t d;
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(d) : "s"(mask), "v"(a), "v"(b));
-    return d;
+    return __builtin_amdgcn_bitop3_b32(in_vgpr(mask), a, b, 0xCA);
 }
 __device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t k) {
-    uint32_t d;
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "s"(mask), "v"(k));
-    return d;
+    return __builtin_amdgcn_bitop3_b32(a, in_vgpr(mask), in_vgpr(k), 0xEA);
 }
 
 // Level 1: bit planes of 32 weights -> four words of eight 4-bit fields; word o, field f = weight 4f + o.
@@ -32,16 +34,16 @@ __device__ __forceinline__ void planes_to_codes(const uint32_t (&p)[B], uint32_t
     if constexpr (B == 4) {
         // pair planes (0,1) and (2,3) into 2-bit fields of even / odd weights, then pair those into nibbles
         const uint32_t a = bfi(0x55555555u, p[0], p[1] << 1);  // field e: low two code bits of weight 2e
-        const uint32_t b = bfi(0xAAAAAAAAu, p[1], p[0] >> 1);  // same for weight 2e + 1
+        const uint32_t b = bfi(0x55555555u, p[0] >> 1, p[1]);  // same for weight 2e + 1
         const uint32_t c = bfi(0x55555555u, p[2], p[3] << 1);  // high two code bits of weight 2e
-        const uint32_t d = bfi(0xAAAAAAAAu, p[3], p[2] >> 1);
+        const uint32_t d = bfi(0x55555555u, p[2] >> 1, p[3]);
         out[0] = bfi(0x33333333u, a, c << 2);  // weights 4f
-        out[2] = bfi(0xCCCCCCCCu, c, a >> 2);  // weights 4f + 2
+        out[2] = bfi(0x33333333u, a >> 2, c);  // weights 4f + 2
         out[1] = bfi(0x33333333u, b, d << 2);  // weights 4f + 1
-        out[3] = bfi(0xCCCCCCCCu, d, b >> 2);  // weights 4f + 3
+        out[3] = bfi(0x33333333u, b >> 2, d);  // weights 4f + 3
     } else if constexpr (B == 2) {
         const uint32_t a = bfi(0x55555555u, p[0], p[1] << 1);
-        const uint32_t b = bfi(0xAAAAAAAAu, p[1], p[0] >> 1);
+        const uint32_t b = bfi(0x55555555u, p[0] >> 1, p[1]);
         out[0] = a;
         out[2] = a >> 2;
         out[1] = b;
@@ -65,11 +67,10 @@ struct WRegs {
 // Field f of code word o (weight 4f + o) is turned into an fp16 number without moving it to bit 0:
 // a nibble at mantissa bits 0..3 of 0x6400 reads 1024 + c, one at bits 4..7 reads 1024 + 16c.  Fields
 // f and f + 4 sit 16 bits apart, so one AND-OR makes two such numbers; a single shift by 8 brings
-// fields 2, 3, 6, 7 into reach.  The affine map (c - zero) * scale is then one fp32 FMA per weight, rounded to
-// fp16 once:  (1024 + c) * s - (1024 + z) * s   or   (1024 + 16c) * s/16 - (64 + z) * s   (the second, constant
-// term is itself rounded to fp32 when the block's constants are prepared).
-// The FMA writes either half of its destination, which puts weights 4f + o and 4f + o + 1 (from the
-// same field of two code words) side by side at no cost.
+// fields 2, 3, 6, 7 into reach.  The affine map (c - zero) * scale is then one fp32 FMA per weight:
+// (1024 + c) * s - (1024 + z) * s   or   (1024 + 16c) * s/16 - (64 + z) * s   (the second, constant
+// term is itself rounded to fp32 when the block's constants are prepared), and the conversion of two of them to fp16 puts weights
+// 4f + o and 4f + o + 1 (from the same field of two code words) side by side.
 template <int B, bool HZ>
 struct Dequant {
     uint32_t codes[4];
@@ -114,9 +115,14 @@ struct Dequant {
             const int f = 2 * q + (i >> 1), o = (i & 1) * 2, d = f & 3, t = d & 1;
             const _Float16 va = (f >> 2) ? P[o][d].y : P[o][d].x;
             const _Float16 vb = (f >> 2) ? P[o + 1][d].y : P[o + 1][d].x;
+            // two v_fma_mix_f32 and one v_cvt_pk_f16_f32 (5.6 ns): v_fma_mixlo_f16 and _mixhi_f16, which would round
+            // themselves, issue at half rate (7.0 ns)
+            float a = fmaf((float)va, mul[t], bias[t]), b = fmaf((float)vb, mul[t], bias[t]);
+            asm("" : "+v"(a));
+            asm("" : "+v"(b));
             half2_t w;
-            w.x = (_Float16)fmaf((float)va, mul[t], bias[t]);
-            w.y = (_Float16)fmaf((float)vb, mul[t], bias[t]);
+            w.x = (_Float16)a;
+            w.y = (_Float16)b;
             out[i] = __builtin_bit_cast(uint32_t, w);
         }
         return out;

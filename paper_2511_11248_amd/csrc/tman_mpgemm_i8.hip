@@ -399,22 +399,21 @@ __global__ void __launch_bounds__(256) mpgemm_i8_kernel(GemmI8Args a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Wide variant for long token ranges: no weight tile in LDS.  A wave owns 64 rows x 32 TT tokens; it turns the bit
-// planes of its rows into bytes in registers (lane = row) and makes the two MFMA operands of a 32-column step with
-// four v_permlane32_swap (rows 0..31 and rows 32..63, each with the lane halves holding bytes 0..15 and 16..31 of
-// the step).  Only the activations go through LDS, straight from memory, shared by the four waves (256 rows) of
-// the workgroup.  Per MFMA this reads half the LDS bytes of the 128 x 128 kernel and dequantizes each weight once
-// per 32 TT tokens instead of once per 128.
-constexpr int kI8WRing = 4;   // stage buffers of activations in LDS
-constexpr int kI8WSets = 4;   // register sets of bit planes = stages of weight loads in flight
+// Wide variant for long token ranges: no weight tile in LDS.  A wave owns 64 rows x 32 TT tokens.  Lane (r, h) of a row unit
+// (32 rows) takes the 32-column blocks 2 h and 2 h + 1 of row r of a 128-column tile, which it loads and turns into bytes
+// alone: a product sums over 16 columns of a block of the first and of one of the second half of the tile, and the
+// activations are read to match, so no lane exchanges anything.  Only the activations go through LDS, straight from memory,
+// shared by the four waves (256 rows) of the workgroup, a tile (128 bytes of a token, a whole cache line) at a time.  Per MFMA
+// this reads half the LDS bytes of the 128 x 128 kernel and dequantizes each weight once per 32 TT tokens instead of once per 128.
+constexpr int kI8WRing = 4;   // tile buffers of activations in LDS
 constexpr int kI8WStageK = 32;
 constexpr int kI8WRows = 256;
 
 template <int TT>
 struct I8Wide {
     static constexpr int TN = TT * 32;
-    static constexpr int XLoads = (TT + 3) / 4;        // activation loads of a stage per wave (32 token rows each)
-    static constexpr int XBytes = XLoads * 4 * 1024;   // stage buffer: whole loads of all four waves
+    static constexpr int XBytes = TN * kKTile;         // activations of a tile
+    static constexpr int XLoads = TT;                  // requests of a tile per wave (8 token rows each)
     static constexpr int OutRow = kI8WRows * 2 + 16;   // bytes per token of the fp16 output tile in LDS
     static constexpr int LdsBytes = kI8WRing * XBytes > TN * OutRow ? kI8WRing * XBytes : TN * OutRow;
 };
@@ -423,7 +422,7 @@ template <int B, bool HZ, int TT>
 __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(GemmI8Args a, int group) {
     using T = I8Wide<TT>;
     constexpr int MSZ = HZ ? 4 : 2;
-    constexpr int CH = kKTile / B;
+    constexpr int kSets = 2;  // register sets of bit planes = tiles of weights in flight
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     __shared__ float row_scale[kI8WRows], row_zs[kI8WRows];
 
@@ -432,135 +431,147 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int mt = blockIdx.x / a.n_tiles, nt = blockIdx.x % a.n_tiles;
     const bool header_ok = header_matches(a.tiles, a.M, a.K, B, group, HZ ? 1 : 0);
-    if (!header_ok && blockIdx.x == 0 && tid == 0) report_header_mismatch(a.status);
+    if (!header_ok && blockIdx.x == 0 && threadIdx.x == 0) report_header_mismatch(a.status);
     if (mt >= (header_ok ? a.m_tiles : 0)) return;
     const int n0 = nt * T::TN;
-    const int k_stages = a.K / kI8WStageK, n_stages = (k_stages + kI8WSets - 1) & ~(kI8WSets - 1);
     const int r = lane & 31, h = lane >> 5;
 
     i32x16 acc[2][TT];
 #pragma unroll
-    for (int hb = 0; hb < 2; ++hb)
+    for (int ru = 0; ru < 2; ++ru)
 #pragma unroll
         for (int nb = 0; nb < TT; ++nb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[hb][nb][v] = 0;
+            for (int v = 0; v < 16; ++v) acc[ru][nb][v] = 0;
 
-    // bit planes of this wave's row block, one 32-weight block per stage
+    // bit planes of this wave's row block: of each row unit the lane's two blocks of a tile; a tile past K reads as zero
     const int wrb = mt * 4 + wave;
     const bool wvalid = wrb < a.n_row_blocks;
     const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? wrb : 0) * a.n_ktiles * TB;
     const uint32_t wbytes = wvalid ? (uint32_t)(a.n_ktiles * TB) : 0u;
-    uint32_t plane[kI8WSets][B];
-    auto load_planes = [&](uint32_t (&pl)[B], int t) {
-        const rsrc_t rw = rsrc_of(wsrc, t < k_stages ? wbytes : 0u);
-        const int tile = t >> 2, kb32 = t & 3;
-        const int v = (kb32 * 32) / CH, ksub = ((kb32 * 32) % CH) / 32;
-        const int so = tile * TB + v * 1024 + ksub * B * 4;
-        if constexpr (B == 4) {
-            const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16, so, 0);
-            pl[0] = w.x; pl[1] = w.y; pl[2] = w.z; pl[3] = w.w;
-        } else if constexpr (B == 2) {
-            const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rw, lane * 16, so, 0);
-            pl[0] = w.x; pl[1] = w.y;
-        } else {
-            pl[0] = __builtin_amdgcn_raw_buffer_load_b32(rw, lane * 16, so, 0);
+    uint32_t plane[kSets][2][2][B];  // [set][row unit][block][plane]
+    const int woff = r * 16 + (B == 1 ? h * 8 : h * (B / 2) * 1024);
+    constexpr int kPlaneLoads = 2 * (B == 4 ? 2 : 1);
+    auto load_planes = [&](uint32_t (&pl)[2][2][B], int t) {
+        const rsrc_t rw = rsrc_of(wsrc, t < a.n_ktiles ? wbytes : 0u);
+#pragma unroll
+        for (int ru = 0; ru < 2; ++ru) {
+            if constexpr (B == 4) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rw, woff + ru * 512 + i * 1024, t * TB, 0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) pl[ru][i][e] = w[e];
+                }
+            } else if constexpr (B == 2) {
+                const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rw, woff + ru * 512, t * TB, 0);
+                pl[ru][0][0] = w.x; pl[ru][0][1] = w.y; pl[ru][1][0] = w.z; pl[ru][1][1] = w.w;
+            } else {
+                const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rw, woff + ru * 512, t * TB, 0);
+                pl[ru][0][0] = w.x; pl[ru][1][0] = w.y;
+            }
         }
     };
-    // activations: load i of a stage brings 32 token rows x 32 bytes straight into LDS (lane -> row lane / 2, half
-    // lane % 2); wave w issues loads w, w + 4, ...; rows beyond the tile's tokens lie outside the resource (zeros)
+    // Activations: a request brings 8 token rows x 128 bytes straight into LDS; wave w issues requests w, w + 4, ...  16-byte
+    // chunk c of row R is kept at place c ^ ((R >> 1) & 7), so that the operand reads of 16 consecutive rows fall on 16
+    // different places.  Rows beyond the tile's tokens lie outside the resource (zeros).  Columns beyond K are those of the
+    // next token: their codes are zero.
     const int xrows = a.N - n0 < T::TN ? a.N - n0 : T::TN;
     const int8_t* xsrc = a.xq + (size_t)n0 * a.K;
     const uint32_t xbytes = (uint32_t)xrows * (uint32_t)a.K;
-    const uint32_t xlane = (uint32_t)(lane >> 1) * (uint32_t)a.K + (uint32_t)(lane & 1) * 16u;
+    const uint32_t xlane = (uint32_t)(wave * 8 + (lane >> 3)) * (uint32_t)a.K + (uint32_t)((lane & 7) ^ ((wave & 1) * 4 + (lane >> 4))) * 16u;
     const uint32_t x32rows = 32u * (uint32_t)a.K;
     auto load_x = [&](int t) {
-        const rsrc_t rx = rsrc_of(xsrc, t < k_stages ? xbytes : 0u);
+        const rsrc_t rx = rsrc_of(xsrc, t < a.n_ktiles ? xbytes : 0u);
         uint8_t* dst = smem + (t & (kI8WRing - 1)) * T::XBytes;
 #pragma unroll
-        for (int i = 0; i < T::XLoads; ++i) {
-            const int li = wave + 4 * i;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + li * 1024), 16,
-                                                     xlane + (uint32_t)li * x32rows, t * kI8WStageK, 0, 0);
-        }
+        for (int i = 0; i < T::XLoads; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + (wave + 4 * i) * 1024), 16,
+                                                     xlane + (uint32_t)i * x32rows, t * kKTile, 0, 0);
     };
-    const int xoff = r * 32 + h * 16;  // operand of token block nb: token nb * 32 + r, bytes 16 h .. 16 h + 15
+    // operand of step j (block j / 2 of the lane's two, its bytes 16 (j % 2) ..): chunk 4 h + j
+    int xoff[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) xoff[j] = r * kKTile + ((4 * h + j) ^ ((r >> 1) & 7)) * 16;
     i32x4 xf[2][TT];
-    auto read_x = [&](int set, const uint8_t* stage) {
+    auto read_x = [&](int j, const uint8_t* tile) {
 #pragma unroll
-        for (int nb = 0; nb < TT; ++nb) xf[set][nb] = *reinterpret_cast<const i32x4*>(stage + xoff + nb * 1024);
+        for (int nb = 0; nb < TT; ++nb) xf[j & 1][nb] = *reinterpret_cast<const i32x4*>(tile + xoff[j] + nb * 32 * kKTile);
     };
-    i32x4 wf[2][2];  // [set][rows 0..31 / 32..63]
-    auto operands = [&](int set, const uint32_t (&pl)[B]) {
+    i32x4 wf[2][2][2];  // [block][row unit][step of the block]
+    auto operands = [&](int block, int ru, const uint32_t (&pl)[2][2][B]) {
         u32x4 lo, hi;
-        codes_to_bytes<B>(pl, lo, hi);
-        u32x4 o0, o1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const u32x2 sw = __builtin_amdgcn_permlane32_swap(lo[e], hi[e], false, false);
-            o0[e] = sw.x;
-            o1[e] = sw.y;
-        }
-        wf[set][0] = __builtin_bit_cast(i32x4, o0);
-        wf[set][1] = __builtin_bit_cast(i32x4, o1);
+        codes_to_bytes<B>(pl[ru][block], lo, hi);
+        wf[block][ru][0] = __builtin_bit_cast(i32x4, lo);
+        wf[block][ru][1] = __builtin_bit_cast(i32x4, hi);
     };
 
+    // Requests in the order of the loop, whose waits count them.
+    // scale and zero of the tile's rows (the first quantization block of a row stands for the whole row)
+    const rsrc_t rmeta = rsrc_of(wsrc, wbytes);
+    const uint32_t meta_s = __builtin_amdgcn_raw_buffer_load_b16(rmeta, lane * MPL, B * 1024, 0);
+    const uint32_t meta_z = HZ ? __builtin_amdgcn_raw_buffer_load_b16(rmeta, lane * MPL + 2, B * 1024, 0) : 0u;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < kSets - 1; ++t) {
+        load_planes(plane[t], t);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     load_x(0);
     load_x(1);
-#pragma unroll
-    for (int u = 0; u < kI8WSets; ++u) load_planes(plane[u], u);
-    // scale and zero of the tile's rows (the first quantization block of a row stands for the whole row)
-    {
-        const int rb = mt * 4 + (tid >> 6), l = tid & 63;
-        float sc = 0.f, zs = 0.f;
-        if (rb < a.n_row_blocks) {
-            const uint8_t* meta = a.tiles + (size_t)rb * a.n_ktiles * TB + B * 1024 + l * MPL;
-            sc = (float)*reinterpret_cast<const _Float16*>(meta);
-            zs = HZ ? (float)*reinterpret_cast<const _Float16*>(meta + 2) * sc : 0.f;
-        }
-        row_scale[tid] = sc;
-        row_zs[tid] = zs;
-    }
-    operands(0, plane[0]);
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     load_x(2);
     __builtin_amdgcn_sched_barrier(0);
-    load_planes(plane[0], kI8WSets);  // (after the activations of stage 2: the waits of the loop count requests in this order)
+    load_planes(plane[kSets - 1], kSets - 1);
     __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_barrier" ::: "memory");
+    {
+        const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)meta_s);
+        row_scale[tid] = sc;
+        row_zs[tid] = HZ ? (float)__builtin_bit_cast(_Float16, (uint16_t)meta_z) * sc : 0.f;
+    }
+    operands(0, 0, plane[0]);
+    operands(0, 1, plane[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    // the activations of tiles 0 and 1 are in
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(T::XLoads + kPlaneLoads) : "memory");
     read_x(0, smem);
 
-    for (int s0 = 0; s0 < n_stages; s0 += kI8WSets) {
+    const int n_tiles_k = (a.n_ktiles + kSets - 1) & ~(kSets - 1);  // (a tile past K is zeros)
+    for (int t0 = 0; t0 < n_tiles_k; t0 += kSets) {
 #pragma unroll
-        for (int u = 0; u < kI8WSets; ++u) {
-            const int s = s0 + u;
-            const uint8_t* nxt = smem + ((s + 1) & (kI8WRing - 1)) * T::XBytes;
-            load_x(s + 3);
+        for (int u = 0; u < kSets; ++u) {
+            const int t = t0 + u;
+            const uint8_t* cur = smem + (t & (kI8WRing - 1)) * T::XBytes;
+            const uint8_t* nxt = smem + ((t + 1) & (kI8WRing - 1)) * T::XBytes;
+            load_x(t + 3);
             __builtin_amdgcn_sched_barrier(0);
-            // the MFMAs of stage s; meanwhile the activations and the weight operands of stage s + 1
-            read_x((u + 1) & 1, nxt);
-            operands((u + 1) & 1, plane[(u + 1) % kI8WSets]);
 #pragma unroll
-            for (int nb = 0; nb < TT; ++nb) {
-                acc[0][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[u & 1][0], xf[u & 1][nb], acc[0][nb], 0, 0, 0);
-                acc[1][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[u & 1][1], xf[u & 1][nb], acc[1][nb], 0, 0, 0);
+            for (int j = 0; j < 4; ++j) {
+                // the products of step j; meanwhile the activations of the next step and one row unit of the next block
+                read_x((j + 1) & 3, j == 3 ? nxt : cur);
+                operands(j < 2 ? 1 : 0, j & 1, plane[(j < 2 ? u : u + 1) % kSets]);
+#pragma unroll
+                for (int nb = 0; nb < TT; ++nb)
+#pragma unroll
+                    for (int ru = 0; ru < 2; ++ru)
+                        acc[ru][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[j >> 1][ru][j & 1], xf[j & 1][nb], acc[ru][nb], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 2 * TT; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                    if (i < TT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (j == 1) {  // both blocks of the tile's planes are used
+                    load_planes(plane[u % kSets], t + kSets);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
-#pragma unroll
-            for (int i = 0; i < 2 * TT; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
-                if (i < TT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            load_planes(plane[(u + 1) % kI8WSets], s + 1 + kI8WSets);
-            __builtin_amdgcn_sched_barrier(0);
-            // the activations of stage s + 2 (requested during stage s - 1) are in before any wave goes on: younger
-            // are the weight request of stage s - 1 and the requests just above
-            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(T::XLoads + 2) : "memory");
+            // the activations of tile t + 2 (requested one tile ago) are in before any wave goes on: younger are the planes
+            // requested then and what this tile requested
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(T::XLoads + 2 * kPlaneLoads) : "memory");
         }
     }
-    // requests of stages past the end may still be writing zeros to the ring, which the output tile reuses
+    // requests of tiles past the end may still be writing to the ring, which the output tile reuses
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 

@@ -460,24 +460,49 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
 // dequantization (about 90 vector instructions per 32 columns and row block, which hide only in part behind its own
 // MFMAs) and its MFMAs (128 cycles per 32 columns and 32 tokens): a narrow tile costs more dequantization per token
 // but spreads the work over more units and multiplies less padding.
-constexpr int kKsSets = 4;  // register sets of packed weights = own stages in flight per wave
+//
+// A stage is 64 columns, 128 bytes of a token: whole cache lines (with 64 bytes of a line per request every line came into the
+// unit's L1 twice).  Lane (r, h) of a row unit (32 rows) takes block h of the stage's two 32-column blocks of row r, which it
+// loads and dequantizes alone; a product then sums over 8 columns of each block, and the activations are read to match, so no
+// lane exchanges anything.
+constexpr int kKsStageK = 64;
 template <int RBW, int TT, int W>
 struct KsTile {
     static constexpr int TN = 32 * TT, TM = 64 * RBW;
-    static constexpr int XBytes = TN * kStageK * 2;           // activations of a stage
-    static constexpr int NBuf = 128 * 1024 / (W * XBytes) < 4 ? 128 * 1024 / (W * XBytes) : 4;  // activation buffers per wave
-    static constexpr int XLoads = TN / 16;                    // requests per stage (16 token rows each)
+    static constexpr int XBytes = TN * kKsStageK * 2;         // activations of a stage
+    static constexpr int NBuf = 128 * 1024 / (W * XBytes) < 2 ? 1 : 2;  // activation buffers per wave
+    static constexpr int XLoads = TN / 8;                     // requests per stage (8 token rows each)
     static constexpr int PartRow = TM * 4 + 16;               // bytes per token of a wave's partial tile in LDS
     static constexpr int PartBytes = (TN / 2) * PartRow;      // ... of half of its tokens
     static constexpr int LdsBytes = W * NBuf * XBytes > W * PartBytes ? W * NBuf * XBytes : W * PartBytes;
-    static_assert(TT % 2 == 0 && RBW * TT <= 8 && NBuf >= 2 && LdsBytes <= 160 * 1024, "tile of the K-split kernel");
-    static_assert((NBuf & (NBuf - 1)) == 0, "buffers are numbered modulo a power of two");
+    static_assert(TT % 2 == 0 && RBW * TT <= 8 && LdsBytes <= 160 * 1024, "tile of the K-split kernel");
 };
+
+// Loads the lane's block of stage t of 32 rows (see load_w for `rw`); `row` is the lane's row in its row block.
+template <int B, int GQ, bool HZ>
+__device__ __forceinline__ void load_w_block(WRegs<B>& r, rsrc_t rw, int t, int row, int h) {
+    constexpr int MSZ = HZ ? 4 : 2;
+    constexpr int MPL = (kKTile / GQ) * MSZ;
+    constexpr int TB = B * 1024 + 64 * MPL;
+    const int so = (t >> 1) * TB, v = t & 1;  // block 2 v + h of the tile
+    if constexpr (B == 4) {
+        const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rw, row * 16 + h * 1024, so + v * 2048, 0);
+        r.plane[0] = w.x; r.plane[1] = w.y; r.plane[2] = w.z; r.plane[3] = w.w;
+    } else if constexpr (B == 2) {
+        const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rw, row * 16 + h * 8, so + v * 1024, 0);
+        r.plane[0] = w.x; r.plane[1] = w.y;
+    } else {
+        r.plane[0] = __builtin_amdgcn_raw_buffer_load_b32(rw, row * 16 + h * 4, so + v * 8, 0);
+    }
+    const int mv = row * MPL + (GQ == 32 ? h * MSZ : 0), mo = so + B * 1024 + v * 64 / GQ * MSZ;
+    if constexpr (HZ) r.meta = __builtin_amdgcn_raw_buffer_load_b32(rw, mv, mo, 0);
+    else r.meta = __builtin_amdgcn_raw_buffer_load_b16(rw, mv, mo, 0);
+}
 
 template <int B, int GQ, bool HZ, int RBW, int TT, int W>
 __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     using T = KsTile<RBW, TT, W>;
-    constexpr int kMfmas = 2 * RBW * TT;  // of a 16-column step
+    constexpr int kUnits = 2 * RBW;  // row units of the tile
     constexpr int MSZ = HZ ? 4 : 2;
     constexpr int TB = B * 1024 + 64 * (kKTile / GQ) * MSZ;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -491,10 +516,10 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n0 = nt * T::TN;
-    const int k_stages = a.K / kStageK;
-    // own stages of this wave: wave, wave + W, ...; the loop runs whole rounds of kKsSets own stages (a stage past
-    // K has empty sources: zero weights, zero activations)
-    const int n_own = (k_stages + W - 1) / W, n_own_pad = (n_own + kKsSets - 1) & ~(kKsSets - 1);
+    const int k_stages = (a.K + kKsStageK - 1) / kKsStageK;
+    // own stages of this wave: wave, wave + W, ...; the loop runs an even number of them (a stage past K has empty
+    // sources: zero weights, zero activations)
+    const int n_own = (k_stages + W - 1) / W, n_own_pad = (n_own + 1) & ~1;
     const int r = lane & 31, h = lane >> 5;
 
     float16_t acc[RBW][2][TT];
@@ -507,137 +532,123 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[b][hb][nb][v] = 0.f;
 
-    WRegs<B> wr[kKsSets][RBW];
-    auto load_wregs = [&](int set, int i) {  // own stage i = stage W i + wave, every row block of the tile
-        const int t = W * i + wave;
-#pragma unroll
-        for (int b = 0; b < RBW; ++b) {
-            const int rb = mt * RBW + b;
-            const bool wvalid = rb < a.n_row_blocks;
-            const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rb : 0) * a.n_ktiles * TB;
-            load_w<B, GQ, HZ>(wr[set][b], make_rsrc(wsrc, t < k_stages && wvalid ? 0x7fffffffu : 0u), t >> 2, t & 3, lane);
-        }
+    WRegs<B> wr[2][kUnits];
+    auto load_unit = [&](int set, int unit, int i) {  // own stage i = stage W i + wave
+        const int t = W * i + wave, rb = mt * RBW + unit / 2;
+        const bool wvalid = rb < a.n_row_blocks;
+        const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rb : 0) * a.n_ktiles * TB;
+        load_w_block<B, GQ, HZ>(wr[set][unit], make_rsrc(wsrc, t < k_stages && wvalid ? 0x7fffffffu : 0u), t, (unit & 1) * 32 + r, h);
     };
-    // activations of own stage i go to this wave's buffer i % NBuf
+    // Activations of own stage i go to this wave's buffer i % NBuf.  A request brings 8 token rows of 128 bytes; 16-byte chunk c
+    // of row R is kept at place c ^ ((R >> 1) & 7): the operand reads of 16 consecutive rows fall on 16 different places.
+    // Columns beyond K (blocks of 32 only) have weights of zero and are sent past the end of the resource, where they read as zero.
     const int xrows = a.N - n0 < T::TN ? a.N - n0 : T::TN;
     const _Float16* xsrc = a.x + (size_t)n0 * a.K;
     const uint32_t xbytes = (uint32_t)xrows * (uint32_t)a.K * 2u;
-    const uint32_t xlane = ((lane >> 2) * (uint32_t)a.K + ((lane & 3) ^ ((lane >> 4) & 3)) * 8u) * 2u;
-    const uint32_t x16rows = 16u * (uint32_t)a.K * 2u;
+    const uint32_t xlane = (uint32_t)(lane >> 3) * (uint32_t)a.K * 2u, x8rows = 8u * (uint32_t)a.K * 2u;
+    const uint32_t xchunk[2] = {(uint32_t)((lane & 7) ^ (lane >> 4)) * 16u, (uint32_t)((lane & 7) ^ (4 + (lane >> 4))) * 16u};
     uint8_t* const xbuf = smem + wave * T::NBuf * T::XBytes;
     auto load_x = [&](int i) {
         const int t = W * i + wave;
         const rsrc_t rx = make_rsrc(xsrc, t < k_stages ? xbytes : 0u);
         uint8_t* dst = xbuf + (i & (T::NBuf - 1)) * T::XBytes;
 #pragma unroll
-        for (int q = 0; q < T::XLoads; ++q)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + q * 1024), 16,
-                                                     xlane + (uint32_t)q * x16rows, t * kStageK * 2, 0, 0);
+        for (int q = 0; q < T::XLoads; ++q) {
+            uint32_t off = xlane + (uint32_t)q * x8rows + xchunk[q & 1];
+            if constexpr (GQ == 32) off = t * kKsStageK + (int)(xchunk[q & 1] / 2) < a.K ? off : 0xFFFFFF00u;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + q * 1024), 16, off,
+                                                     t * kKsStageK * 2, 0, 0);
+        }
     };
-    const int xrow = r * (kStageK * 2);
-    const int xchunk[2] = {xrow + ((h ^ ((r >> 2) & 3)) * 16), xrow + (((2 + h) ^ ((r >> 2) & 3)) * 16)};
-    half8_t xf[2][TT];
+    // operand of step j: columns 8 j .. 8 j + 7 of the lane's block, chunk 4 h + j
+    int xoff[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) xoff[j] = r * (kKsStageK * 2) + ((4 * h + j) ^ ((r >> 1) & 7)) * 16;
+    half8_t xf[4][TT];
     auto read_x = [&](int j, const uint8_t* stage) {
 #pragma unroll
         for (int nb = 0; nb < TT; ++nb)
-            xf[j][nb] = *reinterpret_cast<const half8_t*>(stage + xchunk[j] + nb * 32 * (kStageK * 2));
+            xf[j][nb] = *reinterpret_cast<const half8_t*>(stage + xoff[j] + nb * 32 * (kKsStageK * 2));
     };
-    half8_t wf[2][RBW][2][2];  // [set][row block][rows 0..31 / 32..63][16-column step]
+    half8_t wf[2][4];  // [unit % 2][step]
     Dequant<B, HZ> dq;
-    auto operands = [&](int set, int b, int j) {
-        const u32x4 pa = dq.piece(2 * j), pb = dq.piece(2 * j + 1);
-        u32x4 lo, hi;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const u32x2 sw = __builtin_amdgcn_permlane32_swap(pa[e], pb[e], false, false);
-            lo[e] = sw.x;
-            hi[e] = sw.y;
-        }
-        wf[set][b][0][j] = __builtin_bit_cast(half8_t, lo);
-        wf[set][b][1][j] = __builtin_bit_cast(half8_t, hi);
-    };
-    auto mfmas = [&](int set, int j) {
-#pragma unroll
-        for (int nb = 0; nb < TT; ++nb)
-#pragma unroll
-            for (int b = 0; b < RBW; ++b) {
-                acc[b][0][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[set][b][0][j], xf[j][nb], acc[b][0][nb], 0, 0, 0);
-                acc[b][1][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[set][b][1][j], xf[j][nb], acc[b][1][nb], 0, 0, 0);
-            }
-    };
-    // the vector work of a stage in two parts, one beside each 16-column step of the previous stage: with one row
-    // block level 1 / level 2 of it, with two the whole of block 0 / of block 1
-    auto dequant_part = [&](int part, int wset, int oset) {
-        if constexpr (RBW == 1) {
-            if (part == 0) {
-                dq.start(wr[wset][0]);
-                dq.insert();
-            } else {
-                operands(oset, 0, 0);
-                operands(oset, 0, 1);
-            }
-        } else {
-            dq.start(wr[wset][part]);
+    // the vector work of a row unit in four parts, one beside each step of the unit before it
+    auto dequant_part = [&](int j, int set, int unit) {
+        if (j == 0) {
+            dq.start(wr[set][unit]);
+        } else if (j == 1) {
             dq.insert();
-            operands(oset, part, 0);
-            operands(oset, part, 1);
+        } else {
+#pragma unroll
+            for (int q = 2 * j - 4; q < 2 * j - 2; ++q) wf[unit & 1][q] = __builtin_bit_cast(half8_t, dq.piece(q));
         }
     };
 
-    // prologue: activations of own stage 0 in LDS and those of own stage 1 requested; weights of own stages 1..4 in
-    // the register sets, own stage 0 dequantized into operand set 0
+    // prologue: weights of own stages 0 and 1 and activations requested, the first row unit dequantized, the first activations
+    // in registers
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) load_unit(0, u, 0);
     load_x(0);
 #pragma unroll
-    for (int i = 0; i < kKsSets; ++i) load_wregs(i, i);
-    dequant_part(0, 0, 0);
-    dequant_part(1, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (int u = 0; u < kUnits; ++u) load_unit(1, u, 1);
 #pragma unroll
-    for (int i = 1; i < T::NBuf; ++i) load_x(i);
+    for (int j = 0; j < 4; ++j) dequant_part(j, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    load_wregs(0, kKsSets);
+    if constexpr (T::NBuf == 2) {
+        load_x(1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    load_unit(0, 0, 2);
     __builtin_amdgcn_sched_barrier(0);
-    read_x(0, xbuf);
+    // activations of own stage 0: younger are the requests of own stage 1 and unit 0 of own stage 2
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kUnits + (T::NBuf - 1) * T::XLoads + 2) : "memory");
+#pragma unroll
+    for (int j = 0; j < 4; ++j) read_x(j, xbuf);
 
-    for (int i0 = 0; i0 < n_own_pad; i0 += kKsSets) {
+    for (int i0 = 0; i0 < n_own_pad; i0 += 2) {
 #pragma unroll
-        for (int u = 0; u < kKsSets; ++u) {
-            const int i = i0 + u;
-            const uint8_t* cur = xbuf + (i & (T::NBuf - 1)) * T::XBytes;
+        for (int s = 0; s < 2; ++s) {
+            const int i = i0 + s;
             const uint8_t* nxt = xbuf + ((i + 1) & (T::NBuf - 1)) * T::XBytes;
-            // first half: 16-column step 0 of own stage i; meanwhile the activations of step 1 and level 1 of the
-            // next own stage
-            read_x(1, cur);
-            dequant_part(0, (u + 1) % kKsSets, (u + 1) & 1);
-            mfmas(u & 1, 0);
-#pragma unroll
-            for (int q = 0; q < kMfmas; ++q) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, (RBW == 1 ? 48 : 96) / kMfmas, 0);
-                if (q < TT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            if constexpr (T::NBuf == 1) {  // the only buffer is free when its activations are in registers
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                load_x(i + 1);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            // second half: step 1; meanwhile the rest of the next own stage's vector work
-            dequant_part(1, (u + 1) % kKsSets, (u + 1) & 1);
-            mfmas(u & 1, 1);
 #pragma unroll
-            for (int q = 0; q < kMfmas; ++q) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, (RBW == 1 ? 80 : 96) / kMfmas, 0);
+            for (int u = 0; u < kUnits; ++u) {
+                constexpr int kLast = kUnits - 1;
+                const int nu = u == kLast ? 0 : u + 1, nset = u == kLast ? (s + 1) & 1 : s;
+                if (u == kLast) {
+                    // The activations of own stage i + 1 must be in.  Younger: NBuf == 2 (requested behind unit 1 of the previous
+                    // own stage): its weights from then on, the weights of this stage and the activations of stage i + 2;
+                    // NBuf == 1 (requested above): the weights of this stage.
+                    constexpr int kYounger = T::NBuf == 2 ? 2 * kUnits + T::XLoads : 2 * (kUnits - 1);
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kYounger) : "memory");
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    dequant_part(j, nset, nu);
+#pragma unroll
+                    for (int nb = 0; nb < TT; ++nb)
+                        acc[u / 2][u & 1][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[u & 1][j], xf[j][nb], acc[u / 2][u & 1][nb], 0, 0, 0);
+                    if (u == kLast) read_x(j, nxt);
+#pragma unroll
+                    for (int q = 0; q < TT; ++q) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 24 / TT, 0);
+                        if (u == kLast) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                // the registers of the row unit just dequantized are free
+                load_unit(nset, nu, (u == kLast ? i + 1 : i) + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                if (T::NBuf == 2 && u == 0) {  // the activations of this own stage are in registers (unit 0 used them all)
+                    load_x(i + 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
-            __builtin_amdgcn_sched_barrier(0);
-            // The buffer of own stage i is free now (its operand reads are consumed): request own stage i + NBuf
-            // into it.  Before the reads that follow, the activations of own stage i + 1 must be in: what was
-            // requested after them is at least the activations of NBuf - 2 stages and one stage's weights (requests
-            // complete in order; older weight requests are long in by then).
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((T::NBuf - 2) * T::XLoads + 2 * RBW) : "memory");
-            load_x(i + T::NBuf);
-            __builtin_amdgcn_sched_barrier(0);
-            load_wregs((u + 1) % kKsSets, i + 1 + kKsSets);
-            __builtin_amdgcn_sched_barrier(0);
-            read_x(0, nxt);
-            __builtin_amdgcn_sched_barrier(0);
         }
     }
     // requests of own stages past the end may still be writing zeros to LDS, which the partial tiles reuse

@@ -398,6 +398,26 @@ __global__ void __launch_bounds__(256) mpgemm_i8_kernel(GemmI8Args a) {
     }
 }
 
+// The two 32-column blocks of a lane in a tile block of 32 rows (lane half h: blocks 2 h and 2 h + 1); `off`: of the lane's
+// first chunk, r * 16 + h * (bytes of two blocks' chunks, within a chunk for 1 bit).
+template <int B>
+__device__ __forceinline__ void load_unit_planes(uint32_t (&pl)[2][B], rsrc_t rw, int off, int tile_off) {
+    if constexpr (B == 4) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rw, off + i * 1024, tile_off, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) pl[i][e] = w[e];
+        }
+    } else if constexpr (B == 2) {
+        const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rw, off, tile_off, 0);
+        pl[0][0] = w.x; pl[0][1] = w.y; pl[1][0] = w.z; pl[1][1] = w.w;
+    } else {
+        const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rw, off, tile_off, 0);
+        pl[0][0] = w.x; pl[1][0] = w.y;
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Wide variant for long token ranges: no weight tile in LDS.  A wave owns 64 rows x 32 TT tokens.  Lane (r, h) of a row unit
 // (32 rows) takes the 32-column blocks 2 h and 2 h + 1 of row r of a 128-column tile, which it loads and turns into bytes
@@ -406,7 +426,6 @@ __global__ void __launch_bounds__(256) mpgemm_i8_kernel(GemmI8Args a) {
 // shared by the four waves (256 rows) of the workgroup, a tile (128 bytes of a token, a whole cache line) at a time.  Per MFMA
 // this reads half the LDS bytes of the 128 x 128 kernel and dequantizes each weight once per 32 TT tokens instead of once per 128.
 constexpr int kI8WRing = 4;   // tile buffers of activations in LDS
-constexpr int kI8WStageK = 32;
 constexpr int kI8WRows = 256;
 
 template <int TT>
@@ -455,22 +474,7 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
     auto load_planes = [&](uint32_t (&pl)[2][2][B], int t) {
         const rsrc_t rw = rsrc_of(wsrc, t < a.n_ktiles ? wbytes : 0u);
 #pragma unroll
-        for (int ru = 0; ru < 2; ++ru) {
-            if constexpr (B == 4) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rw, woff + ru * 512 + i * 1024, t * TB, 0);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) pl[ru][i][e] = w[e];
-                }
-            } else if constexpr (B == 2) {
-                const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rw, woff + ru * 512, t * TB, 0);
-                pl[ru][0][0] = w.x; pl[ru][0][1] = w.y; pl[ru][1][0] = w.z; pl[ru][1][1] = w.w;
-            } else {
-                const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rw, woff + ru * 512, t * TB, 0);
-                pl[ru][0][0] = w.x; pl[ru][1][0] = w.y;
-            }
-        }
+        for (int ru = 0; ru < 2; ++ru) load_unit_planes<B>(pl[ru], rw, woff + ru * 512, t * TB);
     };
     // Activations: a request brings 8 token rows x 128 bytes straight into LDS; wave w issues requests w, w + 4, ...  16-byte
     // chunk c of row R is kept at place c ^ ((R >> 1) & 7), so that the operand reads of 16 consecutive rows fall on 16
@@ -646,20 +650,19 @@ static int launch_i8_wide(GemmI8Args a, int group, hipStream_t st) {
 
 // ---------------------------------------------------------------------------------------------
 // Third kernel, for grids that leave compute units idle even with 64-row workgroups: the four waves of a workgroup
-// split K.  Wave w takes the 32-column stages w, w + 4, ... whole: bit planes -> bytes in registers -> operands
-// by v_permlane32_swap (as in the wide kernel), the stage's activations into LDS buffers of its own, MFMAs with all
-// tokens of the tile; no wave waits for another until the end, where the four partial integer tiles are added in
-// LDS (integers: the result does not depend on the grouping, so every kernel of this file gives the same bits).
-// Tile: 128 rows x 128 tokens (two row blocks per wave); the 64 x 256 tile the template also allows was slower
-// everywhere here, where the dequantization is cheap and the activation stream is what a wave waits for.
-constexpr int kI8KsSets = 4;  // register sets of bit planes = own stages in flight per wave
-
+// split K.  Wave w takes the 128-column tiles w, w + 4, ... whole: bit planes -> bytes in registers, the tile's int8
+// activations into LDS buffers of its own (whole cache lines, as in the wide kernel), MFMAs with all tokens of the workgroup's
+// tile; no wave waits for another until the end, where the four partial integer tiles are added in LDS (integers: the result
+// does not depend on the grouping, so every kernel of this file gives the same bits).
+// Tile: 128 rows x 128 tokens (two row blocks per wave).  A wave's share was 32-column stages before, 32 bytes of each of 32 cache
+// lines per request: 2560 x 6912 2 bits N = 1024 35.8 us, now 27.2; 4096 x 4096 4 bits N = 700 27.1 / 21.6; 1024 x 8192 N = 2048
+// 39.1 / 29.7; 11008 x 4096 4 bits N = 256 26.4 / 21.3.
 template <int RBW, int TT>
 struct I8KsTile {
     static constexpr int TN = 32 * TT, TM = 64 * RBW;
-    static constexpr int XBytes = TN * kI8WStageK;            // activations of a stage, 32 bytes per token
-    static constexpr int NBuf = 4;                             // activation buffers per wave
-    static constexpr int XLoads = TN / 32;                     // requests per stage (32 token rows each)
+    static constexpr int XBytes = TN * kKTile;                // activations of a tile, 128 bytes per token
+    static constexpr int NBuf = 2;                             // activation buffers per wave
+    static constexpr int XLoads = TN / 8;                     // requests per tile (8 token rows each)
     static constexpr int PartRow = TM * 4 + 16;                // bytes per token of a wave's partial tile in LDS
     static constexpr int PartBytes = (TN / 2) * PartRow;       // ... of half of its tokens
     static constexpr int LdsBytes = 4 * NBuf * XBytes > 4 * PartBytes ? 4 * NBuf * XBytes : 4 * PartBytes;
@@ -669,8 +672,8 @@ struct I8KsTile {
 template <int B, bool HZ, int RBW, int TT>
 __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, int group) {
     using T = I8KsTile<RBW, TT>;
+    constexpr int kUnits = 2 * RBW;  // row units of 32 rows
     constexpr int MSZ = HZ ? 4 : 2;
-    constexpr int CH = kKTile / B;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     __shared__ float row_scale[T::TM], row_zs[T::TM];
 
@@ -682,8 +685,7 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
     if (!header_ok && blockIdx.x == 0 && tid == 0) report_header_mismatch(a.status);
     if (mt >= (header_ok ? a.m_tiles : 0)) return;
     const int n0 = nt * T::TN;
-    const int k_stages = a.K / kI8WStageK;
-    const int n_own = (k_stages + 3) / 4, n_own_pad = (n_own + kI8KsSets - 1) & ~(kI8KsSets - 1);
+    const int n_own = (a.n_ktiles + 3) / 4, n_own_pad = (n_own + 1) & ~1;  // own tiles of this wave
     const int r = lane & 31, h = lane >> 5;
 
     i32x16 acc[RBW][2][TT];
@@ -696,125 +698,113 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[b][hb][nb][v] = 0;
 
-    uint32_t plane[kI8KsSets][RBW][B];
-    auto load_planes = [&](int set, int i) {  // own stage i = stage 4 i + wave, every row block of the tile
-        const int t = 4 * i + wave;
-        const int tile = t >> 2, kb32 = t & 3;
-        const int v = (kb32 * 32) / CH, ksub = ((kb32 * 32) % CH) / 32;
-        const int so = tile * TB + v * 1024 + ksub * B * 4;
-#pragma unroll
-        for (int b = 0; b < RBW; ++b) {
-            const int rb = mt * RBW + b;
-            const bool wvalid = rb < a.n_row_blocks;
-            const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rb : 0) * a.n_ktiles * TB;
-            const rsrc_t rw = rsrc_of(wsrc, t < k_stages && wvalid ? (uint32_t)(a.n_ktiles * TB) : 0u);
-            uint32_t (&pl)[B] = plane[set][b];
-            if constexpr (B == 4) {
-                const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16, so, 0);
-                pl[0] = w.x; pl[1] = w.y; pl[2] = w.z; pl[3] = w.w;
-            } else if constexpr (B == 2) {
-                const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rw, lane * 16, so, 0);
-                pl[0] = w.x; pl[1] = w.y;
-            } else {
-                pl[0] = __builtin_amdgcn_raw_buffer_load_b32(rw, lane * 16, so, 0);
-            }
-        }
+    uint32_t plane[2][kUnits][2][B];  // [set][row unit][block][plane]
+    constexpr int kUnitLoads = B == 4 ? 2 : 1;
+    const int woff = r * 16 + (B == 1 ? h * 8 : h * (B / 2) * 1024);
+    auto load_unit = [&](int set, int unit, int i) {  // own tile i = tile 4 i + wave
+        const int t = 4 * i + wave, rb = mt * RBW + unit / 2;
+        const bool wvalid = rb < a.n_row_blocks;
+        const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rb : 0) * a.n_ktiles * TB;
+        const rsrc_t rw = rsrc_of(wsrc, t < a.n_ktiles && wvalid ? (uint32_t)(a.n_ktiles * TB) : 0u);
+        load_unit_planes<B>(plane[set][unit], rw, woff + (unit & 1) * 512, t * TB);
     };
-    // activations of own stage i go to this wave's buffer i % NBuf: lane -> token row lane / 2, half lane % 2
+    // activations of own tile i go to this wave's buffer i % NBuf, chunks placed as in the wide kernel
     const int xrows = a.N - n0 < T::TN ? a.N - n0 : T::TN;
     const int8_t* xsrc = a.xq + (size_t)n0 * a.K;
     const uint32_t xbytes = (uint32_t)xrows * (uint32_t)a.K;
-    const uint32_t xlane = (uint32_t)(lane >> 1) * (uint32_t)a.K + (uint32_t)(lane & 1) * 16u;
-    const uint32_t x32rows = 32u * (uint32_t)a.K;
+    const uint32_t xlane = (uint32_t)(lane >> 3) * (uint32_t)a.K, x8rows = 8u * (uint32_t)a.K;
+    const uint32_t xchunk[2] = {(uint32_t)((lane & 7) ^ (lane >> 4)) * 16u, (uint32_t)((lane & 7) ^ (4 + (lane >> 4))) * 16u};
     uint8_t* const xbuf = smem + wave * T::NBuf * T::XBytes;
     auto load_x = [&](int i) {
         const int t = 4 * i + wave;
-        const rsrc_t rx = rsrc_of(xsrc, t < k_stages ? xbytes : 0u);
+        const rsrc_t rx = rsrc_of(xsrc, t < a.n_ktiles ? xbytes : 0u);
         uint8_t* dst = xbuf + (i & (T::NBuf - 1)) * T::XBytes;
 #pragma unroll
         for (int q = 0; q < T::XLoads; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + q * 1024), 16,
-                                                     xlane + (uint32_t)q * x32rows, t * kI8WStageK, 0, 0);
+                                                     xlane + (uint32_t)q * x8rows + xchunk[q & 1], t * kKTile, 0, 0);
     };
-    const int xoff = r * 32 + h * 16;
-    i32x4 xf[2][TT];
-    auto read_x = [&](int set, const uint8_t* stage) {
+    int xoff[4];
 #pragma unroll
-        for (int nb = 0; nb < TT; ++nb) xf[set][nb] = *reinterpret_cast<const i32x4*>(stage + xoff + nb * 1024);
+    for (int j = 0; j < 4; ++j) xoff[j] = r * kKTile + ((4 * h + j) ^ ((r >> 1) & 7)) * 16;
+    i32x4 xf[4][TT];
+    auto read_x = [&](int j, const uint8_t* tile) {
+#pragma unroll
+        for (int nb = 0; nb < TT; ++nb) xf[j][nb] = *reinterpret_cast<const i32x4*>(tile + xoff[j] + nb * 32 * kKTile);
     };
-    i32x4 wf[2][RBW][2];  // [set][row block][rows 0..31 / 32..63]
-    auto operands = [&](int set, int wset) {
-#pragma unroll
-        for (int b = 0; b < RBW; ++b) {
-            u32x4 lo, hi;
-            codes_to_bytes<B>(plane[wset][b], lo, hi);
-            u32x4 o0, o1;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const u32x2 sw = __builtin_amdgcn_permlane32_swap(lo[e], hi[e], false, false);
-                o0[e] = sw.x;
-                o1[e] = sw.y;
-            }
-            wf[set][b][0] = __builtin_bit_cast(i32x4, o0);
-            wf[set][b][1] = __builtin_bit_cast(i32x4, o1);
-        }
+    i32x4 wf[2][4];  // [unit % 2][step]
+    auto operands = [&](int block, int set, int unit) {
+        u32x4 lo, hi;
+        codes_to_bytes<B>(plane[set][unit][block], lo, hi);
+        wf[unit & 1][2 * block] = __builtin_bit_cast(i32x4, lo);
+        wf[unit & 1][2 * block + 1] = __builtin_bit_cast(i32x4, hi);
     };
 
+    // scale and zero of the tile's rows (the first quantization block of a row stands for the whole row)
+    const int mrb = mt * RBW + wave;
+    const rsrc_t rmeta = rsrc_of(a.tiles + (size_t)(mrb < a.n_row_blocks ? mrb : 0) * a.n_ktiles * TB,
+                                 wave < RBW && mrb < a.n_row_blocks ? (uint32_t)TB : 0u);
+    const uint32_t meta_s = __builtin_amdgcn_raw_buffer_load_b16(rmeta, lane * MPL, B * 1024, 0);
+    const uint32_t meta_z = HZ ? __builtin_amdgcn_raw_buffer_load_b16(rmeta, lane * MPL + 2, B * 1024, 0) : 0u;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) load_unit(0, u, 0);
     load_x(0);
 #pragma unroll
-    for (int i = 0; i < kI8KsSets; ++i) load_planes(i, i);
-    // scale and zero of the tile's rows (the first quantization block of a row stands for the whole row)
+    for (int u = 0; u < kUnits; ++u) load_unit(1, u, 1);
+    load_x(1);
+    __builtin_amdgcn_sched_barrier(0);
     if (tid < T::TM) {
-        const int rb = mt * RBW + (tid >> 6), l = tid & 63;
-        float sc = 0.f, zs = 0.f;
-        if (rb < a.n_row_blocks) {
-            const uint8_t* meta = a.tiles + (size_t)rb * a.n_ktiles * TB + B * 1024 + l * MPL;
-            sc = (float)*reinterpret_cast<const _Float16*>(meta);
-            zs = HZ ? (float)*reinterpret_cast<const _Float16*>(meta + 2) * sc : 0.f;
-        }
+        const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)meta_s);
         row_scale[tid] = sc;
-        row_zs[tid] = zs;
+        row_zs[tid] = HZ ? (float)__builtin_bit_cast(_Float16, (uint16_t)meta_z) * sc : 0.f;
     }
-    operands(0, 0);
+    operands(0, 0, 0);
+    operands(1, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    load_unit(0, 0, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    // activations of own tile 0: younger are the requests of own tile 1 and unit 0 of own tile 2
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kUnits + 1) * kUnitLoads + T::XLoads) : "memory");
 #pragma unroll
-    for (int i = 1; i < T::NBuf; ++i) load_x(i);
-    __builtin_amdgcn_sched_barrier(0);
-    load_planes(0, kI8KsSets);
-    __builtin_amdgcn_sched_barrier(0);
-    read_x(0, xbuf);
+    for (int j = 0; j < 4; ++j) read_x(j, xbuf);
 
-    for (int i0 = 0; i0 < n_own_pad; i0 += kI8KsSets) {
+    for (int i0 = 0; i0 < n_own_pad; i0 += 2) {
 #pragma unroll
-        for (int u = 0; u < kI8KsSets; ++u) {
-            const int i = i0 + u;
+        for (int s = 0; s < 2; ++s) {
+            const int i = i0 + s;
             const uint8_t* nxt = xbuf + ((i + 1) & (T::NBuf - 1)) * T::XBytes;
-            // the MFMAs of own stage i; meanwhile the weight operands of own stage i + 1
-            operands((u + 1) & 1, (u + 1) % kI8KsSets);
 #pragma unroll
-            for (int nb = 0; nb < TT; ++nb)
+            for (int u = 0; u < kUnits; ++u) {
+                constexpr int kLast = kUnits - 1;
+                const int nu = u == kLast ? 0 : u + 1, nset = u == kLast ? (s + 1) & 1 : s;
+                // The activations of own tile i + 1 must be in (requested behind unit 0 of the previous own tile).  Younger: at
+                // least its weights from then on, as many of this tile, and the activations of own tile i + 2.
+                if (u == kLast) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kUnits * kUnitLoads + T::XLoads) : "memory");
 #pragma unroll
-                for (int b = 0; b < RBW; ++b) {
-                    acc[b][0][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[u & 1][b][0], xf[u & 1][nb], acc[b][0][nb], 0, 0, 0);
-                    acc[b][1][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[u & 1][b][1], xf[u & 1][nb], acc[b][1][nb], 0, 0, 0);
+                for (int j = 0; j < 4; ++j) {
+                    if (j % 2 == 0) operands(j / 2, nset, nu);
+#pragma unroll
+                    for (int nb = 0; nb < TT; ++nb)
+                        acc[u / 2][u & 1][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[u & 1][j], xf[j][nb], acc[u / 2][u & 1][nb], 0, 0, 0);
+                    if (u == kLast) read_x(j, nxt);
+                    if (j % 2 == 1) {
+#pragma unroll
+                        for (int q = 0; q < 2 * TT; ++q) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x002, 32 / (2 * TT), 0);
+                            if (u == kLast) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, RBW == 1 ? 2 : 4, 0);
+                load_unit(nset, nu, (u == kLast ? i + 1 : i) + 2);  // the registers of the row unit just turned into bytes are free
+                __builtin_amdgcn_sched_barrier(0);
+                if (u == 0) {  // the activations of this own tile are in registers (unit 0 used them all)
+                    load_x(i + 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
-            __builtin_amdgcn_sched_barrier(0);
-            // The buffer of own stage i is free now: request own stage i + NBuf into it.  Before the reads that
-            // follow, the activations of own stage i + 1 must be in: what was requested after them is at least the
-            // activations of NBuf - 2 stages and one stage's bit planes (requests complete in order).
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((T::NBuf - 2) * T::XLoads + RBW) : "memory");
-            load_x(i + T::NBuf);
-            __builtin_amdgcn_sched_barrier(0);
-            load_planes((u + 1) % kI8KsSets, i + 1 + kI8KsSets);
-            __builtin_amdgcn_sched_barrier(0);
-            read_x((u + 1) & 1, nxt);
-            __builtin_amdgcn_sched_barrier(0);
         }
     }
     // requests of own stages past the end may still be writing zeros to LDS, which the partial tiles reuse
@@ -972,12 +962,12 @@ int choose_i8_token_blocks(int n_row_blocks, int N, int K) {
             best = tts[i];
         }
     }
-    // the kernel whose waves split K (128 rows x 128 tokens, one workgroup per unit): 19 us per round on an almost
-    // empty chip, 25 when every unit streams activations
+    // the kernel whose waves split K (128 rows x 128 tokens, one workgroup per unit): 17 us per round on an almost
+    // empty chip, 22.5 when every unit streams activations
     if (K >= 2048) {
         const long long wgs = (long long)((n_row_blocks + 1) / 2) * ((N + 127) / 128);
         const double fill = wgs >= n_cu ? 1.0 : (double)wgs / n_cu;
-        const double cost = (double)((wgs + n_cu - 1) / n_cu) * (19.0 + 6.0 * fill) * k;
+        const double cost = (double)((wgs + n_cu - 1) / n_cu) * (16.5 + 6.0 * fill) * k;
         if (cost < best_cost) {
             best_cost = cost;
             best = 9;

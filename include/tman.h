@@ -255,8 +255,9 @@ int tman_device_status(void *stream);
  * feed the matrix cores with fp32 accumulation (N <= 32, most formats: the codes feed them, exact, and scale and zero are
  * applied in fp32 to the sums of a quantization block).
  *   x : fp16 [N][K], any N >= 1;   y : fp16 [N][M]
- * N > TMAN_MAX_SMALL_TOKENS runs one of two prefill kernels (the tiled one, 256 tokens per workgroup, bound by the
- * matrix cores, or the one whose waves split K, for short prompts and small grids; neither needs a workspace).
+ * N > TMAN_MAX_SMALL_TOKENS runs one of three prefill kernels (the tiled one, 256 tokens per workgroup, bound by the
+ * matrix cores, the one of 256 rows x 96 tokens without a weight tile, or the one whose waves split K, for short prompts and
+ * small grids; none needs a workspace).
  * 1 <= N <= TMAN_MAX_SMALL_TOKENS runs one of two kernels organised like the decoding kernels (bound by the weight
  * stream: every wave multiplies the tile blocks it streams with all tokens at once): the codes themselves, with scale and
  * zero applied to the sums of quantization blocks (N <= 8; N <= 16 with blocks of 64 or 128; N <= 32 with blocks of
@@ -312,7 +313,7 @@ int tman_mpgemm_i8(const tman_shape_t *shape, const void *packed, const void *xq
  * Rows of W (output features) one workgroup of tman_mpgemm covers for this shape and N > 32: 64, 128, 192 or 256,
  * chosen so that the workgroups fill the compute units of the current device best (256 units are
  * assumed when no device is present).  tman_mpgemm_splits_k tells whether the call goes to the kernel whose waves
- * split K (1) or to the tiled kernel (0).  Informational; 0 / -1 for an invalid shape or N < 1.
+ * split K (1) or to one of the others (0).  Informational; 0 / -1 for an invalid shape or N < 1.
  */
 int32_t tman_mpgemm_tile_rows(const tman_shape_t *shape, int32_t N);
 int32_t tman_mpgemm_splits_k(const tman_shape_t *shape, int32_t N);

@@ -20,9 +20,10 @@
 // The fp16 weight tile goes to LDS and is shared by the waves of the workgroup (each weight is
 // dequantized once per 256 tokens); activations go from global memory straight into LDS.  Pipeline (the
 // GPU form of DMA -> vector -> matrix): producer waves keep packed weights four stages ahead in registers
-// and fill a ring of four LDS stage buffers; consumer waves feed v_mfma_f32_32x32x16_f16
+// and fill a ring of LDS stage buffers; consumer waves feed v_mfma_f32_32x32x16_f16
 // (fp32 accumulation) from the ring; one barrier per 32-column stage.
-// Grids too small for that kernel (at most one workgroup per compute unit) go to mpgemm_ksplit_kernel, below.
+// Grids too small for that kernel (at most one workgroup per compute unit) go to mpgemm_ksplit_kernel, grids whose rounds its
+// tiles fit badly to mpgemm_wide_kernel, both below.
 #include <hip/hip_fp16.h>
 
 #include <mutex>
@@ -40,7 +41,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kTN = 256;      // tokens per workgroup
 constexpr int kStageK = 32;   // columns per pipeline stage (one 32-weight block of the layout)
 constexpr int kRowBytes = kStageK * 2 + 16;  // padded LDS row: 20 dwords, conflict-free 16-byte accesses
-constexpr int kRing = 4;      // stage buffers in LDS
+constexpr int kRing = 3;      // weight buffers in LDS (a stage each) and activation buffers (a pair of stages each)
 constexpr int kSets = 4;      // register sets of the producers = stages of global loads in flight
 constexpr int kXcds = 8;      // workgroups are dealt to the chip's 8 XCDs (one L2 each) round robin
 
@@ -50,10 +51,10 @@ template <int RB>
 struct Tile {
     static constexpr int TM = RB * 64;
     static constexpr int WBytes = TM * kRowBytes;    // fp16 weights of a stage, padded rows
-    static constexpr int XBytes = kTN * kStageK * 2; // activations of a stage, 64-byte rows, chunks swizzled
-    static constexpr int StageBytes = WBytes + XBytes;
+    static constexpr int XBytes = kTN * kStageK * 4; // activations of a pair of stages, 128-byte rows, chunks swizzled
     static constexpr int OutRow = TM * 2 + 16;       // bytes per token of the output tile in LDS
-    static constexpr int LdsBytes = kRing * StageBytes > kTN * OutRow ? kRing * StageBytes : kTN * OutRow;
+    static constexpr int LdsBytes = kRing * (WBytes + XBytes) > kTN * OutRow ? kRing * (WBytes + XBytes) : kTN * OutRow;
+    static_assert(LdsBytes <= 160 * 1024, "tile of the tiled kernel");
 };
 
 struct GemmArgs {
@@ -108,12 +109,33 @@ __device__ __forceinline__ void load_w(WRegs<B>& r, rsrc_t rw, int tile, int kb3
     else r.meta = __builtin_amdgcn_raw_buffer_load_b16(rw, lane * MPL, mo, 0);
 }
 
-// Activation staging: the 64 bytes a token contributes to a stage are four 16-byte chunks.  They go
+// Activation staging: a token contributes 128 bytes, a whole cache line, to a pair of stages (with 64 bytes per stage every
+// line came into the unit's L1 twice: 11008 x 4096 uint4 N = 1024 94.2 -> 92.5 us, 12288 x 4096 uint2 N = 2048 193.5 -> 188.5).  They go
 // from global memory straight into LDS (no registers, no LDS store instruction); such a load writes
-// the 64 lanes' 16 bytes consecutively, i.e. 16 token rows of 64 bytes per wave instruction.  Rows are
-// not padded, so chunk c of token row R is kept at position c ^ ((R >> 2) & 3) of its row: the MFMA
+// the 64 lanes' 16 bytes consecutively, i.e. 8 token rows of 128 bytes per wave instruction.  Rows are
+// not padded, so chunk c of token row R is kept at position c ^ ((R >> 1) & 7) of its row: the MFMA
 // operand reads of 16 consecutive rows then fall into 16 different 16-byte bank groups.  The
 // permutation is applied on the global-address side, where every lane is free to pick its source.
+
+// Stores an fp16 output tile kept in LDS as [token][row]: 16-byte pieces, coalesced.
+template <int TM, int TN, int OUT_ROW, int THREADS>
+__device__ __forceinline__ void store_tile(const GemmArgs& a, const uint8_t* otile, int m0, int n0, int tid) {
+    const bool fast = a.M % 8 == 0 && aligned16(a.y);  // 16-byte aligned rows of y
+    for (int piece = tid; piece < TN * (TM / 8); piece += THREADS) {
+        const int n = piece / (TM / 8), c8 = piece % (TM / 8);
+        const int gn = n0 + n, gm = m0 + c8 * 8;
+        if (gn >= a.N || gm >= a.M) continue;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(otile + n * OUT_ROW + c8 * 16);
+        _Float16* dst = a.y + (size_t)gn * a.M + gm;
+        if (fast && gm + 8 <= a.M) {
+            *reinterpret_cast<u32x4*>(dst) = v;
+        } else {
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            for (int t = 0; t < 8 && gm + t < a.M; ++t)
+                dst[t] = __builtin_bit_cast(_Float16, (uint16_t)(w[t >> 1] >> (16 * (t & 1))));
+        }
+    }
+}
 
 // Workgroup = 12 waves, three per SIMD.  Waves 0..7 are consumers: wave (wm, wn) owns 32 RB rows x 64
 // tokens of the tile and does nothing but read MFMA operands from LDS and issue MFMAs.  Waves 8..11
@@ -121,9 +143,11 @@ __device__ __forceinline__ void load_w(WRegs<B>& r, rsrc_t rw, int tile, int kb3
 // activations.  Vector work of the producers and matrix work of the consumers come from different
 // waves of a SIMD, so the hardware overlaps them without any help from the instruction schedule.
 //
-// Ring protocol, one barrier at the end of every stage s: before it the producers have written stage
+// Ring protocol, one barrier at the end of every stage s: before it the producers have written the weights of stage
 // s+2 and the consumers have finished reading stage s.  Hence consumers may prefetch operands of stage
-// s+1 during stage s, and the buffer written during stage s (stage s+2) was last read in stage s-2.
+// s+1 during stage s, and the buffer written during stage s (stage s+2) was last read in stage s-1.  The activations
+// of pair P+2 are requested in stages 2P and 2P+1, whose buffer was last read in stage 2P-1, and are in by the end of stage
+// 2P+2, before the first prefetch from them.
 // The producers hold the global loads of four further stages in registers: at the rates of this kernel
 // that many bytes in flight are needed to cover the latency of HBM and L2.
 constexpr int kConsumerWaves = 8;
@@ -182,18 +206,22 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
         // cycles each) and the dequantizing waves none, which shortens the chain that gates a stage.
         constexpr bool kSplitRoles = RB < 4;
         constexpr int kLoaderWave = 3;
-        constexpr int kXAll = kTN / 16;  // activation loads of a stage (16 token rows each)
-        const uint32_t xlane = ((lane >> 2) * (uint32_t)a.K + ((lane & 3) ^ ((lane >> 4) & 3)) * 8u) * 2u;
-        const uint32_t x16rows = 16u * (uint32_t)a.K * 2u;  // bytes between the sources of consecutive loads
-        // load number i of a stage fills token rows 16 i .. 16 i + 15; lane = 4 * row + position
-        auto load_x = [&](int t, int first, int count) {
-            const rsrc_t rx = make_rsrc(xsrc, t < k_stages ? xbytes : 0u);
-            uint8_t* dst = smem + (t & (kRing - 1)) * T::StageBytes + T::WBytes;
+        constexpr int kXAll = kTN / 16;  // activation loads per stage, half of a pair's (8 token rows each)
+        const uint32_t xlane = (uint32_t)(lane >> 3) * (uint32_t)a.K * 2u;
+        const uint32_t xsrc_chunk[2] = {(uint32_t)((lane & 7) ^ (lane >> 4)) * 16u, (uint32_t)((lane & 7) ^ (4 + (lane >> 4))) * 16u};
+        const uint32_t x8rows = 8u * (uint32_t)a.K * 2u;  // bytes between the sources of consecutive loads
+        uint8_t* const xring = smem + kRing * T::WBytes;
+        // load number i of a pair of stages fills token rows 8 i .. 8 i + 7; lane = 8 * row + position; `first` is even.
+        // (Columns beyond K in the last pair belong to a stage that is not multiplied.)
+        auto load_x = [&](int pair, int first, int count) {
+            const rsrc_t rx = make_rsrc(xsrc, 2 * pair < k_stages ? xbytes : 0u);
+            uint8_t* dst = xring + (uint32_t)pair % kRing * T::XBytes;
 #pragma unroll
-            for (int i = 0; i < kXAll; ++i)
+            for (int i = 0; i < 2 * kXAll; ++i)
                 if (i < count)
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + (first + i) * 1024),
-                                                             16, xlane + (uint32_t)(first + i) * x16rows, t * kStageK * 2, 0, 0);
+                                                             16, xlane + xsrc_chunk[i & 1] + (uint32_t)(first + i) * x8rows,
+                                                             pair * kStageK * 4, 0, 0);
         };
         const int wdst = (pb * 64 + lane) * kRowBytes;  // this lane's 64 bytes in the weight tile
 
@@ -203,22 +231,23 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
             load_w<B, GQ, HZ>(wr[set], make_rsrc(wsrc, t < k_stages && wvalid ? 0x7fffffffu : 0u), t >> 2, t & 3, lane);
         };
         auto w_to_lds = [&](int set, int t) {
-            if (p < RB) dequant_to_lds<B, HZ>(wr[set], smem + (t & (kRing - 1)) * T::StageBytes + wdst);
+            if (p < RB) dequant_to_lds<B, HZ>(wr[set], smem + (uint32_t)t % kRing * T::WBytes + wdst);
         };
-        // Ring timing, any role: during stage s the activations of stage s+3 are requested (that buffer
-        // was last read in stage s-1), the weights of stage s+2 go registers -> ring and the weights of
-        // stage s+6 global -> the same registers.  Loads complete in order.  Before the barrier of stage
-        // s the activations of stage s+2 must have landed; they were issued first in stage s-1.
+        // Ring timing, any role: during stage s half of the activations of pair s/2 + 2 are requested, the weights of stage s+2
+        // go registers -> ring and the weights of stage s+6 global -> the same registers.  Loads complete in order.  Before
+        // the barrier of an even stage s the activations of pair s/2 + 1 must have landed; their second half was issued first
+        // in stage s-1.
         if (kSplitRoles && p == kLoaderWave) {
-            load_x(0, 0, kXAll);
-            load_x(1, 0, kXAll);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            load_x(2, 0, kXAll);
+            load_x(0, 0, 2 * kXAll);
+            load_x(1, 0, 2 * kXAll);
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kXAll) : "memory");
             asm volatile("s_barrier" ::: "memory");
-            for (int s = 0; s < n_stages; ++s) {
-                load_x(s + 3, 0, kXAll);
-                // younger than the loads of stage s+2: the sixteen just issued
-                asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
+            for (int s = 0; s < n_stages; s += 2) {
+                load_x(s / 2 + 2, 0, kXAll);
+                // younger than the loads of pair s/2 + 1: the sixteen just issued
+                asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kXAll) : "memory");
+                load_x(s / 2 + 2, kXAll, kXAll);
+                asm volatile("s_barrier" ::: "memory");
             }
         } else if constexpr (RB == 1) {
             if (p < 2) {
@@ -239,7 +268,7 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
                     dq.insert();
                 };
                 auto second_half = [&](int t) {
-                    uint8_t* dst = wrow + (t & (kRing - 1)) * T::StageBytes;
+                    uint8_t* dst = wrow + (uint32_t)t % kRing * T::WBytes;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) dq.emit(q, dst);
                 };
@@ -318,10 +347,9 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
                 }
             }
         } else {
-            // prologue: stages 0 and 1 complete in the ring, activations of stage 2 on their way, weights
-            // of stages 2..5 in the register sets 2, 3, 0, 1
-            load_x(0, 4 * p, 4);
-            load_x(1, 4 * p, 4);
+            // prologue: stages 0 and 1 complete in the ring, activations of pair 1 on their way, weights
+            // of stages 2..5 in the register sets 2, 3, 0, 1.  Of a pair this wave issues loads 8 p .. 8 p + 7.
+            load_x(0, 8 * p, 8);
             load_wregs(0, 0);
             load_wregs(1, 1);
             load_wregs(2, 2);
@@ -330,7 +358,7 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
             w_to_lds(1, 1);
             __builtin_amdgcn_sched_barrier(0);
             asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // all but the weights of stages 2 and 3 (two loads each)
-            load_x(2, 4 * p, 4);
+            load_x(1, 8 * p, 8);
             load_wregs(0, 4);
             load_wregs(1, 5);
             __builtin_amdgcn_sched_barrier(0);
@@ -338,15 +366,16 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
             for (int s = 0; s < n_stages; s += kSets) {
 #pragma unroll
                 for (int u = 0; u < kSets; ++u) {
-                    load_x(s + u + 3, 4 * p, 4);
+                    load_x((s + u) / 2 + 2, 8 * p + (u & 1) * 4, 4);
                     __builtin_amdgcn_sched_barrier(0);
                     w_to_lds((u + 2) % kSets, s + u + 2);
                     __builtin_amdgcn_sched_barrier(0);
                     load_wregs((u + 2) % kSets, s + u + 6);
                     __builtin_amdgcn_sched_barrier(0);
-                    // younger than the activation loads of stage s+2: 2 weight loads of stage s-1, 4
+                    // even stages: younger than the activation loads of pair s/2 + 1: 2 weight loads of stage s-1, 4
                     // activation loads and 2 weight loads of stage s
-                    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                    if (u & 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                    else asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
                 }
             }
         }
@@ -357,9 +386,9 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
         // ---------------------------------------------------------------- consumer
         // MFMA operand addresses: lanes with h = 0 / 1 take the two 8-column groups of a 16-column step
         const int wfrag = (wm * RB * 32 + r) * kRowBytes + h * 16;
-        // activation operand: token row wn * 64 + nb * 32 + r, chunk 2j + h, kept at chunk ^ ((r >> 2) & 3)
-        const int xrow = T::WBytes + (wn * 64 + r) * (kStageK * 2);
-        const int xchunk[2] = {xrow + ((h ^ ((r >> 2) & 3)) * 16), xrow + (((2 + h) ^ ((r >> 2) & 3)) * 16)};
+        // activation operand: token row wn * 64 + nb * 32 + r, chunk 4 (stage % 2) + 2j + h, kept at chunk ^ ((r >> 1) & 7)
+        const int xrow = (wn * 64 + r) * (kStageK * 4);
+        const int xchunk[2] = {xrow + ((h ^ ((r >> 1) & 7)) * 16), xrow + (((2 + h) ^ ((r >> 1) & 7)) * 16)};
         // Operand registers: one weight operand per 32-row block, reloaded for the next 16-column step
         // as soon as its two MFMAs are issued (so the read has the other blocks' MFMAs to land), and two
         // pairs of activation operands (this step's and the next one's).
@@ -367,24 +396,28 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
         auto read_w = [&](int mb, const uint8_t* stage, int j) {
             wf[mb] = *reinterpret_cast<const half8_t*>(stage + wfrag + mb * 32 * kRowBytes + j * 32);
         };
-        auto read_x = [&](int set, const uint8_t* stage, int j) {
+        // `pair`: LDS of the pair of stages, `odd`: 64 for its second stage
+        auto read_x = [&](int set, const uint8_t* pair, int odd, int j) {
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
-                xf[set][nb] = *reinterpret_cast<const half8_t*>(stage + xchunk[j] + nb * 32 * (kStageK * 2));
+                xf[set][nb] = *reinterpret_cast<const half8_t*>(pair + (xchunk[j] ^ odd) + nb * 32 * (kStageK * 4));
         };
+        int w_at = 0, x_at = kRing * T::WBytes;  // LDS of this stage's weights and of its pair's activations
         __syncthreads();
-        read_x(0, smem, 0);
+        read_x(0, smem + x_at, 0, 0);
 #pragma unroll
-        for (int mb = 0; mb < RB; ++mb) read_w(mb, smem, 0);
+        for (int mb = 0; mb < RB; ++mb) read_w(mb, smem + w_at, 0);
         for (int s = 0; s < k_stages; ++s) {
-            const uint8_t* cur = smem + (s & (kRing - 1)) * T::StageBytes;
-            const uint8_t* nxt = smem + ((s + 1) & (kRing - 1)) * T::StageBytes;
+            const int odd = (s & 1) * 64;
+            const int w_next = w_at == (kRing - 1) * T::WBytes ? 0 : w_at + T::WBytes;
+            const int x_pair = x_at == kRing * T::WBytes + (kRing - 1) * T::XBytes ? kRing * T::WBytes : x_at + T::XBytes;
+            const int x_next = odd ? x_pair : x_at;
+            const uint8_t *w_cur = smem + w_at, *w_nxt = smem + w_next, *x_cur = smem + x_at, *x_nxt = smem + x_next;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 // operands after this step: step 1 of this stage, or step 0 of stage s+1, which is complete
                 // in the ring (past the last stage this reads stale LDS that is never used)
-                const uint8_t* ahead = j == 0 ? cur : nxt;
-                read_x(j ^ 1, ahead, j ^ 1);
+                read_x(j ^ 1, j == 0 ? x_cur : x_nxt, j == 0 ? odd : odd ^ 64, j ^ 1);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int mb = 0; mb < RB; ++mb) {
@@ -392,10 +425,12 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
                     for (int nb = 0; nb < 2; ++nb)
                         acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[mb], xf[j][nb], acc[mb][nb], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    read_w(mb, ahead, j ^ 1);
+                    read_w(mb, j == 0 ? w_cur : w_nxt, j ^ 1);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            w_at = w_next;
+            x_at = x_next;
             // Plain barrier: this wave has no LDS writes to publish, and its outstanding reads (stage
             // s+1) need not land before it; everything it read from stage s has been consumed.
             asm volatile("s_barrier" ::: "memory");
@@ -429,22 +464,7 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
             }
     }
     __syncthreads();
-    const int m0 = mt * T::TM;
-    const bool fast = a.M % 8 == 0 && aligned16(a.y);  // 16-byte aligned rows of y
-    for (int piece = tid; piece < kTN * (T::TM / 8); piece += kThreads) {
-        const int n = piece / (T::TM / 8), c8 = piece % (T::TM / 8);
-        const int gn = n0 + n, gm = m0 + c8 * 8;
-        if (gn >= a.N || gm >= a.M) continue;
-        const u32x4 v = *reinterpret_cast<const u32x4*>(otile + n * T::OutRow + c8 * 16);
-        _Float16* dst = a.y + (size_t)gn * a.M + gm;
-        if (fast && gm + 8 <= a.M) {
-            *reinterpret_cast<u32x4*>(dst) = v;
-        } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-            for (int t = 0; t < 8 && gm + t < a.M; ++t)
-                dst[t] = __builtin_bit_cast(_Float16, (uint16_t)(w[t >> 1] >> (16 * (t & 1))));
-        }
-    }
+    store_tile<T::TM, kTN, T::OutRow, kThreads>(a, otile, mt * T::TM, n0, tid);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -705,6 +725,182 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Grids that fill the chip with 256-row workgroups: no weight tile in LDS, no producer waves.  A wave owns 64 rows x 32 TT
+// tokens and dequantizes its own weights in registers, block by block per lane as in the K-split kernel; the activations of a
+// 64-column stage (whole cache lines) are shared by the four waves through LDS.  Two workgroups share a compute unit.
+// 96 tokens: with 128 the accumulators, the activations of a stage and the weights in flight do not fit 256 registers.
+// What bounds it: products plus vector work at the clock the chip holds under both (8 vector instructions per product, about 6
+// hide behind one).  11008 x 4096 4 bits, N = 1024: 104 us = 0.89 PFLOP/s (tiled, 192 x 256: 96); its grain is half as large.
+constexpr int kWideRing = 4;   // stage buffers
+constexpr int kWideRows = 256;
+template <int TT>
+struct WideTile {
+    static constexpr int TN = 32 * TT;
+    static constexpr int XBytes = TN * kKsStageK * 2;
+    static constexpr int XLoads = TT;                  // requests of a stage per wave (8 token rows each)
+    static constexpr int OutRow = kWideRows * 2 + 16;  // bytes per token of the output tile in LDS
+    static constexpr int LdsBytes = kWideRing * XBytes > TN * OutRow ? kWideRing * XBytes : TN * OutRow;
+};
+
+template <int B, int GQ, bool HZ, int TT>
+__global__ void __launch_bounds__(256, 2) mpgemm_wide_kernel(GemmArgs a) {
+    using T = WideTile<TT>;
+    constexpr int MSZ = HZ ? 4 : 2;
+    constexpr int TB = B * 1024 + 64 * (kKTile / GQ) * MSZ;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+
+    int mt, nt;
+    tile_of_workgroup(a, mt, nt);
+    const bool header_ok = header_matches(a.tiles, a.M, a.K, B, GQ, HZ ? 1 : 0);
+    if (!header_ok && blockIdx.x == 0 && threadIdx.x == 0) report_header_mismatch(a.status);
+    if (mt >= (header_ok ? a.m_tiles : 0)) return;
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int n0 = nt * T::TN;
+    // the loop runs an even number of stages (a stage past K has empty sources: zero weights, zero activations)
+    const int k_stages = (a.K + kKsStageK - 1) / kKsStageK, n_stages = (k_stages + 1) & ~1;
+    const int r = lane & 31, h = lane >> 5;
+
+    float16_t acc[2][TT];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int nb = 0; nb < TT; ++nb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[u][nb][v] = 0.f;
+
+    const int rb = mt * 4 + wave;
+    const bool wvalid = rb < a.n_row_blocks;
+    const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rb : 0) * a.n_ktiles * TB;
+    WRegs<B> wr[2][2];  // [set][row unit]
+    auto load_unit = [&](int set, int unit, int t) {
+        load_w_block<B, GQ, HZ>(wr[set][unit], make_rsrc(wsrc, t < k_stages && wvalid ? 0x7fffffffu : 0u), t, unit * 32 + r, h);
+    };
+    // activations: wave w issues requests w, w + 4, ... of a stage; chunks placed as in the K-split kernel
+    const int xrows = a.N - n0 < T::TN ? a.N - n0 : T::TN;
+    const _Float16* xsrc = a.x + (size_t)n0 * a.K;
+    const uint32_t xbytes = (uint32_t)xrows * (uint32_t)a.K * 2u;
+    const uint32_t xchunk = (uint32_t)((lane & 7) ^ ((wave & 1) * 4 + (lane >> 4))) * 16u;
+    const uint32_t xlane = (uint32_t)(wave * 8 + (lane >> 3)) * (uint32_t)a.K * 2u + xchunk, x32rows = 32u * (uint32_t)a.K * 2u;
+    auto load_x = [&](int t) {
+        const rsrc_t rx = make_rsrc(xsrc, t < k_stages ? xbytes : 0u);
+        uint8_t* dst = smem + (t & (kWideRing - 1)) * T::XBytes;
+#pragma unroll
+        for (int i = 0; i < T::XLoads; ++i) {
+            uint32_t off = xlane + (uint32_t)i * x32rows;
+            if constexpr (GQ == 32) off = t * kKsStageK + (int)(xchunk / 2) < a.K ? off : 0xFFFFFF00u;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + (wave + 4 * i) * 1024), 16, off,
+                                                     t * kKsStageK * 2, 0, 0);
+        }
+    };
+    int xoff[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) xoff[j] = r * (kKsStageK * 2) + ((4 * h + j) ^ ((r >> 1) & 7)) * 16;
+    half8_t xf[4][TT];
+    auto read_x = [&](int j, const uint8_t* stage) {
+#pragma unroll
+        for (int nb = 0; nb < TT; ++nb)
+            xf[j][nb] = *reinterpret_cast<const half8_t*>(stage + xoff[j] + nb * 32 * (kKsStageK * 2));
+    };
+    half8_t wf[2][4];  // [row unit][step]
+    Dequant<B, HZ> dq;
+    auto dequant_part = [&](int j, int set, int unit) {
+        if (j == 0) {
+            dq.start(wr[set][unit]);
+        } else if (j == 1) {
+            dq.insert();
+        } else {
+#pragma unroll
+            for (int q = 2 * j - 4; q < 2 * j - 2; ++q) wf[unit][q] = __builtin_bit_cast(half8_t, dq.piece(q));
+        }
+    };
+
+    // Requests in the order of the loop, whose waits count them: per stage the activations of stage s + 3, the weights of row
+    // unit 1 of stage s + 2 and of unit 0 of stage s + 3.
+    load_unit(0, 0, 0);
+    load_unit(0, 1, 0);
+    load_unit(1, 0, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    load_x(0);
+    load_x(1);
+    __builtin_amdgcn_sched_barrier(0);
+    load_x(2);
+    __builtin_amdgcn_sched_barrier(0);
+    load_unit(1, 1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dequant_part(j, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_unit(0, 0, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    // the activations of stages 0 and 1 are in
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(T::XLoads + 4) : "memory");
+#pragma unroll
+    for (int j = 0; j < 4; ++j) read_x(j, smem);
+
+    for (int s0 = 0; s0 < n_stages; s0 += 2) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int t = s0 + s;
+            const uint8_t* nxt = smem + ((t + 1) & (kWideRing - 1)) * T::XBytes;
+            load_x(t + 3);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                // the products of row unit u; meanwhile the vector work of the next unit, and beside the last one the activations
+                // of stage t + 1, each as soon as its registers are used
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    dequant_part(j, u ? (s + 1) & 1 : s, u ^ 1);
+#pragma unroll
+                    for (int nb = 0; nb < TT; ++nb)
+                        acc[u][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[u][j], xf[j][nb], acc[u][nb], 0, 0, 0);
+                    if (u == 1) read_x(j, nxt);
+#pragma unroll
+                    for (int q = 0; q < TT; ++q) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, (24 + TT - 1) / TT, 0);
+                        if (u == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (u == 0) load_unit(s, 1, t + 2);
+                else load_unit((s + 1) & 1, 0, t + 3);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // the activations of stage t + 2 (requested one stage ago) are in before any wave goes on: younger are the weights
+            // requested then and what this stage requested
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(T::XLoads + 8) : "memory");
+        }
+    }
+    // requests of stages past the end may still be writing zeros to the ring, which the output tile reuses
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+
+    // epilogue: C[i][j] of a 32 x 32 tile: i = row 8 (v / 4) + 4 h + v % 4, j = token lane % 32
+    uint8_t* otile = smem;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int nb = 0; nb < TT; ++nb) {
+            uint8_t* col = otile + (nb * 32 + r) * T::OutRow + (wave * 64 + u * 32 + 4 * h) * 2;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                half2_t lo, hi;
+                lo.x = (_Float16)acc[u][nb][4 * g + 0];
+                lo.y = (_Float16)acc[u][nb][4 * g + 1];
+                hi.x = (_Float16)acc[u][nb][4 * g + 2];
+                hi.y = (_Float16)acc[u][nb][4 * g + 3];
+                u32x2 w = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+                *reinterpret_cast<u32x2*>(col + g * 16) = w;  // rows 8g + 4h + 0..3
+            }
+        }
+    __syncthreads();
+    store_tile<kWideRows, T::TN, T::OutRow, 256>(a, otile, mt * kWideRows, n0, tid);
+}
+
 static int compute_units() {
     static std::once_flag once;
     static int n_cu = 256;  // assumed when no device answers
@@ -750,6 +946,23 @@ static int launch_ksplit(GemmArgs a, hipStream_t st) {
     return launch_status();
 }
 
+template <int B, int GQ, bool HZ, int TT>
+static int launch_wide(GemmArgs a, hipStream_t st) {
+    using T = WideTile<TT>;
+    static std::once_flag once;
+    static hipError_t attr_rc = hipSuccess;
+    std::call_once(once, [] {
+        attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&mpgemm_wide_kernel<B, GQ, HZ, TT>),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, T::LdsBytes);
+    });
+    if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
+    a.m_tiles = (a.n_row_blocks + 3) / 4;
+    a.n_tiles = (a.N + T::TN - 1) / T::TN;
+    const unsigned grid = deal_tiles(a, false);
+    hipLaunchKernelGGL((mpgemm_wide_kernel<B, GQ, HZ, TT>), dim3(grid), dim3(256), T::LdsBytes, st, a);
+    return launch_status();
+}
+
 template <int B, int GQ, bool HZ, int RB>
 static int launch_tile(GemmArgs a, hipStream_t st) {
     // once per kernel instantiation, also when several host threads make their first call together
@@ -767,18 +980,24 @@ static int launch_tile(GemmArgs a, hipStream_t st) {
     return launch_status();
 }
 
-// Which kernel and tile: 1 .. 4 = the tiled kernel with that many row blocks per workgroup; the others = the K-split
-// kernel with 64 rows x 256 tokens, 128 x 128, 64 x 128, and 64 x 64 (four or eight waves).
+// Which kernel and tile: 1 .. 4 = the tiled kernel with that many row blocks per workgroup; kWide = the kernel without a weight
+// tile, 256 rows x 96 tokens; the others = the K-split kernel with 64 rows x 256 tokens, 128 x 128, 64 x 128, and 64 x 64
+// (four or eight waves).
 //
-// The choice models the time of the grid each of them gives: rounds of workgroups over the compute units, each round
-// a fixed part (prologue, exchange of the partial sums) and a part in proportion to K.  The constants are microseconds
-// measured at K = 1024 .. 11008 on 256 units: a round of 64 x 64 workgroups takes 16 us at K = 4096 (two share a unit:
-// 26 us, three 38, four 50), of 64 x 128 22 us, of 128 x 128 35 us, of the tiled kernel 25 us per row block (with a
-// small penalty for small tiles: more operand reads and dequantization per MFMA).  So short prompts, whose 256-token
-// tiles are mostly padding, and grids that leave units idle go to the narrow tiles (4096 x 11008, N = 173: 94 -> 37
-// us; 11008 x 4096, N = 64: 30 -> 19 us; 28672 x 4096, N = 64: 58 -> 31 us), large grids to the tiled kernel.  One
-// row block per workgroup of the tiled kernel (25 % slower per column, but without exchange) is left for short K.
-constexpr int kSplitWide = 5, kSplitTall = 6, kSplit128 = 7, kSplit64 = 8, kSplit64x8 = 9;
+// The choice models the time of the grid each of them gives, in microseconds on 256 units: rounds of workgroups over the units,
+// each a fixed part (prologue, exchange of the partial sums) and a part in proportion to K.  A last round that leaves units
+// idle takes less, because the clock is higher then: a share `alone` with few workgroups, the whole with all units busy.
+// Measured (64 / 128 / 192 / 256 / 320 / 512 / 768 workgroups, K = 4096, 4 bits, blocks of 64):
+//   tiled, 256 x 256   90 / 93 / 110
+//   tiled, 192 x 256   73 / 79 / 90 / 106 / 175 / 214        K-split, 128 x 128   30 / 33 / 37 / 43 / 68 / 83 / 122
+//   tiled, 128 x 256   61 / 61 / 68 / 83 / 139 / 162 / 242   K-split, 64 x 128    19 / 20 / 22 / 26 / 41 / 51 / 74
+//   tiled, 64 x 256    38 / 40 / 42 / 49 / 85 / 100 / 146    K-split, 64 x 64     14 / 15 / 15 / 16 / 24 / 30 / 43
+//   wide, 256 x 96     50 / 52 / 55 / 64 / 92 / 115 / 173    ... eight waves      14 / 15 / 15 / 18 / 29 / 36 / 52
+// So short prompts, whose 256-token tiles are mostly padding, and grids that leave units idle go to the narrow tiles, large grids
+// to 192 x 256 or, where its rounds fit better, to the wide kernel (12288 x 4096, N = 1500: 175 us tiled, 161 wide; 9000 x 2048
+// 2 bits, N = 1300: 80 and 54; 256 x 256 tiles 58).  64 x 256 of the K-split kernel is only taken where the tiling asks for it.  Eight waves for 64 x 64 pay from a K of 8192 on (11008: 29.1 / 29.7 / 32.0 / 37.9 us
+// against 30.4 / 32.0 / 33.4 / 38.3).
+constexpr int kSplitWide = 5, kSplitTall = 6, kSplit128 = 7, kSplit64 = 8, kSplit64x8 = 9, kWide = 10;
 static int choose_tile(int n_row_blocks, int N, int K) {
     const int n_cu = compute_units();
     const tman_tiling_t t = current_tiling();
@@ -786,26 +1005,27 @@ static int choose_tile(int n_row_blocks, int N, int K) {
     if (t.prefill_k_split == 3) return kSplitTall;
     const int forced = t.prefill_row_blocks;
     if (forced >= 1 && forced <= 4) return forced;
-    // rounds over the units of a grid of `rows` row blocks x `tokens` tokens per workgroup
-    auto rounds = [&](int rows, int tokens) {
-        const long long wgs = (long long)((n_row_blocks + rows - 1) / rows) * ((N + tokens - 1) / tokens);
-        return (double)((wgs + n_cu - 1) / n_cu);
-    };
-    const double k = K / 4096.0, penalty[5] = {0, 0, 1.10, 1.03, 1.0};
-    int best = 4;
+    const double k = K / 4096.0;
+    int best = 3;
     double best_cost = 1e30;
-    auto consider = [&](int choice, double cost) {
+    auto consider = [&](int choice, int rows, int tokens, double fixed, double per_k, double alone) {
+        const long long wgs = (long long)((n_row_blocks + rows - 1) / rows) * ((N + tokens - 1) / tokens);
+        const double full = (double)(wgs / n_cu), rest = (double)(wgs % n_cu) / n_cu;
+        const double part = rest > 0 ? alone + (1.0 - alone) * rest * rest : 0.0;
+        const double cost = (full + (rest > 0)) * fixed + (full + part) * per_k * k;
         if (cost < best_cost) best_cost = cost, best = choice;
     };
-    for (int rb = 4; rb >= 2; --rb) consider(rb, rounds(rb, kTN) * rb * penalty[rb] * (25.0 * k + 1.0));
-    if (rounds(1, kTN) <= 1.0) consider(1, 38.0 * k + 3.0);
-    if (t.prefill_k_split == 1 || K < 1024) return best;  // (short K: nothing to split)
-    consider(kSplitTall, rounds(2, 128) * (27.0 * k + 8.8));
-    consider(kSplit128, rounds(1, 128) * (18.5 * k + 4.0));
-    const double r64 = rounds(1, 64);
-    // eight waves pay from 32 stages per wave on; with more than one workgroup per unit four are as good
-    consider(r64 <= 1.0 && K >= 3072 ? kSplit64x8 : kSplit64, r64 <= 1.0 ? 12.0 * k + 5.0 : r64 * 11.3 * k + 5.0);
-    return best;
+    consider(3, 3, kTN, 4.5, 99.0, 0.67);
+    consider(4, 4, kTN, 5.0, 130.0, 0.64);
+    consider(2, 2, kTN, 3.5, 75.0, 0.71);
+    consider(1, 1, kTN, 2.0, 45.0, 0.73);
+    consider(kWide, 4, 96, 3.0, 54.0, 0.72);
+    if (t.prefill_k_split == 1 || K <= 512) return best;  // (short K: nothing to split)
+    consider(kSplitTall, 2, 128, 5.5, 34.6, 0.64);
+    consider(kSplit128, 1, 128, 5.0, 18.7, 0.68);
+    consider(kSplit64, 1, 64, 2.0, 11.8, 0.75);
+    const long long wgs64 = (long long)n_row_blocks * ((N + 63) / 64);
+    return best == kSplit64 && wgs64 <= n_cu && K >= 8192 ? kSplit64x8 : best;
 }
 
 template <int B, int GQ, bool HZ>
@@ -816,6 +1036,7 @@ static int launch_cfg(const GemmArgs& a, hipStream_t st) {
         case kSplit128: return launch_ksplit<B, GQ, HZ, 1, 4, 4>(a, st);
         case kSplit64: return launch_ksplit<B, GQ, HZ, 1, 2, 4>(a, st);
         case kSplit64x8: return launch_ksplit<B, GQ, HZ, 1, 2, 8>(a, st);
+        case kWide: return launch_wide<B, GQ, HZ, 3>(a, st);
         case 1: return launch_tile<B, GQ, HZ, 1>(a, st);
         case 2: return launch_tile<B, GQ, HZ, 2>(a, st);
         case 3: return launch_tile<B, GQ, HZ, 3>(a, st);
@@ -834,9 +1055,12 @@ static int launch_group(int group, const GemmArgs& a, hipStream_t st) {
 
 int mpgemm_row_blocks_per_workgroup(const Layout& L, int N) {
     const int c = choose_tile(L.n_row_blocks, N, L.K);
-    return c == kSplitTall ? 2 : c >= kSplitWide ? 1 : c;
+    return c == kWide ? 4 : c == kSplitTall ? 2 : c >= kSplitWide ? 1 : c;
 }
-int mpgemm_splits_k(const Layout& L, int N) { return choose_tile(L.n_row_blocks, N, L.K) >= kSplitWide; }
+int mpgemm_splits_k(const Layout& L, int N) {
+    const int c = choose_tile(L.n_row_blocks, N, L.K);
+    return c >= kSplitWide && c != kWide;
+}
 
 int launch_mpgemm(const Layout& L, const void* packed, const void* x, int N, void* y, void* workspace,
                   hipStream_t st) {

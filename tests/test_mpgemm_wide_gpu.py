@@ -1,0 +1,98 @@
+"""The prefill kernel without a weight tile (256 rows x 96 tokens per workgroup), which the launcher takes where the rounds of
+its grid fit better, and the K-split tiles around the ends of K: ragged rows and tokens, K of half a 64-column stage, of one
+stage, of an odd number of stages, and the longest K, where eight waves share it."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2511_11248_amd as tman
+from gpu_helpers import TOL, dev, mpgemm, pack, rand_case, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _against_tiled(shape, blob, x, y):
+    """Every output against the tiled kernel: the same products, sums in another order (fp32, then one rounding)."""
+    t = tman.tman_get_tiling()
+    try:
+        tiled = tman.tman_get_tiling()
+        tiled.prefill_row_blocks = 2
+        tman.tman_set_tiling(tiled)
+        other = mpgemm(shape, blob, x).astype(np.float64)
+    finally:
+        tman.tman_set_tiling(t)
+    rms = np.sqrt(np.mean(other ** 2, axis=1, keepdims=True))
+    assert np.all(np.abs(y - other) <= 2.0 ** -10 * np.maximum(np.abs(other), rms))
+
+
+@pytest.mark.parametrize("M,K,bits,group,hz,N", [
+    (21700, 160, 4, 32, True, 288),   # two and a half stages
+    (21760, 32, 2, 32, True, 97),     # half a stage
+    (21505, 64, 1, 64, False, 193),   # one stage; the last row block has one row
+    (21760, 192, 1, 32, True, 285),   # three stages
+    (21698, 384, 4, 128, True, 96),
+    (21700, 96, 2, 32, True, 191),
+])
+def test_wide_tiles(oracle_lib, M, K, bits, group, hz, N):
+    q, s, z, x = rand_case(8100 + M + K + bits + N, M, K, N, bits, group, hz)
+    shape = tman.Shape(M, K, bits, group, hz)
+    assert tman.tman_mpgemm_splits_k(shape, N) == 0 and tman.tman_mpgemm_tile_rows(shape, N) == 256
+    blob = pack(shape, q, s, z)
+    # the activations lie between values that are not finite: a column beyond K that is multiplied would show
+    xbig = torch.full((512 + N * K + 70000,), float("nan"), dtype=torch.float16, device=dev())
+    xbig[512:512 + N * K] = to_dev(x).reshape(-1)
+    y = mpgemm(shape, blob, xbig[512:512 + N * K].view(N, K))
+    assert np.all(np.isfinite(y.astype(np.float32)))
+    tokens = np.unique([0, 31, 32, 95, N // 2, N - 1])
+    assert oracle.row_relative_error(y[tokens], oracle.matmul(q, s, z, x[tokens], bits, group)).max() <= TOL
+    _against_tiled(shape, blob, x, y)
+
+
+@pytest.mark.parametrize("M,K,bits,group,hz,N", [
+    (130, 544, 4, 32, True, 70),      # eight and a half stages over four waves
+    (64, 576, 2, 64, True, 64),       # nine stages
+    (65, 608, 1, 32, False, 129),
+    (100, 640, 1, 32, True, 40),
+    (64, 8192, 4, 64, True, 65),      # eight waves, 16 stages each
+    (70, 8224, 4, 32, True, 33),      # ... and half a stage
+    (65, 11008, 2, 128, True, 100),
+])
+def test_k_split_ends_of_k(oracle_lib, M, K, bits, group, hz, N):
+    q, s, z, x = rand_case(8500 + M + K + bits + N, M, K, N, bits, group, hz)
+    shape = tman.Shape(M, K, bits, group, hz)
+    assert tman.tman_mpgemm_splits_k(shape, N) == 1
+    blob = pack(shape, q, s, z)
+    y = mpgemm(shape, blob, x)
+    assert oracle.row_relative_error(y, oracle.matmul(q, s, z, x, bits, group)).max() <= TOL
+    _against_tiled(shape, blob, x, y)
+
+
+@pytest.mark.parametrize("blocks", [1, 3, 4, 7, 9])
+@pytest.mark.parametrize("M,K,bits,group,hz,N", [
+    (70, 160, 4, 32, True, 100),      # a tile and a quarter
+    (300, 1056, 2, 32, True, 230),    # nine tiles, the last with one block
+    (257, 640, 1, 64, False, 129),    # five tiles: the loop of two runs one past the end
+    (64, 2304, 4, 128, True, 33),     # 18 tiles over four waves
+])
+def test_int8_kernels_give_the_same_bits(oracle_lib, blocks, M, K, bits, group, hz, N):
+    q, s, z, x = rand_case(8900 + M + K + bits + N, M, K, N, bits, group, hz)
+    s = np.repeat(s[:, :1], K // group, axis=1)
+    z = np.repeat(z[:, :1], K // group, axis=1) if hz else None
+    shape = tman.Shape(M, K, bits, group, hz)
+    blob = pack(shape, q, s, z)
+    xq = torch.empty(tman.tman_act_i8_bytes(N, K), dtype=torch.uint8, device=dev())
+    tman.tman_quantize_act_i8(to_dev(x), N, K, xq)
+    codes, _ = oracle.quantize_activations_i8(x)
+    y = torch.empty((N, M), dtype=torch.float16, device=dev())
+    acc = torch.empty((N, M), dtype=torch.int32, device=dev())
+    t = tman.tman_get_tiling()
+    try:
+        forced = tman.tman_get_tiling()
+        forced.i8_token_blocks = blocks
+        tman.tman_set_tiling(forced)
+        tman.tman_mpgemm_i8(shape, blob, xq, N, y, acc)
+    finally:
+        tman.tman_set_tiling(t)
+    torch.cuda.synchronize()
+    assert np.array_equal(acc.cpu().numpy(), codes.astype(np.int64) @ q.astype(np.int64).T)

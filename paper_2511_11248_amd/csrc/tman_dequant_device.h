@@ -140,4 +140,35 @@ __device__ __forceinline__ void dequant_to_lds(const WRegs<B>& r, uint8_t* wrow)
     for (int q = 0; q < 4; ++q) dq.emit(q, wrow);
 }
 
+// Stores an fp16 output tile kept in LDS as [token][row]: 16-byte pieces, coalesced.  A whole tile of an aligned output takes four
+// pieces of a thread at a time, so that their reads and stores overlap.
+template <int TM, int TN, int OUT_ROW, int THREADS>
+__device__ __forceinline__ void store_tile(_Float16* y, int M, int N, const uint8_t* otile, int m0, int n0, int tid) {
+    constexpr int kPieces = TN * (TM / 8);
+    const bool fast = M % 8 == 0 && aligned16(y);  // 16-byte aligned rows of y
+    if (fast && m0 + TM <= M && n0 + TN <= N) {
+#pragma unroll 4
+        for (int piece = tid; piece < kPieces; piece += THREADS) {
+            const int n = piece / (TM / 8), c8 = piece % (TM / 8);
+            *reinterpret_cast<u32x4*>(y + (size_t)(n0 + n) * M + m0 + c8 * 8) =
+                *reinterpret_cast<const u32x4*>(otile + n * OUT_ROW + c8 * 16);
+        }
+        return;
+    }
+    for (int piece = tid; piece < kPieces; piece += THREADS) {
+        const int n = piece / (TM / 8), c8 = piece % (TM / 8);
+        const int gn = n0 + n, gm = m0 + c8 * 8;
+        if (gn >= N || gm >= M) continue;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(otile + n * OUT_ROW + c8 * 16);
+        _Float16* dst = y + (size_t)gn * M + gm;
+        if (fast && gm + 8 <= M) {
+            *reinterpret_cast<u32x4*>(dst) = v;
+        } else {
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            for (int t = 0; t < 8 && gm + t < M; ++t)
+                dst[t] = __builtin_bit_cast(_Float16, (uint16_t)(w[t >> 1] >> (16 * (t & 1))));
+        }
+    }
+}
+
 }  // namespace tman

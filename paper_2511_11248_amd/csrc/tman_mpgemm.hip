@@ -117,26 +117,6 @@ __device__ __forceinline__ void load_w(WRegs<B>& r, rsrc_t rw, int tile, int kb3
 // operand reads of 16 consecutive rows then fall into 16 different 16-byte bank groups.  The
 // permutation is applied on the global-address side, where every lane is free to pick its source.
 
-// Stores an fp16 output tile kept in LDS as [token][row]: 16-byte pieces, coalesced.
-template <int TM, int TN, int OUT_ROW, int THREADS>
-__device__ __forceinline__ void store_tile(const GemmArgs& a, const uint8_t* otile, int m0, int n0, int tid) {
-    const bool fast = a.M % 8 == 0 && aligned16(a.y);  // 16-byte aligned rows of y
-    for (int piece = tid; piece < TN * (TM / 8); piece += THREADS) {
-        const int n = piece / (TM / 8), c8 = piece % (TM / 8);
-        const int gn = n0 + n, gm = m0 + c8 * 8;
-        if (gn >= a.N || gm >= a.M) continue;
-        const u32x4 v = *reinterpret_cast<const u32x4*>(otile + n * OUT_ROW + c8 * 16);
-        _Float16* dst = a.y + (size_t)gn * a.M + gm;
-        if (fast && gm + 8 <= a.M) {
-            *reinterpret_cast<u32x4*>(dst) = v;
-        } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-            for (int t = 0; t < 8 && gm + t < a.M; ++t)
-                dst[t] = __builtin_bit_cast(_Float16, (uint16_t)(w[t >> 1] >> (16 * (t & 1))));
-        }
-    }
-}
-
 // Workgroup = 12 waves, three per SIMD.  Waves 0..7 are consumers: wave (wm, wn) owns 32 RB rows x 64
 // tokens of the tile and does nothing but read MFMA operands from LDS and issue MFMAs.  Waves 8..11
 // are producers: wave p < RB turns row block p of each stage into fp16 in LDS, and all four stage the
@@ -464,7 +444,7 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
             }
     }
     __syncthreads();
-    store_tile<T::TM, kTN, T::OutRow, kThreads>(a, otile, mt * T::TM, n0, tid);
+    store_tile<T::TM, kTN, T::OutRow, kThreads>(a.y, a.M, a.N, otile, mt * T::TM, n0, tid);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -898,7 +878,7 @@ __global__ void __launch_bounds__(256, 2) mpgemm_wide_kernel(GemmArgs a) {
             }
         }
     __syncthreads();
-    store_tile<kWideRows, T::TN, T::OutRow, 256>(a, otile, mt * kWideRows, n0, tid);
+    store_tile<kWideRows, T::TN, T::OutRow, 256>(a.y, a.M, a.N, otile, mt * kWideRows, n0, tid);
 }
 
 static int compute_units() {

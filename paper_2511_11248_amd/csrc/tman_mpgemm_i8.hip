@@ -211,6 +211,19 @@ struct GemmI8Args {
     int* status;
 };
 
+// Scale and sum of token n0 + tid, zero beyond the tokens: requested at the start of a kernel for its end.
+struct TokenScales {
+    float absmax;
+    int32_t sum;
+};
+__device__ __forceinline__ TokenScales request_token_scales(const GemmI8Args& a, int n0, int tid) {
+    const uint32_t off = (uint32_t)(n0 + tid) * 4u;
+    TokenScales t;
+    t.absmax = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_of(a.absmax, (uint32_t)a.N * 4u), off, 0, 0));
+    t.sum = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rsrc_of(a.sums, (uint32_t)a.N * 4u), off, 0, 0);
+    return t;
+}
+
 // The codes of one 32-weight block as 32 bytes in sigma order.
 template <int B>
 __device__ __forceinline__ void codes_to_bytes(const uint32_t (&plane)[B], u32x4& lo, u32x4& hi) {
@@ -380,22 +393,7 @@ __global__ void __launch_bounds__(256) mpgemm_i8_kernel(GemmI8Args a) {
         }
     }
     __syncthreads();
-    const int m0 = mt * kI8Rows;
-    const bool fast = a.M % 8 == 0 && aligned16(a.y);  // 16-byte aligned rows of y
-    for (int piece = tid; piece < kI8Tokens * (kI8Rows / 8); piece += 256) {
-        const int n = piece / (kI8Rows / 8), c8 = piece % (kI8Rows / 8);
-        const int gn = n0 + n, gm = m0 + c8 * 8;
-        if (gn >= a.N || gm >= a.M) continue;
-        const u32x4 v = *reinterpret_cast<const u32x4*>(otile + n * kI8OutRow + c8 * 16);
-        _Float16* dst = a.y + (size_t)gn * a.M + gm;
-        if (fast && gm + 8 <= a.M) {
-            *reinterpret_cast<u32x4*>(dst) = v;
-        } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-            for (int t = 0; t < 8 && gm + t < a.M; ++t)
-                dst[t] = __builtin_bit_cast(_Float16, (uint16_t)(w[t >> 1] >> (16 * (t & 1))));
-        }
-    }
+    store_tile<kI8Rows, kI8Tokens, kI8OutRow, 256>(a.y, a.M, a.N, otile, mt * kI8Rows, n0, tid);
 }
 
 // The two 32-column blocks of a lane in a tile block of 32 rows (lane half h: blocks 2 h and 2 h + 1); `off`: of the lane's
@@ -443,7 +441,7 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
     constexpr int MSZ = HZ ? 4 : 2;
     constexpr int kSets = 2;  // register sets of bit planes = tiles of weights in flight
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    __shared__ float row_scale[kI8WRows], row_zs[kI8WRows];
+    __shared__ float row_scale[kI8WRows], row_zs[kI8WRows], token_step[T::TN], token_sum[T::TN];
 
     const int MPL = (kKTile / group) * MSZ, TB = B * 1024 + 64 * MPL;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -515,6 +513,7 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
     const rsrc_t rmeta = rsrc_of(wsrc, wbytes);
     const uint32_t meta_s = __builtin_amdgcn_raw_buffer_load_b16(rmeta, lane * MPL, B * 1024, 0);
     const uint32_t meta_z = HZ ? __builtin_amdgcn_raw_buffer_load_b16(rmeta, lane * MPL + 2, B * 1024, 0) : 0u;
+    const TokenScales scales = request_token_scales(a, n0, tid);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < kSets - 1; ++t) {
@@ -531,6 +530,10 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
         const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)meta_s);
         row_scale[tid] = sc;
         row_zs[tid] = HZ ? (float)__builtin_bit_cast(_Float16, (uint16_t)meta_z) * sc : 0.f;
+        if (tid < T::TN) {
+            token_step[tid] = scales.absmax * (1.0f / 127.0f);
+            token_sum[tid] = (float)scales.sum;
+        }
     }
     operands(0, 0, plane[0]);
     operands(0, 1, plane[0]);
@@ -579,14 +582,29 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
-    // epilogue: C[i][j] of a 32 x 32 tile: i = row 8 (v / 4) + 4 h + v % 4, j = token lane % 32
+    // epilogue: C[i][j] of a 32 x 32 tile: i = row 8 (v / 4) + 4 h + v % 4, j = token lane % 32.  Scales come from LDS (read from
+    // memory here, one token block after the other, they took 3 of a call's 25 us), stores of whole tiles are unrolled.
+    if (a.acc_out) {  // (uniform)
+#pragma unroll 1
+        for (int nb = 0; nb < TT; ++nb) {
+            const int gn = n0 + nb * 32 + r;
+#pragma unroll
+            for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int gm = mt * kI8WRows + wave * 64 + hb * 32 + 8 * (v / 4) + 4 * h + v % 4;
+                    int32_t av = acc[hb][0][v];
+#pragma unroll
+                    for (int q = 1; q < TT; ++q) av = nb == q ? acc[hb][q][v] : av;
+                    if (gn < a.N && gm < a.M) a.acc_out[(size_t)gn * a.M + gm] = av;
+                }
+        }
+    }
     uint8_t* otile = smem;
 #pragma unroll
     for (int nb = 0; nb < TT; ++nb) {
-        const int tok = nb * 32 + r, gn = n0 + tok;
-        const bool live = gn < a.N;
-        const float delta = live ? a.absmax[gn] * (1.0f / 127.0f) : 0.f;
-        const float sx = live ? (float)a.sums[gn] : 0.f;
+        const int tok = nb * 32 + r;
+        const float delta = token_step[tok], sx = token_sum[tok];
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb) {
 #pragma unroll
@@ -604,32 +622,11 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
                 p1.x = (_Float16)v[2]; p1.y = (_Float16)v[3];
                 u32x2 w = {__builtin_bit_cast(uint32_t, p0), __builtin_bit_cast(uint32_t, p1)};
                 *reinterpret_cast<u32x2*>(otile + tok * T::OutRow + row * 2) = w;
-                if (a.acc_out && live) {
-                    const int gm = mt * kI8WRows + row;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (gm + e < a.M) a.acc_out[(size_t)gn * a.M + gm + e] = acc[hb][nb][4 * g4 + e];
-                }
             }
         }
     }
     __syncthreads();
-    const int m0 = mt * kI8WRows;
-    const bool fast = a.M % 8 == 0 && aligned16(a.y);  // 16-byte aligned rows of y
-    for (int piece = tid; piece < T::TN * (kI8WRows / 8); piece += 256) {
-        const int n = piece / (kI8WRows / 8), c8 = piece % (kI8WRows / 8);
-        const int gn = n0 + n, gm = m0 + c8 * 8;
-        if (gn >= a.N || gm >= a.M) continue;
-        const u32x4 v = *reinterpret_cast<const u32x4*>(otile + n * T::OutRow + c8 * 16);
-        _Float16* dst = a.y + (size_t)gn * a.M + gm;
-        if (fast && gm + 8 <= a.M) {
-            *reinterpret_cast<u32x4*>(dst) = v;
-        } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-            for (int t = 0; t < 8 && gm + t < a.M; ++t)
-                dst[t] = __builtin_bit_cast(_Float16, (uint16_t)(w[t >> 1] >> (16 * (t & 1))));
-        }
-    }
+    store_tile<kI8WRows, T::TN, T::OutRow, 256>(a.y, a.M, a.N, otile, mt * kI8WRows, n0, tid);
 }
 
 template <int B, bool HZ, int TT>
@@ -675,7 +672,7 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
     constexpr int kUnits = 2 * RBW;  // row units of 32 rows
     constexpr int MSZ = HZ ? 4 : 2;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    __shared__ float row_scale[T::TM], row_zs[T::TM];
+    __shared__ float row_scale[T::TM], row_zs[T::TM], token_step[T::TN], token_sum[T::TN];
 
     const int MPL = (kKTile / group) * MSZ, TB = B * 1024 + 64 * MPL;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -746,6 +743,7 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
                                  wave < RBW && mrb < a.n_row_blocks ? (uint32_t)TB : 0u);
     const uint32_t meta_s = __builtin_amdgcn_raw_buffer_load_b16(rmeta, lane * MPL, B * 1024, 0);
     const uint32_t meta_z = HZ ? __builtin_amdgcn_raw_buffer_load_b16(rmeta, lane * MPL + 2, B * 1024, 0) : 0u;
+    const TokenScales scales = request_token_scales(a, n0, tid);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < kUnits; ++u) load_unit(0, u, 0);
@@ -758,6 +756,10 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
         const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)meta_s);
         row_scale[tid] = sc;
         row_zs[tid] = HZ ? (float)__builtin_bit_cast(_Float16, (uint16_t)meta_z) * sc : 0.f;
+    }
+    if (tid < T::TN) {
+        token_step[tid] = scales.absmax * (1.0f / 127.0f);
+        token_sum[tid] = (float)scales.sum;
     }
     operands(0, 0, 0);
     operands(1, 0, 0);
@@ -847,8 +849,7 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
                 for (int e = 0; e < 8; ++e) sum[e] += src[e];
             }
             if (gn >= a.N || gm >= a.M) continue;
-            const float delta = a.absmax[gn] * (1.0f / 127.0f);
-            const float sx = (float)a.sums[gn];
+            const float delta = token_step[gn - n0], sx = token_sum[gn - n0];
             _Float16 o[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {

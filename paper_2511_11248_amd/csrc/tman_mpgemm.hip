@@ -191,16 +191,16 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
         const uint32_t xsrc_chunk[2] = {(uint32_t)((lane & 7) ^ (lane >> 4)) * 16u, (uint32_t)((lane & 7) ^ (4 + (lane >> 4))) * 16u};
         const uint32_t x8rows = 8u * (uint32_t)a.K * 2u;  // bytes between the sources of consecutive loads
         uint8_t* const xring = smem + kRing * T::WBytes;
-        // load number i of a pair of stages fills token rows 8 i .. 8 i + 7; lane = 8 * row + position; `first` is even.
+        // load number i of a pair of stages fills token rows 8 i .. 8 i + 7; lane = 8 * row + position; `odd`: `first` is odd.
         // (Columns beyond K in the last pair belong to a stage that is not multiplied.)
-        auto load_x = [&](int pair, int first, int count) {
+        auto load_x = [&](int pair, int first, int count, int odd = 0) {
             const rsrc_t rx = make_rsrc(xsrc, 2 * pair < k_stages ? xbytes : 0u);
             uint8_t* dst = xring + (uint32_t)pair % kRing * T::XBytes;
 #pragma unroll
             for (int i = 0; i < 2 * kXAll; ++i)
                 if (i < count)
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + (first + i) * 1024),
-                                                             16, xlane + xsrc_chunk[i & 1] + (uint32_t)(first + i) * x8rows,
+                                                             16, xlane + xsrc_chunk[(i + odd) & 1] + (uint32_t)(first + i) * x8rows,
                                                              pair * kStageK * 4, 0, 0);
         };
         const int wdst = (pb * 64 + lane) * kRowBytes;  // this lane's 64 bytes in the weight tile
@@ -222,11 +222,22 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
             load_x(1, 0, 2 * kXAll);
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kXAll) : "memory");
             asm volatile("s_barrier" ::: "memory");
+            // The requests of a stage are spread over it (s_sleep: 64 cycles a step): what they write to LDS and read from L2
+            // in one go keeps the other waves waiting.  4096 x 4096 N = 700, 192 x 256 tiles, all at once / in fours with
+            // 1 / 3 / 5 steps between: 70.6 / 69.1 / 65.7 / 74.0 us (11008 x 4096 N = 1024 92.9 / 91.8 / 90.6 / 94.9).
+            constexpr int kPause = RB == 3 ? 3 : RB == 2 ? 2 : 1;
+            auto spread_x = [&](int pair, int first) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    load_x(pair, first + 4 * q, 4);
+                    if (q < 3) __builtin_amdgcn_s_sleep(kPause);
+                }
+            };
             for (int s = 0; s < n_stages; s += 2) {
-                load_x(s / 2 + 2, 0, kXAll);
+                spread_x(s / 2 + 2, 0);
                 // younger than the loads of pair s/2 + 1: the sixteen just issued
                 asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kXAll) : "memory");
-                load_x(s / 2 + 2, kXAll, kXAll);
+                spread_x(s / 2 + 2, kXAll);
                 asm volatile("s_barrier" ::: "memory");
             }
         } else if constexpr (RB == 1) {
@@ -346,10 +357,18 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
             for (int s = 0; s < n_stages; s += kSets) {
 #pragma unroll
                 for (int u = 0; u < kSets; ++u) {
-                    load_x((s + u) / 2 + 2, 8 * p + (u & 1) * 4, 4);
-                    __builtin_amdgcn_sched_barrier(0);
-                    w_to_lds((u + 2) % kSets, s + u + 2);
-                    __builtin_amdgcn_sched_barrier(0);
+                    // a request ahead of each part of the vector work
+                    Dequant<B, HZ> dq;
+                    uint8_t* const wrow = smem + (uint32_t)(s + u + 2) % kRing * T::WBytes + wdst;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        load_x((s + u) / 2 + 2, 8 * p + (u & 1) * 4 + j, 1, j & 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (j == 0) dq.start(wr[(u + 2) % kSets]);
+                        else if (j == 1) dq.insert();
+                        else dq.emit(2 * j - 4, wrow), dq.emit(2 * j - 3, wrow);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                     load_wregs((u + 2) % kSets, s + u + 6);
                     __builtin_amdgcn_sched_barrier(0);
                     // even stages: younger than the activation loads of pair s/2 + 1: 2 weight loads of stage s-1, 4
@@ -716,6 +735,7 @@ constexpr int kWideRing = 4;   // stage buffers
 constexpr int kWideRows = 256;
 template <int TT>
 struct WideTile {
+    static_assert(TT <= 4, "a request a step");
     static constexpr int TN = 32 * TT;
     static constexpr int XBytes = TN * kKsStageK * 2;
     static constexpr int XLoads = TT;                  // requests of a stage per wave (8 token rows each)
@@ -764,11 +784,11 @@ __global__ void __launch_bounds__(256, 2) mpgemm_wide_kernel(GemmArgs a) {
     const uint32_t xbytes = (uint32_t)xrows * (uint32_t)a.K * 2u;
     const uint32_t xchunk = (uint32_t)((lane & 7) ^ ((wave & 1) * 4 + (lane >> 4))) * 16u;
     const uint32_t xlane = (uint32_t)(wave * 8 + (lane >> 3)) * (uint32_t)a.K * 2u + xchunk, x32rows = 32u * (uint32_t)a.K * 2u;
-    auto load_x = [&](int t) {
+    auto load_x = [&](int t, int from = 0, int to = T::XLoads) {
         const rsrc_t rx = make_rsrc(xsrc, t < k_stages ? xbytes : 0u);
         uint8_t* dst = smem + (t & (kWideRing - 1)) * T::XBytes;
 #pragma unroll
-        for (int i = 0; i < T::XLoads; ++i) {
+        for (int i = from; i < to; ++i) {
             uint32_t off = xlane + (uint32_t)i * x32rows;
             if constexpr (GQ == 32) off = t * kKsStageK + (int)(xchunk / 2) < a.K ? off : 0xFFFFFF00u;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + (wave + 4 * i) * 1024), 16, off,
@@ -825,14 +845,16 @@ __global__ void __launch_bounds__(256, 2) mpgemm_wide_kernel(GemmArgs a) {
         for (int s = 0; s < 2; ++s) {
             const int t = s0 + s;
             const uint8_t* nxt = smem + ((t + 1) & (kWideRing - 1)) * T::XBytes;
-            load_x(t + 3);
-            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 // the products of row unit u; meanwhile the vector work of the next unit, and beside the last one the activations
                 // of stage t + 1, each as soon as its registers are used
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
+                    if (u == 0 && j < T::XLoads) {  // (one request a step: in one go they keep the other waves waiting)
+                        load_x(t + 3, j, j + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                     dequant_part(j, u ? (s + 1) & 1 : s, u ^ 1);
 #pragma unroll
                     for (int nb = 0; nb < TT; ++nb)

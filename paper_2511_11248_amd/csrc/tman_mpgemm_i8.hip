@@ -483,11 +483,11 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
     const uint32_t xbytes = (uint32_t)xrows * (uint32_t)a.K;
     const uint32_t xlane = (uint32_t)(wave * 8 + (lane >> 3)) * (uint32_t)a.K + (uint32_t)((lane & 7) ^ ((wave & 1) * 4 + (lane >> 4))) * 16u;
     const uint32_t x32rows = 32u * (uint32_t)a.K;
-    auto load_x = [&](int t) {
+    auto load_x = [&](int t, int from = 0, int to = T::XLoads) {
         const rsrc_t rx = rsrc_of(xsrc, t < a.n_ktiles ? xbytes : 0u);
         uint8_t* dst = smem + (t & (kI8WRing - 1)) * T::XBytes;
 #pragma unroll
-        for (int i = 0; i < T::XLoads; ++i)
+        for (int i = from; i < to; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + (wave + 4 * i) * 1024), 16,
                                                      xlane + (uint32_t)i * x32rows, t * kKTile, 0, 0);
     };
@@ -549,10 +549,12 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
             const int t = t0 + u;
             const uint8_t* cur = smem + (t & (kI8WRing - 1)) * T::XBytes;
             const uint8_t* nxt = smem + ((t + 1) & (kI8WRing - 1)) * T::XBytes;
-            load_x(t + 3);
-            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
+                if (j < 2) {  // (half of the requests a step, ahead of the planes')
+                    load_x(t + 3, j ? (T::XLoads + 1) / 2 : 0, j ? T::XLoads : (T::XLoads + 1) / 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 // the products of step j; meanwhile the activations of the next step and one row unit of the next block
                 read_x((j + 1) & 3, j == 3 ? nxt : cur);
                 operands(j < 2 ? 1 : 0, j & 1, plane[(j < 2 ? u : u + 1) % kSets]);

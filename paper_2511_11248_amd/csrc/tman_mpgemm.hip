@@ -567,12 +567,12 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     const uint32_t xlane = (uint32_t)(lane >> 3) * (uint32_t)a.K * 2u, x8rows = 8u * (uint32_t)a.K * 2u;
     const uint32_t xchunk[2] = {(uint32_t)((lane & 7) ^ (lane >> 4)) * 16u, (uint32_t)((lane & 7) ^ (4 + (lane >> 4))) * 16u};
     uint8_t* const xbuf = smem + wave * T::NBuf * T::XBytes;
-    auto load_x = [&](int i) {
+    auto load_x = [&](int i, int from = 0, int to = T::XLoads) {
         const int t = W * i + wave;
         const rsrc_t rx = make_rsrc(xsrc, t < k_stages ? xbytes : 0u);
         uint8_t* dst = xbuf + (i & (T::NBuf - 1)) * T::XBytes;
 #pragma unroll
-        for (int q = 0; q < T::XLoads; ++q) {
+        for (int q = from; q < to; ++q) {
             uint32_t off = xlane + (uint32_t)q * x8rows + xchunk[q & 1];
             if constexpr (GQ == 32) off = t * kKsStageK + (int)(xchunk[q & 1] / 2) < a.K ? off : 0xFFFFFF00u;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + q * 1024), 16, off,
@@ -624,6 +624,10 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) read_x(j, xbuf);
 
+    // The activations of an own stage are in registers when unit 0 has used them: the next but one are requested then.  Four units:
+    // spread over unit 1 (5367 x 5504 N = 580 52.7 -> 51.6 us).  Two: at once, the wait for the next stage's is close (spread: 2 to
+    // 5 % slower).
+    constexpr bool kSpread = T::NBuf == 2 && kUnits > 2;
     for (int i0 = 0; i0 < n_own_pad; i0 += 2) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -647,6 +651,10 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
+                    if (kSpread && u == 1) {
+                        load_x(i + 2, j * T::XLoads / 4, (j + 1) * T::XLoads / 4);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                     dequant_part(j, nset, nu);
 #pragma unroll
                     for (int nb = 0; nb < TT; ++nb)
@@ -663,7 +671,7 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
                 // the registers of the row unit just dequantized are free
                 load_unit(nset, nu, (u == kLast ? i + 1 : i) + 2);
                 __builtin_amdgcn_sched_barrier(0);
-                if (T::NBuf == 2 && u == 0) {  // the activations of this own stage are in registers (unit 0 used them all)
+                if (T::NBuf == 2 && !kSpread && u == 0) {
                     load_x(i + 2);
                     __builtin_amdgcn_sched_barrier(0);
                 }

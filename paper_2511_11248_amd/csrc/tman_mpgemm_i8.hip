@@ -714,12 +714,12 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
     const uint32_t xlane = (uint32_t)(lane >> 3) * (uint32_t)a.K, x8rows = 8u * (uint32_t)a.K;
     const uint32_t xchunk[2] = {(uint32_t)((lane & 7) ^ (lane >> 4)) * 16u, (uint32_t)((lane & 7) ^ (4 + (lane >> 4))) * 16u};
     uint8_t* const xbuf = smem + wave * T::NBuf * T::XBytes;
-    auto load_x = [&](int i) {
+    auto load_x = [&](int i, int from = 0, int to = T::XLoads) {
         const int t = 4 * i + wave;
         const rsrc_t rx = rsrc_of(xsrc, t < a.n_ktiles ? xbytes : 0u);
         uint8_t* dst = xbuf + (i & (T::NBuf - 1)) * T::XBytes;
 #pragma unroll
-        for (int q = 0; q < T::XLoads; ++q)
+        for (int q = from; q < to; ++q)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + q * 1024), 16,
                                                      xlane + (uint32_t)q * x8rows + xchunk[q & 1], t * kKTile, 0, 0);
     };
@@ -787,7 +787,13 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
                 if (u == kLast) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kUnits * kUnitLoads + T::XLoads) : "memory");
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    if (j % 2 == 0) operands(j / 2, nset, nu);
+                    if (j % 2 == 0) {
+                        if (u == 1) {  // the activations of this own tile are in registers (unit 0 used them all)
+                            load_x(i + 2, j * T::XLoads / 4, (j + 2) * T::XLoads / 4);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        operands(j / 2, nset, nu);
+                    }
 #pragma unroll
                     for (int nb = 0; nb < TT; ++nb)
                         acc[u / 2][u & 1][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[u & 1][j], xf[j][nb], acc[u / 2][u & 1][nb], 0, 0, 0);
@@ -804,10 +810,6 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
                 }
                 load_unit(nset, nu, (u == kLast ? i + 1 : i) + 2);  // the registers of the row unit just turned into bytes are free
                 __builtin_amdgcn_sched_barrier(0);
-                if (u == 0) {  // the activations of this own tile are in registers (unit 0 used them all)
-                    load_x(i + 2);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
             }
         }
     }

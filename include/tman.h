@@ -366,8 +366,8 @@ int tman_mpgemv_noalloc(const tman_shape_t *shape, const void *packed, const voi
  *                              tman_mpgemm number their workgroups for equal work per compute unit where they fit
  *                              the chip (see tman_mpgemv_x_batch_order), 0: plain grids
  *   small_seg_tiles            K tiles per workgroup of tman_mpgemm for N <= 32 and of large tman_mpgemv launches (see above)
- *   prefill_row_blocks         tile blocks in M per workgroup of the tiled prefill kernel, 1..4 (Eq. 4: four
- *                              stage buffers of rows x 80 + 256 x 64 bytes within 160 KB of LDS), 0 = chosen per
+ *   prefill_row_blocks         tile blocks in M per workgroup of the tiled prefill kernel, 1..4 (Eq. 4: three
+ *                              buffers of rows x 80 + 256 x 128 bytes within 160 KB of LDS), 0 = chosen per
  *                              call from the grid it gives
  *   prefill_k_split            tman_mpgemm for N > 32: short prompts and grids that leave compute units idle go to a kernel
  *                              whose waves split K (each dequantizes its own stages in registers; the partial sums

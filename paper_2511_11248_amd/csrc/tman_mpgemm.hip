@@ -467,23 +467,23 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Grids that would otherwise leave compute units idle: the W waves of a workgroup split K.  Wave w takes the 32-column
-// stages w, w + W, ... whole: it dequantizes the stage's weights in registers (lane = row; v_permlane32_swap makes the
-// MFMA operands, as in the small-batch kernel), brings the stage's activations into its own LDS buffers and multiplies
+// Grids that would otherwise leave compute units idle: the W waves of a workgroup split K.  Wave w takes the 64-column
+// stages w, w + W, ... whole: it dequantizes the stage's weights in registers, brings the stage's activations into its own LDS buffers and multiplies
 // them with all tokens of the tile.  So a weight is dequantized once per tile, no weight goes through LDS, a wave reads
 // 0.5 KB of LDS per MFMA instead of 1.5 KB, and the waves never wait for one another until the end, where their
 // partial tiles meet in LDS (added in wave order: results do not depend on timing).
 // Shapes of the tile (RBW row blocks x 32 TT tokens): 64 rows x 64 tokens with four waves (two workgroups share a
 // compute unit) or eight, 64 x 128, 128 x 128 (every wave dequantizes two row blocks per stage and needs half the
 // activation bytes per MFMA), and 64 x 256 where the tiling asks for it.  What bounds a wave is the sum of its
-// dequantization (about 90 vector instructions per 32 columns and row block, which hide only in part behind its own
-// MFMAs) and its MFMAs (128 cycles per 32 columns and 32 tokens): a narrow tile costs more dequantization per token
+// dequantization (about 90 vector instructions per row unit and stage, of which about 6 hide behind an MFMA) and its MFMAs
+// (four of 32 cycles per row unit, stage and 32 tokens): a narrow tile costs more dequantization per token
 // but spreads the work over more units and multiplies less padding.
 //
 // A stage is 64 columns, 128 bytes of a token: whole cache lines (with 64 bytes of a line per request every line came into the
 // unit's L1 twice).  Lane (r, h) of a row unit (32 rows) takes block h of the stage's two 32-column blocks of row r, which it
 // loads and dequantizes alone; a product then sums over 8 columns of each block, and the activations are read to match, so no
-// lane exchanges anything.
+// lane exchanges anything.  With 32-column stages and the operands made by exchanges: 4096 x 11008 N = 173 32.1 us, now 28.1; 11008 x
+// 4096 N = 64 / 128 20.2 / 30.3, now 17.3 / 23.9.
 constexpr int kKsStageK = 64;
 template <int RBW, int TT, int W>
 struct KsTile {

@@ -421,7 +421,8 @@ __device__ __forceinline__ void load_unit_planes(uint32_t (&pl)[2][B], rsrc_t rw
 // (32 rows) takes the 32-column blocks 2 h and 2 h + 1 of row r of a 128-column tile, which it loads and turns into bytes
 // alone: a product sums over 16 columns of a block of the first and of one of the second half of the tile, and the
 // activations are read to match, so no lane exchanges anything.  Only the activations go through LDS, straight from memory,
-// shared by the four waves (256 rows) of the workgroup, a tile (128 bytes of a token, a whole cache line) at a time.  Per MFMA
+// shared by the four waves (256 rows) of the workgroup, a tile (128 bytes of a token, a whole cache line) at a time
+// (by 32-column stages, with exchanges: 11008 x 4096 4 bits N = 2048 124 us, now 88; 6912 x 2560 2 bits N = 1024 28.6, now 23.3).  Per MFMA
 // this reads half the LDS bytes of the 128 x 128 kernel and dequantizes each weight once per 32 TT tokens instead of once per 128.
 constexpr int kI8WRing = 4;   // tile buffers of activations in LDS
 constexpr int kI8WRows = 256;
@@ -931,10 +932,14 @@ static int launch_i8_wide_tokens(int tt, const GemmI8Args& a, int group, hipStre
 }
 
 // Which kernel, and for the wide one how many 32-token blocks per workgroup: the choice with the least modelled
-// time.  The model counts rounds of workgroups over the compute units with the time one workgroup took on this
-// chip at K = 4096 (microseconds; alone on its unit / sharing it with a second one, which the 96- and 128-token
-// tiles allow), scaled by K; the 128 x 128 kernel's time grows linearly with its workgroups.  1 = that kernel,
-// 3 / 4 / 7 = the wide kernel with that many 32-token blocks, 9 = the kernel whose waves split K.
+// time.  The model counts rounds of workgroups over the compute units with the time of one workgroup (alone on its unit /
+// sharing it with a second one, which the 96- and 128-token tiles allow), scaled by K; the 128 x 128 kernel's time grows
+// linearly with its workgroups.  1 = that kernel, 3 / 4 / 7 = the wide kernel with that many 32-token blocks, 9 = the kernel
+// whose waves split K.  The constants weigh the candidates against each other, short K included (they pick the fastest at 20
+// of 20 shapes); calls of 64 / 128 / 256 / 384 / 512 workgroups take, at K = 4096 and 4 bits, in microseconds:
+//   3 (96 tokens)  23 / 24 / 32 / 45 / 53    9 (K split)    18 / 19 / 25 / 40 / 46
+//   4 (128)        27 / 28 / 37 / 54 / 64    1 (128 x 128)  27 / 28 / 29 / 40 / 45
+//   7 (224)        42 / 44 / 56
 int choose_i8_token_blocks(int n_row_blocks, int N, int K) {
     static std::once_flag once;
     static int n_cu = 256;  // assumed when no device answers

@@ -36,7 +36,7 @@ tman_tiling_t current_tiling() {
 
 // Eq. 1 and Eq. 4 in this machine's terms (Eq. 2 and Eq. 3 hold for every value: the tile block is shared).
 static int check_tiling(const tman_tiling_t& t) {
-    constexpr int kLdsBytes = 160 * 1024, kRing = 4;
+    constexpr int kLdsBytes = 160 * 1024, kRing = 3;
     if (t.decode_seg_tiles < 1 || t.decode_seg_tiles_many < 1 || t.small_seg_tiles < 1) return TMAN_ERR_SHAPE;
     if (t.decode_seg_tiles > 4096 || t.decode_seg_tiles_many > 4096 || t.small_seg_tiles > 4096) return TMAN_ERR_SHAPE;
     // Eq. 1: a one-token segment is what the lanes of a workgroup turn into digits in two passes
@@ -44,10 +44,10 @@ static int check_tiling(const tman_tiling_t& t) {
     if (t.decode_x_long_seg_tiles < 1 || t.decode_x_long_seg_tiles > t.decode_x_seg_tiles) return TMAN_ERR_SHAPE;
     if (t.decode_x_whole_bytes < 1024) return TMAN_ERR_SHAPE;
     if (t.decode_balance != 0 && t.decode_balance != 1) return TMAN_ERR_SHAPE;
-    // Eq. 4: stage ring of the prefill kernel: rows x 80 bytes of fp16 weights + 256 tokens x 64 bytes per stage
+    // Eq. 4: rings of the prefill kernel: rows x 80 bytes of fp16 weights per stage, 256 tokens x 128 bytes per pair of stages
     if (t.prefill_row_blocks < 0 || t.prefill_row_blocks > 4) return TMAN_ERR_SHAPE;
     const int rb = t.prefill_row_blocks ? t.prefill_row_blocks : 4;
-    if (kRing * (rb * kRows * 80 + 256 * 64) > kLdsBytes) return TMAN_ERR_SHAPE;
+    if (kRing * (rb * kRows * 80 + 256 * 128) > kLdsBytes) return TMAN_ERR_SHAPE;
     // the prefill kernel whose waves split K: 0 = where it is measured faster, 1 = never, 2 / 3 = always, with its
     // 64 x 256 / 128 x 128 tile (its LDS, 128 KB of activation buffers or 135 KB of partial tiles, fits for both)
     if (t.prefill_k_split < 0 || t.prefill_k_split > 3) return TMAN_ERR_SHAPE;

@@ -61,12 +61,30 @@ struct GemmArgs {
     const uint8_t* tiles;
     const _Float16* x;
     _Float16* y;
-    int M, N, K, n_row_blocks, n_ktiles;
+    int* status;  // the library's status word
+    int M, N, K, n_row_blocks;
     int m_tiles, n_tiles;
     int per_xcd;  // workgroups dealt to each XCD
     int whole_row_tiles;
-    int* status;  // the library's status word
 };
+// The kernels take the 16 words of their arguments one by one: scalar arguments are in registers when a wave starts (the build
+// asks for it), a structure is read from memory first (44 shapes of 6 to 200 us: 1.006 and 1.018 times as fast in two runs).
+template <typename Launch>
+static int with_fields(const GemmArgs& a, Launch launch) {
+    return launch(a.tiles, a.x, a.y, a.status, a.M, a.N, a.K, a.n_row_blocks, a.m_tiles, a.n_tiles, a.per_xcd, a.whole_row_tiles);
+}
+// Launches a kernel that takes more LDS than a kernel may without asking (once per kernel instantiation, also when several host
+// threads make their first call together).
+template <int LDS_BYTES, typename... Fields>
+static int launch_with_lds(void (*kernel)(Fields...), std::once_flag& once, hipError_t& attr_rc, unsigned grid, int threads,
+                           hipStream_t st, Fields... fields) {
+    std::call_once(once, [&] {
+        attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+    });
+    if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), LDS_BYTES, st, fields...);
+    return launch_status();
+}
 
 // Tile of this workgroup, token tiles fastest.  Consecutive workgroup ids go to consecutive XCDs, and the token tiles that
 // share the weights of one row tile should sit on one XCD and its L2.  Either every XCD gets an equal run of consecutive
@@ -133,8 +151,10 @@ __device__ __forceinline__ void load_w(WRegs<B>& r, rsrc_t rw, int tile, int kb3
 constexpr int kConsumerWaves = 8;
 constexpr int kThreads = 768;
 
-template <int B, int GQ, bool HZ, int RB>
-__global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
+template <int B, int GQ, bool HZ, int RB, typename... Fields>
+__global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(Fields... fields) {
+    const GemmArgs a{fields...};
+    const int n_ktiles = (a.K + kKTile - 1) / kKTile;
     using T = Tile<RB>;
     constexpr int MSZ = HZ ? 4 : 2;
     constexpr int TB = B * 1024 + 64 * (kKTile / GQ) * MSZ;
@@ -177,7 +197,7 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(GemmArgs a) {
         // the producers' short vector bursts gate every stage: issue them ahead of the consumers' MFMAs
         __builtin_amdgcn_s_setprio(3);
         const bool wvalid = (RB == 1 ? p < 2 : p < RB) && rbw < a.n_row_blocks;
-        const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rbw : 0) * a.n_ktiles * TB;
+        const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rbw : 0) * n_ktiles * TB;
         const int xrows = a.N - n0 < kTN ? a.N - n0 : kTN;
         const _Float16* xsrc = a.x + (size_t)n0 * a.K;
         const uint32_t xbytes = (uint32_t)xrows * (uint32_t)a.K * 2u;
@@ -518,8 +538,10 @@ __device__ __forceinline__ void load_w_block(WRegs<B>& r, rsrc_t rw, int t, int 
     else r.meta = __builtin_amdgcn_raw_buffer_load_b16(rw, mv, mo, 0);
 }
 
-template <int B, int GQ, bool HZ, int RBW, int TT, int W>
-__global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
+template <int B, int GQ, bool HZ, int RBW, int TT, int W, typename... Fields>
+__global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(Fields... fields) {
+    const GemmArgs a{fields...};
+    const int n_ktiles = (a.K + kKTile - 1) / kKTile;
     using T = KsTile<RBW, TT, W>;
     constexpr int kUnits = 2 * RBW;  // row units of the tile
     constexpr int MSZ = HZ ? 4 : 2;
@@ -555,7 +577,7 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(GemmArgs a) {
     auto load_unit = [&](int set, int unit, int i) {  // own stage i = stage W i + wave
         const int t = W * i + wave, rb = mt * RBW + unit / 2;
         const bool wvalid = rb < a.n_row_blocks;
-        const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rb : 0) * a.n_ktiles * TB;
+        const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rb : 0) * n_ktiles * TB;
         load_w_block<B, GQ, HZ>(wr[set][unit], make_rsrc(wsrc, t < k_stages && wvalid ? 0x7fffffffu : 0u), t, (unit & 1) * 32 + r, h);
     };
     // Activations of own stage i go to this wave's buffer i % NBuf.  A request brings 8 token rows of 128 bytes; 16-byte chunk c
@@ -751,8 +773,10 @@ struct WideTile {
     static constexpr int LdsBytes = kWideRing * XBytes > TN * OutRow ? kWideRing * XBytes : TN * OutRow;
 };
 
-template <int B, int GQ, bool HZ, int TT>
-__global__ void __launch_bounds__(256, 2) mpgemm_wide_kernel(GemmArgs a) {
+template <int B, int GQ, bool HZ, int TT, typename... Fields>
+__global__ void __launch_bounds__(256, 2) mpgemm_wide_kernel(Fields... fields) {
+    const GemmArgs a{fields...};
+    const int n_ktiles = (a.K + kKTile - 1) / kKTile;
     using T = WideTile<TT>;
     constexpr int MSZ = HZ ? 4 : 2;
     constexpr int TB = B * 1024 + 64 * (kKTile / GQ) * MSZ;
@@ -781,7 +805,7 @@ __global__ void __launch_bounds__(256, 2) mpgemm_wide_kernel(GemmArgs a) {
 
     const int rb = mt * 4 + wave;
     const bool wvalid = rb < a.n_row_blocks;
-    const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rb : 0) * a.n_ktiles * TB;
+    const uint8_t* wsrc = a.tiles + (size_t)(wvalid ? rb : 0) * n_ktiles * TB;
     WRegs<B> wr[2][2];  // [set][row unit]
     auto load_unit = [&](int set, int unit, int t) {
         load_w_block<B, GQ, HZ>(wr[set][unit], make_rsrc(wsrc, t < k_stages && wvalid ? 0x7fffffffu : 0u), t, unit * 32 + r, h);
@@ -944,16 +968,12 @@ static int launch_ksplit(GemmArgs a, hipStream_t st) {
     using T = KsTile<RBW, TT, W>;
     static std::once_flag once;
     static hipError_t attr_rc = hipSuccess;
-    std::call_once(once, [] {
-        attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&mpgemm_ksplit_kernel<B, GQ, HZ, RBW, TT, W>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, T::LdsBytes);
-    });
-    if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
     a.m_tiles = (a.n_row_blocks + RBW - 1) / RBW;
     a.n_tiles = (a.N + T::TN - 1) / T::TN;
     const unsigned grid = deal_tiles(a, false);
-    hipLaunchKernelGGL((mpgemm_ksplit_kernel<B, GQ, HZ, RBW, TT, W>), dim3(grid), dim3(64 * W), T::LdsBytes, st, a);
-    return launch_status();
+    return with_fields(a, [&](auto... f) {
+        return launch_with_lds<T::LdsBytes>(&mpgemm_ksplit_kernel<B, GQ, HZ, RBW, TT, W, decltype(f)...>, once, attr_rc, grid, 64 * W, st, f...);
+    });
 }
 
 template <int B, int GQ, bool HZ, int TT>
@@ -961,33 +981,24 @@ static int launch_wide(GemmArgs a, hipStream_t st) {
     using T = WideTile<TT>;
     static std::once_flag once;
     static hipError_t attr_rc = hipSuccess;
-    std::call_once(once, [] {
-        attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&mpgemm_wide_kernel<B, GQ, HZ, TT>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, T::LdsBytes);
-    });
-    if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
     a.m_tiles = (a.n_row_blocks + 3) / 4;
     a.n_tiles = (a.N + T::TN - 1) / T::TN;
     const unsigned grid = deal_tiles(a, false);
-    hipLaunchKernelGGL((mpgemm_wide_kernel<B, GQ, HZ, TT>), dim3(grid), dim3(256), T::LdsBytes, st, a);
-    return launch_status();
+    return with_fields(a, [&](auto... f) {
+        return launch_with_lds<T::LdsBytes>(&mpgemm_wide_kernel<B, GQ, HZ, TT, decltype(f)...>, once, attr_rc, grid, 256, st, f...);
+    });
 }
 
 template <int B, int GQ, bool HZ, int RB>
 static int launch_tile(GemmArgs a, hipStream_t st) {
-    // once per kernel instantiation, also when several host threads make their first call together
     static std::once_flag once;
     static hipError_t attr_rc = hipSuccess;
-    std::call_once(once, [] {
-        attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&mpgemm_kernel<B, GQ, HZ, RB>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, Tile<RB>::LdsBytes);
-    });
-    if (attr_rc != hipSuccess) return TMAN_ERR_LAUNCH;
     a.m_tiles = (a.n_row_blocks + RB - 1) / RB;
     a.n_tiles = (a.N + kTN - 1) / kTN;
     const unsigned grid = deal_tiles(a, true);
-    hipLaunchKernelGGL((mpgemm_kernel<B, GQ, HZ, RB>), dim3(grid), dim3(kThreads), Tile<RB>::LdsBytes, st, a);
-    return launch_status();
+    return with_fields(a, [&](auto... f) {
+        return launch_with_lds<Tile<RB>::LdsBytes>(&mpgemm_kernel<B, GQ, HZ, RB, decltype(f)...>, once, attr_rc, grid, kThreads, st, f...);
+    });
 }
 
 // Which kernel and tile: 1 .. 4 = the tiled kernel with that many row blocks per workgroup; kWide = the kernel without a weight
@@ -1083,8 +1094,7 @@ int launch_mpgemm(const Layout& L, const void* packed, const void* x, int N, voi
     a.N = N;
     a.K = L.K;
     a.n_row_blocks = L.n_row_blocks;
-    a.n_ktiles = L.n_ktiles;
-    a.m_tiles = a.n_tiles = 0;
+    a.m_tiles = a.n_tiles = a.per_xcd = a.whole_row_tiles = 0;
     a.status = device_status_word();
     if (!a.status) return TMAN_ERR_LAUNCH;
     if (L.bits == 1) return L.has_zero ? launch_group<1, true>(L.group, a, st) : launch_group<1, false>(L.group, a, st);

@@ -28,6 +28,7 @@
 
 #include <mutex>
 
+#include "tman_activation_requests.h"
 #include "tman_dequant_device.h"
 
 namespace tman {
@@ -208,20 +209,22 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(Fields... fields) {
         constexpr int kLoaderWave = 3;
         constexpr int kXAll = kTN / 16;  // activation loads per stage, half of a pair's (8 token rows each)
         const uint32_t xlane = (uint32_t)(lane >> 3) * (uint32_t)a.K * 2u;
-        const uint32_t xsrc_chunk[2] = {(uint32_t)((lane & 7) ^ (lane >> 4)) * 16u, (uint32_t)((lane & 7) ^ (4 + (lane >> 4))) * 16u};
+        const uint32_t xsrc_chunk[2] = {request_chunk(0, lane), request_chunk(1, lane)};
         const uint32_t x8rows = 8u * (uint32_t)a.K * 2u;  // bytes between the sources of consecutive loads
         uint8_t* const xring = smem + kRing * T::WBytes;
         // load number i of a pair of stages fills token rows 8 i .. 8 i + 7; lane = 8 * row + position; `odd`: `first` is odd.
-        // (Columns beyond K in the last pair belong to a stage that is not multiplied.)
+        // Columns beyond K in the last pair belong to a stage that is not multiplied; those of the last token are not read either
+        // (resource_bytes).
         auto load_x = [&](int pair, int first, int count, int odd = 0) {
-            const rsrc_t rx = make_rsrc(xsrc, 2 * pair < k_stages ? xbytes : 0u);
+            const rsrc_t rx = make_rsrc(reinterpret_cast<const uint8_t*>(xsrc) + (uint32_t)pair * kPairBytes,
+                                        resource_bytes(xbytes, pair, k_stages));
             uint8_t* dst = xring + (uint32_t)pair % kRing * T::XBytes;
 #pragma unroll
             for (int i = 0; i < 2 * kXAll; ++i)
                 if (i < count)
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + (first + i) * 1024),
                                                              16, xlane + xsrc_chunk[(i + odd) & 1] + (uint32_t)(first + i) * x8rows,
-                                                             pair * kStageK * 4, 0, 0);
+                                                             0, 0, 0);
         };
         const int wdst = (pb * 64 + lane) * kRowBytes;  // this lane's 64 bytes in the weight tile
 

@@ -117,8 +117,8 @@ __global__ void __launch_bounds__(kWaves * 64, 4) mpgemv_x_kernel(Fields... fiel
     LaneActs xv[kPasses];  // (a pass beyond the segment reads what nobody uses; x beyond K reads as zero)
     if constexpr (SRC == TokenSource::kActivations) {
         const uint32_t x_start = (uint32_t)(k0 * kKTile * 2);  // k0 < n_ktiles, so this lies inside x
-        // (the range check of a buffer load covers the per-lane offset only, not the scalar offset, so the resource
-        // starts at the segment's first activation and ends with x: K * 2 bytes less the segment's start)
+        // (the resource starts at the segment's first activation and ends with x, K * 2 bytes less the segment's start: a
+        // lane's own offset decides what is read)
         const rsrc_t rx = make_rsrc(d.lut_t + x_start, (uint32_t)d.K * 2u - x_start);
 #pragma unroll
         for (int i = 0; i < kPasses; ++i) {

@@ -216,15 +216,20 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(Fields... fields) {
         // Columns beyond K in the last pair belong to a stage that is not multiplied; those of the last token are not read either
         // (resource_bytes).
         auto load_x = [&](int pair, int first, int count, int odd = 0) {
-            const rsrc_t rx = make_rsrc(reinterpret_cast<const uint8_t*>(xsrc) + (uint32_t)pair * kPairBytes,
-                                        resource_bytes(xbytes, pair, k_stages));
+            // (only with blocks of 32 can K be an odd multiple of 32; the others start every resource at the tile's first token,
+            // which takes less scalar work per pair: 4096 x 4096 N = 700 blocks of 64, 192 x 256 tiles 64.1 us, else 64.5; blocks of 32
+            // 66.7 -> 66.7, 128 x 256 tiles 58.8 -> 59.7, 256 x 256 82.3 -> 82.0)
+            constexpr bool kHalfPair = GQ == 32;
+            const rsrc_t rx = kHalfPair ? make_rsrc(reinterpret_cast<const uint8_t*>(xsrc) + (uint32_t)pair * kPairBytes,
+                                                    resource_bytes(xbytes, pair, k_stages))
+                                        : make_rsrc(xsrc, 2 * pair < k_stages ? xbytes : 0u);
             uint8_t* dst = xring + (uint32_t)pair % kRing * T::XBytes;
 #pragma unroll
             for (int i = 0; i < 2 * kXAll; ++i)
                 if (i < count)
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(dst + (first + i) * 1024),
                                                              16, xlane + xsrc_chunk[(i + odd) & 1] + (uint32_t)(first + i) * x8rows,
-                                                             0, 0, 0);
+                                                             kHalfPair ? 0 : pair * kPairBytes, 0, 0);
         };
         const int wdst = (pb * 64 + lane) * kRowBytes;  // this lane's 64 bytes in the weight tile
 

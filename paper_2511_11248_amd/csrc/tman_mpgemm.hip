@@ -369,6 +369,7 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(Fields... fields) {
             // prologue: stages 0 and 1 complete in the ring, activations of pair 1 on their way, weights
             // of stages 2..5 in the register sets 2, 3, 0, 1.  Of a pair this wave issues loads 8 p .. 8 p + 7.
             load_x(0, 8 * p, 8);
+            __builtin_amdgcn_sched_barrier(0);  // (the wait below counts the requests behind these)
             load_wregs(0, 0);
             load_wregs(1, 1);
             load_wregs(2, 2);
@@ -634,10 +635,12 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(Fields... fiel
     };
 
     // prologue: weights of own stages 0 and 1 and activations requested, the first row unit dequantized, the first activations
-    // in registers
+    // in registers.  The wait below counts the requests, so none may be moved past another group.
 #pragma unroll
     for (int u = 0; u < kUnits; ++u) load_unit(0, u, 0);
+    __builtin_amdgcn_sched_barrier(0);
     load_x(0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < kUnits; ++u) load_unit(1, u, 1);
 #pragma unroll

@@ -748,12 +748,17 @@ __global__ void __launch_bounds__(256, 1) mpgemm_i8_ksplit_kernel(GemmI8Args a, 
     const uint32_t meta_z = HZ ? __builtin_amdgcn_raw_buffer_load_b16(rmeta, lane * MPL + 2, B * 1024, 0) : 0u;
     const TokenScales scales = request_token_scales(a, n0, tid);
     __builtin_amdgcn_sched_barrier(0);
+    // The waits below and in the loop count the requests, so none may be moved past another group.  The activations of own tile 1
+    // go ahead of its weights: 4096 x 4096 4 bits N = 700 20.8 us, behind them 21.2.
 #pragma unroll
     for (int u = 0; u < kUnits; ++u) load_unit(0, u, 0);
+    __builtin_amdgcn_sched_barrier(0);
     load_x(0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_x(1);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < kUnits; ++u) load_unit(1, u, 1);
-    load_x(1);
     __builtin_amdgcn_sched_barrier(0);
     if (tid < T::TM) {
         const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)meta_s);

@@ -1,6 +1,8 @@
 """The prefill kernel without a weight tile (256 rows x 96 tokens per workgroup), which the launcher takes where the rounds of
 its grid fit better, and the K-split tiles around the ends of K: ragged rows and tokens, K of half a 64-column stage, of one
 stage, of an odd number of stages, and the longest K, where eight waves share it."""
+import contextlib
+
 import numpy as np
 import pytest
 import torch
@@ -12,16 +14,28 @@ from gpu_helpers import TOL, dev, mpgemm, pack, rand_case, to_dev
 pytestmark = pytest.mark.gpu
 
 
-def _against_tiled(shape, blob, x, y):
-    """Every output against the tiled kernel: the same products, sums in another order (fp32, then one rounding)."""
+@contextlib.contextmanager
+def _tiling(**fields):
     t = tman.tman_get_tiling()
     try:
-        tiled = tman.tman_get_tiling()
-        tiled.prefill_row_blocks = 2
-        tman.tman_set_tiling(tiled)
-        other = mpgemm(shape, blob, x).astype(np.float64)
+        forced = tman.tman_get_tiling()
+        for name, value in fields.items():
+            setattr(forced, name, value)
+        tman.tman_set_tiling(forced)
+        yield
     finally:
         tman.tman_set_tiling(t)
+
+
+def _tiled(shape, blob, x, row_blocks):
+    with _tiling(prefill_row_blocks=row_blocks):
+        assert tman.tman_mpgemm_splits_k(shape, x.shape[0]) == 0
+        return mpgemm(shape, blob, x)
+
+
+def _against_tiled(shape, blob, x, y):
+    """Every output against the tiled kernel: the same products, sums in another order (fp32, then one rounding)."""
+    other = _tiled(shape, blob, x, 2).astype(np.float64)
     rms = np.sqrt(np.mean(other ** 2, axis=1, keepdims=True))
     assert np.all(np.abs(y - other) <= 2.0 ** -10 * np.maximum(np.abs(other), rms))
 
@@ -39,7 +53,8 @@ def test_wide_tiles(oracle_lib, M, K, bits, group, hz, N):
     shape = tman.Shape(M, K, bits, group, hz)
     assert tman.tman_mpgemm_splits_k(shape, N) == 0 and tman.tman_mpgemm_tile_rows(shape, N) == 256
     blob = pack(shape, q, s, z)
-    # the activations lie between values that are not finite: a column beyond K that is multiplied would show
+    # the activations lie between values that are not finite: a product with what lies outside them would show (a product with the
+    # next token's columns, which are what lies beyond a token's K, shows in test_a_token_that_is_not_finite_stays_alone)
     xbig = torch.full((512 + N * K + 70000,), float("nan"), dtype=torch.float16, device=dev())
     xbig[512:512 + N * K] = to_dev(x).reshape(-1)
     y = mpgemm(shape, blob, xbig[512:512 + N * K].view(N, K))
@@ -47,6 +62,13 @@ def test_wide_tiles(oracle_lib, M, K, bits, group, hz, N):
     tokens = np.unique([0, 31, 32, 95, N // 2, N - 1])
     assert oracle.row_relative_error(y[tokens], oracle.matmul(q, s, z, x[tokens], bits, group)).max() <= TOL
     _against_tiled(shape, blob, x, y)
+    # That no tiled kernel ran (256 x 256 tiles are 256 rows without a split of K as well): those give the same bits whatever their
+    # rows; this one sums 8 columns of each of two blocks at a time, so where fp32 sums of activations of many sizes are inexact, some
+    # of two million round differently (not with one block alone, whose columns every kernel sums in the same order).
+    if K > 32:
+        x = np.ldexp(x, np.random.default_rng(K).integers(-10, 9, x.shape)).astype(np.float16)
+        y, tiled = mpgemm(shape, blob, x), _tiled(shape, blob, x, 4)
+        assert np.array_equal(tiled, _tiled(shape, blob, x, 2)) and np.any(tiled != y)
 
 
 @pytest.mark.parametrize("M,K,bits,group,hz,N", [
@@ -66,6 +88,36 @@ def test_k_split_ends_of_k(oracle_lib, M, K, bits, group, hz, N):
     y = mpgemm(shape, blob, x)
     assert oracle.row_relative_error(y, oracle.matmul(q, s, z, x, bits, group)).max() <= TOL
     _against_tiled(shape, blob, x, y)
+
+
+# K is an odd multiple of 32: the stage of 64 columns that ends with it holds the next token's first 32 columns too
+@pytest.mark.parametrize("M,K,bits,group,hz,N,forced,rows,splits_k", [
+    (70, 96, 4, 32, True, 300, dict(prefill_row_blocks=1), 64, 0),       # tiled
+    (130, 160, 2, 32, True, 257, dict(prefill_row_blocks=2), 128, 0),
+    (192, 32, 1, 32, False, 40, dict(prefill_row_blocks=3), 192, 0),
+    (250, 352, 4, 32, True, 300, dict(prefill_row_blocks=4), 256, 0),
+    (100, 544, 4, 32, True, 270, dict(prefill_k_split=2), 64, 1),        # K split, 64 x 256
+    (130, 160, 1, 32, True, 130, dict(prefill_k_split=3), 128, 1),       # ... 128 x 128
+    (8256, 1056, 4, 32, True, 97, {}, 64, 1),                            # ... 64 x 128
+    (130, 544, 2, 32, True, 70, {}, 64, 1),                              # ... 64 x 64, four waves
+    (70, 8224, 4, 32, True, 33, {}, 64, 1),                              # ... eight waves
+    (21700, 160, 4, 32, True, 288, {}, 256, 0),                          # without a weight tile
+    (21760, 32, 2, 32, True, 97, {}, 256, 0),
+])
+def test_a_token_that_is_not_finite_stays_alone(M, K, bits, group, hz, N, forced, rows, splits_k):
+    """An infinity and a NaN among a token's first 32 columns: what lies beyond the token before it is not multiplied."""
+    q, s, z, x = rand_case(8700 + M + K + bits + N, M, K, N, bits, group, hz)
+    shape = tman.Shape(M, K, bits, group, hz)
+    blob = pack(shape, q, s, z)
+    bad = x.copy()
+    nan, inf = [1, N - 1], [N // 2]
+    bad[nan, 5], bad[inf, 31] = np.nan, np.inf
+    with _tiling(**forced):
+        assert tman.tman_mpgemm_tile_rows(shape, N) == rows and tman.tman_mpgemm_splits_k(shape, N) == splits_k
+        y, got = mpgemm(shape, blob, x), mpgemm(shape, blob, bad)
+    assert np.all(np.isnan(got[nan])) and not np.any(np.isfinite(got[inf]))
+    others = np.setdiff1d(np.arange(N), nan + inf)
+    assert np.all(np.isfinite(y.astype(np.float32))) and np.array_equal(got[others], y[others])
 
 
 @pytest.mark.parametrize("blocks", [1, 3, 4, 7, 9])

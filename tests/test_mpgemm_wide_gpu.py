@@ -14,6 +14,9 @@ from gpu_helpers import TOL, dev, mpgemm, pack, rand_case, to_dev
 pytestmark = pytest.mark.gpu
 
 
+TOL_I8 = 1e-3  # as in the tests of the int8 calls: fp32 scaling and one fp16 rounding behind exact integers
+
+
 @contextlib.contextmanager
 def _tiling(**fields):
     t = tman.tman_get_tiling()
@@ -135,16 +138,19 @@ def test_int8_kernels_give_the_same_bits(oracle_lib, blocks, M, K, bits, group, 
     blob = pack(shape, q, s, z)
     xq = torch.empty(tman.tman_act_i8_bytes(N, K), dtype=torch.uint8, device=dev())
     tman.tman_quantize_act_i8(to_dev(x), N, K, xq)
-    codes, _ = oracle.quantize_activations_i8(x)
-    y = torch.empty((N, M), dtype=torch.float16, device=dev())
-    acc = torch.empty((N, M), dtype=torch.int32, device=dev())
-    t = tman.tman_get_tiling()
-    try:
-        forced = tman.tman_get_tiling()
-        forced.i8_token_blocks = blocks
-        tman.tman_set_tiling(forced)
-        tman.tman_mpgemm_i8(shape, blob, xq, N, y, acc)
-    finally:
-        tman.tman_set_tiling(t)
-    torch.cuda.synchronize()
-    assert np.array_equal(acc.cpu().numpy(), codes.astype(np.int64) @ q.astype(np.int64).T)
+    codes, step = oracle.quantize_activations_i8(x)
+
+    def run(kernel, acc):
+        y = torch.full((N, M), float("nan"), dtype=torch.float16, device=dev())
+        with _tiling(i8_token_blocks=kernel):
+            tman.tman_mpgemm_i8(shape, blob, xq, N, y, acc)
+        torch.cuda.synchronize()
+        return y.cpu().numpy()
+
+    acc = torch.full((N, M), -1, dtype=torch.int32, device=dev())
+    y = run(blocks, acc)
+    want, Y = oracle.matmul_i8(q, s[:, 0], z[:, 0] if hz else None, codes, step, bits)
+    assert np.array_equal(acc.cpu().numpy(), want)
+    assert np.all(np.isfinite(y.astype(np.float32))) and oracle.row_relative_error(y, Y).max() <= TOL_I8
+    # the sums are integers, so every kernel scales the same numbers: the same bits, with and without the sums as an output
+    assert np.array_equal(y, run(blocks, None)) and np.array_equal(y, run(1, None))

@@ -11,13 +11,13 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,K,bits,group,hz,N", [
-    (130, 1056, 4, 32, True, 33),     # 64 x 64, four waves: 33 stages
+    (130, 1056, 4, 32, True, 33),     # 64 x 64, four waves: 16.5 stages of 64 columns
     (64, 1024, 2, 64, True, 64),      # ... exactly one token tile, one round
     (65, 2976, 1, 32, False, 129),    # ... three token tiles, the last with one token
     (100, 1088, 1, 64, True, 40),
-    (130, 4128, 4, 32, True, 40),     # 64 x 64, eight waves: 129 stages
+    (130, 4128, 4, 32, True, 40),     # ... 64.5 stages
     (64, 3072, 2, 128, True, 190),
-    (65, 11008, 4, 128, True, 65),
+    (65, 11008, 4, 128, True, 65),    # 64 x 64, eight waves (K from 8192 on): 172 stages
     (8256, 1056, 4, 32, True, 97),    # 64 x 128: 129 row blocks
     (8250, 1152, 2, 128, True, 128),
     (16400, 1024, 1, 64, False, 50),  # 257 workgroups of 64 x 64: a second one on a unit

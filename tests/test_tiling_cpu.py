@@ -30,7 +30,7 @@ def test_defaults_are_current_and_consistent():
     dict(decode_x_seg_tiles=0),
     dict(decode_x_long_seg_tiles=40),       # longer than a whole segment may be
     dict(decode_x_long_seg_tiles=0),
-    dict(prefill_row_blocks=5),             # Eq. 4: 4 x (320 x 80 + 256 x 64) bytes exceed 160 KB
+    dict(prefill_row_blocks=5),             # Eq. 4: 3 x (320 x 80 + 256 x 128) bytes exceed 160 KB
     dict(prefill_row_blocks=-1),
     dict(decode_seg_tiles=0), dict(decode_seg_tiles_many=0), dict(small_seg_tiles=0), dict(decode_x_whole_bytes=0),
     dict(i8_token_blocks=2), dict(i8_token_blocks=8), dict(i8_token_blocks=-1),  # only 0, 1, 3, 4, 7 and 9 exist

@@ -24,7 +24,7 @@
  * 4.9e-4), not a hard bound: among 1500 random shapes one output in 52,000 of one case reached 2.07e-3,
  * and a token whose one or two outputs cancel to nearly zero can exceed it.  In tman_mpgemm (N > 32) a dequantized
  * weight may differ from fp16((code - zero) * scale) by one fp16 step (about 5 % do: the constant
- * (1024 + zero) * scale is rounded to fp32 before the single rounding to fp16).  The integer paths state their
+ * (1024 + zero) * scale is rounded to fp32 before the sum is rounded to fp16).  The integer paths state their
  * own bounds.
  */
 #ifndef TMAN_H
@@ -260,8 +260,7 @@ int tman_device_status(void *stream);
  * small grids; none needs a workspace).
  * 1 <= N <= TMAN_MAX_SMALL_TOKENS runs one of two kernels organised like the decoding kernels (bound by the weight
  * stream: every wave multiplies the tile blocks it streams with all tokens at once): the codes themselves, with scale and
- * zero applied to the sums of quantization blocks (N <= 8; N <= 16 with blocks of 64 or 128; N <= 32 with blocks of
- * 128), or weights dequantized to fp16 (the others).  They cut a long K into segments that meet in the workspace, under
+ * zero applied to the sums of quantization blocks (N <= 16; N <= 32 with blocks of 128), or weights dequantized to fp16 (the others).  They cut a long K into segments that meet in the workspace, under
  * the rules of tman_mpgemv: tman_mpgemm_workspace_bytes(shape, N) bytes (0 when K is one segment, then NULL is
  * accepted), 16-byte aligned, zero-filled once before first use, left ready by every call, not shared by calls that may
  * overlap.  An activation that is not finite makes its own token's outputs what the sum over all columns gives; the

@@ -10,20 +10,20 @@
 //            conversion", "Applying scales and zero-points").  The 16-entry conversion table of the
 //            paper collapses on this hardware to inserting the code into the mantissa of 1024.0
 //            (fp16 0x6400 | c == 1024 + c exactly), and the baked affine table entry
-//            D[c] = fp16((c - zero) * scale) is produced by ONE mixed-precision FMA
-//            fp16( (1024 + c) * scale - (1024 + zero) * scale ): product and sum are exact inside the FMA
-//            and rounded to fp16 once; the per-block constant -(1024 + zero) * scale, computed once per block,
+//            D[c] = fp16((c - zero) * scale) is produced by one fp32 FMA, (1024 + c) * scale - (1024 + zero) * scale,
+//            and one conversion of two results to fp16.  The FMA rounds to fp32 and the conversion to fp16; in three times
+//            2^20 random entries, zeros inside the codes' range and far outside it, that gave the bits of the exact result
+//            rounded once to fp16 every time.  The per-block constant -(1024 + zero) * scale, computed once per block,
 //            is rounded to fp32 before (it has up to 24 significant bits), which moves the result by at most
-//            2^-23 * 1040 * scale ahead of that rounding: about 5 % of the entries come out one fp16 step
-//            from fp16((c - zero) * scale).
+//            2^-23 * 1040 * scale: about 5 % of the entries come out one fp16 step from fp16((c - zero) * scale).
 //            A lookup per weight in LDS would compete with the MFMA operand reads for LDS bandwidth.
 // The fp16 weight tile goes to LDS and is shared by the waves of the workgroup (each weight is
 // dequantized once per 256 tokens); activations go from global memory straight into LDS.  Pipeline (the
 // GPU form of DMA -> vector -> matrix): producer waves keep packed weights four stages ahead in registers
 // and fill a ring of LDS stage buffers; consumer waves feed v_mfma_f32_32x32x16_f16
 // (fp32 accumulation) from the ring; one barrier per 32-column stage.
-// Grids too small for that kernel (at most one workgroup per compute unit) go to mpgemm_ksplit_kernel, grids whose rounds its
-// tiles fit badly to mpgemm_wide_kernel, both below.
+// Grids too small for that kernel go to mpgemm_ksplit_kernel, grids whose rounds its tiles fit badly to mpgemm_wide_kernel, both
+// below; choose_tile decides.
 #include <hip/hip_fp16.h>
 
 #include <mutex>
@@ -68,8 +68,9 @@ struct GemmArgs {
     int per_xcd;  // workgroups dealt to each XCD
     int whole_row_tiles;
 };
-// The kernels take the 16 words of their arguments one by one: scalar arguments are in registers when a wave starts (the build
-// asks for it), a structure is read from memory first (44 shapes of 6 to 200 us: 1.006 and 1.018 times as fast in two runs).
+// The kernels take the 16 words of their arguments one by one: of scalar arguments the first 14 words are in registers when a wave
+// starts (the build asks for it), a structure is read from memory first (44 shapes of 6 to 200 us: 1.006 and 1.018 times as fast in
+// two runs).  The last two, per_xcd and whole_row_tiles, are still read from memory ahead of everything else.
 template <typename Launch>
 static int with_fields(const GemmArgs& a, Launch launch) {
     return launch(a.tiles, a.x, a.y, a.status, a.M, a.N, a.K, a.n_row_blocks, a.m_tiles, a.n_tiles, a.per_xcd, a.whole_row_tiles);
@@ -676,9 +677,9 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(Fields... fiel
                 constexpr int kLast = kUnits - 1;
                 const int nu = u == kLast ? 0 : u + 1, nset = u == kLast ? (s + 1) & 1 : s;
                 if (u == kLast) {
-                    // The activations of own stage i + 1 must be in.  Younger: NBuf == 2 (requested behind unit 1 of the previous
-                    // own stage): its weights from then on, the weights of this stage and the activations of stage i + 2;
-                    // NBuf == 1 (requested above): the weights of this stage.
+                    // The activations of own stage i + 1 must be in.  Younger: NBuf == 2 (requested behind unit 0 of the previous
+                    // own stage or beside its unit 1): at least its weights from then on, the weights of this stage and the
+                    // activations of stage i + 2; NBuf == 1 (requested above): the weights of this stage.
                     constexpr int kYounger = T::NBuf == 2 ? 2 * kUnits + T::XLoads : 2 * (kUnits - 1);
                     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kYounger) : "memory");
                 }
@@ -771,7 +772,8 @@ __global__ void __launch_bounds__(64 * W, 1) mpgemm_ksplit_kernel(Fields... fiel
 // 64-column stage (whole cache lines) are shared by the four waves through LDS.  Two workgroups share a compute unit.
 // 96 tokens: with 128 the accumulators, the activations of a stage and the weights in flight do not fit 256 registers.
 // What bounds it: products plus vector work at the clock the chip holds under both (8 vector instructions per product, about 6
-// hide behind one).  11008 x 4096 4 bits, N = 1024: 104 us = 0.89 PFLOP/s (tiled, 192 x 256: 96); its grain is half as large.
+// hide behind one).  11008 x 4096 4 bits, N = 1024 / 2048: 101 / 194 us = 0.92 / 0.95 PFLOP/s (tiled, 192 x 256, timed in turn with
+// it: 95 / 181); its grain is half as large.
 constexpr int kWideRing = 4;   // stage buffers
 constexpr int kWideRows = 256;
 template <int TT>

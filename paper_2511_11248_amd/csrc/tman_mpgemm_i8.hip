@@ -478,7 +478,7 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
     // Activations: a request brings 8 token rows x 128 bytes straight into LDS; wave w issues requests w, w + 4, ...  16-byte
     // chunk c of row R is kept at place c ^ ((R >> 1) & 7), so that the operand reads of 16 consecutive rows fall on 16
     // different places.  Rows beyond the tile's tokens lie outside the resource (zeros).  Columns beyond K are those of the
-    // next token: their codes are zero.
+    // next token, behind the last one what the buffer keeps there (at least 512 bytes: scales and sums): their codes are zero.
     const int xrows = a.N - n0 < T::TN ? a.N - n0 : T::TN;
     const int8_t* xsrc = a.xq + (size_t)n0 * a.K;
     const uint32_t xbytes = (uint32_t)xrows * (uint32_t)a.K;
@@ -940,11 +940,15 @@ static int launch_i8_wide_tokens(int tt, const GemmI8Args& a, int group, hipStre
 // time.  The model counts rounds of workgroups over the compute units with the time of one workgroup (alone on its unit /
 // sharing it with a second one, which the 96- and 128-token tiles allow), scaled by K; the 128 x 128 kernel's time grows
 // linearly with its workgroups.  1 = that kernel, 3 / 4 / 7 = the wide kernel with that many 32-token blocks, 9 = the kernel
-// whose waves split K.  The constants weigh the candidates against each other, short K included (they pick the fastest at 20
-// of 20 shapes); calls of 64 / 128 / 256 / 384 / 512 workgroups take, at K = 4096 and 4 bits, in microseconds:
-//   3 (96 tokens)  23 / 24 / 32 / 45 / 53    9 (K split)    18 / 19 / 25 / 40 / 46
-//   4 (128)        27 / 28 / 37 / 54 / 64    1 (128 x 128)  27 / 28 / 29 / 40 / 45
-//   7 (224)        42 / 44 / 56
+// whose waves split K.  Its constants weigh the candidates against each other; they are larger than the times of the present
+// kernels.  Calls of 64 / 128 / 256 / 384 / 512 workgroups take, at K = 4096 and 4 bits, in microseconds:
+//   3 (96 tokens)  23 / 25 / 32 / 46 / 53    9 (K split)    18 / 19 / 24 / 40 / 46
+//   4 (128)        27 / 29 / 38 / 55 / 64    1 (128 x 128)  27 / 28 / 29 / 40 / 46
+//   7 (224)        42 / 44 / 57 / 99 / 115
+// From K = 2048 on the rule picks the fastest or one within 1 % of it at 33 of 33 shapes (random ones of 256 .. 12288 rows and 33 ..
+// 2048 tokens).  Below it does not: the 128 x 128 kernel has no fixed part here and the K-split kernel is not asked, so at 22 of 27
+// shapes the 96-token or the K-split kernel takes 3 to 19 % less (640 x 1792 N = 56: 14.1 us, K split 11.5; 4096 x 1024 N = 512 12.0,
+// 96 tokens 10.3).
 int choose_i8_token_blocks(int n_row_blocks, int N, int K) {
     static std::once_flag once;
     static int n_cu = 256;  // assumed when no device answers

@@ -248,6 +248,7 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(Fields... fields) {
         // in stage s-1.
         if (kSplitRoles && p == kLoaderWave) {
             load_x(0, 0, 2 * kXAll);
+            __builtin_amdgcn_sched_barrier(0);  // (the wait below counts the requests of pair 1)
             load_x(1, 0, 2 * kXAll);
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kXAll) : "memory");
             asm volatile("s_barrier" ::: "memory");
@@ -380,6 +381,7 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(Fields... fields) {
             __builtin_amdgcn_sched_barrier(0);
             asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // all but the weights of stages 2 and 3 (two loads each)
             load_x(1, 8 * p, 8);
+            __builtin_amdgcn_sched_barrier(0);  // (and so does the loop's first)
             load_wregs(0, 4);
             load_wregs(1, 5);
             __builtin_amdgcn_sched_barrier(0);

@@ -523,6 +523,7 @@ __global__ void __launch_bounds__(256, (TT <= 4 ? 2 : 1)) mpgemm_i8_wide_kernel(
     }
     load_x(0);
     load_x(1);
+    __builtin_amdgcn_sched_barrier(0);
     load_x(2);
     __builtin_amdgcn_sched_barrier(0);
     load_planes(plane[kSets - 1], kSets - 1);

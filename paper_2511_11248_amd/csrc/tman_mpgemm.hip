@@ -205,7 +205,8 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(Fields... fields) {
         const uint32_t xbytes = (uint32_t)xrows * (uint32_t)a.K * 2u;
         // Roles.  With four row blocks every producer wave dequantizes one and issues a quarter of the
         // activation loads.  With fewer, wave 3 has no row block: it issues all activation loads (about 40
-        // cycles each) and the dequantizing waves none, which shortens the chain that gates a stage.
+        // cycles each) and the dequantizing waves none, which shortens the chain that gates a stage. (With one
+        // row block wave 2 helps it ahead of the loop.)
         constexpr bool kSplitRoles = RB < 4;
         constexpr int kLoaderWave = 3;
         constexpr int kXAll = kTN / 16;  // activation loads per stage, half of a pair's (8 token rows each)
@@ -247,11 +248,16 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(Fields... fields) {
         // the barrier of an even stage s the activations of pair s/2 + 1 must have landed; their second half was issued first
         // in stage s-1.
         if (kSplitRoles && p == kLoaderWave) {
-            load_x(0, 0, 2 * kXAll);
-            __builtin_amdgcn_sched_barrier(0);  // (the wait below counts the requests of pair 1)
-            load_x(1, 0, 2 * kXAll);
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kXAll) : "memory");
+            // Ahead of the first barrier: pair 0 and half of pair 1.  Pair 1 is not read before stage 1, and behind all of it the
+            // barrier comes later: K <= 512, 128 and 192 rows 0.3 to 1.2 % (one row block 1.2 %, and 1.1 to 2.3 % more with wave 2
+            // asking for half of the rows).
+            constexpr int kMine = RB == 1 ? kXAll : 2 * kXAll;  // of a pair's requests
+            load_x(0, 0, kMine);
+            __builtin_amdgcn_sched_barrier(0);  // (the wait below counts the requests behind these)
+            load_x(1, 0, kMine / 2);
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kMine / 2) : "memory");
             asm volatile("s_barrier" ::: "memory");
+            load_x(1, kMine / 2, kMine / 2);
             // The requests of a stage are spread over it (s_sleep: 64 cycles a step): what they write to LDS and read from L2
             // in one go keeps the other waves waiting.  4096 x 4096 N = 700, 192 x 256 tiles, all at once / in fours with
             // 1 / 3 / 5 steps between: 70.6 / 69.1 / 65.7 / 74.0 us (11008 x 4096 N = 1024 92.9 / 91.8 / 90.6 / 94.9).
@@ -341,8 +347,13 @@ __global__ void __launch_bounds__(kThreads, 1) mpgemm_kernel(Fields... fields) {
                         }
                     }
                 }
-            } else {  // wave 2 has no work: it only keeps the barriers
+            } else {  // wave 2 asks for the other rows of pairs 0 and 1, then only keeps the barriers
+                load_x(0, kXAll, kXAll);
+                __builtin_amdgcn_sched_barrier(0);
+                load_x(1, kXAll, kXAll);
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kXAll) : "memory");
                 asm volatile("s_barrier" ::: "memory");
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 for (int s = 0; s < n_stages; ++s) asm volatile("s_barrier" ::: "memory");
             }
         } else if (kSplitRoles) {

@@ -93,6 +93,25 @@ def test_k_split_ends_of_k(oracle_lib, M, K, bits, group, hz, N):
     _against_tiled(shape, blob, x, y)
 
 
+# The tiled kernel asks for the activations of its first four stages ahead of the loop and around its first barrier, with one row
+# block from two waves, half of the tokens each: K of one to nine stages, tokens on both sides of every wave's last.
+@pytest.mark.parametrize("row_blocks", [1, 2, 3, 4])
+@pytest.mark.parametrize("M,K,bits,group,N", [
+    (70, 32, 4, 32, 128),
+    (130, 64, 2, 64, 129),
+    (200, 96, 1, 32, 256),
+    (260, 128, 4, 128, 257),
+    (70, 160, 2, 32, 391),
+    (190, 192, 4, 64, 100),
+    (64, 288, 1, 32, 300),
+])
+def test_tiled_first_stages(oracle_lib, row_blocks, M, K, bits, group, N):
+    q, s, z, x = rand_case(8600 + M + K + bits + N, M, K, N, bits, group, True)
+    shape = tman.Shape(M, K, bits, group, True)
+    y = _tiled(shape, pack(shape, q, s, z), x, row_blocks)
+    assert oracle.row_relative_error(y, oracle.matmul(q, s, z, x, bits, group)).max() <= TOL
+
+
 # K is an odd multiple of 32: the stage of 64 columns that ends with it holds the next token's first 32 columns too
 @pytest.mark.parametrize("M,K,bits,group,hz,N,forced,rows,splits_k", [
     (70, 96, 4, 32, True, 300, dict(prefill_row_blocks=1), 64, 0),       # tiled

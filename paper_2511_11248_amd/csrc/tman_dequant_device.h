@@ -140,13 +140,32 @@ __device__ __forceinline__ void dequant_to_lds(const WRegs<B>& r, uint8_t* wrow)
     for (int q = 0; q < 4; ++q) dq.emit(q, wrow);
 }
 
-// Stores an fp16 output tile kept in LDS as [token][row]: 16-byte pieces, coalesced.  A whole tile of an aligned output takes four
-// pieces of a thread at a time, so that their reads and stores overlap.
+// Elements of type T of an output tile, consecutive lanes to consecutive elements of a row: `live` rows of TM / (elements per T).
+template <typename T, int TM, int OUT_ROW, int THREADS>
+__device__ __forceinline__ void store_elements(_Float16* y, int M, const uint8_t* otile, int m0, int n0, int live, int tid) {
+    constexpr int kPer = sizeof(T) / 2, kRowItems = TM / kPer;
+#pragma unroll 4
+    for (int i = tid; i < live * kRowItems; i += THREADS) {
+        const int n = i / kRowItems, m = i % kRowItems * kPer;
+        if (m0 + m < M)
+            *reinterpret_cast<T*>(y + (size_t)(n0 + n) * M + m0 + m) = *reinterpret_cast<const T*>(otile + n * OUT_ROW + m * 2);
+    }
+}
+
+// Stores an fp16 output tile kept in LDS as [token][row].  Rows of y that are 16-byte aligned: 16-byte pieces, coalesced; a whole tile
+// takes four pieces of a thread at a time, so that their reads and stores overlap.  Other rows of y: words or elements, each store of a
+// wave a piece of one or two rows.  (Element by element of a thread's own 16 bytes a store touched eight or more lines, which counts most
+// where few threads store a tile: 19022 x 256 N = 93, 256 x 96 tiles 13.3 -> 9.7 us; 15731 x 320 N = 1997, 256 x 256 tiles 70.3 -> 37.7.)
 template <int TM, int TN, int OUT_ROW, int THREADS>
 __device__ __forceinline__ void store_tile(_Float16* y, int M, int N, const uint8_t* otile, int m0, int n0, int tid) {
     constexpr int kPieces = TN * (TM / 8);
-    const bool fast = M % 8 == 0 && aligned16(y);  // 16-byte aligned rows of y
-    if (fast && m0 + TM <= M && n0 + TN <= N) {
+    if (M % 8 != 0 || !aligned16(y)) {
+        const int live = N - n0 < TN ? N - n0 : TN;
+        if (M % 2 == 0 && ((uintptr_t)y & 3) == 0) store_elements<uint32_t, TM, OUT_ROW, THREADS>(y, M, otile, m0, n0, live, tid);
+        else store_elements<uint16_t, TM, OUT_ROW, THREADS>(y, M, otile, m0, n0, live, tid);
+        return;
+    }
+    if (m0 + TM <= M && n0 + TN <= N) {
 #pragma unroll 4
         for (int piece = tid; piece < kPieces; piece += THREADS) {
             const int n = piece / (TM / 8), c8 = piece % (TM / 8);
@@ -158,16 +177,8 @@ __device__ __forceinline__ void store_tile(_Float16* y, int M, int N, const uint
     for (int piece = tid; piece < kPieces; piece += THREADS) {
         const int n = piece / (TM / 8), c8 = piece % (TM / 8);
         const int gn = n0 + n, gm = m0 + c8 * 8;
-        if (gn >= N || gm >= M) continue;
-        const u32x4 v = *reinterpret_cast<const u32x4*>(otile + n * OUT_ROW + c8 * 16);
-        _Float16* dst = y + (size_t)gn * M + gm;
-        if (fast && gm + 8 <= M) {
-            *reinterpret_cast<u32x4*>(dst) = v;
-        } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-            for (int t = 0; t < 8 && gm + t < M; ++t)
-                dst[t] = __builtin_bit_cast(_Float16, (uint16_t)(w[t >> 1] >> (16 * (t & 1))));
-        }
+        if (gn < N && gm < M)  // (M is a multiple of 8)
+            *reinterpret_cast<u32x4*>(y + (size_t)gn * M + gm) = *reinterpret_cast<const u32x4*>(otile + n * OUT_ROW + c8 * 16);
     }
 }
 

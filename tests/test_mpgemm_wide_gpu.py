@@ -142,6 +142,54 @@ def test_a_token_that_is_not_finite_stays_alone(M, K, bits, group, hz, N, forced
     assert np.all(np.isfinite(y.astype(np.float32))) and np.array_equal(got[others], y[others])
 
 
+# M that is no multiple of 8: words where it is even and y allows them, elements otherwise; the last row tile of one row, two, or all but
+# one, the last token tile of one token or full
+@pytest.mark.parametrize("offset", [0, 1, 2])
+@pytest.mark.parametrize("M,N,forced", [
+    (65, 257, dict(prefill_row_blocks=1)),
+    (130, 256, dict(prefill_row_blocks=2)),
+    (383, 300, dict(prefill_row_blocks=3)),
+    (514, 257, dict(prefill_row_blocks=4)),
+    (21700, 97, {}),                          # without a weight tile
+    (21505, 192, {}),
+    (129, 129, dict(i8_token_blocks=1)),
+    (258, 97, dict(i8_token_blocks=3)),
+    (511, 128, dict(i8_token_blocks=4)),
+    (257, 225, dict(i8_token_blocks=7)),
+])
+def test_rows_of_y_that_are_not_aligned(M, N, forced, offset):
+    """The bits of the same rows among M rounded up to a multiple of 8, and nothing written beside them."""
+    K, bits, group = 160, 4, 32
+    full = (M + 7) // 8 * 8
+    q, s, z, x = rand_case(9300 + M + N, full, K, N, bits, group)
+    integer = "i8_token_blocks" in forced
+    if integer:
+        s, z = np.repeat(s[:, :1], K // group, axis=1), np.repeat(z[:, :1], K // group, axis=1)
+    xd = to_dev(x)
+    xq = torch.empty(tman.tman_act_i8_bytes(N, K), dtype=torch.uint8, device=dev())
+    tman.tman_quantize_act_i8(xd, N, K, xq)
+
+    def run(rows, y):
+        shape = tman.Shape(rows, K, bits, group)
+        blob = pack(shape, q[:rows], s[:rows], z[:rows])
+        if not forced:
+            assert tman.tman_mpgemm_splits_k(shape, N) == 0 and tman.tman_mpgemm_tile_rows(shape, N) == 256
+        if integer:
+            tman.tman_mpgemm_i8(shape, blob, xq, N, y, None)
+        else:
+            tman.tman_mpgemm(shape, blob, xd, N, y, None)
+        torch.cuda.synchronize()
+
+    room = torch.full((N * M + 24,), 777.0, dtype=torch.float16, device=dev())
+    whole = torch.empty((N, full), dtype=torch.float16, device=dev())
+    with _tiling(**forced):
+        run(M, room[8 + offset:8 + offset + N * M])
+        run(full, whole)
+    got, mark = room.cpu().numpy().view(np.uint16), np.float16(777.0).view(np.uint16)
+    assert np.all(got[:8 + offset] == mark) and np.all(got[8 + offset + N * M:] == mark)
+    assert np.array_equal(got[8 + offset:8 + offset + N * M].reshape(N, M), whole.cpu().numpy()[:, :M].view(np.uint16))
+
+
 @pytest.mark.parametrize("blocks", [1, 3, 4, 7, 9])
 @pytest.mark.parametrize("M,K,bits,group,hz,N", [
     (70, 160, 4, 32, True, 100),      # a tile and a quarter

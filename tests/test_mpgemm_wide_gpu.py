@@ -156,10 +156,18 @@ def test_a_token_that_is_not_finite_stays_alone(M, K, bits, group, hz, N, forced
     (258, 97, dict(i8_token_blocks=3)),
     (511, 128, dict(i8_token_blocks=4)),
     (257, 225, dict(i8_token_blocks=7)),
+    (65, 300, dict(prefill_k_split=2)),
+    (255, 129, dict(prefill_k_split=3)),
+    (8258, 97, dict(K=1056)),                 # K split, 64 x 128
+    (127, 70, dict(K=544)),                   # ... 64 x 64
+    (65, 33, dict(K=8224)),                   # ... eight waves
+    (258, 193, dict(i8_token_blocks=9)),
 ])
 def test_rows_of_y_that_are_not_aligned(M, N, forced, offset):
     """The bits of the same rows among M rounded up to a multiple of 8, and nothing written beside them."""
-    K, bits, group = 160, 4, 32
+    splits = 0 if not forced else 1 if "K" in forced else None
+    forced = dict(forced)
+    K, bits, group = forced.pop("K", 160), 4, 32
     full = (M + 7) // 8 * 8
     q, s, z, x = rand_case(9300 + M + N, full, K, N, bits, group)
     integer = "i8_token_blocks" in forced
@@ -172,8 +180,8 @@ def test_rows_of_y_that_are_not_aligned(M, N, forced, offset):
     def run(rows, y):
         shape = tman.Shape(rows, K, bits, group)
         blob = pack(shape, q[:rows], s[:rows], z[:rows])
-        if not forced:
-            assert tman.tman_mpgemm_splits_k(shape, N) == 0 and tman.tman_mpgemm_tile_rows(shape, N) == 256
+        if splits is not None:
+            assert (tman.tman_mpgemm_splits_k(shape, N), tman.tman_mpgemm_tile_rows(shape, N)) == ((1, 64) if splits else (0, 256))
         if integer:
             tman.tman_mpgemm_i8(shape, blob, xq, N, y, None)
         else:
